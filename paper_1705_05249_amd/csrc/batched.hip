@@ -15,11 +15,8 @@
 // Per-instance offsets and scalars are wave-uniform and come in through scalar loads; this is
 // the overhead the paper points out when it compares the generic with the strided interface.
 // Instances only need element alignment (the vector accesses are issued at element alignment).
-// Shapes up to 64 x 64 x 64 are covered by three register-block sizes; anything larger goes to
-// the direct batched kernel.  The 64-wide block splits an instance's columns over the four
-// wavefronts of a work-group (each re-reads A, which the L1 serves): a quarter of the registers
-// per wavefront means four times the resident wavefronts, so loads of some instances overlap
-// the MFMAs of others.
+// Shapes up to 32 x 32 x 32 are covered by two register-block sizes, whole 64 x 64 x 64 instances in one operand order by
+// kernels of their own (below); everything else goes to the LDS-staged kernels of batched_tile.hip.
 #include "internal.h"
 
 namespace mg {
@@ -91,20 +88,15 @@ __device__ inline typename Vec4<T>::type load4(const T *__restrict__ X, int64_t 
     return v;
 }
 
-// NS: wavefronts per instance (each takes NB_ALL / NS of the 16-column blocks).
-// IPW: instances per wavefront (NS == 1 only).  With more instances than resident wavefronts (256 compute
+// IPW: instances per wavefront.  With more instances than resident wavefronts (256 compute
 // units x 32) a second round of wavefronts pays the whole load-to-store latency chain again; a wavefront that
 // takes two neighbouring instances issues the loads of both before it waits for either.
-template <typename T, int MB, int NB_ALL, int KB, int NS, bool A_KC, bool B_KC, bool FULL, int IPW = 1>
+template <typename T, int MB, int NB, int KB, bool A_KC, bool B_KC, bool FULL, int IPW = 1>
 __global__ __launch_bounds__(256) void batched_wave_kernel(const BatchedArgs a)
 {
-    static_assert(IPW == 1 || NS == 1, "several instances per wavefront only when one wavefront covers an instance");
     using V = typename Vec4<T>::type;
-    constexpr int NB = NB_ALL / NS;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-    const int64_t gw = static_cast<int64_t>(blockIdx.x) * 4 + wave;
-    const int64_t inst0 = gw / NS * IPW;
-    const int col0 = static_cast<int>(gw % NS) * NB * 16;       // first column of this wavefront's share
+    const int64_t inst0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * IPW;
     if (inst0 >= a.batch) return;
     const int lane = threadIdx.x % 64, r16 = lane % 16, g = lane / 16;
 
@@ -133,25 +125,17 @@ __global__ __launch_bounds__(256) void batched_wave_kernel(const BatchedArgs a)
 #pragma unroll
             for (int bi = 0; bi < MB; ++bi) acc[q][bj][bi] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // Small instances: C_old first (the longest latency chain ends in the store), then the operands, all in flight
-    // at once.  An instance of 64^3 per wavefront has no registers for that (A, B and C_old are 64 each): its
-    // operands go first, all of them at once, and C_old is asked for when half of the MFMAs are done and the
-    // registers of the first K blocks are free again (with C_old first the compiler kept ten operand loads in
-    // flight and every group of MFMAs waited for memory).
-    constexpr bool LATE_C = MB * NB * IPW >= 16;
+    // C_old first (the longest latency chain ends in the store), then the operands, all in flight at once
     V cold[IPW][NB][MB];
-    auto fetch_c = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < IPW; ++q)
-            if (beta[q] != 0.f) {
+    for (int q = 0; q < IPW; ++q)
+        if (beta[q] != 0.f) {
 #pragma unroll
-                for (int bj = 0; bj < NB; ++bj)
+            for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
-                    for (int bi = 0; bi < MB; ++bi)
-                        cold[q][bj][bi] = load4<T, true, FULL>(C[q], a.ldc, col0 + bj * 16 + r16, bi * 16 + 4 * g, a.n, a.m);
-            }
-    };
-    if constexpr (!LATE_C) fetch_c();
+                for (int bi = 0; bi < MB; ++bi)
+                    cold[q][bj][bi] = load4<T, true, FULL>(C[q], a.ldc, bj * 16 + r16, bi * 16 + 4 * g, a.n, a.m);
+        }
 
     V av[IPW][MB][KB], bv[IPW][NB][KB];
 #pragma unroll
@@ -164,10 +148,9 @@ __global__ __launch_bounds__(256) void batched_wave_kernel(const BatchedArgs a)
                     av[q][bi][kb] = load4<T, A_KC, FULL>(A[q], a.lda, bi * 16 + r16, kb * 16 + 4 * g, a.m, a.k);
 #pragma unroll
                 for (int bj = 0; bj < NB; ++bj)
-                    bv[q][bj][kb] = load4<T, B_KC, FULL>(B[q], a.ldb, col0 + bj * 16 + r16, kb * 16 + 4 * g, a.n, a.k);
+                    bv[q][bj][kb] = load4<T, B_KC, FULL>(B[q], a.ldb, bj * 16 + r16, kb * 16 + 4 * g, a.n, a.k);
             }
         }
-    if constexpr (LATE_C) __builtin_amdgcn_sched_barrier(0);      // every operand load is issued before the first MFMA
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
 #pragma unroll
@@ -178,13 +161,6 @@ __global__ __launch_bounds__(256) void batched_wave_kernel(const BatchedArgs a)
 #pragma unroll
                     for (int bi = 0; bi < MB; ++bi) acc[q][bj][bi] = block_mma(av[q][bi][kb], bv[q][bj][kb], acc[q][bj][bi]);
             }
-        if constexpr (LATE_C) {
-            if (kb == (KB - 1) / 2) {
-                __builtin_amdgcn_sched_barrier(0);
-                fetch_c();
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
     }
 
     // lane (r16, g) holds C(i = 16 bi + 4g + r, j = 16 bj + r16), r = 0..3: four consecutive rows of one column
@@ -195,7 +171,7 @@ __global__ __launch_bounds__(256) void batched_wave_kernel(const BatchedArgs a)
         for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
             for (int bi = 0; bi < MB; ++bi) {
-                const int j = col0 + bj * 16 + r16, i0 = bi * 16 + 4 * g;
+                const int j = bj * 16 + r16, i0 = bi * 16 + 4 * g;
                 floatx4 o = alpha[q] * acc[q][bj][bi];
                 if (beta[q] != 0.f) o += beta[q] * widen(cold[q][bj][bi]);
                 T *p = C[q] + i0 + j * a.ldc;
@@ -425,14 +401,14 @@ template <int DTYPE, int NS = 1> hipError_t rows64_launch(const BatchedProblem &
 
 // ---------------------------------------------------------------------------------- host side
 
-template <typename T, int MB, int NB, int KB, int NS, bool A_KC, bool B_KC, bool FULL, int IPW = 1> struct WaveConfig {
+template <typename T, int MB, int NB, int KB, bool A_KC, bool B_KC, bool FULL, int IPW = 1> struct WaveConfig {
     static constexpr int DTYPE = sizeof(T) == 4 ? MG_F32 : MG_F16;
     static bool legal(const BatchedProblem &p)
     {
         if (p.dtype != DTYPE || p.a_trans != A_KC || p.b_trans == B_KC) return false;
         if (p.m > 16 * MB || p.n > 16 * NB || p.k > 16 * KB) return false;
         if (FULL && (p.m != 16 * MB || p.n != 16 * NB || p.k != 16 * KB)) return false;
-        if (p.batch * NS >= (int64_t(1) << 32)) return false;
+        if (p.batch >= (int64_t(1) << 32)) return false;
         // offsets inside one instance are 32-bit in the kernel
         const int64_t lim = int64_t(1) << 24;
         return p.lda < lim && p.ldb < lim && p.ldc < lim;
@@ -442,8 +418,8 @@ template <typename T, int MB, int NB, int KB, int NS, bool A_KC, bool B_KC, bool
         BatchedArgs a{p.A, p.B, p.C, p.a_off, p.b_off, p.c_off, p.alphas, p.betas, p.lda, p.ldb, p.ldc,
                       static_cast<int>(p.m), static_cast<int>(p.n), static_cast<int>(p.k), p.batch,
                       p.strided ? 1 : 0, p.stride_a, p.stride_b, p.stride_c, p.alpha, p.beta};
-        hipLaunchKernelGGL((batched_wave_kernel<T, MB, NB, KB, NS, A_KC, B_KC, FULL, IPW>),
-                           dim3(static_cast<unsigned>(ceil_div(ceil_div(p.batch, IPW) * NS, 4))), dim3(256), 0, p.stream, a);
+        hipLaunchKernelGGL((batched_wave_kernel<T, MB, NB, KB, A_KC, B_KC, FULL, IPW>),
+                           dim3(static_cast<unsigned>(ceil_div(ceil_div(p.batch, IPW), 4))), dim3(256), 0, p.stream, a);
         return hipGetLastError();
     }
     static KernelEntry entry(const char *name)
@@ -452,7 +428,7 @@ template <typename T, int MB, int NB, int KB, int NS, bool A_KC, bool B_KC, bool
         c.family = MG_FAMILY_BATCHED;
         c.dtype = DTYPE;
         c.tile_m = 16 * MB; c.tile_n = 16 * NB; c.tile_k = 16 * KB;
-        c.waves_m = 1; c.waves_n = NS;
+        c.waves_m = 1; c.waves_n = 1;
         c.split_k = 1;
         c.threads = 256;
         c.lds_bytes = 0;
@@ -460,20 +436,13 @@ template <typename T, int MB, int NB, int KB, int NS, bool A_KC, bool B_KC, bool
     }
 };
 
-#define MG_BATCHED_REGISTER(table, T, tag, B, NS)                                                    \
-    table.push_back(WaveConfig<T, B, B, B, NS, false, true, true>::entry(tag "_mk_full"));           \
-    table.push_back(WaveConfig<T, B, B, B, NS, false, true, false>::entry(tag "_mk"));               \
-    table.push_back(WaveConfig<T, B, B, B, NS, true, true, false>::entry(tag "_kk"));                \
-    table.push_back(WaveConfig<T, B, B, B, NS, false, false, false>::entry(tag "_mn"));              \
-    table.push_back(WaveConfig<T, B, B, B, NS, true, false, false>::entry(tag "_kn"));
-
-// the same five kernels with two instances per wavefront
-#define MG_BATCHED_REGISTER_PAIRS(table, T, tag, B)                                                  \
-    table.push_back(WaveConfig<T, B, B, B, 1, false, true, true, 2>::entry(tag "_mk_full"));        \
-    table.push_back(WaveConfig<T, B, B, B, 1, false, true, false, 2>::entry(tag "_mk"));            \
-    table.push_back(WaveConfig<T, B, B, B, 1, true, true, false, 2>::entry(tag "_kk"));             \
-    table.push_back(WaveConfig<T, B, B, B, 1, false, false, false, 2>::entry(tag "_mn"));           \
-    table.push_back(WaveConfig<T, B, B, B, 1, true, false, false, 2>::entry(tag "_kn"));
+// the five flavours of a block size; IPW: instances per wavefront
+#define MG_BATCHED_REGISTER(table, T, tag, B, IPW)                                                \
+    table.push_back(WaveConfig<T, B, B, B, false, true, true, IPW>::entry(tag "_mk_full"));       \
+    table.push_back(WaveConfig<T, B, B, B, false, true, false, IPW>::entry(tag "_mk"));           \
+    table.push_back(WaveConfig<T, B, B, B, true, true, false, IPW>::entry(tag "_kk"));            \
+    table.push_back(WaveConfig<T, B, B, B, false, false, false, IPW>::entry(tag "_mn"));          \
+    table.push_back(WaveConfig<T, B, B, B, true, false, false, IPW>::entry(tag "_kn"));
 
 }  // namespace
 
@@ -481,13 +450,10 @@ void register_batched(std::vector<KernelEntry> &table)
 {
     MG_BATCHED_REGISTER(table, float, "batched_wave_16", 1, 1)
     MG_BATCHED_REGISTER(table, float, "batched_wave_32", 2, 1)
-    MG_BATCHED_REGISTER(table, float, "batched_wave_64", 4, 4)
-    MG_BATCHED_REGISTER(table, float, "batched_wave_64w1", 4, 1)
     MG_BATCHED_REGISTER(table, _Float16, "hbatched_wave_16", 1, 1)
     MG_BATCHED_REGISTER(table, _Float16, "hbatched_wave_32", 2, 1)
-    MG_BATCHED_REGISTER(table, _Float16, "hbatched_wave_64w1", 4, 1)
-    MG_BATCHED_REGISTER_PAIRS(table, float, "batched_wave_16x2", 1)
-    MG_BATCHED_REGISTER_PAIRS(table, _Float16, "hbatched_wave_16x2", 1)
+    MG_BATCHED_REGISTER(table, float, "batched_wave_16x2", 1, 2)
+    MG_BATCHED_REGISTER(table, _Float16, "hbatched_wave_16x2", 1, 2)
     {
         mg_config c{};
         c.family = MG_FAMILY_BATCHED;

@@ -1,7 +1,6 @@
 // Direct kernels: one bounds-checked kernel per call, no assumption on shape, stride or
 // alignment (the "direct" single-kernel design of the paper's Section 3.2, used where
-// the tiled MFMA path does not apply), plus the scale-only kernel for alpha == 0 / k == 0
-// and the batched form of the same kernel (Section 4.6).
+// the tiled MFMA path does not apply), plus the scale-only kernel for alpha == 0 / k == 0.
 //
 // Work-group = 256 threads, 64 x 64 tile of C, K in steps of 16 staged through LDS as FP32,
 // each thread owns a 4 x 4 register tile with rows tx + 16r (so that consecutive lanes
@@ -104,31 +103,6 @@ __global__ __launch_bounds__(256) void scale_kernel(int64_t m, int64_t n, T *__r
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void direct_batched_kernel(int64_t m, int64_t n, int64_t k,
-                                                              const T *__restrict__ A,
-                                                              const int64_t *__restrict__ a_off, int64_t a_sm,
-                                                              int64_t a_sk, const T *__restrict__ B,
-                                                              const int64_t *__restrict__ b_off, int64_t b_sk,
-                                                              int64_t b_sn, T *__restrict__ C,
-                                                              const int64_t *__restrict__ c_off, int64_t ldc,
-                                                              const float *__restrict__ alphas,
-                                                              const float *__restrict__ betas, int64_t tiles_m,
-                                                              int64_t tiles, int strided, int64_t stride_a,
-                                                              int64_t stride_b, int64_t stride_c, float alpha_all,
-                                                              float beta_all)
-{
-    const int64_t inst = blockIdx.x / tiles;
-    const int64_t t = blockIdx.x % tiles;
-    const float alpha = strided ? alpha_all : alphas[inst], beta = strided ? beta_all : betas[inst];
-    const int64_t oa = strided ? inst * stride_a : a_off[inst];
-    const int64_t ob = strided ? inst * stride_b : b_off[inst];
-    const int64_t oc = strided ? inst * stride_c : c_off[inst];
-    // alpha == 0: A and B must not contribute (they may hold NaN/Inf) -> run with k = 0
-    direct_tile<T>(m, n, alpha == 0.f ? 0 : k, A + oa, a_sm, a_sk, B + ob, b_sk, b_sn, C + oc, ldc, alpha, beta,
-                       t % tiles_m, t / tiles_m);
-}
-
 // ---------------------------------------------------------------------------------- host side
 
 bool always_legal(const Problem &p, int split_k, int64_t)
@@ -160,23 +134,6 @@ bool scale_legal(const Problem &p, int split_k, int64_t)
     return split_k == 1 && p.fringe_m == 0 && p.fringe_n == 0 && p.clip_m == 0 && p.clip_n == 0 && (p.alpha == 0.f || p.k == 0) && ceil_div(p.m, 256) < (int64_t(1) << 31);
 }
 
-template <typename T> bool batched_direct_legal(const BatchedProblem &p)
-{
-    return p.dtype == (sizeof(T) == 4 ? MG_F32 : MG_F16) && ceil_div(p.m, DT) * ceil_div(p.n, DT) * p.batch < (int64_t(1) << 31);
-}
-
-template <typename T> hipError_t launch_batched_direct(const BatchedProblem &p)
-{
-    const int64_t tiles_m = ceil_div(p.m, DT), tiles_n = ceil_div(p.n, DT);
-    const int64_t tiles = tiles_m * tiles_n;
-    hipLaunchKernelGGL(direct_batched_kernel<T>, dim3(static_cast<unsigned>(tiles * p.batch)), dim3(256), 0, p.stream,
-                       p.m, p.n, p.k, static_cast<const T *>(p.A), p.a_off, p.a_trans ? p.lda : 1, p.a_trans ? 1 : p.lda,
-                       static_cast<const T *>(p.B), p.b_off, p.b_trans ? p.ldb : 1, p.b_trans ? 1 : p.ldb,
-                       static_cast<T *>(p.C), p.c_off, p.ldc, p.alphas, p.betas,
-                       tiles_m, tiles, p.strided ? 1 : 0, p.stride_a, p.stride_b, p.stride_c, p.alpha, p.beta);
-    return hipGetLastError();
-}
-
 mg_config make_cfg(int family, int dtype, int tm, int tn, int tk, int lds)
 {
     mg_config c{};
@@ -206,10 +163,6 @@ void register_direct(std::vector<KernelEntry> &table)
                      launch_scale<float>, nullptr, nullptr});
     table.push_back({"scale_f16", make_cfg(MG_FAMILY_SCALE, MG_F16, 256, 1, 0, 0), scale_legal, no_workspace,
                      launch_scale<_Float16>, nullptr, nullptr});
-    table.push_back({"batched_direct_f32_64x64x16", make_cfg(MG_FAMILY_BATCHED, MG_F32, DT, DT, DK, lds), nullptr,
-                     nullptr, nullptr, batched_direct_legal<float>, launch_batched_direct<float>});
-    table.push_back({"batched_direct_f16_64x64x16", make_cfg(MG_FAMILY_BATCHED, MG_F16, DT, DT, DK, lds), nullptr,
-                     nullptr, nullptr, batched_direct_legal<_Float16>, launch_batched_direct<_Float16>});
 }
 
 }  // namespace mg

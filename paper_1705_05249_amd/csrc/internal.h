@@ -147,6 +147,7 @@ void register_direct(std::vector<KernelEntry> &table);
 void register_mfma(std::vector<KernelEntry> &table);
 void register_gemv(std::vector<KernelEntry> &table);
 void register_batched(std::vector<KernelEntry> &table);
+void register_batched_tile(std::vector<KernelEntry> &table);
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

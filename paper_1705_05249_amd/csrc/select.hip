@@ -376,12 +376,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
 
 int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProblem &p)
 {
-    // one wavefront per instance while the instance fits the register blocks (<= 64 in every extent); with
-    // more 16^3 instances than wavefronts fit on the chip at once (256 compute units x 32), two per wavefront:
-    // measured 7.0 -> 6.4 us (FP32) and 5.3 -> 4.7 us (FP16) for 10000 instances, no gain from four, a loss
-    // below ~4000 instances
-    static const char *const few[] = {"batched_wave_16", "batched_wave_32", "batched_wave_64w1"};
-    static const char *const many[] = {"batched_wave_16x2", "batched_wave_32", "batched_wave_64w1"};
+    // One wavefront per instance while the instance fits the register blocks (<= 32 in every extent); with more 16^3
+    // instances than wavefronts fit on the chip at once (256 compute units x 32), two per wavefront: measured 7.0 -> 6.4 us
+    // (FP32) and 5.3 -> 4.7 us (FP16) for 10000 instances, no gain from four, a loss below ~4000 instances
     // (FP32 instances smaller than 16^3 take the bounds-checked flavour, which gains nothing from the second
     // instance: 10000 x 8^3 5.5 us one per wavefront, 5.9 us two)
     const bool whole16 = p.m == 16 && p.n == 16 && p.k == 16;
@@ -391,8 +388,7 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
     // 505 MB: 141.0 / 122.5).
     const double operand_bytes = static_cast<double>(p.batch) * static_cast<double>(p.m * p.k + p.k * p.n + p.m * p.n) * (p.dtype == MG_F32 ? 4.0 : 2.0);
     const bool streams_from_hbm = p.dtype == MG_F32 && operand_bytes > 410.0e6;
-    const char *const *tags = p.batch >= 32 * kComputeUnits && !streams_from_hbm &&
-                              (p.dtype != MG_F32 || whole16 || p.m > 16 || p.n > 16 || p.k > 16) ? many : few;
+    const bool pairs = p.batch >= 32 * kComputeUnits && !streams_from_hbm && (p.dtype != MG_F32 || whole16);
     const char *prefix = p.dtype == MG_F32 ? "" : "h";
     const char *contig = p.a_trans ? (p.b_trans ? "kn" : "kk") : (p.b_trans ? "mn" : "mk");
     // whole 64^3 instances with A along m and B along k: the kernels whose lanes are rows of C ask for A, B and C in whole
@@ -403,18 +399,36 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         const int32_t id = find(table, name);
         if (id >= 0 && table[id].legal_batched(p)) return id;
     }
-    for (int t = 0; t < 3; ++t) {
-        const char *tag = tags[t];
+    auto take = [&](const char *tag, const char *suffix) {
         char name[96];
-        snprintf(name, sizeof name, "%s%s_%s_full", prefix, tag, contig);
-        int32_t id = find(table, name);
-        if (id >= 0 && table[id].legal_batched(p)) return id;
-        snprintf(name, sizeof name, "%s%s_%s", prefix, tag, contig);
-        id = find(table, name);
-        if (id >= 0 && table[id].legal_batched(p)) return id;
+        snprintf(name, sizeof name, "%s%s_%s%s", prefix, tag, contig, suffix);
+        const int32_t id = find(table, name);
+        return id >= 0 && table[id].legal_batched(p) ? id : -1;
+    };
+    // (FP32 instances that fill the 32 x 32 block and stream from memory lose more to the one-wavefront kernel's 4-byte and
+    // unaligned requests than its shorter latency chain gains: 31^3, four operand orders, LDS-staged / one wavefront: 10000
+    // instances 28 / 35 us, 1000 instances 6.6 / 5.8 us; 28^3 24.5 / 21-25 us, FP16 31^3 26-34 / 20-24 us; whole 32^3 with A along m
+    // and B along k 25.7 / 24.6 us)
+    const bool filled = p.dtype == MG_F32 && p.m > 28 && p.n > 28 && p.k > 28 && p.m <= 32 && p.n <= 32 && p.k <= 32 && p.batch >= 4096;
+    for (const char *tag : {pairs ? "batched_wave_16x2" : "batched_wave_16", "batched_wave_32"}) {
+        int32_t id = take(tag, "_full");
+        if (id < 0 && !filled) id = take(tag, "");
+        if (id >= 0) return id;
     }
-    const int32_t id = find(table, p.dtype == MG_F32 ? "batched_direct_f32_64x64x16" : "batched_direct_f16_64x64x16");
-    if (id >= 0 && table[id].legal_batched(p)) return id;
+    // LDS-staged tiles.  A longer sum with at most 32 x 32 outputs: one wavefront per instance (24 x 16 x 40, 6300 FP32
+    // instances: 13 us against 17 us with four).  Else four wavefronts on a 64 x 64 tile, or on 32 x 64 where that pads less: FP32
+    // 93^3 (856 instances) 31 us on 32 x 64, 39 us on 64 x 64; 64^3 (5000) 73 / 69 us; 99^3 201 / 191 us; FP16 19 x 80 x 144
+    // (2100) 23 / 25 us, 81^3 (800) 17 / 15 us, 37^3 (2300) 15 / 12 us: FP16, whose loads are the smaller part, only below 33 rows.
+    // (96 x 64, 128 x 64 and 128 x 128 tiles, whose teams leave fewer work-groups to overlap: 10-60 % slower on most of these.)
+    const bool thin = p.dtype == MG_F32 ? ceil_div(p.m, 32) % 2 != 0 : p.m <= 32;
+    if (p.m <= 32 && p.n <= 32) {
+        const int32_t id = take("batched_tile_32x32", "");
+        if (id >= 0) return id;
+    }
+    for (const char *tag : {thin ? "batched_tile_32x64" : "batched_tile_64x64", "batched_tile_64x64"}) {
+        const int32_t id = take(tag, "");
+        if (id >= 0) return id;
+    }
     return -1;
 }
 
