@@ -7,13 +7,14 @@
 //   n == 1:  Mat = op(A) (o = row i),  vec = column 0 of op(B),  out = column 0 of C
 //   m == 1:  Mat = op(B)^T (o = column j),  vec = row 0 of op(A),  out = row 0 of C
 //
-// Two kernels by how the matrix lies in memory:
+// Kernels by how the matrix lies in memory:
 //   dot   Mat(o, .) contiguous along l: one wavefront per output (four outputs when there are
 //         thousands of them), lanes stride over l with 16-byte loads (issued at element alignment:
 //         rows of a padded matrix are not 16-byte aligned), cross-lane sum at the end;
 //   axpy  Mat(., l) contiguous along o: a work-group owns 64 x (16 bytes / element size)
 //         consecutive outputs, each lane a 16-byte run of them; its four wavefronts take
-//         l = w, w+4, ... with eight loads in flight per lane and meet in LDS.
+//         l = w, w+4, ... with eight loads in flight per lane and meet in LDS;
+//   panel the same order, with a work-group on fewer outputs and more of the sum.
 // Few outputs and a long sum leave most compute units idle, so both kernels can cut the sum into
 // `split` slices (grid.y): each slice writes FP32 partial sums to the workspace and a small
 // second kernel adds them and applies alpha and beta.
@@ -187,6 +188,93 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
     }
 }
 
+// axpy order with few outputs: the kernel above gives a work-group 64 x 16 bytes of outputs, so 4096 of them make sixteen work-groups
+// and the sum must be cut into slices, with partial sums through memory and a second launch.  Here LR lanes side by side take a
+// run of LR x 16 bytes of a column, the other 64 / LR lanes of the wavefront the next columns, and sixteen wavefronts share
+// the sum of one work-group; lanes, then wavefronts (through LDS), are added at the end.
+// STREAM: non-temporal loads, see gemv_launch.
+template <typename T, int LR, bool STREAM>
+__global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64_t k, int64_t k_per_split,
+                                                           const T *__restrict__ mat, int64_t stride_l,
+                                                           const T *__restrict__ vec, int64_t stride_v,
+                                                           T *__restrict__ out, int64_t stride_out,
+                                                           float *__restrict__ partial, float alpha, float beta)
+{
+    constexpr int V = 16 / static_cast<int>(sizeof(T));
+    constexpr int OB = LR * V;                      // outputs per work-group
+    constexpr int CL = 64 / LR;                     // columns per wavefront and load instruction
+    constexpr int WAVES = 16;
+    constexpr int U = 8;                            // load instructions in flight per wavefront
+    constexpr int STEP = WAVES * CL;
+    using Vec = PackedVec<T, V>;
+    __shared__ float part[WAVES][OB];
+    auto load = [](const T *p) {
+        if constexpr (STREAM) return stream_load<T, V>(p);
+        else return *reinterpret_cast<const Vec *>(p);
+    };
+    const int lane = threadIdx.x % 64;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    // neighbours in memory on the same XCD: they share cache lines
+    const int xcd = blockIdx.x % 8, q = gridDim.x / 8, rem = gridDim.x % 8;
+    const int group = xcd * q + (xcd < rem ? xcd : rem) + blockIdx.x / 8;
+    const int64_t first = static_cast<int64_t>(group) * OB;
+    const int64_t o = first + lane % LR * V;
+    const int64_t k0 = static_cast<int64_t>(blockIdx.y) * k_per_split;
+    const int64_t k1 = k0 + k_per_split < k ? k0 + k_per_split : k;
+    float acc[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) acc[e] = 0.f;
+    int64_t l = k0 + w * CL + lane / LR;
+    if (o + V <= outputs) {
+        const T *__restrict__ col = mat + o;
+        for (; l + STEP * (U - 1) < k1; l += STEP * U) {
+            Vec a[U];
+            T x[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a[u] = load(col + (l + STEP * u) * stride_l);
+                x[u] = vec[(l + STEP * u) * stride_v];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < V; ++e) acc[e] = fmaf(static_cast<float>(a[u].v[e]), static_cast<float>(x[u]), acc[e]);
+        }
+#pragma unroll 2
+        for (; l < k1; l += STEP) {
+            const Vec a = load(col + l * stride_l);
+            const float x = static_cast<float>(vec[l * stride_v]);
+#pragma unroll
+            for (int e = 0; e < V; ++e) acc[e] = fmaf(static_cast<float>(a.v[e]), x, acc[e]);
+        }
+    } else if (o < outputs) {
+        // the ragged last run of outputs: element by element
+        for (; l < k1; l += STEP) {
+            const float x = static_cast<float>(vec[l * stride_v]);
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+                if (o + e < outputs) acc[e] = fmaf(static_cast<float>(mat[o + e + l * stride_l]), x, acc[e]);
+        }
+    }
+#pragma unroll
+    for (int off = LR; off < 64; off *= 2)
+#pragma unroll
+        for (int e = 0; e < V; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
+    if (lane < LR) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) part[w][lane * V + e] = acc[e];
+    }
+    __syncthreads();
+    const int i = threadIdx.x;
+    if (i < OB && first + i < outputs) {
+        float s = 0.f;
+#pragma unroll
+        for (int z = 0; z < WAVES; ++z) s += part[z][i];
+        if (partial != nullptr) partial[static_cast<int64_t>(blockIdx.y) * outputs + first + i] = s;
+        else finish(out + (first + i) * stride_out, s, alpha, beta);
+    }
+}
+
 // out[o] <- alpha * sum_z partial[z][o] + beta * out[o]: 16 outputs per work-group, 16 threads share the
 // slices of each output
 template <typename T>
@@ -240,12 +328,12 @@ View view_of(const Problem &p)
     return v;
 }
 
-// R: rows per wavefront of the dot kernel; 0 selects the axpy kernel
+// R > 0: rows per wavefront of the dot kernel; R = 0: the axpy kernel; R < 0: the panel kernel with LR = -R
 template <typename T, int R> struct GemvShape {
     static constexpr bool DOT = R > 0;
     static constexpr int V = 16 / static_cast<int>(sizeof(T));
-    static constexpr int OUTPUTS_PER_GROUP = DOT ? 4 * R : 64 * V;
-    static constexpr int K_GRAIN = DOT ? 64 * V : 32;          // one round of loads of a work-group
+    static constexpr int OUTPUTS_PER_GROUP = DOT ? 4 * R : (R < 0 ? -R : 64) * V;
+    static constexpr int K_GRAIN = DOT ? 64 * V : (R < 0 ? 1024 / (R < 0 ? -R : 1) : 32);          // one round of loads of a work-group
     static int64_t k_per_split(const Problem &p, int split) { return ceil_div(ceil_div(p.k, split), K_GRAIN) * K_GRAIN; }
 };
 
@@ -276,6 +364,14 @@ template <typename T, int R> hipError_t gemv_launch(const Problem &p, int split)
                            S::k_per_split(p, split), static_cast<const T *>(v.mat), v.stride_o,
                            static_cast<const T *>(v.vec), v.stride_v, static_cast<T *>(p.C), v.stride_out, partial,
                            p.alpha, p.beta);
+    } else if constexpr (R < 0) {
+        // A matrix that the last-level cache (256 MB) can still hold from an earlier call or from the kernel that wrote it is read
+        // with plain loads, a larger one as a stream: three FP32 matrices in turn, us plain / streamed: 4096^2 (67 MB) 13.0 / 14.2,
+        // 4160 x 4096 11.7 / 14.1, 5120^2 (105 MB) 20.0 / 19.8, 8192^2 45.5 / 42.8, 65536 x 2048 91 / 80
+        const bool stream = static_cast<double>(v.outputs) * static_cast<double>(v.k) * sizeof(T) > 96.0e6;
+        hipLaunchKernelGGL((stream ? gemv_panel_kernel<T, -R, true> : gemv_panel_kernel<T, -R, false>), grid, dim3(1024), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
+                           static_cast<const T *>(v.mat), v.stride_l, static_cast<const T *>(v.vec), v.stride_v,
+                           static_cast<T *>(p.C), v.stride_out, partial, p.alpha, p.beta);
     } else {
         hipLaunchKernelGGL(gemv_axpy_kernel<T>, grid, dim3(256), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
                            static_cast<const T *>(v.mat), v.stride_l, static_cast<const T *>(v.vec), v.stride_v,
@@ -298,11 +394,11 @@ template <typename T, int R> KernelEntry gemv_entry(const char *name)
     c.tile_m = S::OUTPUTS_PER_GROUP;
     c.tile_n = 1;
     c.tile_k = S::K_GRAIN;
-    c.waves_m = 4;
+    c.waves_m = R < 0 ? 16 : 4;
     c.waves_n = 1;
     c.split_k = 1;
-    c.threads = 256;
-    c.lds_bytes = R > 0 ? 0 : 4 * 64 * S::V * 4;
+    c.threads = R < 0 ? 1024 : 256;
+    c.lds_bytes = R > 0 ? 0 : c.waves_m * S::OUTPUTS_PER_GROUP * 4;
     return KernelEntry{name, c, gemv_legal<T, R>, gemv_workspace, gemv_launch<T, R>, nullptr, nullptr};
 }
 
@@ -313,9 +409,15 @@ void register_gemv(std::vector<KernelEntry> &table)
     table.push_back(gemv_entry<float, 1>("gemv_dot_f32"));
     table.push_back(gemv_entry<float, 4>("gemv_dot4_f32"));
     table.push_back(gemv_entry<float, 0>("gemv_axpy_f32"));
+    table.push_back(gemv_entry<float, -4>("gemv_panel4_f32"));
+    table.push_back(gemv_entry<float, -8>("gemv_panel8_f32"));
+    table.push_back(gemv_entry<float, -16>("gemv_panel16_f32"));
     table.push_back(gemv_entry<_Float16, 1>("gemv_dot_f16"));
     table.push_back(gemv_entry<_Float16, 4>("gemv_dot4_f16"));
     table.push_back(gemv_entry<_Float16, 0>("gemv_axpy_f16"));
+    table.push_back(gemv_entry<_Float16, -4>("gemv_panel4_f16"));
+    table.push_back(gemv_entry<_Float16, -8>("gemv_panel8_f16"));
+    table.push_back(gemv_entry<_Float16, -16>("gemv_panel16_f16"));
 }
 
 }  // namespace mg

@@ -106,6 +106,48 @@ int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t wor
     return split < 1 ? 1 : static_cast<int>(split);
 }
 
+// Matrix-vector product whose matrix lies along the outputs: the kernel and its slices.  us, FP32 unless said, axpy kernel (with
+// its slices) / panel kernel:
+//   a sum of at most 2560 terms (4224 where the columns do not lie a multiple of 4 KB apart) needs no second launch: 1024^2
+//   11.7 / 8.2, 2048^2 11.3 / 9.7, 6144 x 3072 15.0 / 14.0, 4160 x 4096 14.3 / 11.7, FP16 11.8 / 9.2 (3072 x 6144 unsliced: 17.7);
+//   else one work-group of sixteen wavefronts per compute unit: 4096^2 20.8 / 13.1, 4097 x 4095 16.7 / 14.2, 1024 x 16384
+//   14.7 / 13.0, FP16 4096^2 11.7 / 10.8;
+//   matrices beyond 96 MB, which stream from memory, only with a long sum and columns a multiple of 4 KB apart (four work-groups
+//   per compute unit): 8192^2 55 / 46, 16384 x 4096 48.7 / 42.8, 2048 x 16384 33 / 27, FP16 8192^2 33 / 26; without:
+//   7000^2 35.0 / 35.2, 10000^2 65.7 / 73.7, 65536 x 1024 41 / 44; and beyond 384 MB not even then: 12288^2 95 / 112,
+//   16384^2 163 / 177;
+//   the axpy kernel also where its work-groups fill the chip by themselves (10^6 x 64: 40 / 66).
+void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
+                             int32_t *kernel, int32_t *split)
+{
+    const bool f32 = p.dtype == MG_F32;
+    const int64_t outputs = p.m * p.n, lane_elems = 16 / static_cast<int64_t>(p.elem());
+    const double bytes = static_cast<double>(outputs) * static_cast<double>(p.k) * static_cast<double>(p.elem());
+    const int64_t stride = (p.n == 1 ? p.a_sk() : p.b_sk()) * static_cast<int64_t>(p.elem());
+    const char *axpy = f32 ? "gemv_axpy_f32" : "gemv_axpy_f16";
+    const bool streams = bytes > 96.0e6;
+    if (bytes > 384.0e6 || (streams && (p.k <= 2560 || stride % 4096 != 0)) || outputs >= 64 * lane_elems * kComputeUnits) {
+        if (!try_pick(table, p, alignment, axpy, 1, kernel, split)) return;
+        const int want = pick_gemv_split(table[*kernel].cfg, outputs, p.k, workspace_bytes);
+        if (want > 1) try_pick(table, p, alignment, axpy, want, kernel, split);
+        return;
+    }
+    auto panel = [&](int lanes, int slices) {
+        char name[32];
+        snprintf(name, sizeof name, "gemv_panel%d_%s", lanes, f32 ? "f32" : "f16");
+        return try_pick(table, p, alignment, name, slices, kernel, split);
+    };
+    if (p.k > 2560 && !(p.k <= 4224 && stride % 4096 != 0 && outputs >= 64 * 8 * lane_elems)) {
+        const int64_t groups = ceil_div(outputs, 16 * lane_elems);
+        int64_t slices = ceil_div((streams ? 4 : 1) * kComputeUnits, groups);
+        if (slices > p.k / 512) slices = p.k / 512;             // one round of a work-group's loads per slice
+        const int64_t fits = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(outputs) * sizeof(float)));
+        if (slices > fits) slices = fits;
+        if (slices > 1 && panel(16, static_cast<int>(slices))) return;
+    }
+    panel(outputs >= 64 * 8 * lane_elems ? 8 : 4, 1);
+}
+
 }  // namespace
 
 void select_config(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
@@ -122,14 +164,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         // short rows, thousands of them: four rows per wavefront keep enough loads in flight (long rows a power
         // of two apart are slower that way than one by one)
         const bool many = p.m * p.n >= 16 * kComputeUnits && p.k * static_cast<int64_t>(p.elem()) <= 4096;
-        const char *names[2] = {f32 ? (many ? "gemv_dot4_f32" : "gemv_dot_f32") : (many ? "gemv_dot4_f16" : "gemv_dot_f16"),
-                                f32 ? "gemv_axpy_f32" : "gemv_axpy_f16"};
-        for (const char *name : names) {
-            if (!try_pick(table, p, alignment, name, 1, kernel, split)) continue;
+        const char *dot = f32 ? (many ? "gemv_dot4_f32" : "gemv_dot_f32") : (many ? "gemv_dot4_f16" : "gemv_dot_f16");
+        if (try_pick(table, p, alignment, dot, 1, kernel, split)) {
             const int want = pick_gemv_split(table[*kernel].cfg, p.m * p.n, p.k, workspace_bytes);
-            if (want > 1) try_pick(table, p, alignment, name, want, kernel, split);
-            return;
+            if (want > 1) try_pick(table, p, alignment, dot, want, kernel, split);
+        } else {
+            pick_gemv_along_outputs(table, p, alignment, workspace_bytes, kernel, split);
         }
+        if (*kernel >= 0) return;
     }
     // Problems of at most one 32 x 32 block per compute unit and a short sum: the kernel whose eight wavefronts share
     // the sum of one block (tiny.hip) beats the macro tiles' software pipeline, which never fills, and saves the
