@@ -77,6 +77,7 @@ struct MfmaArgs {
     int group_m;           // tile rasterisation: tiles are walked in column groups of this many rows
     int shape;             // ProblemShape: K range per tile narrowed to the non-zero part / tiles outside C's triangle skipped
     int reversed;          // walk the tiles in reverse order (longest K ranges first)
+    int early_c;           // ask for the old C before the K loop (SHORT kernels)
     int mask;              // with shape C_LOWER / C_UPPER: write (and read) nothing outside that triangle of C
     ConvGeom conv;         // kernels built with CONV: A is the image, op(A) its column matrix (m = oh * ow positions)
 };
@@ -594,9 +595,37 @@ constexpr int share_begin(int slot, int total, int slots) { return slot * total 
 // Only this wavefront touches its region and the LDS executes a wavefront's operations in order, so the
 // two phases need no barrier, only a fence that keeps the compiler from moving one lane's reads across
 // the writes other lanes depend on.  The caller has made sure that nobody still uses the LDS.
-template <typename T, int RB, int FM, int FN, int WTM, int WTN, bool EDGE>
+//
+// EarlyC: the wavefront tile's pieces of the old C, asked for before the K loop by kernels whose sum may be so short that
+// the traffic of C is what bounds them (`held` is the same for the whole grid; pieces that end inside the matrix are
+// read in the epilogue as without it).
+template <typename T, int WTM, int WTN, bool EDGE> struct EarlyC {
+    static constexpr int PER = 16 / static_cast<int>(sizeof(T));
+    static constexpr int CPRW = WTM / PER, COLS = 64 / CPRW, PASSES = 32 / COLS, NBLK = WTN / 32;
+    Pack<T, PER> v[NBLK][PASSES];
+    bool held;
+    __device__ inline void fetch(const MfmaArgs &args, int64_t m0, int64_t n0, int wm, int wn, int lane)
+    {
+        held = args.early_c != 0;
+        if (!held) return;
+        const T *C = static_cast<const T *>(args.C);
+        const int64_t gm = m0 + wm * WTM + lane % CPRW * PER;
+#pragma unroll
+        for (int j = 0; j < NBLK; ++j)
+#pragma unroll
+            for (int pass = 0; pass < PASSES; ++pass) {
+                const int64_t gn = n0 + wn * WTN + j * 32 + lane / CPRW + pass * COLS;
+                if (!EDGE || (gn < args.n_main && args.m_main - gm >= PER)) v[j][pass] = *reinterpret_cast<const Pack<T, PER> *>(C + gm + gn * args.ldc);
+            }
+    }
+};
+struct NoEarlyC {
+    static constexpr bool held = false;
+};
+
+template <typename T, int RB, int FM, int FN, int WTM, int WTN, bool EDGE, typename Early = NoEarlyC>
 __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM], const MfmaArgs &args, char *lds,
-                                     int64_t m0, int64_t n0, int wm, int wn, int wave, int lane)
+                                     int64_t m0, int64_t n0, int wm, int wn, int wave, int lane, const Early &early = {})
 {
     constexpr int NBLK = WTN / 32;                     // 32-column blocks of the wavefront tile
     const int wm_u = __builtin_amdgcn_readfirstlane(wm), wn_u = __builtin_amdgcn_readfirstlane(wn);
@@ -659,7 +688,7 @@ __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM],
                 const floatx4 x = *reinterpret_cast<const floatx4 *>(region + r * ROWB + (c * PER + 4 * h) * 4);
                 v[4 * h] = x.x; v[4 * h + 1] = x.y; v[4 * h + 2] = x.z; v[4 * h + 3] = x.w;
             }
-            if (valid > first) emit(base + gm + gn * ld, v, first, valid);
+            if (valid > first) emit(base + gm + gn * ld, v, first, valid, j, pass);
         }
     };
 
@@ -668,7 +697,7 @@ __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM],
 #pragma unroll
         for (int j = 0; j < NBLK; ++j) {
             stage_block(j);
-            drain_block(base, static_cast<int64_t>(args.m), j, [](float *p, const float (&v)[4], int first, int valid) {
+            drain_block(base, static_cast<int64_t>(args.m), j, [](float *p, const float (&v)[4], int first, int valid, int, int) {
                 if (first == 0 && valid == 4) *reinterpret_cast<Pack<float, 4> *>(p) = Pack<float, 4>{{v[0], v[1], v[2], v[3]}};
                 else {
 #pragma unroll
@@ -680,11 +709,14 @@ __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM],
     } else {
         constexpr int PER = 16 / static_cast<int>(sizeof(T));
         T *base = static_cast<T *>(args.C);
-        auto emit = [alpha, beta](T *p, const float (&v)[PER], int first, int valid) {
+        auto emit = [alpha, beta, &early](T *p, const float (&v)[PER], int first, int valid, int j, int pass) {
             if (first == 0 && valid == PER) {
                 Pack<T, PER> o;
                 if (beta != 0.f) {
-                    const Pack<T, PER> c = *reinterpret_cast<const Pack<T, PER> *>(p);
+                    Pack<T, PER> c;
+                    if constexpr (std::is_same_v<Early, NoEarlyC>) c = *reinterpret_cast<const Pack<T, PER> *>(p);
+                    else if (early.held) c = early.v[j][pass];
+                    else c = *reinterpret_cast<const Pack<T, PER> *>(p);
 #pragma unroll
                     for (int e = 0; e < PER; ++e) o.v[e] = static_cast<T>(fmaf(beta, static_cast<float>(c.v[e]), alpha * v[e]));
                 } else {
@@ -759,7 +791,11 @@ template <int NT, bool A_KCONTIG, bool B_KCONTIG> __device__ inline void fringe_
 // how a K-tile body reloads the staging registers: bounds-checked loads, the fast flavour's loads, or not at all
 constexpr int LOADS_CHECKED = 0, LOADS_FAST = 1, LOADS_NONE = 2;
 
-template <typename T, int BM, int BN, int BK, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, bool EDGE, int RB = 32, bool CONV = false>
+// SHORT: for sums of a few K-tiles, where the traffic of C and of the first tiles is the time: the old C is asked for before the K
+// loop, and nothing is reloaded past the end of the sum.  (8192, 8192, 64) with beta = 1 and odd leading dimensions
+// 185 -> 147 us on 128 x 64 tiles, beta = 0 with even ones 129 -> 125 us, (8192, 8192, 128) 235 -> 216 us.  A kernel of its own: the
+// registers that hold C cost long sums 1.5-2 % on 64 x 64 tiles.
+template <typename T, int BM, int BN, int BK, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, bool EDGE, int RB = 32, bool CONV = false, bool SHORT = false>
 __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs args)
 {
     constexpr int NT = WM * WN * 64;
@@ -850,6 +886,9 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
 #pragma unroll
             for (int r = 0; r < static_cast<int>(sizeof(Acc) / 4); ++r) acc[j][i][r] = 0.f;
 
+    [[maybe_unused]] std::conditional_t<SHORT, EarlyC<T, WTM, WTN, EDGE>, NoEarlyC> early;
+    if constexpr (SHORT) early.held = false;
+
     LoadA la;
     LoadB lb;
     const int ktiles = (ke - kb + BK - 1) / BK;
@@ -898,6 +937,7 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
         aim_tile(1);
         la.load_all();
         lb.load_all();
+        if constexpr (SHORT) early.fetch(args, m0, n0, __builtin_amdgcn_readfirstlane(wm), __builtin_amdgcn_readfirstlane(wn), lane);
         __syncthreads();
         static_for<FRAGS>([&](auto F) { read_frag(F, Stage0{}, 0, 0); });
     }
@@ -1021,6 +1061,21 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
         }
         if (left >= 1) tile_body(Stage0{}, None{}, t);
         if (left >= 2) tile_body(Stage1{}, None{}, t + 1);
+    } else if constexpr (SHORT) {
+        // nothing is reloaded in the last two bodies: of a sum of two K-tiles that is all of the reload traffic
+        for (; t + 3 < ktiles; t += 2) {
+            tile_body(Stage0{}, Checked{}, t);
+            tile_body(Stage1{}, Checked{}, t + 1);
+        }
+        int left = ktiles - t;                     // 0 .. 3
+        if (left == 3) {
+            tile_body(Stage0{}, Checked{}, t);
+            tile_body(Stage1{}, None{}, t + 1);
+            tile_body(Stage0{}, None{}, t + 2);
+            left = 0;
+        }
+        if (left >= 1) tile_body(Stage0{}, None{}, t);
+        if (left >= 2) tile_body(Stage1{}, None{}, t + 1);
     } else {
         for (; t + 1 < ktiles; t += 2) {
             tile_body(Stage0{}, Checked{}, t);
@@ -1030,7 +1085,7 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
     }
 
     __syncthreads();                                   // every wavefront is done reading the operand stages
-    tile_epilogue<T, RB, FM, FN, WTM, WTN, EDGE>(acc, args, lds, m0, n0, wm, wn, wave, lane);
+    tile_epilogue<T, RB, FM, FN, WTM, WTN, EDGE>(acc, args, lds, m0, n0, wm, wn, wave, lane, early);
 }
 
 // C <- alpha * sum_z partial[z] + beta * C   (finishes a split-K product).  A thread takes V consecutive

@@ -352,10 +352,21 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             int free_slices = 0;
             for (int i = 0; i < count; ++i) {
                 if (tried[i]) continue;
-                // FP32 with a very short K is bound by the traffic of C, which the large tiles overlap worst (one
-                // epilogue per compute unit at a time): (8192, 8192, 64) with beta = 1 takes 223 us on 256 x 256
-                // tiles, 155-175 us on 64 x 64
+                // FP32 with a short K is bound by the traffic of C, which the large tiles overlap worst (one epilogue per
+                // compute unit at a time).  us, the tile the estimate would take (256 x 256 or 128 x 128) / 128 x 64 / 64 x 64,
+                // beta != 0: (8192, 8192, 64) 200 / 154 / 157, (8192, 8192, 256) 351 / 310 / 322, (8192, 8192, 512) 574 / 534 / 551,
+                // (4096, 4096, 160) 60 / 59 / 54, (3000, 3000, 256) 67 / 53 / 47, (2048, 2048, 512) 41 / 40 / 36, (5000, 5000,
+                // 64) - / 69 / 70; beta = 0: (2048, 2048, 160) 18.1 / 17.4 / 16.7, (3000, 3000, 160) 43 / 38 / 33, from
+                // k = 256 on within 2 %; ragged problems of several turns whose 128 x 64 tiles need no more of them stay
+                // on those: (1393, 4318, 136) 31.3 / 33.9 (five turns against nine: (3000, 3000, 160) above)
                 if (f32 && p.k <= 128 && tiles[i].bm * tiles[i].bn > 128 * 64) continue;
+                if (f32 && p.shape == MG_SHAPE_GENERAL && p.k <= (p.beta != 0.f ? 512 : 192)) {
+                    const int64_t turns64 = ceil_div(ceil_div(tm, 64) * ceil_div(tn, 64), kComputeUnits);
+                    const int64_t turns128 = ceil_div(ceil_div(tm, 128) * ceil_div(tn, 64), kComputeUnits);
+                    const bool whole = tm % 128 == 0 && tn % 64 == 0 && p.k % 32 == 0;
+                    const bool wide = whole ? p.m * p.n > 25000000 : p.k > 128 && turns64 >= 6 && 2 * turns128 <= turns64;
+                    if (tiles[i].bm * tiles[i].bn > (wide ? 128 * 64 : 64 * 64)) continue;
+                }
                 const bool last = i == count - 1;
                 const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
                 const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn);
