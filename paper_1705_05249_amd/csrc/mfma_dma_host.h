@@ -9,10 +9,12 @@ namespace mg {
 
 // CLIP: the flavour for operands padded to whole tiles in a workspace and the caller's own C (Problem::clip_m, clip_n):
 // its epilogue is the bounds-checked one, so the padded product needs no copy of C in and out.
-template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int RB = 32, bool CLIP = false> struct MfmaDmaConfig {
+template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int RB = 32, bool CLIP = false, int STAGES = 2> struct MfmaDmaConfig {
     using Staged = MfmaConfig<_Float16, BM, BN, 64, WM, WN, AK, BKC, false>;   // same legality and split-K rules
     static constexpr int NT = WM * WN * 64;
-    static constexpr int LDS = Staged::LDS;
+    static constexpr int STAGE_BYTES = (BM + BN) * 128;
+    static constexpr int LDS = STAGES * STAGE_BYTES > Staged::LDS ? STAGES * STAGE_BYTES : Staged::LDS;
+    static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
 
     // the direct-to-LDS loads keep the 16-byte alignment of whole chunks
     static bool legal(const Problem &p, int split, int64_t alignment)
@@ -31,13 +33,14 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int RB = 32, bool C
     static hipError_t launch(const Problem &p, int split)
     {
         static bool attr_set = false;   // raising the dynamic LDS limit is idempotent; races are harmless
-        return launch_tile_kernel<_Float16>(hgemm_dma_kernel<BM, BN, WM, WN, AK, BKC, RB, 0, CLIP>, &attr_set, LDS, NT, BM, BN,
+        return launch_tile_kernel<_Float16>(hgemm_dma_kernel<BM, BN, WM, WN, AK, BKC, RB, 0, CLIP, STAGES>, &attr_set, LDS, NT, BM, BN,
                                             Staged::k_per_split(p, split), p, split);
     }
 
     static KernelEntry entry(const char *name)
     {
         KernelEntry e = Staged::entry(name);
+        e.cfg.lds_bytes = LDS;
         e.legal = legal;
         e.launch = launch;
         return e;

@@ -23,7 +23,8 @@
 // Both forms give lane l the eight k values (512 / RB) s + 8 (l / RB) + 0..7 of row l % RB in K-step s (RB = 32 or
 // 16 rows per fragment).
 //
-// Pipeline: two LDS stages.  During K-tile t (read from stage t % 2) the loads of tile t + 1 into the other
+// Pipeline with two LDS stages (more stages: the loads are those of tile t + STAGES - 1, into the stage of tile t - 1, and the wait
+// leaves the loads of the tiles behind t + 1 in flight).  During K-tile t (read from stage t % 2) the loads of tile t + 1 into the other
 // stage are issued in the first slots; every wavefront waits for its own loads just before the single barrier
 // of the tile, which sits inside the last K-step: at that point every wavefront has finished reading stage
 // t % 2 (the operands of the last step are in registers), so the loads of tile t + 2 may overwrite it right
@@ -93,18 +94,34 @@ template <int ROWS, int NT, bool KCONTIG, int RB = 32> struct DmaLoader {
 // read does not touch the stage the load writes), which put the full memory latency of every load into the K
 // loop.  The price: the compiler does not know that these registers are written later, by the LDS, so the
 // kernel itself waits (wait_fragments) before the first MFMA of every K-step.
-template <bool KCONTIG, int ROWS, int F, int RB, int S, int STAGE>
+// 16-byte LDS read the compiler's wait-count bookkeeping does not see (the kernel waits itself): a visible LDS
+// read that follows a direct-to-LDS load in program order can draw a wait for that load.
+template <int OFFSET> __device__ inline u32x4 lds_read_b128_untracked(uint32_t at)
+{
+    static_assert(OFFSET >= 0 && OFFSET < 65536, "LDS instruction offsets have 16 bits");
+    u32x4 r;
+    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(r) : "v"(at), "n"(OFFSET) : "memory");
+    return r;
+}
+
+// UNTRACKED: the k-contiguous form as inline assembly too (kernels with loads of several K-tiles in flight).  What of STAGE the
+// instruction's offset field cannot hold is added to the address.
+template <bool KCONTIG, int ROWS, int F, int RB, int S, int STAGE_OFFSET, bool UNTRACKED = false>
 __device__ inline u32x4 read_operand(lds_char *lds3, const int (&frag)[8])
 {
-    if constexpr (KCONTIG) {
+    constexpr int FAR = STAGE_OFFSET >= 32768 ? STAGE_OFFSET : 0, STAGE = STAGE_OFFSET - FAR;
+    if constexpr (KCONTIG && UNTRACKED) {
+        const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds3)) + static_cast<uint32_t>(frag[frag_select<RB>(F, S)] + FAR);
+        return lds_read_b128_untracked<F * RB * 128 + STAGE>(at);
+    } else if constexpr (KCONTIG) {
         return *reinterpret_cast<const __attribute__((address_space(3))) u32x4 *>(
-            lds3 + frag[frag_select<RB>(F, S)] + F * RB * 128 + STAGE);
+            lds3 + frag[frag_select<RB>(F, S)] + F * RB * 128 + STAGE_OFFSET);
     } else {
         static_assert(F < 8, "one address per fragment");
         constexpr int LINE = 2 * ROWS;                                    // bytes per k line
         constexpr int OFFSET = S * ((512 / RB) * LINE) + STAGE;          // a K-step is 16 (RB = 32) or 32 k lines
         static_assert(OFFSET + 4 * LINE < 65536, "LDS instruction offsets have 16 bits");
-        const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds3)) + static_cast<uint32_t>(frag[F]);
+        const uint32_t at = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds3)) + static_cast<uint32_t>(frag[F] + FAR);
         shortx4 lo, hi;
         asm volatile("ds_read_b64_tr_b16 %0, %2 offset:%3\n\tds_read_b64_tr_b16 %1, %2 offset:%4"
                      : "=&v"(lo), "=&v"(hi)
@@ -114,7 +131,7 @@ __device__ inline u32x4 read_operand(lds_char *lds3, const int (&frag)[8])
     }
 }
 
-template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int PROBE = 0, bool CLIP = false>
+template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int PROBE = 0, bool CLIP = false, int STAGES = 2>
 __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs args)
 {
 #if defined(__HIP_DEVICE_COMPILE__)      // the host pass needs the kernel's symbol only (LDS address-space code is device code)
@@ -131,7 +148,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
     static_assert((A_KCONTIG || BM >= 128) && (B_KCONTIG || BN >= 128), "an operand that is not contiguous along k needs 128 rows");
     using LoadA = DmaLoader<BM, NT, A_KCONTIG, RB>;
     using LoadB = DmaLoader<BN, NT, B_KCONTIG, RB>;
-    constexpr int A_BYTES = LoadA::LDS_BYTES, B_BYTES = LoadB::LDS_BYTES;   // LDS: [A stage 0][A stage 1][B stage 0][B stage 1]
+    constexpr int A_BYTES = LoadA::LDS_BYTES, B_BYTES = LoadB::LDS_BYTES;   // LDS: [A stage 0][A stage 1] ... [B stage 0][B stage 1] ...
     constexpr int SLOTS = FM * FN, FRAGS = FM + FN;
     constexpr int PIECES = LoadA::COUNT + LoadB::COUNT;
 
@@ -166,7 +183,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
         }
     };
     frag_setup(A_KCONTIG, wm * WTM, 0, BM, frag_a);
-    frag_setup(B_KCONTIG, wn * WTN, 2 * A_BYTES, BN, frag_b);
+    frag_setup(B_KCONTIG, wn * WTN, STAGES * A_BYTES, BN, frag_b);
 
     using Acc = typename BlockAcc<RB>::type;
     Acc acc[FN][FM];
@@ -189,7 +206,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
         lb.aim(B, args.ldb, n0, l0);
     };
     lds_char *const mine_a = lds3 + wave_u * (LoadA::COUNT * 1024);
-    lds_char *const mine_b = lds3 + 2 * A_BYTES + wave_u * (LoadB::COUNT * 1024);
+    lds_char *const mine_b = lds3 + STAGES * A_BYTES + wave_u * (LoadB::COUNT * 1024);
     auto issue_piece = [&](auto P, auto PAR) {          // piece P of the tile aimed at, into stage PAR
         constexpr int p = decltype(P)::value, par = decltype(PAR)::value;
         if constexpr (p < LoadA::COUNT) {
@@ -199,17 +216,20 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
             lb.template issue<pb>(mine_b + par * B_BYTES);
         }
     };
-    auto wait_loads = [] { __builtin_amdgcn_s_waitcnt(0x0F70); };    // vmcnt(0): this wavefront's loads are in LDS
+    // vmcnt: this wavefront's loads are in LDS, but for those of the STAGES - 2 K-tiles behind the next one (loads return in order)
+    constexpr int AHEAD = (STAGES - 2) * PIECES;
+    static_assert(STAGES >= 2 && AHEAD < 16, "the low four bits of the wait count");
+    auto wait_loads = [] { __builtin_amdgcn_s_waitcnt(0x0F70 + AHEAD); };
 
     u32x4 fa[2][FM], fb[2][FN];
     // fragment F of K-step s in stage `par`: F < FM -> A fragment F, else B fragment F - FM
     auto read_frag = [&](auto F, auto PAR, auto S, int buf) {
         constexpr int f = decltype(F)::value, par = decltype(PAR)::value, s = decltype(S)::value;
-        if constexpr (f < FM) fa[buf][f] = read_operand<A_KCONTIG, BM, f, RB, s, par * A_BYTES>(lds3, frag_a);
-        else fb[buf][f - FM] = read_operand<B_KCONTIG, BN, f - FM, RB, s, par * B_BYTES>(lds3, frag_b);
+        if constexpr (f < FM) fa[buf][f] = read_operand<A_KCONTIG, BM, f, RB, s, par * A_BYTES, (STAGES > 2)>(lds3, frag_a);
+        else fb[buf][f - FM] = read_operand<B_KCONTIG, BN, f - FM, RB, s, par * B_BYTES, (STAGES > 2)>(lds3, frag_b);
     };
     // the transposing reads are invisible to the compiler's wait-count bookkeeping (see read_operand)
-    constexpr bool MANUAL_WAIT = !A_KCONTIG || !B_KCONTIG;
+    constexpr bool MANUAL_WAIT = STAGES > 2 || !A_KCONTIG || !B_KCONTIG;
     auto wait_fragments = [] {
         if constexpr (MANUAL_WAIT) {
             __builtin_amdgcn_s_waitcnt(0xC07F);            // lgkmcnt(0)
@@ -219,13 +239,25 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
     using Step0 = std::integral_constant<int, 0>;
     using Stage0 = std::integral_constant<int, 0>;
     using Stage1 = std::integral_constant<int, 1>;
+    // (a barrier with the memory model's fences waits for every load in flight)
+    auto barrier = [] {
+        if constexpr (STAGES == 2) {
+            __syncthreads();
+        } else {
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
 
     if (ktiles > 0) {
-        aim_tile(0);
-        static_for<PIECES>([&](auto P) { issue_piece(P, Stage0{}); });
+        static_for<STAGES - 1>([&](auto PAR) {
+            aim_tile(decltype(PAR)::value);
+            static_for<PIECES>([&](auto P) { issue_piece(P, PAR); });
+        });
         if constexpr ((PROBE & 1) != 0) static_for<PIECES>([&](auto P) { issue_piece(P, Stage1{}); });
         wait_loads();
-        __syncthreads();
+        barrier();
         static_for<FRAGS>([&](auto F) { read_frag(F, Stage0{}, Step0{}, 0); });
     }
 
@@ -250,8 +282,9 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
 
     auto tile_body = [&](auto CUR, int t) {
         using Cur = decltype(CUR);
-        using Nxt = std::integral_constant<int, 1 - Cur::value>;
-        aim_tile(t + 1);
+        using Nxt = std::integral_constant<int, (Cur::value + 1) % STAGES>;
+        using Far = std::integral_constant<int, (Cur::value + STAGES - 1) % STAGES>;      // read last one tile ago
+        aim_tile(t + STAGES - 1);
         static_for<KSTEPS>([&](auto S) {
             constexpr int s = decltype(S)::value;
             static_for<SLOTS>([&](auto Q) {
@@ -261,7 +294,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
                     if constexpr (STAMPS) stamp_a = __builtin_amdgcn_s_memtime();
                     wait_loads();
                     if constexpr (STAMPS) stamp_b = __builtin_amdgcn_s_memtime();
-                    __syncthreads();                     // tile t+1 is complete in the other stage
+                    barrier();                           // tile t+1 is complete in its stage
                     if constexpr (STAMPS) stamp_c = __builtin_amdgcn_s_memtime();
                 }
                 if constexpr (q == 0) wait_fragments();  // this step's operands, read during the previous step
@@ -287,18 +320,18 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
                     });
                 }
                 if constexpr ((PROBE & 1) == 0 && g % MG_DMA_SPACING == 0 && g / MG_DMA_SPACING < PIECES)
-                    issue_piece(std::integral_constant<int, g / MG_DMA_SPACING>{}, Nxt{});
+                    issue_piece(std::integral_constant<int, g / MG_DMA_SPACING>{}, Far{});
                 __builtin_amdgcn_sched_barrier(0);
             });
         });
     };
     int t = 0;
-    for (; t + 1 < ktiles; t += 2) {
-        tile_body(Stage0{}, t);
-        tile_body(Stage1{}, t + 1);
-    }
-    if (t < ktiles) tile_body(Stage0{}, t);
+    for (; t + STAGES - 1 < ktiles; t += STAGES) static_for<STAGES>([&](auto CUR) { tile_body(CUR, t + decltype(CUR)::value); });
+    static_for<STAGES - 1>([&](auto CUR) {
+        if (t + decltype(CUR)::value < ktiles) tile_body(CUR, t + decltype(CUR)::value);
+    });
 
+    if constexpr (STAGES > 2) __builtin_amdgcn_s_waitcnt(0x0F70);       // the reloads past the end of the sum
     wait_fragments();       // the reads issued behind the last barrier still write registers: let them land
     __syncthreads();        // all loads have landed (waited for before the last barrier) and all fragment reads are done
     if constexpr (STAMPS) {

@@ -24,16 +24,6 @@
 
 namespace mg {
 
-// 16-byte LDS read the compiler's wait-count bookkeeping does not see (the kernel waits itself): a visible LDS
-// read that follows a direct-to-LDS load in program order can draw a wait for that load.
-template <int OFFSET> __device__ inline u32x4 lds_read_b128_untracked(uint32_t at)
-{
-    static_assert(OFFSET >= 0 && OFFSET < 65536, "LDS instruction offsets have 16 bits");
-    u32x4 r;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(r) : "v"(at), "n"(OFFSET) : "memory");
-    return r;
-}
-
 // MFMA operand of fragment F, K-step S from the operand stage at byte offset STAGE.  `at`: the lane's LDS address
 // for fragment 0 / swizzle phase 0 (see hgemm_dma_kernel); the others differ from it by an XOR below 256 (the LDS
 // allocation of the kernel starts on a 1 KB boundary) and an immediate offset.

@@ -205,13 +205,15 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         // tiles of ragged problems count as whole ones.  The direct-to-LDS kernels need whole tiles and 16-byte aligned
         // operands; where they are illegal the next best estimate is tried.
         static const TileChoice f16_tiles[] = {{"hdma16_256x256x64_w2x4", 256, 256, 64, 4.88f, 4.83f, 1},
-                                               {"hdma16_256x128x64_w4x2", 256, 128, 64, 3.93f, 3.65f, 1},
+                                               {"hdma16_256x128x64_w4x2", 256, 128, 64, 4.4f, 4.3f, 1},
                                                {"hdma16_128x128x64_w2x4", 128, 128, 64, 4.07f, 2.75f, 2},
                                                {"hmfma_256x256x64_w2x2", 256, 256, 64, 4.54f, 4.40f, 1},
                                                {"hmfma_256x128x64_w2x2", 256, 128, 64, 3.72f, 3.72f, 1},
                                                {"hmfma_128x128x64_w2x2", 128, 128, 64, 3.61f, 3.0f, 2},
                                                {"hmfma_128x64x64_w2x2", 128, 64, 64, 2.85f, 1.87f, 3},
-                                               {"hmfma_64x64x64_w2x2", 64, 64, 64, 2.30f, 1.65f, 5}};
+                                               {"hmfma_64x64x64_w2x2", 64, 64, 64, 2.30f, 1.65f, 5},
+                                               {"hdeep16_128x128x64_w2x4", 128, 128, 64, 4.0f, 4.0f, 1}};
+        constexpr int kDeep = 8;            // index of the last one
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
         // LDS; the smaller the tile, the more that shows.  Measured rates relative to the (m, k) order (A along m,
         // B along k; tiles up to 128 x 64 / up to 256 x 128 / 256 x 256): both operands along k 1.10 / 1.06 / 1.02,
@@ -241,8 +243,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                {"smfma_64x64x32_w2x2", 64, 64, 32, 0.571f, 0.565f, 5}};
         static const double f32_round_cost[5] = {0.0, 0.0, 1.0e6, 2.0e6, 1.8e6};
         const TileChoice *tiles = f32 ? f32_tiles : f16_tiles;
-        const int count = f32 ? 5 : 8;
-        bool tried[8] = {false, false, false, false, false, false, false, false};
+        const int count = f32 ? 5 : 9;
+        const int smallest = f32 ? 4 : 7;
+        bool tried[9] = {false, false, false, false, false, false, false, false, false};
         // estimated time (in 1e-6 us) of tile i with the sum cut into `slices`
         auto estimate = [&](int i, int slices) {
             const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn) * slices;
@@ -253,6 +256,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // sliced sums run the large register-staged tiles about a tenth below their rate (256 x 8192 x 8192 with
             // both operands along k in four slices: 53-55 us against 48 us on the direct-to-LDS tile of that size)
             if (!f32 && tiles[i].tag[1] == 'm' && slices > 1 && tiles[i].bm * tiles[i].bn >= 256 * 128) order *= 0.9;
+            if (!f32 && i == kDeep && !(p.a_trans && !p.b_trans)) order = 0.95;
             // the 128 x 128 direct-to-LDS tile is slower with A along k (3.7-3.8 against 4.0)
             if (!f32 && i == 2 && p.a_trans) order = 0.94;
             // ragged or unaligned FP16 problems run the bounds-checked flavour, which costs the smaller tiles more
@@ -306,14 +310,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // most 1.4; e fitted per kernel: 256 x 256 direct-to-LDS 0.55 (144 tiles at 3072^3 run at 6.7
                 // Mflop/us per compute unit against 4.8 on a full chip), 256 x 128 0.3 (direct-to-LDS and
                 // register-staged), 128 x 128 direct-to-LDS 1.3 when the busiest compute units hold two work-groups
-                // (324 tiles at 2304^3: 4.8 Mflop/us against 3.6) but 0.1 with one, the smaller register-staged
+                // (324 tiles at 2304^3: 4.8 Mflop/us against 3.6) but 0.1 with one, its four-stage sibling 0.4, the smaller register-staged
                 // kernels 0.1; the bounds-checked flavour shows no gain; the 128 x 128 direct-to-LDS tile at most 1.2
                 if (!ragged || (dword_rows && i == 3)) {
                     const int64_t busiest = blocks - static_cast<int64_t>(kComputeUnits) * (per_unit - 1);
                     const double lower = per_unit > 1 ? shared_rate(per_unit - 1) : 0.0;
                     const double load = (static_cast<double>(busiest) * rate + static_cast<double>(kComputeUnits - busiest) * lower) /
                                         (static_cast<double>(kComputeUnits) * rate);
-                    const double exponent = i == 0 ? 0.55 : (i == 2 ? (per_unit > 1 ? 1.3 : 0.1) : (tiles[i].bm == 256 ? 0.3 : 0.1));
+                    const double exponent = i == 0 ? 0.55 : (i == 1 ? 0.5 : (i == kDeep ? 0.4 : (i == 2 ? (per_unit > 1 ? 1.3 : 0.1) : (tiles[i].bm == 256 ? 0.3 : 0.1))));
                     const double boost = pow(load, -exponent);
                     const double most = i == 2 ? 1.2 : 1.4;
                     rate *= boost < most ? boost : most;
@@ -340,6 +344,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                     time = whole * round_time + 0.8 * static_cast<double>(u) * tile_flops / (shared_rate(u) * order);
                 }
             }
+            // the kernels with three and four stages: their first loads and the epilogue beside the loop's rate (128 x 128 tiles:
+            // 24 K-tiles on 144 compute units 14.7 us, 64 on 128 units 26.8 us, 16 on 64 units 10.7 us)
+            if (!f32 && (i == 1 || i == kDeep)) time += 2.0e6;
             // split-K: the partial sums are written and read back (8 bytes per slice and output at ~4 TB/s) by
             // a second launch (2.5 us; 4 us behind the bounds-checked FP32 flavour, fitted with the rates above)
             if (slices > 1) time += 1.0e6 * ((f32 && ragged ? 4.0 : 2.5) + (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) / 4.0e6);
@@ -367,7 +374,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                     const bool wide = whole ? p.m * p.n > 25000000 : p.k > 128 && turns64 >= 6 && 2 * turns128 <= turns64;
                     if (tiles[i].bm * tiles[i].bn > (wide ? 128 * 64 : 64 * 64)) continue;
                 }
-                const bool last = i == count - 1;
+                const bool last = i == smallest;
                 const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
                 const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn);
                 // slices tried: none; for the smallest tile the factor of the sweep's rule; for grids that do not
