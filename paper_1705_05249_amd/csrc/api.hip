@@ -127,7 +127,7 @@ void plan_fringe(Problem &p, bool forced)
 }
 
 // Also decides the problem's fringe (p.fringe_m, p.fringe_n).
-mg_status choose(Problem &p, int64_t alignment, size_t workspace_bytes, int32_t *kernel, int32_t *split)
+mg_status choose(Problem &p, int64_t alignment, size_t workspace_bytes, int32_t *kernel, int32_t *split, double *estimated_us = nullptr)
 {
     const auto &t = table();
     const int32_t forced = g_override_kernel[p.dtype];
@@ -140,7 +140,7 @@ mg_status choose(Problem &p, int64_t alignment, size_t workspace_bytes, int32_t 
         *split = forced_split;
         return MG_OK;
     }
-    select_config(t, p, alignment, workspace_bytes, kernel, split);
+    select_config(t, p, alignment, workspace_bytes, kernel, split, estimated_us);
     if (*kernel < 0 && (p.fringe_m != 0 || p.fringe_n != 0)) {
         p.fringe_m = p.fringe_n = 0;                   // no kernel for the problem less its fringe: the whole problem
         select_config(t, p, alignment, workspace_bytes, kernel, split);
@@ -162,8 +162,22 @@ size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
 struct IndirectPlan {
     int64_t mp, np, kp;
     size_t a_bytes, b_bytes, c_bytes;
+    bool compare;            // take it only if its estimate is below the direct route's
     size_t total() const { return a_bytes + b_bytes + c_bytes; }
 };
+
+IndirectPlan padded_to(const Problem &p, int64_t tile_m, int64_t tile_n, int64_t tile_k)
+{
+    const size_t elem = p.elem();
+    IndirectPlan plan{};
+    plan.mp = ceil_div(p.m, tile_m) * tile_m;
+    plan.np = ceil_div(p.n, tile_n) * tile_n;
+    plan.kp = ceil_div(p.k, tile_k) * tile_k;
+    plan.a_bytes = round_up_256(static_cast<size_t>(plan.mp) * plan.kp * elem);
+    plan.b_bytes = round_up_256(static_cast<size_t>(plan.kp) * plan.np * elem);
+    plan.c_bytes = round_up_256(static_cast<size_t>(plan.mp) * plan.np * elem);
+    return plan;
+}
 
 bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
 {
@@ -172,6 +186,7 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     const double work = static_cast<double>(p.m) * static_cast<double>(p.n) * static_cast<double>(p.k);
     const size_t elem = p.elem();
     int64_t tile = 0, ktile = 0;
+    bool compare = false;
     if (p.dtype == MG_F16) {
         // four extra launches and ~33 us of copies at 4096^2: measured a loss at 1000^3 (28 against 22 us), a gain
         // at 2049^3 (56 against 96 us)
@@ -181,19 +196,16 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
                              (!pointers_known || (pointer_alignment(p.A) >= 16 && pointer_alignment(p.B) >= 16));
         if (whole && aligned) return false;                            // the fast kernels take it directly
         // Operands whose rows start on dwords run most of their K-tiles on the fast flavour's schedule inside the
-        // bounds-checked kernels, and the copies pay only where the product is long next to the matrices: below about
-        // 900 multiply-adds per element moved the direct route wins (re-measured with the copies of C gone from the
-        // larger problems, direct / through the copies: 2051^3 42-44 / 47, 2501^3 56 / 57, 2801^3 66-68 / 69-71, 3001^3
-        // 73-86 / 71-73, (2051, 2051, 8201) 142-161 / 126-127).  Even leading dimensions, us direct / through
-        // the copies (A along m | along k): 1300^3 17.6 / 25.0 | 15.6 / 23.5, 1800^3 25.9 / 32.6 | 24.7 / 30.8, 2050^3
-        // 46.5 / 46.4 | 46.2 / 45.8, 2500^3 62.2 / 55.4 | 55.5 / 55.3, 3000^3 81.7 / 74.7 | 65.4 / 74.2, 3500^3 115 / 98 |
-        // 96 / 97, 4104^3 205 / 196, 6002^3 533 / 442 | 572 / 441; (4100, 4100, 512) 43.7 / 52.0 | 36.5 / 50.0,
-        // (8200, 1030, 2050) 60.9 / 78.1 | 53.9 / 81.5, (2050, 2050, 8200) 126 / 126 | 120 / 123.  (Without the
-        // pointers, for the workspace query, the copies are assumed: an upper bound.)
+        // bounds-checked kernels: there the two routes' estimates are compared, up to about 900 multiply-adds per element moved;
+        // beyond, the copies always pay.  Even leading dimensions, us direct / through the copies of A and B (A along m | along
+        // k): 1300^3 21.6 / 25.1 | 19.2 / 25.1, 1500^3 37 / 27 | 33 / 28, 1800^3 30 / 27 | 29 / 28, 2050^3 45 / 41 | 47 / 40, 2500^3
+        // 60 / 49 | 59 / 50, 2700^3 59 / 58 | 60 / 60, (8200, 1030, 2050) - | 62 / 76, (4100, 4100, 512) 53 / 54 | -.  (Without
+        // the pointers, for the workspace query, the copies are assumed: an upper bound.)
         const bool dword_rows = p.lda % 2 == 0 && p.ldb % 2 == 0 && pointers_known && pointer_alignment(p.A) >= 4 &&
                                 pointer_alignment(p.B) >= 4;
         const double moved = static_cast<double>(p.m) * p.k + static_cast<double>(p.k) * p.n + static_cast<double>(p.m) * p.n;
-        if (dword_rows && work < 900.0 * moved) return false;
+        if (dword_rows && work < 350.0 * moved) return false;
+        compare = dword_rows && work < 900.0 * moved;
         tile = p.m >= 2048 && p.n >= 2048 ? 256 : 128;
         ktile = 64;
     } else {
@@ -204,57 +216,98 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
         // 5001^3 1990 / 1940 against 2068 (the copies cost ~70 us at 4096^2).
         return false;
     }
-    plan->mp = ceil_div(p.m, tile) * tile;
-    plan->np = ceil_div(p.n, tile) * tile;
-    plan->kp = ceil_div(p.k, ktile) * ktile;
-    plan->a_bytes = round_up_256(static_cast<size_t>(plan->mp) * plan->kp * elem);
-    plan->b_bytes = round_up_256(static_cast<size_t>(plan->kp) * plan->np * elem);
-    plan->c_bytes = round_up_256(static_cast<size_t>(plan->mp) * plan->np * elem);
+    *plan = padded_to(p, tile, tile, ktile);
+    plan->compare = compare;
     return true;
 }
 
 mg_status run_canonical(Problem p);
 
-mg_status run_indirect(const Problem &p, const IndirectPlan &plan)
+// The copies of A and B (and C) for a plan, and the padded product on them, C left to the caller.
+Problem padded_problem(const Problem &p, const IndirectPlan &plan, PadCopy (&copies)[3])
 {
     char *ws = static_cast<char *>(p.workspace);
     void *ap = ws, *bp = ws + plan.a_bytes, *cp = ws + plan.a_bytes + plan.b_bytes;
-    hipStream_t st = p.stream;
     // an operand keeps its storage order: stored rows x columns (column-major view) = m x k or k x m
     const int64_t a_minor = p.a_trans ? p.k : p.m, a_major = p.a_trans ? p.m : p.k;
     const int64_t a_minor_p = p.a_trans ? plan.kp : plan.mp, a_major_p = p.a_trans ? plan.mp : plan.kp;
     const int64_t b_minor = p.b_trans ? p.n : p.k, b_major = p.b_trans ? p.k : p.n;
     const int64_t b_minor_p = p.b_trans ? plan.np : plan.kp, b_major_p = p.b_trans ? plan.kp : plan.np;
-    const PadCopy copies[3] = {{a_minor, a_major, p.A, p.lda, ap, a_minor_p, a_minor_p, a_major_p},
-                               {b_minor, b_major, p.B, p.ldb, bp, b_minor_p, b_minor_p, b_major_p},
-                               {p.m, p.n, p.C, p.ldc, cp, plan.mp, plan.mp, plan.np}};
+    copies[0] = PadCopy{a_minor, a_major, p.A, p.lda, ap, a_minor_p, a_minor_p, a_major_p};
+    copies[1] = PadCopy{b_minor, b_major, p.B, p.ldb, bp, b_minor_p, b_minor_p, b_major_p};
+    copies[2] = PadCopy{p.m, p.n, p.C, p.ldc, cp, plan.mp, plan.mp, plan.np};
     Problem q = p;
     q.m = plan.mp; q.n = plan.np; q.k = plan.kp;
     q.A = ap; q.lda = a_minor_p;
     q.B = bp; q.ldb = b_minor_p;
+    return q;
+}
+
+// *taken = false: nothing was launched, the direct route is the better one.
+mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken)
+{
+    *taken = true;
+    hipStream_t st = p.stream;
+    PadCopy copies[3];
+    // Only A and B are copied and C stays where it is, by the direct-to-LDS kernels' flavour with a bounds-checked epilogue: no
+    // copy of C in (beta != 0) and none out (each 5-6 us at 2051^2 FP16, ~12 us at 4097^2, plus the 3.5-4 us gap of a
+    // dependent launch).  Of the paddings that fit into the plan's workspace the one whose product is estimated fastest:
+    // 2051^3 (odd leading dimensions) to 2304 x 2176 in place 38 us, to 2304 x 2304 with the copies of C 46 us.
     {
-        // Where a kernel with direct-to-LDS loads and a bounds-checked epilogue takes the padded product, only A and B
-        // are copied and C stays where it is: no copy of C in (beta != 0) and none out (each ~12 us at 4097^2 FP16, plus
-        // the 3.5-4 us gap of a dependent launch).
-        Problem direct_c = q;
-        direct_c.clip_m = p.m;
-        direct_c.clip_n = p.n;
-        direct_c.workspace = nullptr;
-        direct_c.workspace_bytes = 0;
-        // (only where the padded product would run on a tile that has such a flavour anyway: forced onto the 256 x 256
-        // tile, 2051^3, which prefers smaller ones, took 53.7 us against 46 us with the copies)
-        Problem padded = q;
-        padded.C = cp;
+        Problem best{};
+        int32_t best_kernel = -1;
+        double best_us = 0.0;
+        IndirectPlan best_plan{};
+        for (const auto &tile : {std::pair<int64_t, int64_t>{256, 256}, {256, 128}, {128, 128}}) {
+            const IndirectPlan candidate = padded_to(p, tile.first, tile.second, 64);
+            if (candidate.total() > plan.total()) continue;
+            Problem in_place = padded_problem(p, candidate, copies);
+            in_place.clip_m = p.m;
+            in_place.clip_n = p.n;
+            in_place.workspace = nullptr;
+            in_place.workspace_bytes = 0;
+            int32_t kernel = -1, split = 1;
+            double us = 0.0;
+            if (choose(in_place, problem_alignment(in_place), 0, &kernel, &split, &us) != MG_OK || split != 1 || us <= 0.0) continue;
+            if (best_kernel >= 0 && us >= best_us) continue;
+            best = in_place;
+            best_kernel = kernel;
+            best_us = us;
+            best_plan = candidate;
+        }
+        if (plan.compare) {
+            // the copies of A and B: a launch, the gap behind it and their traffic at ~3.5 TB/s (the bounds-checked kernels run
+            // 10-25 % above their estimate at these sizes)
+            const double copies_us = 5.0 + 4.0 * static_cast<double>(p.k) * (static_cast<double>(p.m) + static_cast<double>(p.n)) / 3.5e6;
+            Problem direct = p;
+            int32_t kernel = -1, split = 1;
+            double us = 0.0;
+            const bool known = choose(direct, problem_alignment(direct), p.workspace_bytes, &kernel, &split, &us) == MG_OK;
+            if (best_kernel < 0 || (known && us > 0.0 && 1.15 * us <= best_us + copies_us)) {
+                *taken = false;
+                return MG_OK;
+            }
+        }
+        // (a small C with a long sum: sliced, if the caller brought workspace for that beside the copies; those of C cost a
+        // dependent launch and their traffic)
+        Problem padded = padded_problem(p, plan, copies);
+        padded.C = copies[2].dst;
         padded.ldc = plan.mp;
-        int32_t wanted = -1, wanted_split = 1, kernel = -1, split = 1;
-        const bool unsplit = choose(padded, problem_alignment(padded), 0, &wanted, &wanted_split) == MG_OK && wanted_split == 1;
-        if (unsplit && choose(direct_c, problem_alignment(direct_c), 0, &kernel, &split) == MG_OK && split == 1 &&
-            table()[kernel].cfg.tile_m == table()[wanted].cfg.tile_m && table()[kernel].cfg.tile_n == table()[wanted].cfg.tile_n &&
-            table()[kernel].cfg.waves_m * table()[kernel].cfg.waves_n == table()[wanted].cfg.waves_m * table()[wanted].cfg.waves_n) {
+        int32_t kernel = -1, split = 1;
+        double us = 0.0;
+        const size_t left = p.workspace_bytes - plan.total();
+        const bool sliced = best_kernel >= 0 && choose(padded, problem_alignment(padded), left, &kernel, &split, &us) == MG_OK && split > 1 &&
+                            us > 0.0 &&
+                            us + 4.0 + 8.0 * static_cast<double>(plan.mp) * static_cast<double>(plan.np) / 3.5e6 < best_us;
+        if (best_kernel >= 0 && !sliced) {
+            padded_problem(p, best_plan, copies);
             if (launch_pad_matrices(p.dtype, copies, 2, st) != hipSuccess) return MG_ERR_LAUNCH;
-            return table()[kernel].launch(direct_c, 1) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
+            return table()[best_kernel].launch(best, 1) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
         }
     }
+    Problem q = padded_problem(p, plan, copies);
+    char *ws = static_cast<char *>(p.workspace);
+    void *cp = copies[2].dst;
     if (launch_pad_matrices(p.dtype, copies, p.beta != 0.f ? 3 : 2, st) != hipSuccess) return MG_ERR_LAUNCH;
     q.C = cp; q.ldc = plan.mp;
     const size_t used = plan.total();
@@ -271,8 +324,11 @@ mg_status run_canonical(Problem p)
     IndirectPlan plan;
     // (the copy back out of the padded result writes all of C: not for a call that may only touch a triangle)
     if (!p.mask_c && indirect_plan(p, true, &plan) && p.workspace != nullptr && pointer_alignment(p.workspace) >= 256 &&
-        p.workspace_bytes >= plan.total())
-        return run_indirect(p, plan);
+        p.workspace_bytes >= plan.total()) {
+        bool taken = false;
+        const mg_status done = run_indirect(p, plan, &taken);
+        if (taken) return done;
+    }
     int32_t kernel = -1, split = 1;
     const bool ws_usable = p.workspace != nullptr && pointer_alignment(p.workspace) >= 256;
     const mg_status s = choose(p, problem_alignment(p), ws_usable ? p.workspace_bytes : 0, &kernel, &split);

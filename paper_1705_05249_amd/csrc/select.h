@@ -7,9 +7,10 @@
 namespace mg {
 
 // Sets *kernel (-1 if nothing applies) and *split.  workspace_bytes: what the caller can offer for split-K
-// partial sums (a configuration that needs more is not chosen).
+// partial sums (a configuration that needs more is not chosen).  estimated_us (optional): the macro tile's estimated time, less what every
+// launch costs; 0 where another kind of kernel is chosen.
 void select_config(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
-                   int32_t *kernel, int32_t *split);
+                   int32_t *kernel, int32_t *split, double *estimated_us = nullptr);
 // Returns the kernel id for a batched problem, or -1.
 int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProblem &p);
 

@@ -31,13 +31,17 @@ bool try_mfma(const std::vector<KernelEntry> &table, const Problem &p, int64_t a
 {
     char name[96];
     const char *contig = p.a_trans ? (p.b_trans ? "kn" : "kk") : (p.b_trans ? "mn" : "mk");
-    // operands padded to whole tiles and the caller's own C (Problem::clip_m, clip_n): the 256 x 256 and the 128 x 128
-    // direct-to-LDS kernels have a flavour whose epilogue checks bounds, nothing else has
+    // operands padded to whole tiles and the caller's own C (Problem::clip_m, clip_n): the direct-to-LDS kernels have a
+    // flavour whose epilogue checks bounds, nothing else has
     if (p.clip_m != 0 || p.clip_n != 0) {
         if (strcmp(tag, "hdma16_256x256x64_w2x4") == 0)
             snprintf(name, sizeof name, "%s_256x256x64_w2x4_%s", p.b_trans ? "hdma16c" : "hpp16c", contig);
         else if (strcmp(tag, "hdma16_128x128x64_w2x4") == 0)
             snprintf(name, sizeof name, "hdma16c_128x128x64_w2x4_%s", contig);
+        else if (strcmp(tag, "hdma16_256x128x64_w4x2") == 0)
+            snprintf(name, sizeof name, "hdma16c_256x128x64_w4x2_%s", contig);
+        else if (strcmp(tag, "hdeep16_128x128x64_w2x4") == 0)
+            snprintf(name, sizeof name, "hdma16c_deep_128x128x64_w2x4_%s", contig);
         else
             return false;
         return try_pick(table, p, alignment, name, split, kernel, out_split);
@@ -151,8 +155,9 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
 }  // namespace
 
 void select_config(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
-                   int32_t *kernel, int32_t *split)
+                   int32_t *kernel, int32_t *split, double *estimated_us)
 {
+    if (estimated_us != nullptr) *estimated_us = 0.0;
     *kernel = -1;
     *split = 1;
     const bool f32 = p.dtype == MG_F32;
@@ -428,7 +433,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             const int want = best_slices;
             // a factor whose last slice would be empty is illegal: take the next smaller one
             for (int w = want; w >= 1; --w)
-                if (try_mfma(table, p, alignment, tc.tag, w, kernel, split)) return;
+                if (try_mfma(table, p, alignment, tc.tag, w, kernel, split)) {
+                    if (estimated_us != nullptr) *estimated_us = best_time * 1.0e-6;
+                    return;
+                }
         }
     }
     try_pick(table, p, alignment, f32 ? "direct_f32_64x64x16" : "direct_f16_64x64x16", 1, kernel, split);
