@@ -251,9 +251,22 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         const int count = f32 ? 5 : 9;
         const int smallest = f32 ? 4 : 7;
         bool tried[9] = {false, false, false, false, false, false, false, false, false};
+        // work-groups that do something: of a product whose C is a triangle, the tiles that touch it (as the kernels skip the others)
+        const bool triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
+        auto wanted_tiles = [&](int bm, int bn) {
+            const int64_t across_m = ceil_div(tm, bm), across_n = ceil_div(tn, bn);
+            if (!triangle || f32) return across_m * across_n;
+            int64_t count = 0;
+            if (p.shape == MG_SHAPE_C_LOWER) {
+                for (int64_t j = 0; j < across_n; ++j) count += across_m > j * bn / bm ? across_m - j * bn / bm : 0;
+            } else {
+                for (int64_t i = 0; i < across_m; ++i) count += across_n > i * bm / bn ? across_n - i * bm / bn : 0;
+            }
+            return count;
+        };
         // estimated time (in 1e-6 us) of tile i with the sum cut into `slices`
         auto estimate = [&](int i, int slices) {
-            const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn) * slices;
+            const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn) * slices;
             const double tile_flops = 2.0 * tiles[i].bm * tiles[i].bn * static_cast<double>(p.k) / slices;
             const int64_t full = static_cast<int64_t>(kComputeUnits) * tiles[i].resident;   // work-groups the chip holds
             double order = 1.0;
@@ -409,10 +422,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 snprintf(name, sizeof name, "htiny_32x32_%s", order_tag);
                 if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
             }
-            // A shape hint (about half of the tile work, unequal tiles) is ranked like the general problem, with one
-            // measured exception: when the 256 x 256 direct-to-LDS grid leaves compute units idle anyway, the
-            // 128 x 128 tiles balance the unequal work better (3072: TRMM 59 against 77 us, SYRK 58 against 76)
-            if (!f32 && p.shape != MG_SHAPE_GENERAL && best == 0 && !tried[2] &&
+            // FP16 products with a triangular C are ranked by the tiles that touch it (us, ranked as all of C / now: 2048^3 25 / 17,
+            // 2560^3 36 / 24, 3584 x 1024 33 / 20, 4096^3 84 both).  A triangular operand (unequal K ranges) is ranked like
+            // the general problem, with one measured exception: when the 256 x 256 direct-to-LDS grid leaves compute units idle
+            // anyway, the 128 x 128 tiles balance the unequal work better (TRMM 3072: 59 against 77 us)
+            if (!f32 && p.shape != MG_SHAPE_GENERAL && !triangle && best == 0 && !tried[2] &&
                 ceil_div(p.m, 256) * ceil_div(p.n, 256) <= (kComputeUnits * 3) / 4)
                 best = 2;
             // FP32 work-groups take turns on a compute unit, so unequal tiles (skipped ones, narrowed K ranges)
