@@ -25,7 +25,8 @@ struct TinyArgs {
     void *C;
     int64_t a_sm, a_sk, b_sn, b_sk, ldc;     // element strides of op(A)(i, l), op(B)(l, j); one of each pair is 1
     int m, n, k;
-    int tiles_m;
+    int share, rest;                         // work-groups per XCD, and how many XCDs have one more
+    int minor, n_first;                      // blocks side by side along the shorter side of C, which is n if n_first
     float alpha, beta;
 };
 
@@ -43,7 +44,13 @@ __global__ __launch_bounds__(512) void tiny_gemm_kernel(const TinyArgs a)
 
     const int tid = threadIdx.x, lane = tid % 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
-    const int64_t m0 = static_cast<int64_t>(blockIdx.x % a.tiles_m) * 32, n0 = static_cast<int64_t>(blockIdx.x / a.tiles_m) * 32;
+    // Blocks of one XCD (ids 8 apart) lie side by side, along the shorter side of C first: its L2 then fetches an eighth of the
+    // larger operand instead of all of it.  Before / after, us: (150, 1500, 600) FP32 11.8 / 9.7, FP16 (512, 196, 2304) 10.9 / 9.9,
+    // (300, 800, 1500) 12.3 / 10.2, (190, 1200, 2000) 10.5 / 8.9.
+    const int xcd = blockIdx.x % 8;
+    const int id = xcd * a.share + (xcd < a.rest ? xcd : a.rest) + blockIdx.x / 8;
+    const int outer = id / a.minor, inner = id - outer * a.minor;
+    const int64_t m0 = static_cast<int64_t>(a.n_first ? outer : inner) * 32, n0 = static_cast<int64_t>(a.n_first ? inner : outer) * 32;
     const T *A = static_cast<const T *>(a.A);
     const T *B = static_cast<const T *>(a.B);
 
@@ -231,9 +238,12 @@ template <typename T, bool AK, bool BKC> struct TinyConfig {
         a.A = p.A; a.B = p.B; a.C = p.C;
         a.a_sm = p.a_sm(); a.a_sk = p.a_sk(); a.b_sn = p.b_sn(); a.b_sk = p.b_sk(); a.ldc = p.ldc;
         a.m = static_cast<int>(p.m); a.n = static_cast<int>(p.n); a.k = static_cast<int>(p.k);
-        a.tiles_m = static_cast<int>(ceil_div(p.m, 32));
         a.alpha = p.alpha; a.beta = p.beta;
-        const unsigned groups = static_cast<unsigned>(a.tiles_m * ceil_div(p.n, 32));
+        const unsigned groups = static_cast<unsigned>(ceil_div(p.m, 32) * ceil_div(p.n, 32));
+        a.share = static_cast<int>(groups / 8);
+        a.rest = static_cast<int>(groups % 8);
+        a.n_first = p.m >= p.n ? 1 : 0;
+        a.minor = static_cast<int>(ceil_div(a.n_first ? p.n : p.m, 32));
         hipLaunchKernelGGL(kernel, dim3(groups), dim3(512), LDS, p.stream, a);
         return hipGetLastError();
     }
