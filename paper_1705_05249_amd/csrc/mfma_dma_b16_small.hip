@@ -1,6 +1,7 @@
 // Direct-to-LDS FP16 kernels on 16x16 MFMA blocks with smaller work-group tiles (256 x 128 and 128 x 128),
 // for problems with too few 256 x 256 tiles to fill the chip.  The 128 x 128 tile comes with four wavefronts of
 // 64 x 64 and with eight of 64 x 32 (two per SIMD: 5-10 % faster when a compute unit holds a single work-group).
+// The 256 x 128 tile, of which a compute unit holds one, has three LDS stages (2304 x 2304 x 2112, 162 tiles: 37.1 -> 29.4 us).
 #include "mfma_dma_host.h"
 namespace mg {
 void register_hdma16_small(std::vector<KernelEntry> &table)
