@@ -21,6 +21,7 @@
 // 105 / 15, (19, 80, 144) x 2100 171 / 23; FP32 64^3 (5000, B along n) 103 / 69 (328 MB, 4.8 TB/s), 93^3 (856) 63 / 31, 99^3 (4122)
 // 313 / 191: there the MFMAs of the padded blocks take half of the time and do not hide behind the loads.
 // A team skips the columns of 16x16 blocks that the instance does not have, and its columns of blocks are dealt out evenly.
+#include "batched_walk.h"
 #include "mfma_kernel.h"
 
 namespace mg {
@@ -257,18 +258,18 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
         lb.load(a.ldb, nt, a.n - j0, k);
     }
     fetch_old(0);
-    for (int k0 = 0; k0 < k; k0 += KC) {
-        if (k0 > 0) meet();                                            // everyone is done with the chunk before
-        la.store(lds, mt, k - k0);
-        lb.store(lds + LoadA::BYTES, nt, k - k0);
+    batchwalk::for_chunks<KC>(k, [&](int left) __attribute__((always_inline)) {
+        if (left < k) meet();                                          // everyone is done with the chunk before
+        la.store(lds, mt, left);
+        lb.store(lds + LoadA::BYTES, nt, left);
         meet();
-        if (k0 + KC < k) {
-            la.load(a.lda, mt, a.m - i0, k - k0 - KC);
-            lb.load(a.ldb, nt, a.n - j0, k - k0 - KC);
+        if (left > KC) {
+            la.load(a.lda, mt, a.m - i0, left - KC);
+            lb.load(a.ldb, nt, a.n - j0, left - KC);
         }
         static_for<KC / 16>([&](auto S) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
-            if (k - k0 <= s * 16) return;
+            if (left <= s * 16) return;
             using Frag = decltype(read_fragment<A_KC, LoadA::LINE>(lds, 0, 0, 0, T{}));
             Frag fa[MB], fb[NB];
 #pragma unroll
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
             for (int bj = 0; bj < NB; ++bj)
                 if (bj < nb) step_mma(fa, fb[bj], acc[bj]);
         });
-    }
+    });
 
     meet();
     static_for<NB>([&](auto J) __attribute__((always_inline)) {
