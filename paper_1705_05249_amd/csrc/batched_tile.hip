@@ -195,11 +195,9 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
     if constexpr (TEAM == 1) {
         inst = static_cast<int64_t>(blockIdx.x) * 4 + wave;
     } else {
-        // the tiles of an instance share its operands: work-groups go to the eight XCDs in turn, so an instance's tiles
-        // sit eight work-groups apart and meet in one XCD's L2
-        const uint32_t local = blockIdx.x / 8;
-        inst = static_cast<int64_t>(local / a.tiles) * 8 + blockIdx.x % 8;
-        tile = static_cast<int>(local % a.tiles);
+        const batchwalk::Place at = batchwalk::place(blockIdx.x, a.batch, static_cast<uint32_t>(a.tiles));
+        inst = at.inst;
+        tile = static_cast<int>(at.tile);
     }
     if (inst >= a.batch) return;
     const float alpha = a.strided ? a.alpha : a.alphas[inst], beta = a.strided ? a.beta : a.betas[inst];
@@ -331,7 +329,7 @@ template <typename T, int WM, int WN, int MB, int NB, bool A_KC, bool B_KC> stru
     static int64_t grid(const BatchedProblem &p)
     {
         if (TEAM == 1) return ceil_div(p.batch, 4);
-        return ceil_div(p.batch, 8) * 8 * ceil_div(p.m, TM) * ceil_div(p.n, TN);
+        return batchwalk::work_groups(p.batch, ceil_div(p.m, TM) * ceil_div(p.n, TN));
     }
     static bool legal(const BatchedProblem &p)
     {
