@@ -37,5 +37,21 @@ MG_HD inline Place place(uint32_t group, int64_t batch, uint32_t tiles)
     return Place{undivided ? static_cast<int64_t>(inst) * 8 + xcd : static_cast<int64_t>(sets) * 8 + inst, q - inst * tiles};
 }
 
+// One launch has fewer than 2^32 threads, so at most this many work-groups of 256 (a multiple of eight keeps the XCDs in step)
+constexpr int64_t MOST_GROUPS = (int64_t(1) << 24) - 8;
+
+// The launches of a call: launch(first instance, instances, first tile, tiles of each instance) for every piece of it, until one
+// returns false.  per_group: instances per work-group, 0: a work-group takes one tile of an instance.
+template <typename Launch> inline bool for_pieces(int64_t batch, int64_t tiles, int64_t per_group, Launch launch)
+{
+    int64_t count = per_group > 0 ? MOST_GROUPS * per_group : (tiles < MOST_GROUPS ? MOST_GROUPS / tiles : 1);
+    if (count >= 8) count -= count % 8;
+    const int64_t most_tiles = per_group > 0 || tiles < MOST_GROUPS ? tiles : MOST_GROUPS;
+    for (int64_t i = 0; i < batch; i += count)
+        for (int64_t t = 0; t < tiles; t += most_tiles)
+            if (!launch(i, batch - i < count ? batch - i : count, t, tiles - t < most_tiles ? tiles - t : most_tiles)) return false;
+    return true;
+}
+
 }  // namespace batchwalk
 }  // namespace mg

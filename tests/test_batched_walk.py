@@ -2,6 +2,7 @@
 that no test can afford on the device."""
 import os
 import subprocess
+import sys
 
 import pytest
 
@@ -72,3 +73,56 @@ def test_every_tile_has_its_work_group_and_no_xcd_idles(tmp_path):
                 }
         }""")
     assert lines == [""]
+
+
+def test_the_pieces_of_a_call_cover_it(tmp_path):
+    """any accepted number of instances and any size of one: launches of fewer than 2^32 threads that take each tile once"""
+    lines = compiled(tmp_path, """
+        #include <cstdio>
+        #include <initializer_list>
+        #include "batched_walk.h"
+        using namespace mg::batchwalk;
+        int main()
+        {
+            const int64_t most = (int64_t(1) << 31) - 1;
+            for (int64_t per_group : {0, 4})
+                for (int64_t batch : {int64_t(1), int64_t(7), int64_t(1000), (int64_t(1) << 24) - 8, int64_t(1) << 24, int64_t(1) << 25, most})
+                    for (int64_t tiles : {int64_t(1), int64_t(3), int64_t(2100000), MOST_GROUPS, MOST_GROUPS + 1, int64_t(1) << 26}) {
+                        if (per_group > 0 && tiles > 1) continue;
+                        if (tiles > 3 && batch > 1000) continue;                   // (beyond any memory)
+                        int64_t at_inst = 0, at_tile = 0;
+                        bool ok = true;
+                        for_pieces(batch, tiles, per_group, [&](int64_t i, int64_t count, int64_t t, int64_t n) {
+                            const int64_t groups = per_group > 0 ? (count + per_group - 1) / per_group : work_groups(count, n);
+                            ok = ok && i == at_inst && t == at_tile && count > 0 && n > 0 && groups <= MOST_GROUPS && groups * 256 < (int64_t(1) << 32);
+                            ok = ok && (n == tiles || count == 1);
+                            at_tile += n;
+                            if (at_tile == tiles) { at_tile = 0; at_inst += count; }
+                            return true;
+                        });
+                        if (!ok || at_inst != batch || at_tile != 0) printf("batch %lld tiles %lld\\n", (long long)batch, (long long)tiles);
+                    }
+        }""")
+    assert lines == [""]
+
+
+def test_no_number_of_instances_is_refused():
+    """more instances than one launch has work-groups for, and one instance of more tiles: there is a kernel for each (without a
+    device the launch fails; a call that no kernel takes fails before it)"""
+    program = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import torch
+assert torch.cuda.device_count() == 0
+from paper_1705_05249_amd import gemm as G
+C, N, P = G.MG_COL_MAJOR, G.MG_NO_TRANS, 0x1000
+for call in (G.mg_sgemm_strided_batched, G.mg_hgemm_strided_batched):
+    for m, n, k, batch in ((40, 1, 1, 17000000), (33, 4, 4, 20000000), (40, 1, 8, 2 ** 24 - 8), (40, 1, 8, 2 ** 24), (1, 40, 8, 2 ** 25),
+                           (8, 8, 40, 2 ** 25), (131072, 131072, 8, 1), (131072, 131072, 8, 3)):
+        print(m, n, k, batch, call(C, N, N, m, n, k, 1.0, P, m, m * k, P, k, k * n, 0.0, P, m, m * n, batch, stream=0, check=False))
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    run = subprocess.run([sys.executable, "-c", program, ROOT], capture_output=True, text=True, timeout=300, env=env)
+    assert run.returncode == 0, run.stderr
+    lines = run.stdout.split("\n")[:-1]
+    assert len(lines) == 16 and all(line.endswith(" -12") for line in lines), run.stdout

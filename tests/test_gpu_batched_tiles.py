@@ -34,3 +34,30 @@ def test_tile_edges_are_exact(oracle, dtype, layout, ta, tb, shape):
     finally:
         G.mg_clear_override()
     H.check_batched(bc, oracle, exact=True)
+
+
+@pytest.mark.parametrize("dtype,m,n,k,strided", [("f16", 40, 1, 1, True), ("f32", 33, 1, 2, False)])
+def test_more_instances_than_one_launch_takes(dtype, m, n, k, strided):
+    """2^24 + 1003 instances on kernels with one work-group per instance: every instance has its own operands and scalars (small
+    integers, exact in either type)"""
+    import torch
+    batch, f32 = 2 ** 24 + 1003, dtype == "f32"
+    gen = torch.Generator(device="cuda").manual_seed(m)
+    draw = lambda *shape: torch.randint(-3, 4, shape, device="cuda", generator=gen, dtype=torch.int8)      # noqa: E731
+    kind = torch.float32 if f32 else torch.float16
+    A, B, Cm = (draw(batch, x, y).to(kind) for x, y in ((k, m), (n, k), (n, m)))                           # column-major instances
+    alphas, betas = draw(batch).float(), draw(batch).float()
+    old = Cm.clone()
+    if strided:
+        (G.mg_sgemm_strided_batched if f32 else G.mg_hgemm_strided_batched)(C, N, N, m, n, k, 2.0, A, m, m * k, B, k, k * n, -1.0,
+                                                                            Cm, m, m * n, batch)
+        alphas, betas = 2.0, -1.0
+    else:
+        place = torch.arange(batch, dtype=torch.int64, device="cuda")
+        (G.mg_sgemm_batched if f32 else G.mg_hgemm_batched)(C, N, N, m, n, k, alphas, A, place * (m * k), m, B, place * (k * n), k,
+                                                            betas, Cm, place * (m * n), m, batch)
+        alphas, betas = alphas.view(-1, 1, 1), betas.view(-1, 1, 1)
+    want = betas * old
+    for l in range(k):
+        want += alphas * B[:, :, l:l + 1] * A[:, l:l + 1, :]
+    assert torch.equal(Cm, want.to(kind))
