@@ -104,6 +104,7 @@ int pick_split(int64_t blocks, int64_t ktiles)
 // work-group) is fastest with about two work-groups per compute unit, the dot kernel (16 KB) with four; more
 // gain nothing and the reduce pass costs.  Each slice keeps at least four rounds of loads, and the partial
 // sums must fit the workspace.
+constexpr int64_t kMostGemvSlices = 256;         // what the matrix-vector kernels take
 int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t workspace_bytes)
 {
     const bool dot = cfg.lds_bytes == 0;
@@ -112,7 +113,7 @@ int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t wor
     if (2 * groups > wanted) return 1;
     int64_t split = ceil_div(wanted, groups);
     if (split > k / (4 * cfg.tile_k)) split = k / (4 * cfg.tile_k);
-    if (split > 256) split = 256;
+    if (split > kMostGemvSlices) split = kMostGemvSlices;
     const int64_t fits = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(outputs) * sizeof(float)));
     if (split > fits) split = fits;
     return split < 1 ? 1 : static_cast<int>(split);
@@ -153,6 +154,7 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
         const int64_t groups = ceil_div(outputs, 16 * lane_elems);
         int64_t slices = ceil_div((streams ? 4 : 1) * kComputeUnits, groups);
         if (slices > p.k / 512) slices = p.k / 512;             // one round of a work-group's loads per slice
+        if (slices > kMostGemvSlices) slices = kMostGemvSlices;
         const int64_t fits = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(outputs) * sizeof(float)));
         if (slices > fits) slices = fits;
         if (slices > 1 && panel(16, static_cast<int>(slices))) return;

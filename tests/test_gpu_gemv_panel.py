@@ -55,3 +55,22 @@ def test_infinities_stay_in_their_row(oracle):
     G.mg_sgemv(C, N, m, n, 1.0, A, m, x, 1, 0.0, y, 1, ws)
     out = y.cpu().numpy()
     assert np.isposinf(out[5]) and np.isfinite(np.delete(out, 5)).all()
+
+
+@pytest.mark.parametrize("dtype,outputs,length,ld", [("f32", 64, 400000, 1024), ("f32", 128, 200001, 1024), ("f32", 2048, 16384, 2048),
+                                                     ("f16", 128, 390001, 2048), ("f16", 4096, 16384, 4096)])
+def test_sums_sliced_over_a_streamed_matrix(dtype, outputs, length, ld):
+    """more than 96 MB with columns a multiple of 4 KB apart, up to as many slices as there are; integers, exact but for the rounding
+    of the result"""
+    import torch
+    f32 = dtype == "f32"
+    kind = torch.float32 if f32 else torch.float16
+    gen = torch.Generator(device="cuda").manual_seed(outputs)
+    A = torch.full((length, ld), float("nan"), device="cuda", dtype=kind)
+    A[:, :outputs] = torch.randint(-3, 4, (length, outputs), device="cuda", generator=gen, dtype=torch.int8).to(kind)
+    x = torch.randint(-3, 4, (length,), device="cuda", generator=gen).to(kind)
+    y = torch.randint(-3, 4, (outputs,), device="cuda", generator=gen).to(kind)
+    want = 2.0 * torch.mv(A[:, :outputs].t().double(), x.double()) - y.double()
+    ws = torch.empty(G.mg_gemv_workspace_bytes(G.MG_F32 if f32 else G.MG_F16, C, N, outputs, length, ld), dtype=torch.uint8, device="cuda")
+    (G.mg_sgemv if f32 else G.mg_hgemv)(C, N, outputs, length, 2.0, A, ld, x, 1, -1.0, y, 1, ws)
+    assert torch.equal(y, want.to(kind))
