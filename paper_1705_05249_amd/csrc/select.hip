@@ -111,7 +111,9 @@ int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t wor
     const int64_t wanted = (dot ? 4 : 2) * kComputeUnits;
     const int64_t groups = ceil_div(outputs, cfg.tile_m);
     if (2 * groups > wanted) return 1;
-    int64_t split = ceil_div(wanted, groups);
+    // (the axpy kernel rounds down: a few work-groups more than two per compute unit take a third turn of their own; us, up / down:
+    // 3072 x 16384 37.8 / 33.5, 9000^2 62.8 / 54.1, FP16 24576 x 7680 71.7 / 60.5, 60000 x 3000 69.2 / 60.4)
+    int64_t split = dot ? ceil_div(wanted, groups) : wanted / groups;
     if (split > k / (4 * cfg.tile_k)) split = k / (4 * cfg.tile_k);
     if (split > kMostGemvSlices) split = kMostGemvSlices;
     const int64_t fits = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(outputs) * sizeof(float)));
@@ -125,10 +127,16 @@ int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t wor
 //   11.7 / 8.2, 2048^2 11.3 / 9.7, 6144 x 3072 15.0 / 14.0, 4160 x 4096 14.3 / 11.7, FP16 11.8 / 9.2 (3072 x 6144 unsliced: 17.7);
 //   else one work-group of sixteen wavefronts per compute unit: 4096^2 20.8 / 13.1, 4097 x 4095 16.7 / 14.2, 1024 x 16384
 //   14.7 / 13.0, FP16 4096^2 11.7 / 10.8;
-//   matrices beyond 96 MB, which stream from memory, only with a long sum and columns a multiple of 4 KB apart (four work-groups
-//   per compute unit): 8192^2 55 / 46, 16384 x 4096 48.7 / 42.8, 2048 x 16384 33 / 27, FP16 8192^2 33 / 26; without:
-//   7000^2 35.0 / 35.2, 10000^2 65.7 / 73.7, 65536 x 1024 41 / 44; and beyond 384 MB not even then: 12288^2 95 / 112,
-//   16384^2 163 / 177;
+//   matrices beyond 96 MB, which stream from memory, stay with the axpy kernel: 7000^2 35.0 / 35.2, 10000^2 65.7 / 73.7,
+//   65536 x 1024 41 / 44, 512 x 97656 35.0 / 42.6, 16384 x 4608 49.9 / 56.6, FP16 1024 x 97656 39.7 / 46.0.  Up to 384 MB
+//   and with columns a multiple of 4 KB apart there are three exceptions, with four work-groups of the panel kernel per
+//   compute unit: the columns are a power of two apart and the axpy kernel's slices a multiple of 2 MB (they meet on the
+//   same channels; 8192^2 55.2 / 49.5, 4096 x 8192 33.1 / 25.6, 2048 x 16384 35.8 / 27.2, FP16 16384 x 4096 31.0 / 26.7;
+//   beside them 8192 x 8200 44.5 / 49.4 and 6144 x 10240 42.9 / 44.5), with neither few work-groups of it along the outputs
+//   (1024 x 65536 44.1 / 46.2, 192 x 260416 33.4 / 43.7) nor one of the panel kernel per compute unit (16384 x 4096 48.7 /
+//   52.3); the outputs leave most lanes of an axpy work-group idle (64 x 390625 36.2 / 20.6, FP16 256 x 390625 54.9 / 37.7;
+//   128 x 390625 38.9 / 37.9, FP16 512 x 195312 40.1 / 43.9); or they end inside a lane's run, which that kernel reads
+//   element by element (FP16 1500 x 66666 123 / 58);
 //   the axpy kernel also where its work-groups fill the chip by themselves (10^6 x 64: 40 / 66).
 void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
                              int32_t *kernel, int32_t *split)
@@ -139,7 +147,16 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
     const int64_t stride = (p.n == 1 ? p.a_sk() : p.b_sk()) * static_cast<int64_t>(p.elem());
     const char *axpy = f32 ? "gemv_axpy_f32" : "gemv_axpy_f16";
     const bool streams = bytes > 96.0e6;
-    if (bytes > 384.0e6 || (streams && (p.k <= 2560 || stride % 4096 != 0)) || outputs >= 64 * lane_elems * kComputeUnits) {
+    const int64_t fits = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(outputs) * sizeof(float)));
+    bool by_axpy = bytes > 384.0e6 || (streams && (p.k <= 2560 || stride % 4096 != 0)) || outputs >= 64 * lane_elems * kComputeUnits;
+    if (streams && !by_axpy) {
+        const mg_config &cfg = table[find(table, axpy)].cfg;
+        const int slices = pick_gemv_split(cfg, outputs, p.k, ~size_t(0));
+        const bool collide = (stride & (stride - 1)) == 0 && ceil_div(ceil_div(p.k, slices), cfg.tile_k) * cfg.tile_k * stride % (int64_t(2) << 20) == 0 &&
+                             outputs >= 8 * cfg.tile_m && outputs < 16 * lane_elems * kComputeUnits;
+        by_axpy = !(collide || outputs <= (f32 ? 64 : 256) || outputs % lane_elems != 0);
+    }
+    if (by_axpy) {
         if (!try_pick(table, p, alignment, axpy, 1, kernel, split)) return;
         const int want = pick_gemv_split(table[*kernel].cfg, outputs, p.k, workspace_bytes);
         if (want > 1) try_pick(table, p, alignment, axpy, want, kernel, split);
@@ -155,7 +172,6 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
         int64_t slices = ceil_div((streams ? 4 : 1) * kComputeUnits, groups);
         if (slices > p.k / 512) slices = p.k / 512;             // one round of a work-group's loads per slice
         if (slices > kMostGemvSlices) slices = kMostGemvSlices;
-        const int64_t fits = static_cast<int64_t>(workspace_bytes / (static_cast<size_t>(outputs) * sizeof(float)));
         if (slices > fits) slices = fits;
         if (slices > 1 && panel(16, static_cast<int>(slices))) return;
     }

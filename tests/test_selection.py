@@ -22,3 +22,22 @@ def test_few_outputs_and_a_long_sum_are_sliced(dtype, outputs, length, ld):
     """a handful of work-groups would otherwise read the whole matrix"""
     name, slices = matvec(dtype, outputs, length, ld)
     assert 64 <= slices <= 256, (name, slices)
+
+
+@pytest.mark.parametrize("dtype,outputs,length,ld,panel", [
+    (G.MG_F32, 8192, 8192, 8192, True), (G.MG_F32, 8192, 8200, 8192, False), (G.MG_F32, 8192, 6000, 8192, True),
+    (G.MG_F32, 4096, 7168, 4096, False), (G.MG_F32, 2048, 16384, 2048, True), (G.MG_F32, 512, 97656, 1024, False),
+    (G.MG_F32, 16384, 4096, 16384, False), (G.MG_F32, 8192, 8192, 8193, False), (G.MG_F32, 64, 400000, 1024, True),
+    (G.MG_F32, 128, 200000, 1024, False), (G.MG_F32, 192, 260416, 1024, False), (G.MG_F32, 1024, 65536, 1024, False), (G.MG_F16, 256, 390625, 2048, True), (G.MG_F16, 1024, 97656, 2048, False),
+    (G.MG_F16, 1500, 66666, 2048, True), (G.MG_F16, 16384, 4608, 16384, False), (G.MG_F32, 12288, 12288, 12288, False)])
+def test_streamed_matrices_take_the_panel_kernel_where_it_gains(dtype, outputs, length, ld, panel):
+    name, slices = matvec(dtype, outputs, length, ld)
+    assert ("panel" in name) == panel and slices > 1, (name, slices)
+
+
+@pytest.mark.parametrize("dtype,outputs,length,slices", [(G.MG_F32, 3072, 16384, 42), (G.MG_F32, 9000, 9000, 14), (G.MG_F16, 24576, 7680, 10),
+                                                         (G.MG_F32, 8200, 8200, 15)])
+def test_slices_of_a_streamed_matrix_fill_whole_turns(dtype, outputs, length, slices):
+    """two work-groups per compute unit, none left over"""
+    name, got = matvec(dtype, outputs, length, outputs)
+    assert "axpy" in name and got == slices
