@@ -175,7 +175,12 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
         if (slices > fits) slices = fits;
         if (slices > 1 && panel(16, static_cast<int>(slices))) return;
     }
-    panel(outputs >= 64 * 8 * lane_elems ? 8 : 4, 1);
+    // Many outputs, and so a short sum: sixteen lanes on a column, as half of the wavefronts would otherwise have no column to load;
+    // us, axpy / panel with 8 / 16 lanes: 60000 x 64 7.6 / 8.2 / 7.7, 60000 x 128 7.8 / 9.7 / 7.9, 50000 x 192 8.6 / 10.5 / 8.6, 65535
+    // x 128 13.8 / 10.1 / 8.3, 40000 x 512 17.7 / 13.7 / 13.0, FP16 60000 x 512 15.0 / 13.0 / 10.6; 32768 x 512 13.7 / 11.7 / 13.0.
+    // (FP16 columns that do not start on 16 bytes only with the shortest: 65535 x 128 21.5 / 9.1 / 8.1, 65535 x 512 33 / 18.6 / 22.9.)
+    if (outputs > 32768 && (f32 || p.k <= 256 || stride % 16 == 0)) panel(16, 1);
+    else panel(outputs >= 64 * 8 * lane_elems ? 8 : 4, 1);
 }
 
 }  // namespace

@@ -15,7 +15,7 @@ C, R, N, T = W.COL_MAJOR, W.ROW_MAJOR, W.NO_TRANS, W.TRANS
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 @pytest.mark.parametrize("layout,trans", [(C, N), (R, T)])
 @pytest.mark.parametrize("outputs,length,pad", [(1, 5, 0), (7, 63, 1), (16, 64, 0), (33, 511, 3), (63, 513, 0), (129, 2047, 1), (250, 2561, 5),
-                                                (2050, 130, 2), (4099, 40, 0)])
+                                                (2050, 130, 2), (4099, 40, 0), (33001, 17, 2), (65535, 130, 0)])
 def test_panel_edges_are_exact(oracle, dtype, layout, trans, outputs, length, pad):
     m, n = (outputs, length) if trans == N else (length, outputs)
     case = W.gemv_case(dtype, layout, trans, m, n, incx=1 + pad % 2, incy=1 + pad % 3, alpha=2.0, beta=-1.0, integer=True, pad=pad,

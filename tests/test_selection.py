@@ -41,3 +41,11 @@ def test_slices_of_a_streamed_matrix_fill_whole_turns(dtype, outputs, length, sl
     """two work-groups per compute unit, none left over"""
     name, got = matvec(dtype, outputs, length, outputs)
     assert "axpy" in name and got == slices
+
+
+@pytest.mark.parametrize("dtype,outputs,length,lanes", [
+    (G.MG_F32, 60000, 64, 16), (G.MG_F32, 65535, 16, 16), (G.MG_F32, 60000, 128, 16), (G.MG_F32, 32768, 512, 8), (G.MG_F32, 20000, 500, 8),
+    (G.MG_F16, 60000, 512, 16), (G.MG_F16, 65535, 128, 16), (G.MG_F16, 65535, 512, 8), (G.MG_F32, 1000, 64, 4)])
+def test_short_sums_over_many_outputs(dtype, outputs, length, lanes):
+    name, slices = matvec(dtype, outputs, length, outputs)
+    assert name.startswith(f"gemv_panel{lanes}_") and slices == 1, name
