@@ -169,18 +169,26 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
     };
     if (p.k > 2560 && !(p.k <= 4224 && stride % 4096 != 0 && outputs >= 64 * 8 * lane_elems)) {
         const int64_t groups = ceil_div(outputs, 16 * lane_elems);
-        int64_t slices = ceil_div((streams ? 4 : 1) * kComputeUnits, groups);
+        // (rounded down: one work-group more than the compute units doubles the time of one of them; us, up / down: 1500 x 12000
+        // 17.2 / 15.9, FP16 3000 x 12000 17.9 / 16.5, 5000 x 8192 18.4 / 17.4)
+        int64_t slices = (streams ? 4 : 1) * kComputeUnits / groups;
         if (slices > p.k / 512) slices = p.k / 512;             // one round of a work-group's loads per slice
         if (slices > kMostGemvSlices) slices = kMostGemvSlices;
         if (slices > fits) slices = fits;
         if (slices > 1 && panel(16, static_cast<int>(slices))) return;
     }
-    // Many outputs, and so a short sum: sixteen lanes on a column, as half of the wavefronts would otherwise have no column to load;
-    // us, axpy / panel with 8 / 16 lanes: 60000 x 64 7.6 / 8.2 / 7.7, 60000 x 128 7.8 / 9.7 / 7.9, 50000 x 192 8.6 / 10.5 / 8.6, 65535
-    // x 128 13.8 / 10.1 / 8.3, 40000 x 512 17.7 / 13.7 / 13.0, FP16 60000 x 512 15.0 / 13.0 / 10.6; 32768 x 512 13.7 / 11.7 / 13.0.
-    // (FP16 columns that do not start on 16 bytes only with the shortest: 65535 x 128 21.5 / 9.1 / 8.1, 65535 x 512 33 / 18.6 / 22.9.)
-    if (outputs > 32768 && (f32 || p.k <= 256 || stride % 16 == 0)) panel(16, 1);
-    else panel(outputs >= 64 * 8 * lane_elems ? 8 : 4, 1);
+    // Unsliced: the fewest lanes on a column that leave no compute unit a second work-group (us, FP32, 4 lanes / 8: 2048 x 4096 with
+    // an odd leading dimension 10.2 / 12.6, 3000 x 4224 11.2 / 14.0, 4000 x 4224 12.4 / 11.8; 8 lanes / 16: 8192 x 2000 12.4 /
+    // 12.7, 9000 x 2560 23.3 / 16.9, FP16 18000 x 2560 24.1 / 17.7; 20000 x 700 10.2 / 10.7, 32768 x 512 11.7 / 13.0).
+    // More outputs, and so a short sum: sixteen, as half of the wavefronts would otherwise have no column to load; axpy
+    // kernel / 8 lanes / 16: 60000 x 64 7.6 / 8.2 / 7.7, 60000 x 128 7.8 / 9.7 / 7.9, 50000 x 192 8.6 / 10.5 / 8.6, 65535 x 128 13.8 / 10.1 /
+    // 8.3, 40000 x 512 17.7 / 13.7 / 13.0, FP16 60000 x 512 15.0 / 13.0 / 10.6.  (FP16 columns that do not start on 16 bytes
+    // only with the shortest: 65535 x 128 21.5 / 9.1 / 8.1, 65535 x 512 33 / 18.6 / 22.9.)
+    const int64_t one_lane = lane_elems * kComputeUnits;        // outputs of a work-group per compute unit, per lane on a column
+    if (outputs <= 3 * one_lane) panel(4, 1);
+    else if (outputs <= 8 * one_lane) panel(8, 1);
+    else if (outputs <= 16 * one_lane) panel(16, 1);
+    else panel(outputs > 32768 && (f32 || p.k <= 256 || stride % 16 == 0) ? 16 : 8, 1);
 }
 
 }  // namespace

@@ -49,3 +49,15 @@ def test_slices_of_a_streamed_matrix_fill_whole_turns(dtype, outputs, length, sl
 def test_short_sums_over_many_outputs(dtype, outputs, length, lanes):
     name, slices = matvec(dtype, outputs, length, outputs)
     assert name.startswith(f"gemv_panel{lanes}_") and slices == 1, name
+
+
+@pytest.mark.parametrize("dtype,outputs,length,ld", [
+    (G.MG_F32, 1500, 12000, 1501), (G.MG_F32, 1500, 8192, 1500), (G.MG_F16, 3000, 12000, 3000), (G.MG_F16, 5000, 8192, 5000),
+    (G.MG_F32, 4096, 4096, 4096), (G.MG_F32, 2048, 4096, 2049), (G.MG_F16, 4096, 4096, 4097), (G.MG_F16, 5000, 4000, 5000),
+    (G.MG_F32, 9000, 2560, 9000), (G.MG_F32, 8192, 2560, 8192), (G.MG_F16, 18000, 2560, 18001)])
+def test_panels_do_not_outnumber_the_compute_units(dtype, outputs, length, ld):
+    """one compute unit with two of the sixteen-wavefront work-groups sets the time"""
+    name, slices = matvec(dtype, outputs, length, ld)
+    lanes, elems = int(name.split("_")[1][5:]), 4 if dtype == G.MG_F32 else 8
+    assert -(-outputs // (lanes * elems)) * slices <= 256, (name, slices)
+    assert slices > 1 or lanes == 4 or outputs > 3 * elems * 256, name
