@@ -156,6 +156,12 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
                              outputs >= 8 * cfg.tile_m && outputs < 16 * lane_elems * kComputeUnits;
         by_axpy = !(collide || outputs <= (f32 ? 64 : 256) || outputs % lane_elems != 0);
     }
+    // A sum of a few terms is over before sixteen wavefronts have met, unless ragged outputs make the axpy kernel read elements
+    // (us, axpy / panel with 16 lanes: 1000 x 4 2.1 / 2.3, 16384 x 16 2.4 / 2.6, 40000 x 32 3.1 / 3.8, 65472 x 32 3.1 / 4.4, 65535 x 32 4.8 / 4.4,
+    // FP16 65472 x 32 3.3 / 3.9; 16384 x 64 3.6 / 2.7), and where FP32 panels would be three or more work-groups a compute unit
+    // (40000 x 64 4.0 / 4.4, 65472 x 128 7.1 / 7.7, x 192 9.4 / 9.6; FP16 x 64 4.3 / 4.0)
+    const bool even = outputs % lane_elems == 0;
+    if (p.k <= 8 || (even && (p.k <= 32 || (f32 && p.k <= 128 && outputs > 32768)))) by_axpy = true;
     if (by_axpy) {
         if (!try_pick(table, p, alignment, axpy, 1, kernel, split)) return;
         const int want = pick_gemv_split(table[*kernel].cfg, outputs, p.k, workspace_bytes);
@@ -179,16 +185,17 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
     }
     // Unsliced: the fewest lanes on a column that leave no compute unit a second work-group (us, FP32, 4 lanes / 8: 2048 x 4096 with
     // an odd leading dimension 10.2 / 12.6, 3000 x 4224 11.2 / 14.0, 4000 x 4224 12.4 / 11.8; 8 lanes / 16: 8192 x 2000 12.4 /
-    // 12.7, 9000 x 2560 23.3 / 16.9, FP16 18000 x 2560 24.1 / 17.7; 20000 x 700 10.2 / 10.7, 32768 x 512 11.7 / 13.0).
-    // More outputs, and so a short sum: sixteen, as half of the wavefronts would otherwise have no column to load; axpy
-    // kernel / 8 lanes / 16: 60000 x 64 7.6 / 8.2 / 7.7, 60000 x 128 7.8 / 9.7 / 7.9, 50000 x 192 8.6 / 10.5 / 8.6, 65535 x 128 13.8 / 10.1 /
-    // 8.3, 40000 x 512 17.7 / 13.7 / 13.0, FP16 60000 x 512 15.0 / 13.0 / 10.6.  (FP16 columns that do not start on 16 bytes
-    // only with the shortest: 65535 x 128 21.5 / 9.1 / 8.1, 65535 x 512 33 / 18.6 / 22.9.)
+    // 12.7, 9000 x 2560 23.3 / 16.9, FP16 18000 x 2560 24.1 / 17.7).  With more outputs, and so a shorter sum, sixteen (8 / 16:
+    // 20000 x 256 6.3 / 5.7, 40000 x 512 13.7 / 13.0, FP16 60000 x 512 13.0 / 10.6), but eight for FP32 sums beyond 256 up to 32768
+    // outputs (20000 x 700 10.2 / 10.7, 32768 x 512 11.7 / 13.0) and where FP16 columns do not start on 16 bytes (65535 x 384
+    // 15.2 / 17.3).  Sums of at most 128 terms leave half of the wavefronts of eight lanes without a column: sixteen (4 / 8 /
+    // 16: 4096 x 64 2.9 / 2.7 / 2.5, 32768 x 64 8.7 / 5.1 / 3.1).
     const int64_t one_lane = lane_elems * kComputeUnits;        // outputs of a work-group per compute unit, per lane on a column
-    if (outputs <= 3 * one_lane) panel(4, 1);
+    if (p.k <= 128) panel(16, 1);
+    else if (outputs <= 3 * one_lane) panel(4, 1);
     else if (outputs <= 8 * one_lane) panel(8, 1);
-    else if (outputs <= 16 * one_lane) panel(16, 1);
-    else panel(outputs > 32768 && (f32 || p.k <= 256 || stride % 16 == 0) ? 16 : 8, 1);
+    else if (outputs <= 16 * one_lane || p.k <= 256) panel(16, 1);
+    else panel(outputs > 32768 && (f32 || stride % 16 == 0) ? 16 : 8, 1);
 }
 
 }  // namespace

@@ -43,12 +43,15 @@ def test_slices_of_a_streamed_matrix_fill_whole_turns(dtype, outputs, length, sl
     assert "axpy" in name and got == slices
 
 
-@pytest.mark.parametrize("dtype,outputs,length,lanes", [
-    (G.MG_F32, 60000, 64, 16), (G.MG_F32, 65535, 16, 16), (G.MG_F32, 60000, 128, 16), (G.MG_F32, 32768, 512, 8), (G.MG_F32, 20000, 500, 8),
-    (G.MG_F16, 60000, 512, 16), (G.MG_F16, 65535, 128, 16), (G.MG_F16, 65535, 512, 8), (G.MG_F32, 1000, 64, 4)])
-def test_short_sums_over_many_outputs(dtype, outputs, length, lanes):
+@pytest.mark.parametrize("dtype,outputs,length,kernel", [
+    (G.MG_F32, 60000, 64, "axpy"), (G.MG_F32, 65532, 16, "axpy"), (G.MG_F32, 60000, 128, "axpy"), (G.MG_F32, 40000, 64, "axpy"), (G.MG_F32, 1000, 4, "axpy"),
+    (G.MG_F32, 65535, 5, "axpy"), (G.MG_F16, 60000, 32, "axpy"), (G.MG_F32, 65535, 32, "panel16"), (G.MG_F32, 32768, 64, "panel16"),
+    (G.MG_F32, 1000, 64, "panel16"), (G.MG_F16, 60000, 64, "panel16"), (G.MG_F16, 65535, 128, "panel16"), (G.MG_F32, 40000, 512, "panel16"),
+    (G.MG_F16, 60000, 512, "panel16"), (G.MG_F16, 65535, 512, "panel8"), (G.MG_F32, 32768, 512, "panel8"), (G.MG_F32, 20000, 256, "panel16"),
+    (G.MG_F32, 20000, 700, "panel8"), (G.MG_F32, 1000, 1000, "panel4")])
+def test_short_sums(dtype, outputs, length, kernel):
     name, slices = matvec(dtype, outputs, length, outputs)
-    assert name.startswith(f"gemv_panel{lanes}_") and slices == 1, name
+    assert name.startswith(f"gemv_{kernel}_") and slices == 1, name
 
 
 @pytest.mark.parametrize("dtype,outputs,length,ld", [
