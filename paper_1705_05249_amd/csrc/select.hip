@@ -6,6 +6,7 @@
 #include <unordered_map>
 
 #include "select.h"
+#include "tile_count.h"
 
 namespace mg {
 namespace {
@@ -301,14 +302,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         const bool triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
         auto wanted_tiles = [&](int bm, int bn) {
             const int64_t across_m = ceil_div(tm, bm), across_n = ceil_div(tn, bn);
-            if (!triangle || f32) return across_m * across_n;
-            int64_t count = 0;
-            if (p.shape == MG_SHAPE_C_LOWER) {
-                for (int64_t j = 0; j < across_n; ++j) count += across_m > j * bn / bm ? across_m - j * bn / bm : 0;
-            } else {
-                for (int64_t i = 0; i < across_m; ++i) count += across_n > i * bm / bn ? across_n - i * bm / bn : 0;
-            }
-            return count;
+            return triangle && !f32 ? triangle_tiles(p.shape == MG_SHAPE_C_LOWER, across_m, across_n, bm, bn) : across_m * across_n;
         };
         // estimated time (in 1e-6 us) of tile i with the sum cut into `slices`
         auto estimate = [&](int i, int slices) {

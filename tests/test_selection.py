@@ -1,8 +1,13 @@
 """Host-only checks of the rules that choose a kernel (csrc/select.hip), through the selection query and the workspace queries."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 from paper_1705_05249_amd import gemm as G
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 C, N = G.MG_COL_MAJOR, G.MG_NO_TRANS
 
 
@@ -64,3 +69,57 @@ def test_panels_do_not_outnumber_the_compute_units(dtype, outputs, length, ld):
     lanes, elems = int(name.split("_")[1][5:]), 4 if dtype == G.MG_F32 else 8
     assert -(-outputs // (lanes * elems)) * slices <= 256, (name, slices)
     assert slices > 1 or lanes == 4 or outputs > 3 * elems * 256, name
+
+
+def test_tiles_of_a_triangle(tmp_path):
+    """the closed form against the tiles counted one by one"""
+    src, exe = tmp_path / "count.cpp", tmp_path / "count"
+    src.write_text("""
+        #include <cstdio>
+        #include "tile_count.h"
+        int main()
+        {
+            const int tiles[][2] = {{256, 256}, {256, 128}, {128, 128}, {128, 64}, {64, 64}};
+            for (const auto &t : tiles)
+                for (int64_t n = 1; n < 3000; n += n < 300 ? 1 : 61) {
+                    const int64_t across_m = (n + t[0] - 1) / t[0], across_n = (n + t[1] - 1) / t[1];
+                    int64_t lower = 0, upper = 0;
+                    for (int64_t i = 0; i < across_m; ++i)
+                        for (int64_t j = 0; j < across_n; ++j) {
+                            lower += (i + 1) * t[0] > j * t[1];                    // the tile's last row reaches its first column
+                            upper += (j + 1) * t[1] > i * t[0];
+                        }
+                    if (lower != mg::triangle_tiles(true, across_m, across_n, t[0], t[1]) ||
+                        upper != mg::triangle_tiles(false, across_m, across_n, t[0], t[1]))
+                        printf("%d x %d, n = %lld\\n", t[0], t[1], (long long)n);
+                }
+        }""")
+    csrc = os.path.join(ROOT, "paper_1705_05249_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout == ""
+
+
+def test_selection_time_does_not_grow_with_the_matrix():
+    """a rank-64 update of 2^20 x 2^20 is ranked in the time that one of 2048 x 2048 takes (no device: the launch fails)"""
+    program = """
+import sys, time
+sys.path.insert(0, sys.argv[1])
+import torch
+assert torch.cuda.device_count() == 0
+from paper_1705_05249_amd import gemm as G
+P, call = 0x10000, G.lib().mg_hsyrk
+def fastest(n):
+    best = 1.0
+    for _ in range(40):
+        t = time.perf_counter()
+        for _ in range(20):
+            assert call(G.MG_COL_MAJOR, G.MG_LOWER, G.MG_NO_TRANS, n, 64, 1.0, P, n, 0.0, P, n, P, 1 << 50, None) == -12
+        best = min(best, (time.perf_counter() - t) / 20)
+    return best * 1e6
+print(fastest(2048), fastest(2 ** 20))
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    run = subprocess.run([sys.executable, "-c", program, ROOT], capture_output=True, text=True, timeout=300, env=env)
+    assert run.returncode == 0, run.stderr
+    small, large = map(float, run.stdout.split())
+    assert large < 3.0 * small + 20.0, (small, large)                  # microseconds
