@@ -184,7 +184,6 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     if (p.shape != MG_SHAPE_GENERAL || p.alpha == 0.f || p.k == 0) return false;
     if (g_override_kernel[p.dtype] >= 0) return false;                 // a forced kernel gets the problem as it is
     const double work = static_cast<double>(p.m) * static_cast<double>(p.n) * static_cast<double>(p.k);
-    const size_t elem = p.elem();
     int64_t tile = 0, ktile = 0;
     bool compare = false;
     if (p.dtype == MG_F16) {
@@ -243,8 +242,14 @@ Problem padded_problem(const Problem &p, const IndirectPlan &plan, PadCopy (&cop
     return q;
 }
 
-// *taken = false: nothing was launched, the direct route is the better one.
-mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken)
+// What choose() decided for a problem (its fringe included); kernel < 0: nothing yet.
+struct Chosen {
+    Problem p;
+    int32_t kernel = -1, split = 1;
+};
+
+// *taken = false: nothing was launched, the direct route is the better one, with the configuration in *direct if that is known.
+mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken, Chosen *direct)
 {
     *taken = true;
     hipStream_t st = p.stream;
@@ -258,9 +263,13 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken)
         int32_t best_kernel = -1;
         double best_us = 0.0;
         IndirectPlan best_plan{};
+        int64_t last_mp = 0, last_np = 0;
         for (const auto &tile : {std::pair<int64_t, int64_t>{256, 256}, {256, 128}, {128, 128}}) {
             const IndirectPlan candidate = padded_to(p, tile.first, tile.second, 64);
-            if (candidate.total() > plan.total()) continue;
+            // (the smaller tiles were ranked with the larger ones' padding if that is the same)
+            if (candidate.total() > plan.total() || (candidate.mp == last_mp && candidate.np == last_np)) continue;
+            last_mp = candidate.mp;
+            last_np = candidate.np;
             Problem in_place = padded_problem(p, candidate, copies);
             in_place.clip_m = p.m;
             in_place.clip_n = p.n;
@@ -279,10 +288,10 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken)
             // the copies of A and B: a launch, the gap behind it and their traffic at ~3.5 TB/s (the bounds-checked kernels run
             // 10-25 % above their estimate at these sizes)
             const double copies_us = 5.0 + 4.0 * static_cast<double>(p.k) * (static_cast<double>(p.m) + static_cast<double>(p.n)) / 3.5e6;
-            Problem direct = p;
-            int32_t kernel = -1, split = 1;
+            direct->p = p;
             double us = 0.0;
-            const bool known = choose(direct, problem_alignment(direct), p.workspace_bytes, &kernel, &split, &us) == MG_OK;
+            const bool known = choose(direct->p, problem_alignment(p), p.workspace_bytes, &direct->kernel, &direct->split, &us) == MG_OK;
+            if (!known) direct->kernel = -1;
             if (best_kernel < 0 || (known && us > 0.0 && 1.15 * us <= best_us + copies_us)) {
                 *taken = false;
                 return MG_OK;
@@ -296,7 +305,8 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken)
         int32_t kernel = -1, split = 1;
         double us = 0.0;
         const size_t left = p.workspace_bytes - plan.total();
-        const bool sliced = best_kernel >= 0 && choose(padded, problem_alignment(padded), left, &kernel, &split, &us) == MG_OK && split > 1 &&
+        const bool slices_fit = left / (2 * sizeof(float)) >= static_cast<size_t>(plan.mp) * static_cast<size_t>(plan.np);
+        const bool sliced = best_kernel >= 0 && slices_fit && choose(padded, problem_alignment(padded), left, &kernel, &split, &us) == MG_OK && split > 1 &&
                             us > 0.0 &&
                             us + 4.0 + 8.0 * static_cast<double>(plan.mp) * static_cast<double>(plan.np) / 3.5e6 < best_us;
         if (best_kernel >= 0 && !sliced) {
@@ -322,18 +332,23 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken)
 mg_status run_canonical(Problem p)
 {
     IndirectPlan plan;
+    Chosen chosen;
     // (the copy back out of the padded result writes all of C: not for a call that may only touch a triangle)
     if (!p.mask_c && indirect_plan(p, true, &plan) && p.workspace != nullptr && pointer_alignment(p.workspace) >= 256 &&
         p.workspace_bytes >= plan.total()) {
         bool taken = false;
-        const mg_status done = run_indirect(p, plan, &taken);
+        const mg_status done = run_indirect(p, plan, &taken, &chosen);
         if (taken) return done;
     }
-    int32_t kernel = -1, split = 1;
     const bool ws_usable = p.workspace != nullptr && pointer_alignment(p.workspace) >= 256;
-    const mg_status s = choose(p, problem_alignment(p), ws_usable ? p.workspace_bytes : 0, &kernel, &split);
-    if (s != MG_OK) return s;
-    const KernelEntry &e = table()[kernel];
+    if (chosen.kernel < 0) {
+        chosen.p = p;
+        const mg_status s = choose(chosen.p, problem_alignment(p), ws_usable ? p.workspace_bytes : 0, &chosen.kernel, &chosen.split);
+        if (s != MG_OK) return s;
+    }
+    p = chosen.p;
+    const int32_t split = chosen.split;
+    const KernelEntry &e = table()[chosen.kernel];
     if (p.mask_c && !e.masks_triangle) return MG_ERR_CONFIG;      // the caller takes the route that sets the rest of C aside
     const size_t need = e.workspace(p, split);
     if (need > 0 && !(ws_usable && p.workspace_bytes >= need)) return MG_ERR_WORKSPACE;

@@ -410,50 +410,59 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (slices > 1) time += 1.0e6 * ((f32 && ragged ? 4.0 : 2.5) + (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) / 4.0e6);
             return time;
         };
-        for (int attempt = 0; attempt < count; ++attempt) {
-            int best = -1, best_slices = 1;
-            double best_time = 0.0;
-            double free_time = 0.0;          // best estimate with all the workspace one could wish for, and its slices
-            int free_slices = 0;
-            for (int i = 0; i < count; ++i) {
-                if (tried[i]) continue;
-                // FP32 with a short K is bound by the traffic of C, which the large tiles overlap worst (one epilogue per
-                // compute unit at a time).  us, the tile the estimate would take (256 x 256 or 128 x 128) / 128 x 64 / 64 x 64,
-                // beta != 0: (8192, 8192, 64) 200 / 154 / 157, (8192, 8192, 256) 351 / 310 / 322, (8192, 8192, 512) 574 / 534 / 551,
-                // (4096, 4096, 160) 60 / 59 / 54, (3000, 3000, 256) 67 / 53 / 47, (2048, 2048, 512) 41 / 40 / 36, (5000, 5000,
-                // 64) - / 69 / 70; beta = 0: (2048, 2048, 160) 18.1 / 17.4 / 16.7, (3000, 3000, 160) 43 / 38 / 33, from
-                // k = 256 on within 2 %; ragged problems of several turns whose 128 x 64 tiles need no more of them stay
-                // on those: (1393, 4318, 136) 31.3 / 33.9 (five turns against nine: (3000, 3000, 160) above)
-                if (f32 && p.k <= 128 && tiles[i].bm * tiles[i].bn > 128 * 64) continue;
-                if (f32 && p.shape == MG_SHAPE_GENERAL && p.k <= (p.beta != 0.f ? 512 : 192)) {
-                    const int64_t turns64 = ceil_div(ceil_div(tm, 64) * ceil_div(tn, 64), kComputeUnits);
-                    const int64_t turns128 = ceil_div(ceil_div(tm, 128) * ceil_div(tn, 64), kComputeUnits);
-                    const bool whole = tm % 128 == 0 && tn % 64 == 0 && p.k % 32 == 0;
-                    const bool wide = whole ? p.m * p.n > 25000000 : p.k > 128 && turns64 >= 6 && 2 * turns128 <= turns64;
-                    if (tiles[i].bm * tiles[i].bn > (wide ? 128 * 64 : 64 * 64)) continue;
-                }
-                const bool last = i == smallest;
-                const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
-                const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn);
-                // slices tried: none; for the smallest tile the factor of the sweep's rule; for grids that do not
-                // fill the chip powers of two that leave every slice at least four K-tiles (never with a shape hint)
-                int options[6] = {1, 0, 0, 0, 0, 0};
-                int n_options = 1;
-                if (p.shape == MG_SHAPE_GENERAL) {
-                    if (last) options[n_options++] = pick_split(blocks, ktiles);
-                    if (blocks < 2 * kComputeUnits)
-                        for (int sl = 2; sl <= 16 && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
-                }
-                for (int o = 0; o < n_options; ++o) {
-                    const int sl = options[o];
-                    if (sl < 1 || (o > 0 && sl == 1)) continue;
-                    const double time = estimate(i, sl);
-                    if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
-                    if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
-                    if (best < 0 || time < best_time) { best = i; best_slices = sl; best_time = time; }
-                }
+        // each tile's estimate with the slices that suit it and the workspace, ranked once for all attempts
+        struct Ranked {
+            int slices;                      // 0: not a candidate
+            double time;
+        } ranked[9] = {};
+        double free_time = 0.0;              // best estimate with all the workspace one could wish for, and its slices
+        int free_slices = 0;
+        const bool in_place = p.clip_m != 0 || p.clip_n != 0;
+        for (int i = 0; i < count; ++i) {
+            if (in_place && i > 2 && i != kDeep) continue;           // (no other tile has the flavour, and it is not sliced)
+            // FP32 with a short K is bound by the traffic of C, which the large tiles overlap worst (one epilogue per
+            // compute unit at a time).  us, the tile the estimate would take (256 x 256 or 128 x 128) / 128 x 64 / 64 x 64,
+            // beta != 0: (8192, 8192, 64) 200 / 154 / 157, (8192, 8192, 256) 351 / 310 / 322, (8192, 8192, 512) 574 / 534 / 551,
+            // (4096, 4096, 160) 60 / 59 / 54, (3000, 3000, 256) 67 / 53 / 47, (2048, 2048, 512) 41 / 40 / 36, (5000, 5000,
+            // 64) - / 69 / 70; beta = 0: (2048, 2048, 160) 18.1 / 17.4 / 16.7, (3000, 3000, 160) 43 / 38 / 33, from
+            // k = 256 on within 2 %; ragged problems of several turns whose 128 x 64 tiles need no more of them stay
+            // on those: (1393, 4318, 136) 31.3 / 33.9 (five turns against nine: (3000, 3000, 160) above)
+            if (f32 && p.k <= 128 && tiles[i].bm * tiles[i].bn > 128 * 64) continue;
+            if (f32 && p.shape == MG_SHAPE_GENERAL && p.k <= (p.beta != 0.f ? 512 : 192)) {
+                const int64_t turns64 = ceil_div(ceil_div(tm, 64) * ceil_div(tn, 64), kComputeUnits);
+                const int64_t turns128 = ceil_div(ceil_div(tm, 128) * ceil_div(tn, 64), kComputeUnits);
+                const bool whole = tm % 128 == 0 && tn % 64 == 0 && p.k % 32 == 0;
+                const bool wide = whole ? p.m * p.n > 25000000 : p.k > 128 && turns64 >= 6 && 2 * turns128 <= turns64;
+                if (tiles[i].bm * tiles[i].bn > (wide ? 128 * 64 : 64 * 64)) continue;
             }
+            const bool last = i == smallest;
+            const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
+            const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn);
+            // slices tried: none; for the smallest tile the factor of the sweep's rule; for grids that do not
+            // fill the chip powers of two that leave every slice at least four K-tiles (never with a shape hint)
+            int options[6] = {1, 0, 0, 0, 0, 0};
+            int n_options = 1;
+            if (p.shape == MG_SHAPE_GENERAL && !in_place) {
+                if (last) options[n_options++] = pick_split(blocks, ktiles);
+                if (blocks < 2 * kComputeUnits)
+                    for (int sl = 2; sl <= 16 && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
+            }
+            for (int o = 0; o < n_options; ++o) {
+                const int sl = options[o];
+                if (sl < 1 || (o > 0 && sl == 1)) continue;
+                const double time = estimate(i, sl);
+                if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
+                if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
+                if (ranked[i].slices == 0 || time < ranked[i].time) ranked[i] = Ranked{sl, time};
+            }
+        }
+        for (int attempt = 0; attempt < count; ++attempt) {
+            int best = -1;
+            for (int i = 0; i < count; ++i)
+                if (!tried[i] && ranked[i].slices != 0 && (best < 0 || ranked[i].time < ranked[best].time)) best = i;
             if (best < 0) break;
+            const int want = ranked[best].slices;
+            const double best_time = ranked[best].time;
             // FP16, other orders and shorter sums: where the macro tiles would cut a sum of at most three 512-wide chunks
             // into slices (a second launch that adds the partial sums), the shared-sum kernel does it in one
             // (whether or not the caller brought the workspace for the slices)
@@ -484,7 +493,6 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             }
             tried[best] = true;
             const TileChoice &tc = tiles[best];
-            const int want = best_slices;
             // a factor whose last slice would be empty is illegal: take the next smaller one
             for (int w = want; w >= 1; --w)
                 if (try_mfma(table, p, alignment, tc.tag, w, kernel, split)) {

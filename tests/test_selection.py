@@ -123,3 +123,31 @@ print(fastest(2048), fastest(2 ** 20))
     assert run.returncode == 0, run.stderr
     small, large = map(float, run.stdout.split())
     assert large < 3.0 * small + 20.0, (small, large)                  # microseconds
+
+
+def test_padded_copies_are_weighed_in_the_time_of_one_selection():
+    """a ragged FP16 product that may take padded copies ranks the tiles for two or three paddings and for the direct route: not
+    in several times what a product without that choice takes (no device: the launch fails)"""
+    program = """
+import sys, time
+sys.path.insert(0, sys.argv[1])
+import torch
+assert torch.cuda.device_count() == 0
+from paper_1705_05249_amd import gemm as G
+P, call = 0x10000, G.lib().mg_hgemm
+def fastest(n):
+    need = G.mg_gemm_workspace_bytes(G.MG_F16, G.MG_COL_MAJOR, G.MG_NO_TRANS, G.MG_NO_TRANS, n, n, n, n, n, n)
+    best = 1.0
+    for _ in range(60):
+        t = time.perf_counter()
+        for _ in range(20):
+            assert call(G.MG_COL_MAJOR, G.MG_NO_TRANS, G.MG_NO_TRANS, n, n, n, 1.0, P, n, P, n, 0.5, P, n, P, need, None) == -12
+        best = min(best, (time.perf_counter() - t) / 20)
+    return best * 1e6
+print(fastest(900), fastest(1500), fastest(2050))
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    run = subprocess.run([sys.executable, "-c", program, ROOT], capture_output=True, text=True, timeout=300, env=env)
+    assert run.returncode == 0, run.stderr
+    direct, *weighed = map(float, run.stdout.split())
+    assert max(weighed) < 2.0 * direct, (direct, weighed)              # microseconds
