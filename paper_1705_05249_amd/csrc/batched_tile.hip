@@ -36,9 +36,10 @@ struct TileBatchArgs {
     const float *alphas, *betas;
     int64_t lda, ldb, ldc;
     int m, n, k;
-    int tiles_m;                   // tiles along m
+    batchwalk::Divisor tiles_m;    // tiles along m
     int64_t inst0, batch;          // of this launch: the instances from inst0 on,
-    uint32_t tile0, tiles;         // and the tiles of each from tile0 on
+    uint32_t tile0;                // and the tiles of each from tile0 on
+    batchwalk::Walk walk;
     int strided;
     int64_t stride_a, stride_b, stride_c;
     float alpha, beta;
@@ -196,15 +197,15 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
     if constexpr (TEAM == 1) {
         inst = static_cast<int64_t>(blockIdx.x) * 4 + wave;
     } else {
-        const batchwalk::Place at = batchwalk::place(blockIdx.x, a.batch, a.tiles);
+        const batchwalk::Place at = batchwalk::place(a.walk, blockIdx.x);
         inst = at.inst;
         tile = a.tile0 + at.tile;
     }
     if (inst >= a.batch) return;
     inst += a.inst0;
     const float alpha = a.strided ? a.alpha : a.alphas[inst], beta = a.strided ? a.beta : a.betas[inst];
-    const uint32_t tile_col = tile / static_cast<uint32_t>(a.tiles_m);
-    const int i0 = static_cast<int>(tile - tile_col * a.tiles_m) * TM, j0 = static_cast<int>(tile_col) * TN;
+    const uint32_t tile_col = a.tiles_m.quot(tile);
+    const int i0 = static_cast<int>(tile - tile_col * a.tiles_m.d) * TM, j0 = static_cast<int>(tile_col) * TN;
     const int mt = a.m - i0 < TM ? a.m - i0 : TM, nt = a.n - j0 < TN ? a.n - j0 : TN;
     const T *A = static_cast<const T *>(a.A) + (a.strided ? inst * a.stride_a : a.a_off[inst]) + (A_KC ? i0 * a.lda : i0);
     const T *B = static_cast<const T *>(a.B) + (a.strided ? inst * a.stride_b : a.b_off[inst]) + (B_KC ? j0 * a.ldb : j0);
@@ -339,14 +340,14 @@ template <typename T, int WM, int WN, int MB, int NB, bool A_KC, bool B_KC> stru
     {
         const int64_t tiles_m = ceil_div(p.m, TM), tiles = tiles_m * ceil_div(p.n, TN);
         TileBatchArgs a{p.A, p.B, p.C, p.a_off, p.b_off, p.c_off, p.alphas, p.betas, p.lda, p.ldb, p.ldc,
-                        static_cast<int>(p.m), static_cast<int>(p.n), static_cast<int>(p.k), static_cast<int>(tiles_m),
-                        0, 0, 0, 0, p.strided ? 1 : 0, p.stride_a, p.stride_b, p.stride_c, p.alpha, p.beta};
+                        static_cast<int>(p.m), static_cast<int>(p.n), static_cast<int>(p.k), batchwalk::divisor(tiles_m),
+                        0, 0, 0, {}, p.strided ? 1 : 0, p.stride_a, p.stride_b, p.stride_c, p.alpha, p.beta};
         hipError_t e = hipSuccess;
         batchwalk::for_pieces(p.batch, tiles, TEAM == 1 ? 4 : 0, [&](int64_t inst0, int64_t count, int64_t tile0, int64_t piece_tiles) {
             a.inst0 = inst0;
             a.batch = count;
             a.tile0 = static_cast<uint32_t>(tile0);
-            a.tiles = static_cast<uint32_t>(piece_tiles);
+            a.walk = batchwalk::walk(count, piece_tiles);
             const int64_t groups = TEAM == 1 ? ceil_div(count, 4) : batchwalk::work_groups(count, piece_tiles);
             hipLaunchKernelGGL((batched_tile_kernel<T, WM, WN, MB, NB, A_KC, B_KC>), dim3(static_cast<unsigned>(groups)), dim3(256), 0,
                                p.stream, a);
