@@ -37,7 +37,7 @@ struct TileBatchArgs {
     int64_t lda, ldb, ldc;
     int m, n, k;
     batchwalk::Divisor tiles_m;    // tiles along m
-    int64_t inst0, batch;          // of this launch: the instances from inst0 on,
+    int64_t batch;                 // of this launch: the instances behind the pointers and offsets,
     uint32_t tile0;                // and the tiles of each from tile0 on
     batchwalk::Walk walk;
     int strided;
@@ -202,7 +202,6 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
         tile = a.tile0 + at.tile;
     }
     if (inst >= a.batch) return;
-    inst += a.inst0;
     const float alpha = a.strided ? a.alpha : a.alphas[inst], beta = a.strided ? a.beta : a.betas[inst];
     const uint32_t tile_col = a.tiles_m.quot(tile);
     const int i0 = static_cast<int>(tile - tile_col * a.tiles_m.d) * TM, j0 = static_cast<int>(tile_col) * TN;
@@ -341,10 +340,20 @@ template <typename T, int WM, int WN, int MB, int NB, bool A_KC, bool B_KC> stru
         const int64_t tiles_m = ceil_div(p.m, TM), tiles = tiles_m * ceil_div(p.n, TN);
         TileBatchArgs a{p.A, p.B, p.C, p.a_off, p.b_off, p.c_off, p.alphas, p.betas, p.lda, p.ldb, p.ldc,
                         static_cast<int>(p.m), static_cast<int>(p.n), static_cast<int>(p.k), batchwalk::divisor(tiles_m),
-                        0, 0, 0, {}, p.strided ? 1 : 0, p.stride_a, p.stride_b, p.stride_c, p.alpha, p.beta};
+                        0, 0, {}, p.strided ? 1 : 0, p.stride_a, p.stride_b, p.stride_c, p.alpha, p.beta};
         hipError_t e = hipSuccess;
         batchwalk::for_pieces(p.batch, tiles, TEAM == 1 ? 4 : 0, [&](int64_t inst0, int64_t count, int64_t tile0, int64_t piece_tiles) {
-            a.inst0 = inst0;
+            if (p.strided) {
+                a.A = static_cast<const T *>(p.A) + inst0 * p.stride_a;
+                a.B = static_cast<const T *>(p.B) + inst0 * p.stride_b;
+                a.C = static_cast<T *>(p.C) + inst0 * p.stride_c;
+            } else {
+                a.a_off = p.a_off + inst0;
+                a.b_off = p.b_off + inst0;
+                a.c_off = p.c_off + inst0;
+                a.alphas = p.alphas + inst0;
+                a.betas = p.betas + inst0;
+            }
             a.batch = count;
             a.tile0 = static_cast<uint32_t>(tile0);
             a.walk = batchwalk::walk(count, piece_tiles);
