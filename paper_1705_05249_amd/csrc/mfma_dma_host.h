@@ -37,12 +37,11 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int RB = 32, bool C
                                             Staged::k_per_split(p, split), p, split);
     }
 
-    static KernelEntry entry(const char *name)
+    static KernelEntry entry(const char *name, hipError_t (*run)(const Problem &, int) = launch)
     {
-        KernelEntry e = Staged::entry(name);
+        KernelEntry e = Staged::entry(name, run);
         e.cfg.lds_bytes = LDS;
         e.legal = legal;
-        e.launch = launch;
         return e;
     }
 };
@@ -62,9 +61,8 @@ template <bool AK, bool CLIP = false> struct MfmaPpConfig {
 
     static KernelEntry entry(const char *name)
     {
-        KernelEntry e = Dma::entry(name);
+        KernelEntry e = Dma::entry(name, launch);
         e.cfg.lds_bytes = LDS;
-        e.launch = launch;
         return e;
     }
 };

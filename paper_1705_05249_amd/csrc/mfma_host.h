@@ -153,7 +153,8 @@ struct MfmaConfig {
                                      k_per_split(p, split), p, split, FRINGE ? fringe_groups(p) : 0);
     }
 
-    static KernelEntry entry(const char *name)
+    // (`run`: what a kernel of the same tile and rules launches instead; this one is then not compiled)
+    static KernelEntry entry(const char *name, hipError_t (*run)(const Problem &, int) = launch)
     {
         mg_config c{};
         c.family = CONV ? MG_FAMILY_CONV : MG_FAMILY_MFMA;
@@ -163,7 +164,7 @@ struct MfmaConfig {
         c.split_k = 1;
         c.threads = NT;
         c.lds_bytes = LDS;
-        KernelEntry e{name, c, legal, workspace, launch, nullptr, nullptr};
+        KernelEntry e{name, c, legal, workspace, run, nullptr, nullptr};
         e.masks_triangle = true;
         return e;
     }

@@ -331,3 +331,17 @@ def test_fringe_planning_and_override():
     finally:
         G.mg_clear_override()
     assert need_auto % (4097 * 129 * 4) == 0                         # partial sums cover all of C, fringe included
+
+
+def test_every_compiled_macro_tile_kernel_is_in_the_table():
+    """a kernel that no configuration launches is dead weight: FP16 ones by their host-side stubs, against the table's names"""
+    import subprocess
+    symbols = subprocess.run(["nm", G.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    names = [t["name"] for t in G.kernel_table()]
+
+    def compiled(kernel):
+        return sum("device_stub" in line and kernel in line for line in symbols.split("\n"))
+
+    assert compiled("mfma_gemm_kernelIDF16_") == sum(n.startswith(("hmfma", "hconv")) for n in names)
+    probes = 1                                                   # (csrc/probe.hip: the kernel with cycle stamps)
+    assert compiled("hgemm_pp_kernel") + compiled("hgemm_dma_kernel") == sum(n.startswith(("hpp", "hdma", "hdeep")) for n in names) + probes
