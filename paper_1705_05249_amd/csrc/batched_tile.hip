@@ -8,7 +8,7 @@
 //     dimensions are; a line's last piece may run into the next line (those elements are zeroed, or belong to rows that
 //     are never stored), only the last piece of the matrix itself is gathered element by element;
 //   * the pieces of the next chunk of k are on their way while the MFMAs of the current one run, and several teams
-//     share a compute unit (34 KB of LDS each), so loads of some overlap the arithmetic of others;
+//     share a compute unit (12 to 20 KB of LDS each; the four one-wavefront teams of a work-group 32 to 48), so loads of some overlap the arithmetic of others;
 //   * results go through LDS, 16 columns per wavefront column at a time, and leave as 16-byte pieces along the columns of C.
 // LDS layouts: an operand along k as [row][k] in 128-byte rows with swizzled chunks (lds_layout.h, 16-row fragments); an
 // operand along m / n as it lies in memory, [k][row], lines padded by 16 (FP32) or 32 bytes (FP16) so that the 16 or 32 lanes
@@ -164,6 +164,15 @@ template <int N, int MB> __device__ inline void step_mma(const halfx4 (&x)[N], h
     for (int i = 0; i < N; ++i) c[i] = __builtin_amdgcn_mfma_f32_16x16x16f16(x[i], y, c[i], 0, 0, 0);
 }
 
+// LDS of a work-group: the operands' chunks of each team, or two strips of its results (floats, columns padded by four)
+template <typename T, int WM, int WN, int MB, int NB, bool A_KC, bool B_KC> struct TileLds {
+    static constexpr int TEAM = WM * WN, TM = WM * MB * 16, TN = WN * NB * 16;
+    static constexpr int OPERANDS = PanelLoader<T, TM, TEAM * 64, A_KC>::BYTES + PanelLoader<T, TN, TEAM * 64, B_KC>::BYTES;
+    static constexpr int STAGE_LD = TM + 4, STAGE = WN * 16 * STAGE_LD * 4;
+    static constexpr int PER_TEAM = OPERANDS > 2 * STAGE ? OPERANDS : 2 * STAGE;
+    static constexpr int BYTES = 4 / TEAM * PER_TEAM;
+};
+
 // WM x WN wavefronts make a team; each owns up to MB x NB blocks of 16 x 16.  A work-group is four wavefronts: one team of
 // four, or four teams of one (instances of at most 32 x 32; no barrier anywhere then).
 template <typename T, int WM, int WN, int MB, int NB, bool A_KC, bool B_KC>
@@ -174,15 +183,13 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
     using LoadA = PanelLoader<T, TM, NT, A_KC>;
     using LoadB = PanelLoader<T, TN, NT, B_KC>;
     constexpr int KC = LoadA::KC;
-    constexpr int STAGE_LD = TM + 4;                                   // floats per column of the result's staging area
-    constexpr int STAGE = WN * 16 * STAGE_LD * 4;
-    constexpr int OPERANDS = LoadA::BYTES + LoadB::BYTES;
-    constexpr int LDS = OPERANDS > 2 * STAGE ? OPERANDS : 2 * STAGE;
-    __shared__ __attribute__((aligned(16))) char shared[4 / TEAM * LDS];
+    using Lds = TileLds<T, WM, WN, MB, NB, A_KC, B_KC>;
+    constexpr int STAGE_LD = Lds::STAGE_LD, STAGE = Lds::STAGE;
+    __shared__ __attribute__((aligned(16))) char shared[Lds::BYTES];
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64), lane = threadIdx.x % 64;
     const int tid = TEAM == 1 ? lane : static_cast<int>(threadIdx.x);
-    char *lds = shared + (TEAM == 1 ? wave * LDS : 0);
+    char *lds = shared + (TEAM == 1 ? wave * Lds::PER_TEAM : 0);
     auto meet = [] {
         if constexpr (TEAM == 1) {
             __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -374,7 +381,7 @@ template <typename T, int WM, int WN, int MB, int NB, bool A_KC, bool B_KC> stru
         c.waves_m = WM; c.waves_n = WN;
         c.split_k = 1;
         c.threads = 256;
-        c.lds_bytes = 0;
+        c.lds_bytes = TileLds<T, WM, WN, MB, NB, A_KC, B_KC>::BYTES;
         return KernelEntry{name, c, nullptr, nullptr, nullptr, legal, launch};
     }
 };

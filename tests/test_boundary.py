@@ -345,3 +345,13 @@ def test_every_compiled_macro_tile_kernel_is_in_the_table():
     assert compiled("mfma_gemm_kernelIDF16_") == sum(n.startswith(("hmfma", "hconv")) for n in names)
     probes = 1                                                   # (csrc/probe.hip: the kernel with cycle stamps)
     assert compiled("hgemm_pp_kernel") + compiled("hgemm_dma_kernel") == sum(n.startswith(("hpp", "hdma", "hdeep")) for n in names) + probes
+
+
+def test_batched_tiles_report_their_local_memory():
+    """two chunks of 128 bytes per row (lines along m or n padded), or two strips of results; four teams in the 32 x 32 kernels"""
+    tiles = {t["name"]: t["lds_bytes"] for t in G.kernel_table() if "batched_tile" in t["name"]}
+    assert len(tiles) == 24
+    assert tiles["batched_tile_64x64_kk"] == max((64 + 64) * 128, 2 * 32 * 68 * 4)
+    assert tiles["hbatched_tile_64x64_mn"] == 2 * 64 * (64 * 2 + 32)
+    assert tiles["hbatched_tile_32x32_mn"] == 4 * 2 * 64 * (32 * 2 + 32)
+    assert all(12 * 1024 <= v <= 49152 for v in tiles.values())
