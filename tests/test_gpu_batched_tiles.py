@@ -23,16 +23,19 @@ def test_tile_edges_are_exact(oracle, dtype, layout, ta, tb, shape):
     bc.alphas[1] = 0.0                                           # A and B must not be used
     bc.A[bc.a_off[1]: bc.a_off[1] + W.storage_len(layout, ta, m, k, bc.lda)] = float("nan")
     bc.betas[2] = 0.0
+    ran = 0
     try:
         for t in G.kernel_table():                               # every tile that takes the shape, then the selection
             if "batched_tile" in t["name"] and t["dtype"] == (G.MG_F32 if dtype == "f32" else G.MG_F16):
                 G.mg_override_batched_config(t["kernel_id"])
                 try:
                     H.check_batched(bc, oracle, exact=True)
+                    ran += 1
                 except G.MgError as e:
                     assert e.status == -11                       # another operand order, or too large for one wavefront
     finally:
         G.mg_clear_override()
+    assert ran == 2 + (m <= 32 and n <= 32)
     H.check_batched(bc, oracle, exact=True)
 
 

@@ -27,10 +27,7 @@ def test_panel_edges_are_exact(oracle, dtype, layout, trans, outputs, length, pa
                     if slices > length:
                         continue
                     G.mg_override_config(t["kernel_id"], slices)
-                    try:
-                        H.check_gemv(case, oracle)
-                    except G.MgError as e:
-                        assert e.status == -11 and slices > 1     # the last slice would be empty
+                    H.check_gemv(case, oracle)
     finally:
         G.mg_clear_override()
     H.check_gemv(case, oracle)

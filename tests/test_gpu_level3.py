@@ -194,6 +194,32 @@ def test_syrk_hint_in_the_direct_to_lds_kernel(level3_oracle, layout, uplo, tran
     _with_forced_tile_kernel(case, level3_oracle, tag="hdma16_256x256x64_w2x4", suffix="")
 
 
+@pytest.mark.parametrize("tag", ["hdeep16_128x128x64_w2x4", "hdma16_256x128x64_w4x2"])
+@pytest.mark.parametrize("layout,side,uplo,trans", list(itertools.product([C, R], [LEFT, RIGHT], [UP, LO], [N, T])))
+def test_trmm_hint_in_the_kernels_with_three_and_four_stages(level3_oracle, tag, layout, side, uplo, trans):
+    """narrowed K ranges from two K-tiles, fewer than the pipeline holds, up to twelve; integers, bit for bit (a row of one term
+    may be subnormal: its rounding error of up to 2^-25 is beyond the relative bound where that term is below 1.5e-5)"""
+    for shape in ((768, 512), (512, 768)):
+        case = W.level3_case("trmm", "f16", layout, *shape, side=side, uplo=uplo, trans=trans, alpha=1.0, case=41, integer=True)
+        _with_forced_tile_kernel(case, level3_oracle, tag=tag, suffix="")
+
+
+@pytest.mark.parametrize("tag", ["hdeep16_128x128x64_w2x4", "hdma16_256x128x64_w4x2"])
+@pytest.mark.parametrize("layout,uplo,trans", list(itertools.product([C, R], [UP, LO], [N, T])))
+def test_syrk_hint_in_the_kernels_with_three_and_four_stages(level3_oracle, tag, layout, uplo, trans):
+    """skipped tiles and the masked epilogue behind sums of one to seven K-tiles"""
+    for k in (64, 128, 192, 320, 448):
+        case = W.level3_case("syrk", "f16", layout, 768, 768, k=k, uplo=uplo, trans=trans, alpha=1.0, beta=-1.0, case=43, integer=True)
+        _with_forced_tile_kernel(case, level3_oracle, tag=tag, suffix="")
+
+
+@pytest.mark.parametrize("routine,n", [("trmm", 1280), ("trmm", 1536), ("syrk", 1536)])
+def test_triangles_under_automatic_selection(level3_oracle, routine, n):
+    """sizes at which the kernels with three and four stages take over"""
+    case = W.level3_case(routine, "f16", C, n, n, k=n, uplo=LO, alpha=1.0, beta=0.0, case=47, integer=True)
+    H.check_level3(case, level3_oracle)
+
+
 @pytest.mark.parametrize("dtype,layout,side,uplo,trans", [("f16", C, LEFT, LO, N), ("f32", C, RIGHT, UP, N),
                                                           ("f16", R, LEFT, UP, T), ("f32", R, RIGHT, LO, T)])
 def test_large_trmm_on_sampled_columns(level3_oracle, dtype, layout, side, uplo, trans):

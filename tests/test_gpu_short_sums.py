@@ -15,7 +15,10 @@ C, R, N, T = W.COL_MAJOR, W.ROW_MAJOR, W.NO_TRANS, W.TRANS
 @pytest.mark.parametrize("m,n", [(128, 64), (256, 192), (129, 65), (67, 131)])
 @pytest.mark.parametrize("k", [1, 31, 32, 33, 64, 96, 100, 128, 192, 224])
 def test_every_ending_of_the_sum_is_exact(oracle, layout, ta, tb, m, n, k):
+    cm, cn = (m, n) if layout == C else (n, m)                           # as the column-major kernels see it
+    whole = [tm for tm in (128, 64) if cm % tm == 0 and cn % 64 == 0 and k % 32 == 0]
     for beta in (0.0, -1.0):
+        ran = 0
         case = W.skinny_case(m, n, k, case=m + k, integer=True, layout=layout, ta=ta, tb=tb, alpha=2.0, beta=beta)
         try:
             for t in G.kernel_table():
@@ -23,8 +26,10 @@ def test_every_ending_of_the_sum_is_exact(oracle, layout, ta, tb, m, n, k):
                     G.mg_override_config(t["kernel_id"], 1)
                     try:
                         H.check_case(case, oracle)
+                        ran += 1
                     except G.MgError as e:
                         assert e.status == -11                       # another operand order, or whole tiles only
         finally:
             G.mg_clear_override()
+        assert ran == 2 + len(whole)                                     # the bounds-checked flavours, and those for whole tiles
         H.check_case(case, oracle)
