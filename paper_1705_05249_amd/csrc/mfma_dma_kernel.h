@@ -131,6 +131,16 @@ __device__ inline u32x4 read_operand(lds_char *lds3, const int (&frag)[8])
     }
 }
 
+// Behind the wait for reads that the compiler does not know to be in flight and whose values nobody needs (those behind the last
+// K-tile): their destinations stay allocated up to here.  Without this use they are free from the moment the reads are issued, and
+// the compiler put what follows (the epilogue's lane numbers, on the 256 x 256 tile with A along m and B along n) where a
+// read was still to write.
+template <int N> __device__ inline void hold_registers(const u32x4 (&f)[N])
+{
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" ::"v"(f[i]));
+}
+
 template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int PROBE = 0, bool CLIP = false, int STAGES = 2>
 __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs args)
 {
@@ -333,6 +343,8 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
 
     if constexpr (STAGES > 2) __builtin_amdgcn_s_waitcnt(0x0F70);       // the reloads past the end of the sum
     wait_fragments();       // the reads issued behind the last barrier still write registers: let them land
+    if constexpr (STAGES > 2 || !A_KCONTIG) hold_registers(fa[0]);
+    if constexpr (STAGES > 2 || !B_KCONTIG) hold_registers(fb[0]);
     __syncthreads();        // all loads have landed (waited for before the last barrier) and all fragment reads are done
     if constexpr (STAMPS) {
         MfmaArgs plain = args;
