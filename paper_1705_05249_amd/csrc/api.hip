@@ -152,13 +152,12 @@ mg_status choose(Problem &p, int64_t alignment, size_t workspace_bytes, int32_t 
 size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
 
 // Indirect GEMM, the paper's Section 3.2 route for problems that break the fast kernel's assumptions: copy the
-// operands into zero-padded, aligned buffers whose sizes are whole tiles, run the fast kernel there, copy the
-// result back.  FP16 needs it most: ragged or unaligned FP16 problems otherwise run the bounds-checked
-// register-staged kernels at 0.2-0.6 of the direct-to-LDS rate (4097^3: 525 us; an odd leading dimension puts
-// every other row at 2-byte alignment), while the copies are O(n^2) (~30 us at 4097^3).  FP32 loses ~20 % in
-// its bounds-checked flavour plus what ragged sizes lose to tile quantisation: large problems gain.  The padded buffers live in
-// the caller's workspace; without enough of it the direct route runs.  One rounding as always: the fast
-// kernel applies alpha and beta in the padded C, whose leading part is then copied out bit for bit.
+// operands into zero-padded, aligned buffers whose sizes are whole tiles and run the fast kernel there.  FP16 needs it:
+// ragged or unaligned FP16 problems otherwise run the bounds-checked register-staged kernels at 0.2-0.6 of the
+// direct-to-LDS rate (4097^3: 525 us; an odd leading dimension puts every other row at 2-byte alignment), while the
+// copies are O(n^2) (~30 us at 4097^3).  The padded buffers live in the caller's workspace; without enough of it
+// the direct route runs.  C stays where it is (run_indirect), but for a sliced sum, whose result is copied back bit for
+// bit.  One rounding as always.
 struct IndirectPlan {
     int64_t mp, np, kp;
     size_t a_bytes, b_bytes, c_bytes;
@@ -187,8 +186,8 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     int64_t tile = 0, ktile = 0;
     bool compare = false;
     if (p.dtype == MG_F16) {
-        // four extra launches and ~33 us of copies at 4096^2: measured a loss at 1000^3 (28 against 22 us), a gain
-        // at 2049^3 (56 against 96 us)
+        // a launch in front, its gap and ~10 us of copies at 2051^2 (~33 us at 4096^2): measured a loss at 1000^3 (28 against
+        // 22 us), a gain at 2049^3 (56 against 96 us; both while C was copied too)
         if (p.m < 1024 || p.n < 1024 || p.k < 256 || work < 2.0e9) return false;
         const bool whole = p.m % 128 == 0 && p.n % 128 == 0 && p.k % 64 == 0;
         const bool aligned = p.lda % 8 == 0 && p.ldb % 8 == 0 &&
@@ -1020,11 +1019,12 @@ size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m,
 {
     if (dtype != MG_F32 && dtype != MG_F16) return 0;
     if (check_shape(layout, ta, tb, m, n, k, lda, ldb, ldc) != MG_OK || m == 0 || n == 0) return 0;
-    // scalars do not change the need except through the scale-only path, which needs none
+    // (the scale-only path of alpha == 0 needs none; FP32 sums of 193 to 512 terms choose among fewer tiles with beta != 0 than
+    // without: of 60000 shapes none needs more with beta == 0)
     Problem p = canonical(dtype, layout, ta, tb, m, n, k, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc,
                           nullptr, 0, nullptr);
     IndirectPlan plan;
-    if (indirect_plan(p, false, &plan)) return plan.total();      // (the padded problem itself never splits K: it is large)
+    if (indirect_plan(p, false, &plan)) return plan.total();      // (room for slices beside the copies is the caller's choice)
     int32_t kernel = -1, split = 1;
     if (choose(p, 256, ~size_t(0), &kernel, &split) != MG_OK) return 0;
     return table()[kernel].workspace(p, split);

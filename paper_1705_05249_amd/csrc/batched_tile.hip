@@ -17,7 +17,7 @@
 // v_mfma_f32_16x16x16_f16, or of four v_mfma_f32_16x16x4_f32.  (The 16x16x32 form would halve the MFMA time, which is a fifth
 // of the memory time, and cost the [k][row] layout its conflict-free reads.)
 // Measured (us; the FMA kernel or the register-resident 64-wide blocks these instances ran on before / this): 512 x (128, 128, 64)
-// FP16 40.0 / 10.3 (33 MB, 3.3 TB/s, the launch included), FP32 30.6 / 19.8; FP16 64^3 (3111, both transposed) 46 / 17.5, 81^3 (800)
+// FP16 40.0 / 9.9 (33 MB, 3.4 TB/s, the launch included), FP32 30.6 / 19.8; FP16 64^3 (3111, both transposed) 46 / 17.5, 81^3 (800)
 // 105 / 15, (19, 80, 144) x 2100 171 / 23; FP32 64^3 (5000, B along n) 103 / 69 (328 MB, 4.8 TB/s), 93^3 (856) 63 / 31, 99^3 (4122)
 // 313 / 191: there the MFMAs of the padded blocks take half of the time and do not hide behind the loads.
 // A team skips the columns of 16x16 blocks that the instance does not have, and its columns of blocks are dealt out evenly.

@@ -86,14 +86,6 @@ template <int ROWS, int NT, bool KCONTIG, int RB = 32> struct DmaLoader {
     }
 };
 
-// MFMA operand of fragment F (32 rows), K-step S, from an operand stage at byte offset STAGE; frag: the
-// lane's addresses prepared by the kernel (k-contiguous layout: one per swizzle phase; the other: one per fragment).
-//
-// The transposing reads are written as inline assembly: as a builtin, every one of them that follows a
-// direct-to-LDS load in program order gets an `s_waitcnt vmcnt(0)` from the compiler (it cannot tell that the
-// read does not touch the stage the load writes), which put the full memory latency of every load into the K
-// loop.  The price: the compiler does not know that these registers are written later, by the LDS, so the
-// kernel itself waits (wait_fragments) before the first MFMA of every K-step.
 // 16-byte LDS read the compiler's wait-count bookkeeping does not see (the kernel waits itself): a visible LDS
 // read that follows a direct-to-LDS load in program order can draw a wait for that load.
 template <int OFFSET> __device__ inline u32x4 lds_read_b128_untracked(uint32_t at)
@@ -104,6 +96,15 @@ template <int OFFSET> __device__ inline u32x4 lds_read_b128_untracked(uint32_t a
     return r;
 }
 
+// MFMA operand of fragment F (32 rows), K-step S, from an operand stage at byte offset STAGE; frag: the
+// lane's addresses prepared by the kernel (k-contiguous layout: one per swizzle phase; the other: one per fragment).
+//
+// The transposing reads are written as inline assembly: as a builtin, every one of them that follows a
+// direct-to-LDS load in program order gets an `s_waitcnt vmcnt(0)` from the compiler (it cannot tell that the
+// read does not touch the stage the load writes), which put the full memory latency of every load into the K
+// loop.  The price: the compiler does not know that these registers are written later, by the LDS, so the
+// kernel itself waits (wait_fragments) before the first MFMA of every K-step.
+//
 // UNTRACKED: the k-contiguous form as inline assembly too (kernels with loads of several K-tiles in flight).  What of STAGE the
 // instruction's offset field cannot hold is added to the address.
 template <bool KCONTIG, int ROWS, int F, int RB, int S, int STAGE_OFFSET, bool UNTRACKED = false>

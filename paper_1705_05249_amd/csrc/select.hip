@@ -473,8 +473,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             }
             // FP16 products with a triangular C are ranked by the tiles that touch it (us, ranked as all of C / now: 2048^3 25 / 17,
             // 2560^3 36 / 24, 3584 x 1024 33 / 20, 4096^3 84 both).  A triangular operand (unequal K ranges) is ranked like
-            // the general problem, with one measured exception: when the 256 x 256 direct-to-LDS grid leaves compute units idle
-            // anyway, the 128 x 128 tiles balance the unequal work better (TRMM 3072: 59 against 77 us)
+            // the general problem (TRMM, us, before the kernels with three and four stages / with them: 1536 25.5 / 21.4, 2048 30.5 /
+            // 26.9, 2304 40.9 / 36.1, 2560 45.1 / 39.5, 2816 52.6 / 44.3, 3072 x 1024 40.5 / 33.6, 3328 60.2 / 61.4, 4096 89.2 / 89.7), with one
+            // measured exception: when the 256 x 256 direct-to-LDS grid leaves compute units idle anyway, the 128 x 128 tiles
+            // balance the unequal work better (3072: 55.5 against 65.4 us)
             if (!f32 && p.shape != MG_SHAPE_GENERAL && !triangle && best == 0 && !tried[2] &&
                 ceil_div(p.m, 256) * ceil_div(p.n, 256) <= (kComputeUnits * 3) / 4)
                 best = 2;
