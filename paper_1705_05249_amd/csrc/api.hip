@@ -566,6 +566,10 @@ mg_status run_conv2d_fused(int dtype, const ConvShape &s, int64_t filters, int64
         const char *fused = nullptr;
         if (name == "hmfma_64x64x64_w2x2_mk" || name == "hmfma_64x64x64_w2x2_mk_edge") fused = "hconv_64x64x64_w2x2";
         else if (name == "smfma_64x64x32_w2x2_mk" || name == "smfma_64x64x32_w2x2_mk_edge") fused = "sconv_64x64x32_w2x2";
+        else if (name.compare(0, 6, "ssplit") == 0) {                        // (no such variant: the FP32 pipes' kernel, unsliced)
+            fused = "sconv_64x64x32_w2x2";
+            split = 1;
+        }
         if (fused == nullptr) return MG_ERR_CONFIG;
         for (size_t i = 0; i < t.size(); ++i)
             if (std::string(t[i].name) == fused) kernel = static_cast<int32_t>(i);

@@ -23,6 +23,9 @@ void register_smfma_256x128x32_w2x2(std::vector<KernelEntry> &table);
 void register_smfma_128x128x32_w2x2(std::vector<KernelEntry> &table);
 void register_smfma_128x64x32_w2x2(std::vector<KernelEntry> &table);
 void register_smfma_64x64x32_w2x2(std::vector<KernelEntry> &table);
+void register_ssplit_256x128x32_w4x2(std::vector<KernelEntry> &table);
+void register_ssplit_128x128x32_w2x4(std::vector<KernelEntry> &table);
+void register_ssplit_slices_64x64(std::vector<KernelEntry> &table);
 
 void register_mfma(std::vector<KernelEntry> &table)
 {
@@ -47,5 +50,8 @@ void register_mfma(std::vector<KernelEntry> &table)
     register_smfma_64x64x32_w2x2(table);
     register_tiny(table);
     register_hdeep16(table);
+    register_ssplit_256x128x32_w4x2(table);
+    register_ssplit_128x128x32_w2x4(table);
+    register_ssplit_slices_64x64(table);
 }
 }  // namespace mg

@@ -292,10 +292,20 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                {"smfma_256x128x32_w4x2", 256, 128, 32, 0.587f, 0.583f, 1},
                                                {"smfma_128x128x32_w2x2", 128, 128, 32, 0.588f, 0.566f, 2},
                                                {"smfma_128x64x32_w2x2", 128, 64, 32, 0.582f, 0.54f, 3},
-                                               {"smfma_64x64x32_w2x2", 64, 64, 32, 0.571f, 0.565f, 5}};
+                                               {"smfma_64x64x32_w2x2", 64, 64, 32, 0.571f, 0.565f, 5},
+                                               {"ssplit_256x128x32_w4x2", 256, 128, 32, 0.f, 0.f, 1},
+                                               {"ssplit_128x128x32_w2x4", 128, 128, 32, 0.f, 0.f, 1},
+                                               {"ssplit_slices_64x64", 64, 64, 32, 0.f, 0.f, 1}};
+        constexpr int kSplit = 5;           // index of the first kernel on the bf16 matrix pipes
+        // Their time in us: turns of one tile per compute unit, each a fixed part and, per K-tile of 32, a part that grows with the
+        // share of the chip that is busy (the power limit); and the traffic of C per MB.
+        struct SplitCost {
+            double turn, ktile, ktile_load, c_mb;
+        };
+        static const SplitCost split_costs[3] = {{7.9, 1.58, 0.49, 0.18}, {5.0, 1.01, 0.25, 0.16}, {4.4, 0.30, 0.09, 0.15}};
         static const double f32_round_cost[5] = {0.0, 0.0, 1.0e6, 2.0e6, 1.8e6};
         const TileChoice *tiles = f32 ? f32_tiles : f16_tiles;
-        const int count = f32 ? 5 : 9;
+        const int count = f32 ? 8 : 9;
         const int smallest = f32 ? 4 : 7;
         bool tried[9] = {false, false, false, false, false, false, false, false, false};
         // work-groups that do something: of a product whose C is a triangle, the tiles that touch it (as the kernels skip the others)
@@ -342,7 +352,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 return tiles[i].ceiling * (1.0 - pow(idle, static_cast<double>(u)));
             };
             double time;
-            if (f32) {
+            if (f32 && i >= kSplit) {
+                const SplitCost &cost = split_costs[i - kSplit];
+                const double turns = static_cast<double>(ceil_div(blocks, kComputeUnits));
+                const double load = static_cast<double>(blocks) / (turns * kComputeUnits);
+                const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, tiles[i].bk), slices));
+                time = 1.0e6 * (turns * (cost.turn + ktiles * (cost.ktile + cost.ktile_load * load)) +
+                                cost.c_mb * 4.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0));
+            } else if (f32) {
                 // work-groups take turns on a compute unit: ceil(blocks / 256) turns of one tile each, whether the
                 // compute units hold them all at once or are refilled as work-groups retire (squares of 1024 to 6144
                 // on every tile: within 6 % of this, the small tiles a little better where the last turn is thin)
@@ -407,7 +424,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (!f32 && (i == 1 || i == kDeep)) time += 2.0e6;
             // split-K: the partial sums are written and read back (8 bytes per slice and output at ~4 TB/s) by
             // a second launch (2.5 us; 4 us behind the bounds-checked FP32 flavour, fitted with the rates above)
-            if (slices > 1) time += 1.0e6 * ((f32 && ragged ? 4.0 : 2.5) + (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) / 4.0e6);
+            if (slices > 1) time += 1.0e6 * ((f32 && i >= kSplit ? 6.0 : (f32 && ragged ? 4.0 : 2.5)) + (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) / 4.0e6);
+            if (f32 && i < kSplit) time += 1.0e6;
             return time;
         };
         // each tile's estimate with the slices that suit it and the workspace, ranked once for all attempts
@@ -419,6 +437,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         int free_slices = 0;
         const bool in_place = p.clip_m != 0 || p.clip_n != 0;
         for (int i = 0; i < count; ++i) {
+            if (f32 && i >= kSplit && p.k < 4) continue;             // (a sum of one or two products: rounded once more than on the FP32 pipes)
             if (in_place && i > 2 && i != kDeep) continue;           // (no other tile has the flavour, and it is not sliced)
             // FP32 with a short K is bound by the traffic of C, which the large tiles overlap worst (one epilogue per
             // compute unit at a time).  us, the tile the estimate would take (256 x 256 or 128 x 128) / 128 x 64 / 64 x 64,
@@ -427,8 +446,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // 64) - / 69 / 70; beta = 0: (2048, 2048, 160) 18.1 / 17.4 / 16.7, (3000, 3000, 160) 43 / 38 / 33, from
             // k = 256 on within 2 %; ragged problems of several turns whose 128 x 64 tiles need no more of them stay
             // on those: (1393, 4318, 136) 31.3 / 33.9 (five turns against nine: (3000, 3000, 160) above)
-            if (f32 && p.k <= 128 && tiles[i].bm * tiles[i].bn > 128 * 64) continue;
-            if (f32 && p.shape == MG_SHAPE_GENERAL && p.k <= (p.beta != 0.f ? 512 : 192)) {
+            if (f32 && i < kSplit && p.k <= 128 && tiles[i].bm * tiles[i].bn > 128 * 64) continue;
+            if (f32 && i < kSplit && p.shape == MG_SHAPE_GENERAL && p.k <= (p.beta != 0.f ? 512 : 192)) {
                 const int64_t turns64 = ceil_div(ceil_div(tm, 64) * ceil_div(tn, 64), kComputeUnits);
                 const int64_t turns128 = ceil_div(ceil_div(tm, 128) * ceil_div(tn, 64), kComputeUnits);
                 const bool whole = tm % 128 == 0 && tn % 64 == 0 && p.k % 32 == 0;
@@ -450,6 +469,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             for (int o = 0; o < n_options; ++o) {
                 const int sl = options[o];
                 if (sl < 1 || (o > 0 && sl == 1)) continue;
+                // (a fringe work-group takes a compute unit of its own beside these kernels' tiles: only behind two turns of tiles and more;
+                // (513, 515, 2000) 19.4 / 24.7 us, (4097, 129, 4095) 51 / 63, 1025^3 27.6 / 31.4, but 4097^3 1021 / 693)
+                if (f32 && i >= kSplit && (p.fringe_m != 0 || p.fringe_n != 0) && (i == kSplit + 2 || sl > 1 || blocks <= kComputeUnits)) continue;
                 const double time = estimate(i, sl);
                 if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
                 if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;

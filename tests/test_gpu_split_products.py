@@ -1,0 +1,110 @@
+"""FP32 kernels on the bf16 matrix pipes (csrc/mfma_split_kernel.h): edges of the tiles and of the sum, values that three bf16
+parts cannot hold, and their error beside that of the kernels on the FP32 pipes."""
+import numpy as np
+import pytest
+
+import helpers as H
+from paper_1705_05249_amd import gemm as G
+from paper_1705_05249_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+C, R, N, T = W.COL_MAJOR, W.ROW_MAJOR, W.NO_TRANS, W.TRANS
+
+
+def forced(prefix, call, slices=1):
+    """runs call() once for every kernel of that name that takes the problem"""
+    ran = 0
+    try:
+        for t in G.kernel_table():
+            if t["name"].startswith(prefix):
+                G.mg_override_config(t["kernel_id"], slices)
+                try:
+                    call()
+                    ran += 1
+                except G.MgError as e:
+                    assert e.status == -11                   # another operand order, whole tiles only, an empty slice
+    finally:
+        G.mg_clear_override()
+    return ran
+
+
+@pytest.mark.parametrize("layout,ta,tb", [(C, N, N), (C, T, N), (C, N, T), (R, N, N)])
+@pytest.mark.parametrize("m,n", [(256, 128), (257, 131), (63, 66), (5, 129), (130, 1)])
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 31, 32, 33, 64, 95, 96, 127, 128, 129, 160, 257, 400])
+def test_every_edge_is_exact(oracle, layout, ta, tb, m, n, k):
+    case = W.skinny_case(m, n, k, case=m + k, integer=True, layout=layout, ta=ta, tb=tb, alpha=2.0, beta=float(k % 2))
+    assert forced("ssplit", lambda: H.check_case(case, oracle)) >= 3
+    if k >= 64:
+        import torch
+        workspace = torch.empty(2 * 4 * m * n, dtype=torch.uint8, device="cuda")
+        forced("ssplit", lambda: H.check_case(case, oracle, workspace=workspace), slices=2)
+
+
+def product(A, B, m, n, k):
+    import torch
+    out = torch.empty(m * n, device="cuda")
+    G.mg_sgemm(C, T, N, m, n, k, 1.0, H.to_gpu(A), k, H.to_gpu(B), k, 0.0, out, m)
+    return out.cpu().numpy().reshape(n, m)
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "huge", "overflow", "tiny", "subnormal", "bf16_subnormal", "low_bits"])
+def test_values_the_parts_cannot_hold(what):
+    m, n, k = 200, 150, 300
+    rng = np.random.default_rng(5)
+    A = rng.uniform(-1, 1, (m, k)).astype(np.float32)
+    B = rng.uniform(-1, 1, (n, k)).astype(np.float32)
+    if what in ("inf", "nan"):
+        A[7, 11] = np.float32(what)
+        A[90, 200:210] = np.float32(what)
+        B[20, 3] = 0.0
+    elif what == "huge":
+        A[5, 9] = 3.4e38
+        A[130, :] *= 1.0e36                                  # (sums near the end of the range overflow or not by their order)
+        B[:, 9] *= 0.01
+    elif what == "overflow":
+        A *= 1.0e25
+        B *= 1.0e25
+    elif what == "tiny":
+        A *= 1.0e-35
+    elif what == "subnormal":
+        A[60:70] *= 1.0e-41
+        B *= 1.0e20
+    elif what == "bf16_subnormal":
+        A[60:70] = np.float32(2.0 ** -130)                    # one part holds it
+        B *= 1.0e20
+    else:
+        A = np.ldexp(A, -108).astype(np.float32)             # parts near the end of bf16's range
+    runs = {}
+    for prefix in ("smfma_64x64", "ssplit"):
+        runs[prefix] = []
+        assert forced(prefix, lambda: runs[prefix].append(product(A, B, m, n, k))) >= 1
+    want = runs["smfma_64x64"][0]
+    exact = B.astype(np.float64) @ A.astype(np.float64).T
+    size = np.abs(B).astype(np.float64) @ np.abs(A).astype(np.float64).T
+    for got in runs["ssplit"]:
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
+        ok = np.isfinite(want)
+        assert np.array_equal(np.sign(got[~ok & ~np.isnan(want)]), np.sign(want[~ok & ~np.isnan(want)]))
+        # k + 1 roundings of sums no larger than `size`, and of subnormals
+        assert np.all(np.abs(got - exact)[ok] <= (k + 1) * (2.0 ** -24 * size[ok] + 2.0 ** -149))
+
+
+@pytest.mark.parametrize("k", [32, 48, 100, 257, 1024, 4096])
+@pytest.mark.parametrize("spread", ["uniform", "wide"])
+def test_no_less_precise_than_the_fp32_pipes(k, spread):
+    m, n = 256, 256
+    rng = np.random.default_rng(k)
+    A = rng.uniform(-1, 1, (m, k)).astype(np.float32)
+    B = rng.uniform(-1, 1, (n, k)).astype(np.float32)
+    if spread == "wide":                                      # magnitudes over forty binades
+        A *= np.exp2(rng.integers(-20, 21, (m, k))).astype(np.float32)
+        B *= np.exp2(rng.integers(-20, 21, (n, k))).astype(np.float32)
+    exact = B.astype(np.float64) @ A.astype(np.float64).T
+    error = {}
+    for prefix in ("smfma_64x64", "ssplit"):
+        outs = []
+        assert forced(prefix, lambda: outs.append(product(A, B, m, n, k))) >= 1
+        error[prefix] = max(np.linalg.norm(o - exact) / np.linalg.norm(exact) for o in outs)
+    # (where a few products dominate the sum, both are the rounding of those: half a unit in the last place)
+    assert error["ssplit"] <= (error["smfma_64x64"] if spread == "uniform" else max(error["smfma_64x64"], 2.0 ** -24))
