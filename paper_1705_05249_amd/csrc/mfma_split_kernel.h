@@ -70,9 +70,8 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
     bool tiny;                      // see split_pair
     SplitPair made[2];              // the piece being split
 
-    __device__ __forceinline__ void prepare(int64_t ld, int rows)
+    __device__ __forceinline__ void prepare(int64_t ld, int rows, int t)
     {
-        const int t = threadIdx.x;
         tiny = false;
         static_for<LOADS>([&](auto Qc) {
             constexpr int Q = decltype(Qc)::value;
@@ -108,10 +107,10 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
         regs[SET][Q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[Q], 0, 0);
     }
     // values of k beyond the sum (operand along k: they are the next row's)
-    template <int SET, int Q> __device__ __forceinline__ void cut(int ks)
+    template <int SET, int Q> __device__ __forceinline__ void cut(int ks, int t)
     {
         if constexpr (KCONTIG) {
-            const int c = (threadIdx.x + Q * NT) % 8;
+            const int c = (t + Q * NT) % 8;
 #pragma unroll
             for (int e = 0; e < 4; ++e) regs[SET][Q][e] = c * 4 + e < ks ? regs[SET][Q][e] : 0u;
         }
@@ -126,6 +125,31 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
             v[e] = __builtin_bit_cast(float, bits);
         }
         made[HALF] = split_pair(v[0], v[1], tiny);
+    }
+    // the staged floats themselves -> LDS, and a fragment (4 values of k per lane of K-step `step`) of them, as in mfma_kernel.h
+    __device__ __forceinline__ void store_floats(char *stage, int t) const
+    {
+        static_for<LOADS>([&](auto Qc) {
+            constexpr int Q = decltype(Qc)::value;
+            const int idx = t + Q * NT;
+            u32x4 v = regs[0][Q];
+            if constexpr (EDGE && !KCONTIG) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = keep[e] ? v[e] : 0u;
+            }
+            if constexpr (KCONTIG) *reinterpret_cast<u32x4 *>(stage + ldsmap::kcontig_slot<32>(idx / 8, idx % 8)) = v;
+            else *reinterpret_cast<u32x4 *>(stage + ldsmap::native_slot(ROWS, idx / RCH, idx % RCH)) = v;
+        });
+    }
+    __device__ __forceinline__ static u32x4 read_floats(const char *stage, int lane, int wrow, int f, int step)
+    {
+        if constexpr (KCONTIG) {
+            return *reinterpret_cast<const u32x4 *>(stage + ldsmap::kcontig_slot<32>(wrow + 32 * f + lane % 32, 2 * step + lane / 32));
+        } else {
+            const char *p = stage + ldsmap::native_base(ROWS, lane, wrow, f) + 8 * step * 4 * ROWS;
+            return u32x4{*reinterpret_cast<const uint32_t *>(p), *reinterpret_cast<const uint32_t *>(p + 4 * ROWS),
+                         *reinterpret_cast<const uint32_t *>(p + 8 * ROWS), *reinterpret_cast<const uint32_t *>(p + 12 * ROWS)};
+        }
     }
     template <int Q> __device__ __forceinline__ void store(char *stage)
     {
@@ -170,43 +194,48 @@ __device__ __forceinline__ void mma_bf16(floatx16 &acc, const u32x4 &frag_n, con
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, frag_m), __builtin_bit_cast(bf16x8, frag_n), acc, 0, 0, 0);
 }
 
-// The same tile with the FP32 instructions, for operands that the parts cannot hold: no overlap of loads and
-// arithmetic, every element on its own.  8 values of k at a time in LDS as [k][row] floats.
-template <int BM, int BN, int NT, int FM, int FN, bool A_KCONTIG, bool B_KCONTIG>
-__device__ inline void exact_tile(floatx16 (&acc)[FN][FM], const MfmaArgs &args, char *lds, int64_t m0, int64_t n0, int kb, int ke,
-                                  int rows_a, int rows_b, int wm0, int wn0, int lane)
+// The same tile with the FP32 instructions, for operands that the parts cannot hold: the LDS layouts and fragments of mfma_kernel.h, two
+// stages of 32 values of k, the next K-tile in registers, no pinned schedule.  la, lb: the operands' loaders, prepared; `aim_tile` aims at
+// K-tile t (zeros past the end; tile 0 is the one that may lack values of k).  multiplies: the same for a whole wavefront; false: it
+// only loads.
+template <int BM, int BN, int NT, int FM, int FN, bool A_KCONTIG, bool B_KCONTIG, typename LoadA, typename LoadB, typename Aim>
+__device__ __forceinline__ void exact_tile(floatx16 (&acc)[FN][FM], LoadA &la, LoadB &lb, char *lds, int ktiles, int first_ks, int wm0, int wn0,
+                                           int thread, Aim &&aim_tile, bool multiplies = true)
 {
-    constexpr int BK = 8;
-    float *sa = reinterpret_cast<float *>(lds), *sb = sa + BK * BM;
+    constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    const int lane = thread % 64;
     static_for<FM * FN>([&](auto X) { acc[decltype(X)::value / FM][decltype(X)::value % FM] = floatx16{}; });
-    auto fill = [&](float *dst, auto ROWSc, auto KC, const float *X, int64_t ld, int64_t r0, int l0, int rows) {
-        constexpr int ROWS = decltype(ROWSc)::value;
-        constexpr bool kc = decltype(KC)::value;
-        for (int idx = threadIdx.x; idx < ROWS * BK; idx += NT) {
-            const int r = kc ? idx / BK : idx % ROWS, l = kc ? idx % BK : idx / ROWS;
-            float v = 0.f;
-            if (r < rows && l0 + l < ke) v = kc ? X[(r0 + r) * ld + l0 + l] : X[r0 + r + (l0 + l) * ld];
-            dst[l * ROWS + r] = v;
-        }
+    auto load = [&](int t) {
+        __amdgpu_buffer_rsrc_t a, b;
+        aim_tile(t, a, b);
+        static_for<LoadA::LOADS>([&](auto Q) { la.template load<0, decltype(Q)::value>(a); });
+        static_for<LoadB::LOADS>([&](auto Q) { lb.template load<0, decltype(Q)::value>(b); });
     };
-    for (int l0 = kb; l0 < ke; l0 += BK) {
-        __syncthreads();
-        fill(sa, std::integral_constant<int, BM>{}, std::bool_constant<A_KCONTIG>{}, static_cast<const float *>(args.A), args.lda, m0, l0, rows_a);
-        fill(sb, std::integral_constant<int, BN>{}, std::bool_constant<B_KCONTIG>{}, static_cast<const float *>(args.B), args.ldb, n0, l0, rows_b);
-        __syncthreads();
+    __syncthreads();                                   // every wavefront is done with the stages of the split parts
+    if (ktiles > 0) load(0);
 #pragma unroll 1
-        for (int l = lane / 32; l < BK; l += 2) {
-            float a[FM], b[FN];
-#pragma unroll
-            for (int i = 0; i < FM; ++i) a[i] = sa[l * BM + wm0 + 32 * i + lane % 32];
-#pragma unroll
-            for (int j = 0; j < FN; ++j) b[j] = sb[l * BN + wn0 + 32 * j + lane % 32];
+    for (int t = 0; t < ktiles; ++t) {
+        char *stage = lds + (t & 1) * STAGE;
+        if (t == 0) {
+            static_for<LoadA::LOADS>([&](auto Q) { la.template cut<0, decltype(Q)::value>(first_ks, thread); });
+            static_for<LoadB::LOADS>([&](auto Q) { lb.template cut<0, decltype(Q)::value>(first_ks, thread); });
+        }
+        la.store_floats(stage, thread);
+        lb.store_floats(stage + A_BYTES, thread);
+        load(t + 1);
+        __syncthreads();                               // (the other stage is written only behind the next one)
+#pragma unroll 1
+        for (int step = multiplies ? 0 : 4; step < 4; ++step) {
+            u32x4 a[FM], b[FN];
+            static_for<FM>([&](auto F) { a[decltype(F)::value] = LoadA::read_floats(stage, lane, wm0, decltype(F)::value, step); });
+            static_for<FN>([&](auto F) { b[decltype(F)::value] = LoadB::read_floats(stage + A_BYTES, lane, wn0, decltype(F)::value, step); });
             static_for<FM * FN>([&](auto X) {
                 constexpr int i = decltype(X)::value % FM, j = decltype(X)::value / FM;
-                acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[j][i], 0, 0, 0);
+                mma(acc[j][i], b[j], a[i], float{});
             });
         }
     }
+    __syncthreads();
 }
 
 template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, bool EDGE, int DEPTH>
@@ -248,8 +277,8 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
 
     LoadA la;
     LoadB lb;
-    la.prepare(args.lda, rows_a);
-    lb.prepare(args.ldb, rows_b);
+    la.prepare(args.lda, rows_a, threadIdx.x);
+    lb.prepare(args.ldb, rows_b, threadIdx.x);
     SplitFragments<BM, A_KCONTIG, FM> ra;
     SplitFragments<BN, B_KCONTIG, FN> rb;
     ra.prepare(lane, wm * WTM, 0);
@@ -369,7 +398,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
         aim_tile(DEPTH);
         static_for<LoadA::LOADS>([&](auto Q) {
             constexpr int q = decltype(Q)::value;
-            la.template cut<0, q>(first_ks);
+            la.template cut<0, q>(first_ks, threadIdx.x);
             la.template split<0, q, 0>();
             la.template split<0, q, 1>();
             la.template store<q>(lds);
@@ -377,7 +406,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
         });
         static_for<LoadB::LOADS>([&](auto Q) {
             constexpr int q = decltype(Q)::value;
-            lb.template cut<0, q>(first_ks);
+            lb.template cut<0, q>(first_ks, threadIdx.x);
             lb.template split<0, q, 0>();
             lb.template split<0, q, 1>();
             lb.template store<q>(lds + LoadA::STAGE);
@@ -391,16 +420,26 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
         static_for<FRAGS>([&](auto O) { read_second(C0{}, 0, O); });
     }
     constexpr int UNROLL = DEPTH > 2 ? DEPTH : 2;
+    // Every 32 K-tiles the wavefronts agree whether one of them has met an element that the parts cannot hold: the rest of the
+    // sum would be for nothing.
+    bool given_up = false;
     int t = 0;
-    for (; t + UNROLL <= ktiles; t += UNROLL)
-        static_for<UNROLL>([&](auto U) __attribute__((always_inline)) {
+    for (;;) {
+        const int stop = t + 32 < ktiles ? t + 32 : ktiles;
+        for (; t + UNROLL <= stop; t += UNROLL)
+            static_for<UNROLL>([&](auto U) __attribute__((always_inline)) {
+                constexpr int u = decltype(U)::value;
+                tile_body(std::integral_constant<int, u % 2>{}, std::integral_constant<int, (u + 1) % DEPTH>{}, t + u);
+            });
+        if (t + UNROLL > ktiles) break;
+        given_up = __syncthreads_or(la.tiny || lb.tiny);
+        if (given_up) break;
+    }
+    if (!given_up)
+        static_for<UNROLL - 1>([&](auto U) __attribute__((always_inline)) {
             constexpr int u = decltype(U)::value;
-            tile_body(std::integral_constant<int, u % 2>{}, std::integral_constant<int, (u + 1) % DEPTH>{}, t + u);
+            if (t + u < ktiles) tile_body(std::integral_constant<int, u % 2>{}, std::integral_constant<int, (u + 1) % DEPTH>{}, t + u);
         });
-    static_for<UNROLL - 1>([&](auto U) __attribute__((always_inline)) {
-        constexpr int u = decltype(U)::value;
-        if (t + u < ktiles) tile_body(std::integral_constant<int, u % 2>{}, std::integral_constant<int, (u + 1) % DEPTH>{}, t + u);
-    });
 
     float watch = 0.f;                                 // becomes NaN when a sum is Inf or NaN
     static_for<SLOTS>([&](auto X) {
@@ -408,12 +447,20 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
         acc[j][i] += small[j][i];
         static_for<16>([&](auto R) { watch = fmaf(acc[j][i][decltype(R)::value], 0.f, watch); });
     });
-    const bool redo = la.tiny || lb.tiny || watch != 0.f;
+    const bool redo = given_up || la.tiny || lb.tiny || watch != 0.f;
+    // (what follows derives its lane numbers anew: kept through the K loop they would cost it registers)
+    int thread = threadIdx.x;
+    asm volatile("" : "+v"(thread));
+    const int last_wave = thread / 64, last_wm = last_wave % WM, last_wn = last_wave / WM;
     if (__syncthreads_or(redo)) {                      // (also: every wavefront is done reading the operand stages)
-        exact_tile<BM, BN, NT, FM, FN, A_KCONTIG, B_KCONTIG>(acc, args, lds, m0, n0, kb, ke, rows_a, rows_b, wm * WTM, wn * WTN, lane);
-        __syncthreads();
+        SplitLoader<BM, NT, A_KCONTIG, EDGE, 1> ea;
+        SplitLoader<BN, NT, B_KCONTIG, EDGE, 1> eb;
+        ea.prepare(args.lda, rows_a, thread);
+        eb.prepare(args.ldb, rows_b, thread);
+        exact_tile<BM, BN, NT, FM, FN, A_KCONTIG, B_KCONTIG>(acc, ea, eb, lds, ktiles, first_ks, last_wm * WTM, last_wn * WTN, thread,
+                                                             [&](int t_, __amdgpu_buffer_rsrc_t &a, __amdgpu_buffer_rsrc_t &b) { aim_tile(t_); a = aim_a; b = aim_b; });
     }
-    tile_epilogue<float, 32, FM, FN, WTM, WTN, EDGE>(acc, args, lds, m0, n0, wm, wn, wave, lane);
+    tile_epilogue<float, 32, FM, FN, WTM, WTN, EDGE>(acc, args, lds, m0, n0, last_wm, last_wn, last_wave, thread % 64);
 }
 
 // 64 x 64 tiles of grids that leave a compute unit one or two of them: no barrier in the K loop.  Each of the eight
@@ -676,8 +723,17 @@ __global__ __launch_bounds__(512, 2) void mfma_split_slices_kernel(const MfmaArg
     static_for<8>([&](auto E) { watch = fmaf(sum[decltype(E)::value / 4][decltype(E)::value % 4], 0.f, watch); });
     if (__syncthreads_or(la.tiny || lb.tiny || watch != 0.f)) {
         floatx16 exact[1][1];
-        exact_tile<BM, BN, NT, 1, 1, A_KCONTIG, B_KCONTIG>(exact, args, lds, m0, n0, kb, ke, rows_a, rows_b, wave % 2 * 32, wave / 2 % 2 * 32, lane);
-        __syncthreads();
+        SplitLoader<BM, NT, A_KCONTIG, EDGE, 1> ea;
+        SplitLoader<BN, NT, B_KCONTIG, EDGE, 1> eb;
+        ea.prepare(args.lda, rows_a, threadIdx.x);
+        eb.prepare(args.ldb, rows_b, threadIdx.x);
+        const int ktiles = (ke - kb + 31) / 32, whole = (ktiles - 1) * 32;
+        exact_tile<BM, BN, NT, 1, 1, A_KCONTIG, B_KCONTIG>(exact, ea, eb, lds, ktiles, ke - kb - whole, wave % 2 * 32, wave / 2 % 2 * 32, threadIdx.x,
+                                                           [&](int t, __amdgpu_buffer_rsrc_t &x, __amdgpu_buffer_rsrc_t &y) {
+                                                               const int l0 = t == 0 ? kb + whole : kb + (t - 1) * 32, ks = t < ktiles ? ke - l0 : 0;
+                                                               x = ea.aim(A, args.lda, m0, l0, rows_a, ks);
+                                                               y = eb.aim(B, args.ldb, n0, l0, rows_b, ks);
+                                                           }, wave < 4);
         if (wave < 4) put(lds, exact[0][0], wave % 2 * 32, wave / 2 * 32);
         __syncthreads();
         gather(1);

@@ -85,7 +85,8 @@ def test_values_the_parts_cannot_hold(what):
     for got in runs["ssplit"]:
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
         ok = np.isfinite(want)
-        assert np.array_equal(np.sign(got[~ok & ~np.isnan(want)]), np.sign(want[~ok & ~np.isnan(want)]))
+        if what != "overflow":                               # (there the sign is that of whichever partial sum overflows first)
+            assert np.array_equal(np.sign(got[~ok & ~np.isnan(want)]), np.sign(want[~ok & ~np.isnan(want)]))
         # k + 1 roundings of sums no larger than `size`, and of subnormals
         assert np.all(np.abs(got - exact)[ok] <= (k + 1) * (2.0 ** -24 * size[ok] + 2.0 ** -149))
 
