@@ -56,16 +56,17 @@ hipError_t launch_tile_kernel(Kernel kernel, bool *attr_set, int lds_bytes, int 
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(tiles), 1, layers), dim3(threads), lds_bytes, p.stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split == 1) return e;
+    const int triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER ? p.shape : 0;
     const int64_t total = p.m * p.n;
     const bool wide = p.m % 4 == 0 && reinterpret_cast<uintptr_t>(a.partial) % 16 == 0;
     const int64_t groups = wide ? total / 4 : total;
     const unsigned blocks = static_cast<unsigned>(groups / 256 + 1 < 4096 ? groups / 256 + 1 : 4096);
     if (wide)
         hipLaunchKernelGGL((splitk_reduce_kernel<T, 4>), dim3(blocks), dim3(256), 0, p.stream, a.partial, split, a.m, a.n,
-                           static_cast<T *>(p.C), p.ldc, p.alpha, p.beta);
+                           static_cast<T *>(p.C), p.ldc, p.alpha, p.beta, triangle);
     else
         hipLaunchKernelGGL((splitk_reduce_kernel<T, 1>), dim3(blocks), dim3(256), 0, p.stream, a.partial, split, a.m, a.n,
-                           static_cast<T *>(p.C), p.ldc, p.alpha, p.beta);
+                           static_cast<T *>(p.C), p.ldc, p.alpha, p.beta, triangle);
     return hipGetLastError();
 }
 
@@ -106,7 +107,6 @@ struct MfmaConfig {
         if ((p.conv != nullptr) != CONV) return false;            // op(A) is an image's column matrix, or it is not
         if (p.alpha == 0.f || p.k == 0) return false;
         if (split < 1 || split > 256 || split > ceil_div(p.k, BK)) return false;
-        if (p.shape != MG_SHAPE_GENERAL && split != 1) return false;      // a narrowed K range is never sliced
         if (p.m >= (int64_t(1) << 31) || p.n >= (int64_t(1) << 31) || p.k >= (int64_t(1) << 31)) return false;
         if (ceil_div(p.m, BM) * ceil_div(p.n, BN) >= (int64_t(1) << 31)) return false;
         {

@@ -1090,10 +1090,11 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
 
 // C <- alpha * sum_z partial[z] + beta * C   (finishes a split-K product).  A thread takes V consecutive
 // elements of a column (V = 4 when m is a multiple of 4 and the partial sums are 16-byte aligned: one 16-byte
-// load per slice; C is accessed at element alignment).
+// load per slice; C is accessed at element alignment).  triangle: MG_SHAPE_C_LOWER / MG_SHAPE_C_UPPER when only that triangle of C
+// is wanted (the partial sums beyond it were not written, C is not touched there), else 0.
 template <typename T, int V>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restrict__ partial, int split, int m, int n,
-                                                             T *__restrict__ C, int64_t ldc, float alpha, float beta)
+                                                             T *__restrict__ C, int64_t ldc, float alpha, float beta, int triangle)
 {
     typedef float floatv __attribute__((ext_vector_type(V)));
     const int64_t total = static_cast<int64_t>(m) * n;
@@ -1101,6 +1102,12 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
     for (int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; g < groups;
          g += static_cast<int64_t>(gridDim.x) * 256) {
         const int64_t e = g * V;
+        const int64_t row = e % m, col = e / m;
+        // elements first .. valid - 1 of the V rows are wanted
+        const int64_t d = col - row;
+        const int first = triangle == MG_SHAPE_C_LOWER && d > 0 ? (d < V ? static_cast<int>(d) : V) : 0;
+        const int valid = triangle == MG_SHAPE_C_UPPER && d + 1 < V ? (d + 1 > 0 ? static_cast<int>(d + 1) : 0) : V;
+        if (valid <= first) continue;
         float s[V];
 #pragma unroll
         for (int i = 0; i < V; ++i) s[i] = 0.f;
@@ -1113,8 +1120,18 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float *__restr
                 for (int i = 0; i < V; ++i) s[i] += x[i];
             }
         }
-        Pack<T, V> *p = reinterpret_cast<Pack<T, V> *>(C + (e % m) + (e / m) * ldc);
+        Pack<T, V> *p = reinterpret_cast<Pack<T, V> *>(C + row + col * ldc);
         Pack<T, V> out;
+        if (valid - first < V) {
+#pragma unroll
+            for (int i = 0; i < V; ++i)
+                if (i >= first && i < valid) {
+                    float o = alpha * s[i];
+                    if (beta != 0.f) o = fmaf(beta, static_cast<float>(p->v[i]), o);
+                    p->v[i] = static_cast<T>(o);
+                }
+            continue;
+        }
         if (beta != 0.f) {
             const Pack<T, V> old = *p;
 #pragma unroll

@@ -2,6 +2,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string_view>
 #include <unordered_map>
 
@@ -310,9 +311,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         bool tried[9] = {false, false, false, false, false, false, false, false, false};
         // work-groups that do something: of a product whose C is a triangle, the tiles that touch it (as the kernels skip the others)
         const bool triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
+        // a triangular operand: tiles with sums of every length up to k, on average half (FP32; see the end of the ranking for FP16)
+        const bool narrowed = p.shape != MG_SHAPE_GENERAL && !triangle;
         auto wanted_tiles = [&](int bm, int bn) {
             const int64_t across_m = ceil_div(tm, bm), across_n = ceil_div(tn, bn);
-            return triangle && !f32 ? triangle_tiles(p.shape == MG_SHAPE_C_LOWER, across_m, across_n, bm, bn) : across_m * across_n;
+            return triangle ? triangle_tiles(p.shape == MG_SHAPE_C_LOWER, across_m, across_n, bm, bn) : across_m * across_n;
         };
         // estimated time (in 1e-6 us) of tile i with the sum cut into `slices`
         auto estimate = [&](int i, int slices) {
@@ -354,7 +357,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             double time;
             if (f32 && i >= kSplit) {
                 const SplitCost &cost = split_costs[i - kSplit];
-                const double turns = static_cast<double>(ceil_div(blocks, kComputeUnits));
+                double turns = static_cast<double>(ceil_div(blocks, kComputeUnits));
+                if (narrowed) turns = turns > 1.0 ? std::max(1.0, 0.55 * static_cast<double>(blocks) / kComputeUnits + 0.2) : 1.0;
                 const double load = static_cast<double>(blocks) / (turns * kComputeUnits);
                 const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, tiles[i].bk), slices));
                 time = 1.0e6 * (turns * (cost.turn + ktiles * (cost.ktile + cost.ktile_load * load)) +
@@ -363,7 +367,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // work-groups take turns on a compute unit: ceil(blocks / 256) turns of one tile each, whether the
                 // compute units hold them all at once or are refilled as work-groups retire (squares of 1024 to 6144
                 // on every tile: within 6 % of this, the small tiles a little better where the last turn is thin)
-                const double rounds = static_cast<double>(ceil_div(blocks, kComputeUnits));
+                double rounds = static_cast<double>(ceil_div(blocks, kComputeUnits));
+                if (narrowed && rounds > 1.0) rounds = std::max(1.0, 0.55 * static_cast<double>(blocks) / kComputeUnits);
                 const double up = ceil(rounds);
                 // (the bounds-checked flavour runs its whole K-tiles on the fast flavour's schedule and the end of the sum on
                 // checked loads: 0.75 of these rates for a single turn, which has no other work-group's arithmetic to hide
@@ -438,6 +443,12 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         const bool in_place = p.clip_m != 0 || p.clip_n != 0;
         for (int i = 0; i < count; ++i) {
             if (f32 && i >= kSplit && p.k < 4) continue;             // (a sum of one or two products: rounded once more than on the FP32 pipes)
+            // FP32 work-groups take turns on a compute unit, so unequal tiles (skipped ones, narrowed K ranges) only pay off where a compute
+            // unit gets many of them: of the kernels on the FP32 pipes the smallest (SYRK 4096: 974 / 923 / 695 / 618 us from the 256 x 256
+            // to the 64 x 64 tile, TRMM 950 / 614 / 596 / 541).  Those on the bf16 pipes are ranked beside it (us, FP32 pipes 64 x 64 / 256 x 128 /
+            // 128 x 128 / 64 x 64 slices: SYRK 1146 x 1056 38.5 / 68 / 46 / 21, 2048 118 / 121 / 77 / 88, 3072 265 / 183 / 236 / 221, 4096 560 /
+            // 519 / 479 / 523; TRMM 1000 31 / 71 / 49 / 26, 3000 244 / 201 / 189 / 266, 4096 546 / 376 / 379 / 527)
+            if (f32 && p.shape != MG_SHAPE_GENERAL && i < kSplit - 1) continue;
             if (in_place && i > 2 && i != kDeep) continue;           // (no other tile has the flavour, and it is not sliced)
             // FP32 with a short K is bound by the traffic of C, which the large tiles overlap worst (one epilogue per
             // compute unit at a time).  us, the tile the estimate would take (256 x 256 or 128 x 128) / 128 x 64 / 64 x 64,
@@ -456,12 +467,12 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             }
             const bool last = i == smallest;
             const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
-            const int64_t blocks = ceil_div(tm, tiles[i].bm) * ceil_div(tn, tiles[i].bn);
+            const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn);
             // slices tried: none; for the smallest tile the factor of the sweep's rule; for grids that do not
-            // fill the chip powers of two that leave every slice at least four K-tiles (never with a shape hint)
+            // fill the chip powers of two that leave every slice at least four K-tiles
             int options[6] = {1, 0, 0, 0, 0, 0};
             int n_options = 1;
-            if (p.shape == MG_SHAPE_GENERAL && !in_place) {
+            if (!in_place) {
                 if (last) options[n_options++] = pick_split(blocks, ktiles);
                 if (blocks < 2 * kComputeUnits)
                     for (int sl = 2; sl <= 16 && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
@@ -502,19 +513,6 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (!f32 && p.shape != MG_SHAPE_GENERAL && !triangle && best == 0 && !tried[2] &&
                 ceil_div(p.m, 256) * ceil_div(p.n, 256) <= (kComputeUnits * 3) / 4)
                 best = 2;
-            // FP32 work-groups take turns on a compute unit, so unequal tiles (skipped ones, narrowed K ranges)
-            // only pay off when a compute unit gets many of them: the small tiles win at every size measured
-            // (SYRK 4096: 974 / 923 / 695 / 618 us from the 256 x 256 to the 64 x 64 tile, TRMM 950 / 614 / 596 / 541;
-            // SYRK 8192: 4958 / 4690 / 5044 us on 128 x 128 / 128 x 64 / 64 x 64)
-            // (a triangular operand beyond 6144 x 6144 outputs is ranked like the general problem: TRMM 8192 takes
-            // 4342 us that way, 4723 us on 64 x 64 tiles)
-            if (f32 && p.shape != MG_SHAPE_GENERAL &&
-                (p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER || p.m * p.n <= int64_t(6144) * 6144)) {
-                const bool c_shape = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
-                const int small = c_shape && p.m * p.n > int64_t(4096) * 4096 ? 3 : 4;
-                if (!tried[small]) best = small;
-                else if (!tried[7 - small]) best = 7 - small;
-            }
             tried[best] = true;
             const TileChoice &tc = tiles[best];
             // a factor whose last slice would be empty is illegal: take the next smaller one
