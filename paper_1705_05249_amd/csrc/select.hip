@@ -472,7 +472,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // fill the chip powers of two that leave every slice at least four K-tiles
             int options[6] = {1, 0, 0, 0, 0, 0};
             int n_options = 1;
-            if (!in_place) {
+            // (a triangular operand already leaves half of the work-groups short sums: slices only where tiles are few; TRMM FP16 3968 x 1181
+            // 55 us unsliced, 76 in two slices, 1797 x 221 73 / 37)
+            if (!in_place && !(narrowed && blocks > kComputeUnits / 4)) {
                 if (last) options[n_options++] = pick_split(blocks, ktiles);
                 if (blocks < 2 * kComputeUnits)
                     for (int sl = 2; sl <= 16 && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
@@ -483,7 +485,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // (a fringe work-group takes a compute unit of its own beside these kernels' tiles: only behind two turns of tiles and more;
                 // (513, 515, 2000) 19.4 / 24.7 us, (4097, 129, 4095) 51 / 63, 1025^3 27.6 / 31.4, but 4097^3 1021 / 693)
                 if (f32 && i >= kSplit && (p.fringe_m != 0 || p.fringe_n != 0) && (i == kSplit + 2 || sl > 1 || blocks <= kComputeUnits)) continue;
-                const double time = estimate(i, sl);
+                // (an unsliced triangular operand runs below its estimate, most of its sums being shorter: TRMM FP16 3000 x 300 33 us, 38 in slices)
+                const double time = estimate(i, sl) * (narrowed && sl > 1 ? 1.25 : 1.0);
                 if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
                 if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
                 if (ranked[i].slices == 0 || time < ranked[i].time) ranked[i] = Ranked{sl, time};
