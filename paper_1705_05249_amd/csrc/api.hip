@@ -647,6 +647,14 @@ struct Carve {
     void *rest() const { return ok && left > 0 ? at : nullptr; }
 };
 
+// Leading dimension of a dense operand in the workspace: columns start on 16 bytes, as the FP16 kernels' loads want it (TRMM FP16
+// 192 x 3159: 57 us with columns at odd elements).  A workspace without room for that gets tight columns.
+int64_t aligned_ld(int64_t minor, size_t elem)
+{
+    const int64_t v = static_cast<int64_t>(16 / elem);
+    return ceil_div(minor, v) * v;
+}
+
 mg_status check_symm(int layout, int side, int uplo, int64_t m, int64_t n, int64_t lda, int64_t ldb, int64_t ldc)
 {
     if (layout != MG_ROW_MAJOR && layout != MG_COL_MAJOR) return MG_ERR_LAYOUT;
@@ -677,16 +685,18 @@ mg_status run_symm(int dtype, int layout, int side, int uplo, int64_t m, int64_t
     const int64_t ka = side == MG_LEFT ? m : n;
     const size_t elem = dtype == MG_F32 ? 4 : 2;
     Carve carve(ws, ws_bytes);
-    void *full = carve.take(static_cast<size_t>(ka) * ka * elem);
+    int64_t ldf = aligned_ld(ka, elem);
+    if (carve.left < round_up_256(static_cast<size_t>(ka) * ldf * elem)) ldf = ka;
+    void *full = carve.take(static_cast<size_t>(ka) * ldf * elem);
     if (full == nullptr) return MG_ERR_WORKSPACE;
-    if (launch_expand_symmetric(dtype, ka, A, lda, lower_in_view(layout, uplo), full, static_cast<hipStream_t>(stream)) !=
+    if (launch_expand_symmetric(dtype, ka, A, lda, lower_in_view(layout, uplo), full, ldf, static_cast<hipStream_t>(stream)) !=
         hipSuccess)
         return MG_ERR_LAUNCH;
-    // a symmetric dense matrix with leading dimension ka reads the same in either layout
+    // a symmetric dense matrix reads the same in either layout
     if (side == MG_LEFT)
-        return run_gemm(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, m, alpha, full, ka, B, ldb, beta, C, ldc, carve.rest(),
+        return run_gemm(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, m, alpha, full, ldf, B, ldb, beta, C, ldc, carve.rest(),
                         carve.left, stream);
-    return run_gemm(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, n, alpha, B, ldb, full, ka, beta, C, ldc, carve.rest(),
+    return run_gemm(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, n, alpha, B, ldb, full, ldf, beta, C, ldc, carve.rest(),
                     carve.left, stream);
 }
 
@@ -776,16 +786,21 @@ mg_status run_trmm(int dtype, int layout, int side, int uplo, int trans, int dia
     }
     const int64_t ka = side == MG_LEFT ? m : n;
     const size_t elem = dtype == MG_F32 ? 4 : 2;
+    const int64_t minor = layout == MG_COL_MAJOR ? m : n, major = layout == MG_COL_MAJOR ? n : m;
     Carve carve(ws, ws_bytes);
-    void *full = carve.take(static_cast<size_t>(ka) * ka * elem);
-    void *copy = carve.take(static_cast<size_t>(m) * n * elem);
+    int64_t ldf = aligned_ld(ka, elem), ldk = aligned_ld(minor, elem);
+    if (carve.left < round_up_256(static_cast<size_t>(ka) * ldf * elem) + round_up_256(static_cast<size_t>(major) * ldk * elem)) {
+        ldf = ka;
+        ldk = minor;
+    }
+    void *full = carve.take(static_cast<size_t>(ka) * ldf * elem);
+    void *copy = carve.take(static_cast<size_t>(major) * ldk * elem);
     if (full == nullptr || copy == nullptr) return MG_ERR_WORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // the product cannot run in place: B is copied (tightly packed, same layout) and then overwritten; the copy and
+    // the product cannot run in place: B is copied (same layout) and then overwritten; the copy and
     // the expansion of the triangular matrix go out as one launch
-    const int64_t minor = layout == MG_COL_MAJOR ? m : n, major = layout == MG_COL_MAJOR ? n : m;
-    if (launch_trmm_prepare(dtype, ka, A, lda, lower_in_view(layout, uplo), diag == MG_UNIT, full, minor, major, B, ldb, copy,
-                            minor, st) != hipSuccess)
+    if (launch_trmm_prepare(dtype, ka, A, lda, lower_in_view(layout, uplo), diag == MG_UNIT, full, ldf, minor, major, B, ldb, copy,
+                            ldk, st) != hipSuccess)
         return MG_ERR_LAUNCH;
     // Which canonical operand is triangular, and how: op(A) is lower when uplo and trans say so; a row-major
     // call runs as the transposed product, which swaps the operands and turns lower into upper.
@@ -796,9 +811,9 @@ mg_status run_trmm(int dtype, int layout, int side, int uplo, int trans, int dia
     const int shape = tri_is_a ? (canonical_lower ? MG_SHAPE_A_LOWER : MG_SHAPE_A_UPPER)
                                : (canonical_lower ? MG_SHAPE_B_LOWER : MG_SHAPE_B_UPPER);
     if (side == MG_LEFT)
-        return run_gemm(dtype, layout, trans, MG_NO_TRANS, m, n, m, alpha, full, ka, copy, minor, 0.f, B, ldb, carve.rest(),
+        return run_gemm(dtype, layout, trans, MG_NO_TRANS, m, n, m, alpha, full, ldf, copy, ldk, 0.f, B, ldb, carve.rest(),
                         carve.left, stream, shape);
-    return run_gemm(dtype, layout, MG_NO_TRANS, trans, m, n, n, alpha, copy, minor, full, ka, 0.f, B, ldb, carve.rest(),
+    return run_gemm(dtype, layout, MG_NO_TRANS, trans, m, n, n, alpha, copy, ldk, full, ldf, 0.f, B, ldb, carve.rest(),
                     carve.left, stream, shape);
 }
 
@@ -987,18 +1002,19 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
     }
     if (!valid_side(side) || m == 0 || n == 0) return 0;
     const int64_t ka = side == MG_LEFT ? m : n;
-    const size_t dense = round_up_256(static_cast<size_t>(ka) * ka * elem);
+    const int64_t ldf = aligned_ld(ka, elem), ldk = aligned_ld(lead, elem), major = layout == MG_COL_MAJOR ? n : m;
+    const size_t dense = round_up_256(static_cast<size_t>(ka) * ldf * elem);
     if (routine == MG_ROUTINE_SYMM) {
         const size_t gemm = side == MG_LEFT
-                                ? mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, m, ka, lead, lead)
-                                : mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, n, lead, ka, lead);
+                                ? mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, m, ldf, lead, lead)
+                                : mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, MG_NO_TRANS, m, n, n, lead, ldf, lead);
         return dense + gemm;
     }
     if (routine == MG_ROUTINE_TRMM) {
         if (!valid_trans(trans)) return 0;
-        const size_t gemm = side == MG_LEFT ? mg_gemm_workspace_bytes(dtype, layout, trans, MG_NO_TRANS, m, n, m, ka, lead, lead)
-                                            : mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, trans, m, n, n, lead, ka, lead);
-        return dense + round_up_256(static_cast<size_t>(m) * n * elem) + gemm;
+        const size_t gemm = side == MG_LEFT ? mg_gemm_workspace_bytes(dtype, layout, trans, MG_NO_TRANS, m, n, m, ldf, ldk, lead)
+                                            : mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, trans, m, n, n, ldk, ldf, lead);
+        return dense + round_up_256(static_cast<size_t>(major) * ldk * elem) + gemm;
     }
     return 0;
 }

@@ -100,13 +100,13 @@ int64_t conv_out_extent(int64_t size, int64_t kernel, int64_t pad, int64_t strid
 hipError_t launch_im2col(int dtype, const ConvShape &s, const void *im, void *col, hipStream_t stream);
 
 // Support kernels of the GEMM-derived level-3 routines.  Matrices are seen in the column-major view of
-// their bytes (element (i, j) at p[i + j*ld]); dtype: mg_dtype; dense outputs have leading dimension n.
+// their bytes (element (i, j) at p[i + j*ld]); dtype: mg_dtype.  What lies between the columns of a destination may be written.
 // dst <- the whole symmetric n x n matrix from its stored lower (i >= j) or upper triangle
-hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_t ld, bool lower, void *dst,
+hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_t ld, bool lower, void *dst, int64_t ldd,
                                    hipStream_t stream);
 // full <- the triangular n x n matrix with zeros outside the triangle and ones on a unit diagonal, and dst <- src
 // (`major` runs of `minor` contiguous elements), in one launch
-hipError_t launch_trmm_prepare(int dtype, int64_t n, const void *tri, int64_t ld, bool lower, bool unit, void *full,
+hipError_t launch_trmm_prepare(int dtype, int64_t n, const void *tri, int64_t ld, bool lower, bool unit, void *full, int64_t ldf,
                                int64_t minor, int64_t major, const void *src, int64_t lds, void *dst, int64_t ldd,
                                hipStream_t stream);
 // dst <- src on the strictly lower (i > j) or strictly upper entries of an n x n matrix

@@ -26,17 +26,30 @@ template <typename U, int V> struct alignas(sizeof(U) * V) Pack {
 // (i >= j) or the upper triangle; what src holds in its other triangle is never used.  One work-group
 // takes the tile (ti, tj), ti >= tj, of the lower half through LDS and writes it twice: in place and
 // mirrored, both as runs of E contiguous elements per lane, LPC lanes side by side.  E x element size is
-// 16 bytes when n, ld and the pointers allow it (LPC = 16), else E = 1 (LPC = 64); the tile edge is
+// 16 bytes when the columns of dst start on 16 bytes (LPC = 16), else E = 1 (LPC = 64); src is read at element alignment
+// and dst written up to the end of a run, in the columns' padding (n = 1151 in FP16: 8.3 us element by element).  The tile edge is
 // LPC * E.  LDS is written and read element by element (an odd pitch in words keeps the transposed
 // reads spread over the banks).
 template <typename U, int E, int LPC>
 __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *__restrict__ src, int64_t ld, bool lower,
-                                                               U *__restrict__ dst)
+                                                               U *__restrict__ dst, int64_t ldd)
 {
     constexpr int TS = LPC * E;
     constexpr int PITCH = TS + (sizeof(U) == 4 ? 1 : 2);
     constexpr int STEP = 256 / LPC;
     struct alignas(sizeof(U) * E) Run { U v[E]; };
+    struct __attribute__((packed, aligned(sizeof(U)))) Loose { U v[E]; };
+    // E elements from src + at, those from `count` on missing (zero)
+    auto fetch = [&](int64_t at, int count) {
+        Loose w{};
+        if (count >= E) w = *reinterpret_cast<const Loose *>(src + at);
+        else {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (e < count) w.v[e] = src[at + e];
+        }
+        return w;
+    };
     __shared__ U tile[TS][PITCH];                    // tile[b][a] = S(ti*TS + a, tj*TS + b), used where a >= b globally
     const int ti = blockIdx.x, tj = blockIdx.y;
     if (ti < tj) return;
@@ -48,7 +61,7 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
             // rows a .. a+E-1 of column b: contiguous in src
             const int a = E * tx, b = ty;
             if (r0 + a < n && c0 + b < n && r0 + a + E - 1 >= c0 + b) {
-                const Run w = *reinterpret_cast<const Run *>(src + (r0 + a) + (c0 + b) * ld);
+                const Loose w = fetch((r0 + a) + (c0 + b) * ld, n - r0 - a);
 #pragma unroll
                 for (int e = 0; e < E; ++e) tile[b][a + e] = w.v[e];
             }
@@ -56,14 +69,13 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
             // S(r, c) with r >= c is stored as the upper entry (c, r): columns b .. b+E-1 of row a are contiguous
             const int a = ty, b = E * tx;
             if (r0 + a < n && c0 + b < n && r0 + a >= c0 + b) {
-                const Run w = *reinterpret_cast<const Run *>(src + (c0 + b) + (r0 + a) * ld);
+                const Loose w = fetch((c0 + b) + (r0 + a) * ld, n - c0 - b);
 #pragma unroll
                 for (int e = 0; e < E; ++e) tile[b + e][a] = w.v[e];
             }
         }
     }
     __syncthreads();
-    const int64_t nn = n;
 #pragma unroll 4
     for (int ty = ty0; ty < TS; ty += STEP) {
         const int a = E * tx, b = ty;
@@ -72,14 +84,14 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
 #pragma unroll
             for (int e = 0; e < E; ++e)     // above the diagonal (diagonal tile only): the mirrored entry of the same tile
                 w.v[e] = r0 + a + e >= c0 + b ? tile[b][a + e] : tile[a + e][b];
-            *reinterpret_cast<Run *>(dst + (r0 + a) + (c0 + b) * nn) = w;
+            *reinterpret_cast<Run *>(dst + (r0 + a) + (c0 + b) * ldd) = w;
         }
         if (ti != tj && c0 + a < n && r0 + b < n) {
             // mirrored tile (tj, ti): S(c0 + a + e, r0 + b) = S(r0 + b, c0 + a + e) = tile[a + e][b]
             Run w;
 #pragma unroll
             for (int e = 0; e < E; ++e) w.v[e] = tile[a + e][b];
-            *reinterpret_cast<Run *>(dst + (c0 + a) + (r0 + b) * nn) = w;
+            *reinterpret_cast<Run *>(dst + (c0 + a) + (r0 + b) * ldd) = w;
         }
     }
 }
@@ -93,40 +105,55 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
 // blockIdx.z == 0: full (n x n, leading dimension n) <- the triangular matrix: zero outside the stored triangle, one
 // on a unit diagonal; neither the other triangle of tri nor (unit) its diagonal is read.  blockIdx.z == 1: dst
 // (leading dimension ldd) <- src (leading dimension lds), `minor` contiguous elements in each of `major` runs.  The
-// grid covers the larger of the two.
+// grid covers the larger of the two.  V > 1: the columns of full and dst start on 16 bytes and have room for whole runs (the
+// sources are read at element alignment; FP16 n = 3159 17.5 us element by element).
 template <typename T, int V>
 __global__ __launch_bounds__(256) void trmm_prepare_kernel(int n, const T *__restrict__ tri, int64_t ld, bool lower, bool unit,
-                                                           T *__restrict__ full, int minor, int major,
+                                                           T *__restrict__ full, int64_t ldf, int minor, int major,
                                                            const T *__restrict__ src, int64_t lds, T *__restrict__ dst, int64_t ldd)
 {
     using P = Pack<T, V>;
+    struct __attribute__((packed, aligned(sizeof(T)))) Loose { T v[V]; };
     const int i = (blockIdx.x * 256 + threadIdx.x) * V;
     if (blockIdx.z == 1) {
         if (i >= minor) return;
+        const bool whole = i + V <= minor;
 #pragma unroll 4
-        for (int j = blockIdx.y; j < major; j += gridDim.y)
-            *reinterpret_cast<P *>(dst + i + j * ldd) = *reinterpret_cast<const P *>(src + i + j * lds);
+        for (int j = blockIdx.y; j < major; j += gridDim.y) {
+            P out;
+            if (whole) {
+                const Loose in = *reinterpret_cast<const Loose *>(src + i + j * lds);
+#pragma unroll
+                for (int e = 0; e < V; ++e) out.v[e] = in.v[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < V; ++e) out.v[e] = i + e < minor ? src[i + e + j * lds] : static_cast<T>(0.f);
+            }
+            *reinterpret_cast<P *>(dst + i + j * ldd) = out;
+        }
         return;
     }
     if (i >= n) return;
 #pragma unroll 4
     for (int j = blockIdx.y; j < n; j += gridDim.y) {
         P out;
-        const bool all_in = lower ? i > j : i + V - 1 < j;            // strictly inside: no diagonal element either
+        const bool all_in = (lower ? i > j : i + V - 1 < j) && i + V <= n;            // strictly inside: no diagonal element either
         const bool all_out = lower ? i + V - 1 < j : i > j;
         if (all_in) {
-            out = *reinterpret_cast<const P *>(tri + i + j * ld);
+            const Loose in = *reinterpret_cast<const Loose *>(tri + i + j * ld);
+#pragma unroll
+            for (int e = 0; e < V; ++e) out.v[e] = in.v[e];
         } else {
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 const int r = i + e;
-                const bool in = lower ? r >= j : r <= j;
+                const bool in = r < n && (lower ? r >= j : r <= j);
                 T v = static_cast<T>(0.f);
                 if (!all_out && in) v = (unit && r == j) ? static_cast<T>(1.f) : tri[r + j * ld];
                 out.v[e] = v;
             }
         }
-        *reinterpret_cast<P *>(full + i + static_cast<int64_t>(j) * n) = out;
+        *reinterpret_cast<P *>(full + i + j * ldf) = out;
     }
 }
 
@@ -264,11 +291,21 @@ bool runs_aligned(int64_t minor, const void *a, int64_t lda, const void *b, int6
 
 }  // namespace
 
-hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_t ld, bool lower, void *dst,
+// 16-byte runs into a destination whose columns start on 16 bytes, the last run of a column ending in its padding: where source and
+// sizes are aligned too, and for any other source from 1024 rows on (below, single elements spread over more work-groups: SYMM FP16 379 x 960
+// 18.8 us, in runs 21.0; 1337 x 322 the other way round 41.9 / 22.4)
+bool runs_fit(int64_t minor, const void *src, int64_t lds, const void *dst, int64_t ldd, int elem)
+{
+    const int v = 16 / elem;
+    if (ldd % v != 0 || ldd < ceil_div(minor, v) * v || pointer_alignment(dst) < 16) return false;
+    return minor >= 1024 || runs_aligned(minor, src, lds, dst, ldd, elem);
+}
+
+hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_t ld, bool lower, void *dst, int64_t ldd,
                                    hipStream_t stream)
 {
     const int elem = dtype == MG_F32 ? 4 : 2;
-    const bool wide = runs_aligned(n, src, ld, dst, n, elem);
+    const bool wide = runs_fit(n, src, ld, dst, ldd, elem);
     const int edge = wide ? 16 * (16 / elem) : 64;
     const unsigned tiles = static_cast<unsigned>(ceil_div(n, edge));
     if (tiles > kMaxGridY) return hipErrorInvalidValue;
@@ -277,13 +314,13 @@ hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_
     if (dtype == MG_F32) {
         const uint32_t *s = static_cast<const uint32_t *>(src);
         uint32_t *d = static_cast<uint32_t *>(dst);
-        if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 4, 16>), grid, dim3(256), 0, stream, nn, s, ld, lower, d);
-        else hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 1, 64>), grid, dim3(256), 0, stream, nn, s, ld, lower, d);
+        if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 4, 16>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
+        else hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 1, 64>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
     } else {
         const uint16_t *s = static_cast<const uint16_t *>(src);
         uint16_t *d = static_cast<uint16_t *>(dst);
-        if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 8, 16>), grid, dim3(256), 0, stream, nn, s, ld, lower, d);
-        else hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 1, 64>), grid, dim3(256), 0, stream, nn, s, ld, lower, d);
+        if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 8, 16>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
+        else hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 1, 64>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
     }
     return hipGetLastError();
 }
@@ -304,25 +341,28 @@ hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_
         }                                                                                                             \
     } while (0)
 
-hipError_t launch_trmm_prepare(int dtype, int64_t n, const void *tri, int64_t ld, bool lower, bool unit, void *full,
+hipError_t launch_trmm_prepare(int dtype, int64_t n, const void *tri, int64_t ld, bool lower, bool unit, void *full, int64_t ldf,
                                int64_t minor, int64_t major, const void *src, int64_t lds, void *dst, int64_t ldd,
                                hipStream_t stream)
 {
     const int elem = dtype == MG_F32 ? 4 : 2;
-    const int v = runs_aligned(n, tri, ld, full, n, elem) && runs_aligned(minor, src, lds, dst, ldd, elem) ? 16 / elem : 1;
+    const int64_t most = n > minor ? n : minor;        // (one flavour for both jobs)
+    const bool fits = ldf % (16 / elem) == 0 && ldd % (16 / elem) == 0 && pointer_alignment(full) >= 16 && pointer_alignment(dst) >= 16;
+    // (room for whole runs: a leading dimension that is a multiple of them holds the last one)
+    const int v = fits && (most >= 1024 || (runs_aligned(n, tri, ld, full, ldf, elem) && runs_aligned(minor, src, lds, dst, ldd, elem))) ? 16 / elem : 1;
     const dim3 a = column_grid(n, n, v), b = column_grid(minor, major, v);
     const dim3 grid(a.x > b.x ? a.x : b.x, a.y > b.y ? a.y : b.y, 2);
     const int nn = static_cast<int>(n), mi = static_cast<int>(minor), ma = static_cast<int>(major);
     if (dtype == MG_F32) {
         const float *t = static_cast<const float *>(tri), *s = static_cast<const float *>(src);
         float *f = static_cast<float *>(full), *d = static_cast<float *>(dst);
-        if (v > 1) hipLaunchKernelGGL((trmm_prepare_kernel<float, 4>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, mi, ma, s, lds, d, ldd);
-        else hipLaunchKernelGGL((trmm_prepare_kernel<float, 1>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, mi, ma, s, lds, d, ldd);
+        if (v > 1) hipLaunchKernelGGL((trmm_prepare_kernel<float, 4>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, ldf, mi, ma, s, lds, d, ldd);
+        else hipLaunchKernelGGL((trmm_prepare_kernel<float, 1>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, ldf, mi, ma, s, lds, d, ldd);
     } else {
         const _Float16 *t = static_cast<const _Float16 *>(tri), *s = static_cast<const _Float16 *>(src);
         _Float16 *f = static_cast<_Float16 *>(full), *d = static_cast<_Float16 *>(dst);
-        if (v > 1) hipLaunchKernelGGL((trmm_prepare_kernel<_Float16, 8>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, mi, ma, s, lds, d, ldd);
-        else hipLaunchKernelGGL((trmm_prepare_kernel<_Float16, 1>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, mi, ma, s, lds, d, ldd);
+        if (v > 1) hipLaunchKernelGGL((trmm_prepare_kernel<_Float16, 8>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, ldf, mi, ma, s, lds, d, ldd);
+        else hipLaunchKernelGGL((trmm_prepare_kernel<_Float16, 1>), grid, dim3(256), 0, stream, nn, t, ld, lower, unit, f, ldf, mi, ma, s, lds, d, ldd);
     }
     return hipGetLastError();
 }
