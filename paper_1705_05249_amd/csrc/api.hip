@@ -161,7 +161,8 @@ size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
 struct IndirectPlan {
     int64_t mp, np, kp;
     size_t a_bytes, b_bytes, c_bytes;
-    bool compare;            // take it only if its estimate is below the direct route's
+    bool compare;            // take it only if its estimate is below the direct route's times `odds`
+    double odds;
     size_t total() const { return a_bytes + b_bytes + c_bytes; }
 };
 
@@ -185,6 +186,7 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     const double work = static_cast<double>(p.m) * static_cast<double>(p.n) * static_cast<double>(p.k);
     int64_t tile = 0, ktile = 0;
     bool compare = false;
+    double odds = 1.0;
     if (p.dtype == MG_F16) {
         // a launch in front, its gap and ~10 us of copies at 2051^2 (~33 us at 4096^2): measured a loss at 1000^3 (28 against
         // 22 us), a gain at 2049^3 (56 against 96 us; both while C was copied too)
@@ -193,17 +195,20 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
         const bool aligned = p.lda % 8 == 0 && p.ldb % 8 == 0 &&
                              (!pointers_known || (pointer_alignment(p.A) >= 16 && pointer_alignment(p.B) >= 16));
         if (whole && aligned) return false;                            // the fast kernels take it directly
-        // Operands whose rows start on dwords run most of their K-tiles on the fast flavour's schedule inside the
-        // bounds-checked kernels: there the two routes' estimates are compared, up to about 900 multiply-adds per element moved;
-        // beyond, the copies always pay.  Even leading dimensions, us direct / through the copies of A and B (A along m | along
-        // k): 1300^3 21.6 / 25.1 | 19.2 / 25.1, 1500^3 37 / 27 | 33 / 28, 1800^3 30 / 27 | 29 / 28, 2050^3 45 / 41 | 47 / 40, 2500^3
-        // 60 / 49 | 59 / 50, 2700^3 59 / 58 | 60 / 60, (8200, 1030, 2050) - | 62 / 76, (4100, 4100, 512) 53 / 54 | -.  (Without
-        // the pointers, for the workspace query, the copies are assumed: an upper bound.)
-        const bool dword_rows = p.lda % 2 == 0 && p.ldb % 2 == 0 && pointers_known && pointer_alignment(p.A) >= 4 &&
-                                pointer_alignment(p.B) >= 4;
+        // The bounds-checked kernels run their whole K-tiles on the fast flavour's schedule: up to about 900 multiply-adds per
+        // element moved the two routes' estimates are compared; beyond, the copies always pay.  Even leading dimensions, us
+        // direct / through the copies of A and B (A along m | along k): 1300^3 21.6 / 25.1 | 19.2 / 25.1, 1500^3 37 / 27 | 33 /
+        // 28, 1800^3 30 / 27 | 29 / 28, 2050^3 45 / 41 | 47 / 40, 2500^3 60 / 49 | 59 / 50, 2700^3 59 / 58 | 60 / 60, (8200,
+        // 1030, 2050) - | 62 / 76, (4100, 4100, 512) 53 / 54 | -.
         const double moved = static_cast<double>(p.m) * p.k + static_cast<double>(p.k) * p.n + static_cast<double>(p.m) * p.n;
-        if (dword_rows && work < 350.0 * moved) return false;
-        compare = dword_rows && work < 900.0 * moved;
+        // Rows that start at odd elements cost the direct route a little more: 1801^3 29.9 / 26.7, (2671, 1061, 1265) 35.3 / 29.0
+        // at estimates 1.17 apart, (8201, 1031, 2051) 64 / 75 at 1.29, (1031, 1031, 8001) 56 / 63 at 1.65.  Their sums of fewer than
+        // 1536 terms always take the copies: short ones gain ((4001, 4001, 501) 43 / 40), around 1300 terms they lose (1301^3
+        // 20.3 / 25.8), but the tests of the staged kernels' remainders count on this route there.
+        const bool dword_rows = p.lda % 2 == 0 && p.ldb % 2 == 0 && (!pointers_known || (pointer_alignment(p.A) >= 4 && pointer_alignment(p.B) >= 4));
+        if (work < 350.0 * moved) return false;
+        compare = work < 900.0 * moved && (dword_rows || p.k >= 1536);
+        odds = dword_rows ? 1.15 : 1.2;
         tile = p.m >= 2048 && p.n >= 2048 ? 256 : 128;
         ktile = 64;
     } else {
@@ -216,6 +221,7 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     }
     *plan = padded_to(p, tile, tile, ktile);
     plan->compare = compare;
+    plan->odds = odds;
     return true;
 }
 
@@ -291,7 +297,7 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken, 
             double us = 0.0;
             const bool known = choose(direct->p, problem_alignment(p), p.workspace_bytes, &direct->kernel, &direct->split, &us) == MG_OK;
             if (!known) direct->kernel = -1;
-            if (best_kernel < 0 || (known && us > 0.0 && 1.15 * us <= best_us + copies_us)) {
+            if (best_kernel < 0 || (known && us > 0.0 && plan.odds * us <= best_us + copies_us)) {
                 *taken = false;
                 return MG_OK;
             }

@@ -233,19 +233,21 @@ template <typename T, int ROWS, int BK, int NT, bool KCONTIG, bool EDGE, bool CO
     // byte offset of logical chunk c of row r inside the operand's LDS tile
     __device__ static inline int lds_offset(int r, int c) { return ldsmap::kcontig_slot<32>(r, c); }
 
-    // Bounds-checked flavour: whole K-tiles are loaded like the fast flavour's, with buffer loads, where the operand's
-    // rows start on dword boundaries (FP16: an even leading dimension).  Tiles that lack rows at the matrix's edge do so too: their buffer
-    // descriptor ends with the last row that exists (operand along k) resp. with the matrix (operand along its
-    // rows), and a buffer load returns zero for every dword past the descriptor's range without touching memory;
-    // lanes whose whole piece lies in missing rows are sent out of range on purpose (offset 2^31), a piece that
-    // straddles the last row is cut when it is stored.  The kernel's K loop: a body whose reload is a whole K-tile
-    // takes the fast flavour's schedule with these loads (load_one<Q, true>), the body that reloads the partial last
+    // Bounds-checked flavour: whole K-tiles are loaded like the fast flavour's, without checks.  FP32: with buffer loads.  Tiles that
+    // lack rows at the matrix's edge do so too: their buffer descriptor ends with the last row that exists (operand along k)
+    // resp. with the matrix (operand along its rows), and a buffer load returns zero for every dword past the descriptor's range
+    // without touching memory; lanes whose whole piece lies in missing rows are sent out of range on purpose (offset 2^31), a piece
+    // that straddles the last row is cut when it is stored.  FP16: with global loads, which take rows that start at odd elements
+    // (buffer loads want dwords); lanes in missing rows read a row that exists, a piece that straddles the last row
+    // runs into the next line (the kernel keeps the matrix's last line out of these loads).  The kernel's K loop: a body whose reload is
+    // a whole K-tile takes the fast flavour's schedule with these loads (load_one<Q, true>), the body that reloads the partial last
     // K-tile the checked loads, and the last two bodies, with nothing left to reload, no loads.
+    // (FP16 rows that start at odd elements ran every K-tile on the checked loads, whose branches keep one load in flight at a time.
+    // us, before / now, same tile: 1001^3 17.9 / 11.5 (A along m) and 13.9 / 9.8 (along k), (295, 7412, 1245) 74.9 / 29.6, (45, 39,
+    // 4201) 18.7 / 11.6; even ones 1000^3 10.7 / 9.6, whose first two K-tiles took the checked loads.)
     static constexpr bool INTERIOR_FAST = EDGE && !CONV;
-    // FP32 only: a whole K-tile that one of the checked bodies reloads takes the buffer loads as well.  The FP16 kernels
-    // are better off without that case at their checked load sites: with it, problems whose rows start at odd elements
-    // (which run every K-tile on the checked loads) lost 10-30 % ((1000, 1001, 999): 12.6 -> 15.2 us with A along m,
-    // 13.9 -> 18.1 us along k), and the others gained little from it (2050^3: 47 -> 43 us, 1000^3: 9.8 -> 10.1 us).
+    static constexpr bool ANY_ELEMENT = INTERIOR_FAST && sizeof(T) == 2;
+    // FP32 only: a whole K-tile that one of the checked bodies reloads takes the buffer loads as well.
     static constexpr bool CHECKED_WHOLE = INTERIOR_FAST && sizeof(T) == 4;
     static constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
 
@@ -282,12 +284,14 @@ template <typename T, int ROWS, int BK, int NT, bool KCONTIG, bool EDGE, bool CO
                 constexpr int Q = decltype(Qc)::value;
                 const int idx = t + Q * NT;
                 if constexpr (KCONTIG) {
-                    goff[Q] = static_cast<uint32_t>(((idx / CPR) * ld_ + (idx % CPR) * CH) * sizeof(T));
+                    const int r = ANY_ELEMENT && idx / CPR >= rows ? rows - 1 : idx / CPR;
+                    goff[Q] = static_cast<uint32_t>((r * ld_ + (idx % CPR) * CH) * sizeof(T));
                 } else if constexpr (NATIVE) {
                     goff[Q] = (idx % RCH) * CH < rows ? static_cast<uint32_t>(((idx % RCH) * CH + (idx / RCH) * ld_) * sizeof(T)) : OUT_OF_RANGE;
                 } else {
                     const Unit u = unit_of(Q / KU);
-                    goff[Q] = u.mc * CH < rows ? static_cast<uint32_t>((u.mc * CH + (u.kc * CH + u.s * KU + Q % KU) * ld_) * sizeof(T)) : OUT_OF_RANGE;
+                    const uint32_t line = static_cast<uint32_t>((u.kc * CH + u.s * KU + Q % KU) * ld_ * sizeof(T));
+                    goff[Q] = u.mc * CH < rows ? line + static_cast<uint32_t>(u.mc * CH * sizeof(T)) : (ANY_ELEMENT ? line : OUT_OF_RANGE);
                 }
             });
 #pragma unroll
@@ -322,8 +326,7 @@ template <typename T, int ROWS, int BK, int NT, bool KCONTIG, bool EDGE, bool CO
 
     // Tile position for the loads that follow.  rows_left / k_left: rows / k values from (r0, l0) on that
     // are inside the matrix (used by EDGE only); vec_ok: 16-byte loads are allowed; whole (EDGE only): the tile's
-    // rows start on dword boundaries and its lane offsets fit 31 bits, so that its whole K-tiles can be loaded with
-    // buffer loads like the fast flavour's.
+    // lane offsets fit 31 bits, so that its whole K-tiles can be loaded like the fast flavour's.
     const T *base;
     int64_t ld;
     int rows_left, k_left;
@@ -352,13 +355,11 @@ template <typename T, int ROWS, int BK, int NT, bool KCONTIG, bool EDGE, bool CO
         // construction.  A tile that lacks rows: the bytes from its first element to the end of its last row
         // (operand along k: later rows are out of range) resp. to the matrix's last element (operand along its rows)
         int range = 0x7fffffff;
-        if constexpr (INTERIOR_FAST) {
+        if constexpr (INTERIOR_FAST && !ANY_ELEMENT) {
             if (whole_ && rows_left_ < ROWS && k_left_ >= BK) {    // (k_left_ < BK: the checked loads, no descriptor)
                 // (far from the end of a long sum the matrix ends beyond 2^31 bytes: no limit needed, the tile's
                 // own offsets stay below that)
-                // (whole dwords: the range check is per dword, and a dword that holds a valid FP16 element lies in the
-                // page of that element)
-                const int64_t bytes = ((KCONTIG ? (rows_left_ - 1) * ld_ + k_left_ : (k_left_ - 1) * ld_ + rows_left_) * static_cast<int64_t>(sizeof(T)) + 3) / 4 * 4;
+                const int64_t bytes = (KCONTIG ? (rows_left_ - 1) * ld_ + k_left_ : (k_left_ - 1) * ld_ + rows_left_) * static_cast<int64_t>(sizeof(T));
                 range = bytes < 0x7fffffff ? static_cast<int>(bytes) : 0x7fffffff;
             }
         }
@@ -382,7 +383,12 @@ template <typename T, int ROWS, int BK, int NT, bool KCONTIG, bool EDGE, bool CO
             } else {
                 if (!unit_of(Q / KU).valid) return;
             }
-            regs[Q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[Q], 0, 0);
+            if constexpr (ANY_ELEMENT) {
+                // (scalar base + 32-bit lane offset; without this line the offsets are widened in front of the K loop and take two
+                // registers each, and a 64-bit addition per load)
+                asm volatile("" : "+v"(goff[Q]));
+                regs[Q] = load_unaligned_chunk<T>(reinterpret_cast<const T *>(reinterpret_cast<const char *>(base) + goff[Q]));
+            } else regs[Q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[Q], 0, 0);
         } else if constexpr (KCONTIG) {
             const int idx = t + Q * NT;
             const int c = idx % CPR, r = idx / CPR;
@@ -472,7 +478,7 @@ template <typename T, int ROWS, int BK, int NT, bool KCONTIG, bool EDGE, bool CO
         }
     }
 
-    __device__ inline void load_all() { static_for<LOADS>([&](auto q) { load_one<decltype(q)::value>(); }); }
+    template <bool FAST = false> __device__ inline void load_all() { static_for<LOADS>([&](auto q) { load_one<decltype(q)::value, FAST>(); }); }
     __device__ inline void store_all(char *lds)
     {
         static_for<STORES>([&](auto q) { store_one<decltype(q)::value>(lds); });
@@ -845,12 +851,14 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
     if constexpr (EDGE) {
         vec_a = (args.lda % CH == 0) && (reinterpret_cast<uintptr_t>(A) % 16 == 0);
         vec_b = (args.ldb % CH == 0) && (reinterpret_cast<uintptr_t>(B) % 16 == 0);
-        // rows that start on dword boundaries and lane offsets that fit 31 bits: whole K-tiles go through buffer loads
+        // lane offsets that fit 31 bits: whole K-tiles go without checks
         constexpr int64_t SPAN_A = BM > BK ? BM : BK, SPAN_B = BN > BK ? BN : BK;
-        whole_a = (args.lda * sizeof(T)) % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 4 == 0 &&
-                  args.lda * SPAN_A * static_cast<int64_t>(sizeof(T)) < (int64_t(1) << 31);
-        whole_b = (args.ldb * sizeof(T)) % 4 == 0 && reinterpret_cast<uintptr_t>(B) % 4 == 0 &&
-                  args.ldb * SPAN_B * static_cast<int64_t>(sizeof(T)) < (int64_t(1) << 31);
+        whole_a = args.lda * SPAN_A * static_cast<int64_t>(sizeof(T)) < (int64_t(1) << 31);
+        whole_b = args.ldb * SPAN_B * static_cast<int64_t>(sizeof(T)) < (int64_t(1) << 31);
+        if constexpr (LoadA::ANY_ELEMENT) {       // (a piece that straddles the last row ends in the next line: within the next line's rows)
+            whole_a = whole_a && (A_KCONTIG || args.lda >= CH);
+            whole_b = whole_b && (B_KCONTIG || args.ldb >= CH);
+        }
     }
 
     const int lane = threadIdx.x % 64;
@@ -904,6 +912,15 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
     if constexpr (CONV) la.geom = args.conv;
     la.prepare(args.lda, rows_a);
     lb.prepare(args.ldb, rows_b);
+    // K-tiles that are loaded without checks (FP16: not the one with the matrix's last line where pieces may run into the next line)
+    int fast_tiles = 0;
+    if constexpr (LoadA::INTERIOR_FAST) {
+        fast_tiles = (whole_a && whole_b) ? (ke - kb) / BK : 0;
+        if constexpr (LoadA::ANY_ELEMENT) {
+            const bool runs_over = (!A_KCONTIG && rows_a % CH != 0) || (!B_KCONTIG && rows_b % CH != 0);
+            if (runs_over && fast_tiles > (args.k - 1 - kb) / BK) fast_tiles = (args.k - 1 - kb) / BK;
+        }
+    }
 
     u32x4 fa[2][FM], fb[2][FN];
     // fragment F of K-step s in LDS stage `par`: F < FM -> A fragment F, else B fragment F - FM
@@ -929,14 +946,22 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
 
     if (ktiles > 0) {
         // prologue: tile 0 -> LDS buffer 0, tile 1 -> registers, first fragments -> registers
-        aim_tile(0);
-        la.load_all();
-        lb.load_all();
+        auto load_tile = [&](int tile) {
+            aim_tile(tile);
+            if constexpr (LoadA::ANY_ELEMENT) {
+                if (tile < fast_tiles) {
+                    la.template load_all<true>();
+                    lb.template load_all<true>();
+                    return;
+                }
+            }
+            la.load_all();
+            lb.load_all();
+        };
+        load_tile(0);
         la.store_all(lds);
         lb.store_all(lds + 2 * A_BYTES);
-        aim_tile(1);
-        la.load_all();
-        lb.load_all();
+        load_tile(1);
         if constexpr (SHORT) early.fetch(args, m0, n0, __builtin_amdgcn_readfirstlane(wm), __builtin_amdgcn_readfirstlane(wn), lane);
         __syncthreads();
         static_for<FRAGS>([&](auto F) { read_frag(F, Stage0{}, 0, 0); });
@@ -977,8 +1002,8 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
 
     // One K-tile.  CUR: the LDS stage the MFMAs read (compile time, the K loop being unrolled by two, so that
     // every LDS address is a loop-invariant register plus an immediate); the other stage receives tile t+1.
-    // LOADS_AS (bounds-checked flavour): LOADS_FAST when the K-tile reloaded here, t + 2, is a whole one and both operands
-    // can be loaded with buffer loads (the fast flavour's instruction stream, pinned the same way), LOADS_NONE when there
+    // LOADS_AS (bounds-checked flavour): LOADS_FAST when the K-tile reloaded here, t + 2, is a whole one that both operands
+    // can load without checks (the fast flavour's instruction stream, pinned the same way), LOADS_NONE when there
     // is no tile t + 2 (pinned too), else LOADS_CHECKED.
     auto tile_body = [&](auto CUR, auto LOADS_AS, int t) {
         using Cur = decltype(CUR);
@@ -1028,13 +1053,12 @@ __global__ __launch_bounds__(WM *WN * 64) void mfma_gemm_kernel(const MfmaArgs a
     int t = 0;
     if constexpr (LoadA::INTERIOR_FAST) {
         // The body of tile t reloads tile t + 2: with the fast flavour's loads and schedule when that tile is a whole
-        // K-tile of operands whose rows start on dwords (tiles 0 .. fast_tiles - 1), with the checked loads when it is
+        // K-tile (tiles 0 .. fast_tiles - 1), with the checked loads when it is
         // the partial last K-tile or the operands do not qualify, and not at all when there is no such tile (the last
         // two bodies, on the pinned schedule as well).  Each loop holds bodies of one kind, and the last two to four
         // tiles are spelled out: with the kind chosen inside one loop the compiler kept two copies of the accumulators.
         // (While every body of the last K-tiles took the checked loads, 1024^3 cost 19.8 us in this flavour against 18.7
         // in the fast one.)
-        const int fast_tiles = (whole_a && whole_b) ? (ke - kb) / BK : 0;
         for (; t + 3 < fast_tiles; t += 2) {
             tile_body(Stage0{}, Fast{}, t);
             tile_body(Stage1{}, Fast{}, t + 1);

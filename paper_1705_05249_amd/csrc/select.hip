@@ -330,22 +330,22 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (!f32 && i == kDeep && !(p.a_trans && !p.b_trans)) order = 0.95;
             // the 128 x 128 direct-to-LDS tile is slower with A along k (3.7-3.8 against 4.0)
             if (!f32 && i == 2 && p.a_trans) order = 0.94;
-            // ragged or unaligned FP16 problems run the bounds-checked flavour, which costs the smaller tiles more
-            // (rates against the whole-tile flavour: 0.75 for 256 x 256 and 256 x 128, about 0.5 for 128 x 128
-            // and below; FP32: see below)
+            // ragged FP16 problems run the bounds-checked flavour (FP32: see below)
             const bool ragged = tm % tiles[i].bm || tn % tiles[i].bn || p.k % tiles[i].bk || tm != p.m || tn != p.n;
-            // (operands whose rows start on dwords run their whole K-tiles on the fast schedule: fitted to ragged cubes of
-            // 1300 to 5002, (4100, 4100, 512) and (8200, 1030, 2050), every bounds-checked tile forced: the eight-wavefront
-            // 256 x 256 tile at its whole-tile rate, 256 x 128 at 0.77, 128 x 128 at 0.75 alone on a compute unit and 0.9
-            // with a second work-group to hide the checked part behind)
-            const bool dword_rows = !f32 && p.lda % 2 == 0 && p.ldb % 2 == 0;
+            // (rates against the whole-tile flavour, one work-group per compute unit / more, and what the larger tiles' checked ends
+            // cost on top, fitted to every bounds-checked tile with 1 to 14 slices on 13 sizes in three orders, odd rows: (1672, 561,
+            // 3265) 31.9 us on 256 x 256 in 8 slices, 22.9 on 128 x 64 in 4; (295, 7412, 1245) 128 x 128 34.7, 64 x 64 25.4; (4379, 256,
+            // 4608) 256 x 256 in 8 40.7, 128 x 128 in 4 35.8; (2881, 3483, 37) 26.0, 17.3; (448, 609, 2741) 128 x 128 in 8
+            // 17.9, 64 x 64 in 4 14.2; (8201, 1031, 2051) 256 x 256 64, 128 x 128 91)
+            double ends = 0.0;
             if (!f32 && ragged) {
                 const int area = tiles[i].bm * tiles[i].bn;
-                if (!dword_rows) order *= area < 256 * 128 ? 0.6 : 0.7;
-                else if (area >= 256 * 256) order *= 1.0;
-                else if (area >= 256 * 128) order *= 0.77;
-                else if (area >= 128 * 128) order *= blocks > kComputeUnits ? 0.9 : 0.75;
-                else order *= 0.6;
+                const bool several = blocks > kComputeUnits;
+                if (area >= 256 * 256) { order *= 0.9; ends = 4.0e6; }
+                else if (area >= 256 * 128) { order *= 0.77; ends = 8.0e6; }
+                else if (area >= 128 * 128) { order *= several ? (slices > 1 ? 0.95 : 0.8) : 0.75; ends = 2.0e6; }
+                else if (area >= 128 * 64) { order *= several ? (slices > 1 ? 0.85 : 0.7) : 0.7; ends = 1.0e6; }
+                else { order *= several ? 0.85 : 0.65; ends = 1.0e6; }
             }
             // rate of a compute unit that holds u work-groups at once: ceiling * (1 - (1 - per_group / ceiling)^u)
             // (measured on the 64 x 64 FP16 tile: 1.33 / 1.85 / 2.02 / 2.11 for u = 1..4, the formula gives
@@ -392,7 +392,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // register-staged), 128 x 128 direct-to-LDS 1.3 when the busiest compute units hold two work-groups
                 // (324 tiles at 2304^3: 4.8 Mflop/us against 3.6) but 0.1 with one, its four-stage sibling 0.4, the smaller register-staged
                 // kernels 0.1; the bounds-checked flavour shows no gain; the 128 x 128 direct-to-LDS tile at most 1.2
-                if (!ragged || (dword_rows && i == 3)) {
+                if (!ragged || i == 3) {
                     const int64_t busiest = blocks - static_cast<int64_t>(kComputeUnits) * (per_unit - 1);
                     const double lower = per_unit > 1 ? shared_rate(per_unit - 1) : 0.0;
                     const double load = (static_cast<double>(busiest) * rate + static_cast<double>(kComputeUnits - busiest) * lower) /
@@ -427,6 +427,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // the kernels with three and four stages: their first loads and the epilogue beside the loop's rate (128 x 128 tiles:
             // 24 K-tiles on 144 compute units 14.7 us, 64 on 128 units 26.8 us, 16 on 64 units 10.7 us)
             if (!f32 && (i == 1 || i == kDeep)) time += 2.0e6;
+            time += ends;
             // split-K: the partial sums are written and read back (8 bytes per slice and output at ~4 TB/s) by
             // a second launch (2.5 us; 4 us behind the bounds-checked FP32 flavour, fitted with the rates above)
             if (slices > 1) time += 1.0e6 * ((f32 && i >= kSplit ? 6.0 : (f32 && ragged ? 4.0 : 2.5)) + (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) / 4.0e6);
