@@ -100,9 +100,5 @@ MG_HD constexpr int split_line_base(int rows, int lane, int wrow)
     return split_line_slot(rows, k, row / 8) + 8 * ((row / 4) % 2);
 }
 
-// 64 rows x 16 values of k of an operand along its rows, as floats: [k][row] lines of sixteen 16-byte chunks.  Lanes 0-31 read 32 rows
-// of line e, lanes 32-63 the same rows of line 8 + e, which lies in the other half of a bank row.
-MG_HD constexpr int slice_line_slot(int k, int chunk) { return k * 256 + ((chunk ^ (8 * ((k >> 3) & 1))) << 4); }
-
 }  // namespace ldsmap
 }  // namespace mg

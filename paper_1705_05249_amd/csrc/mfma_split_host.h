@@ -26,27 +26,6 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKC, bool EDGE, int DEPT
     }
 };
 
-// 64 x 64 tiles, eight wavefronts that share the sum
-template <bool AK, bool BKC, bool EDGE> struct SplitSlicesConfig {
-    using Plain = MfmaConfig<float, 64, 64, 32, 4, 2, AK, BKC, EDGE>;         // (of the same number of threads)
-    static constexpr int NT = 512, LDS = 8 * 64 * (64 * 4 + 16);
-
-    static hipError_t launch(const Problem &p, int split)
-    {
-        static bool attr_set = false;
-        return launch_tile_kernel<float>(mfma_split_slices_kernel<AK, BKC, EDGE>, &attr_set, LDS, NT, 64, 64,
-                                         Plain::k_per_split(p, split), p, split, EDGE ? Plain::fringe_groups(p) : 0);
-    }
-    static KernelEntry entry(const char *name)
-    {
-        KernelEntry e = Plain::entry(name, launch);
-        e.cfg.waves_m = e.cfg.waves_n = 1;
-        e.cfg.threads = NT;
-        e.cfg.lds_bytes = LDS;
-        return e;
-    }
-};
-
 #define MG_SPLIT_REGISTER(table, tag, BM, BN, WM, WN, DEPTH)                                          \
     table.push_back(SplitConfig<BM, BN, WM, WN, false, true, false, DEPTH>::entry(tag "_mk"));        \
     table.push_back(SplitConfig<BM, BN, WM, WN, true, true, false, DEPTH>::entry(tag "_kk"));         \

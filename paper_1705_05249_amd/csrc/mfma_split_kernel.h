@@ -1,12 +1,13 @@
 // FP32 macro-tile GEMM kernel on the bf16 matrix pipes.
 //
 // Every FP32 element is the sum of three bf16 values, x = x1 + x2 + x3 (each the rounded rest of the one before: 3 x 8
-// significand bits and their signs hold all 24), and of the nine products of two such elements the six that matter are
-// taken:  a1 b1 + (a1 b2 + a2 b1 + a2 b2 + a1 b3 + a3 b1); the rest is below 2^-26 of |a b|, a quarter of what rounding
-// a b to FP32 costs.  Products of bf16 values are exact in the matrix pipes' FP32 accumulators; a1 b1 has accumulators of its own, the five
-// small products share others that are added once at the end, so the large sums see one rounding per four values of k
-// (v_mfma_f32_32x32x16_bf16) where v_mfma_f32_32x32x2_f32 rounds for each.  Six bf16 instructions of 32 cycles take the
-// place of eight FP32 ones of 64 (16 values of k).
+// significand bits and their signs hold all 24), and of the nine products of two such elements all but a3 b3 are taken:  a1 b1 +
+// (a1 b2 + a2 b1 + a2 b2 + a1 b3 + a3 b1 + a2 b3 + a3 b2).  With |x2| <= 2^-8 |x| and |x3| <= 2^-17 |x| the one left out is at most 2^-34
+// of |a b|; a2 b3 + a3 b2 reach 2^-24, what rounding a b to FP32 costs (without them a sum that one product dominates was off by
+// up to 0.95 units in its last place; with them 0.506, FP32 pipes 0.5).  Products of bf16 values are exact in the matrix pipes' FP32
+// accumulators; a1 b1 has accumulators of its own, the seven small products share others that are added once at the end, so the large
+// sums see one rounding per four values of k (v_mfma_f32_32x32x16_bf16) where v_mfma_f32_32x32x2_f32 rounds for each.  Eight bf16
+// instructions of 32 cycles take the place of eight FP32 ones of 64 (16 values of k).
 //
 // The sums differ from FP32 arithmetic where a part cannot hold its share: elements below 2^-110 (but not 0), whose last bits lie
 // below bf16's smallest value, and elements or products near the end of the range, which leave Inf or NaN in an
@@ -196,11 +197,10 @@ __device__ __forceinline__ void mma_bf16(floatx16 &acc, const u32x4 &frag_n, con
 
 // The same tile with the FP32 instructions, for operands that the parts cannot hold: the LDS layouts and fragments of mfma_kernel.h, two
 // stages of 32 values of k, the next K-tile in registers, no pinned schedule.  la, lb: the operands' loaders, prepared; `aim_tile` aims at
-// K-tile t (zeros past the end; tile 0 is the one that may lack values of k).  multiplies: the same for a whole wavefront; false: it
-// only loads.
+// K-tile t (zeros past the end; tile 0 is the one that may lack values of k).
 template <int BM, int BN, int NT, int FM, int FN, bool A_KCONTIG, bool B_KCONTIG, typename LoadA, typename LoadB, typename Aim>
 __device__ __forceinline__ void exact_tile(floatx16 (&acc)[FN][FM], LoadA &la, LoadB &lb, char *lds, int ktiles, int first_ks, int wm0, int wn0,
-                                           int thread, Aim &&aim_tile, bool multiplies = true)
+                                           int thread, Aim &&aim_tile)
 {
     constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
     const int lane = thread % 64;
@@ -225,7 +225,7 @@ __device__ __forceinline__ void exact_tile(floatx16 (&acc)[FN][FM], LoadA &la, L
         load(t + 1);
         __syncthreads();                               // (the other stage is written only behind the next one)
 #pragma unroll 1
-        for (int step = multiplies ? 0 : 4; step < 4; ++step) {
+        for (int step = 0; step < 4; ++step) {
             u32x4 a[FM], b[FN];
             static_for<FM>([&](auto F) { a[decltype(F)::value] = LoadA::read_floats(stage, lane, wm0, decltype(F)::value, step); });
             static_for<FN>([&](auto F) { b[decltype(F)::value] = LoadB::read_floats(stage + A_BYTES, lane, wn0, decltype(F)::value, step); });
@@ -318,8 +318,8 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
 
     // staging work of a K-tile: per piece the split of its two halves and its stores with the reload behind them
     constexpr int PIECES = LoadA::LOADS + LoadB::LOADS, EVENTS = 3 * PIECES;
-    // one K-step: six products of SLOTS MFMAs; the barrier of a K-tile sits in front of the fifth product of its last step
-    constexpr int STEP_SLOTS = 6 * SLOTS, BARRIER_SLOT = STEP_SLOTS + 4 * SLOTS;
+    // one K-step: eight products of SLOTS MFMAs; the barrier of a K-tile sits in front of the seventh product of its last step
+    constexpr int STEP_SLOTS = 8 * SLOTS, BARRIER_SLOT = STEP_SLOTS + 6 * SLOTS;
     auto event = [&](auto E, auto SET, int stage) __attribute__((always_inline)) {
         constexpr int e = decltype(E)::value, set = decltype(SET)::value;
         constexpr int piece = e / 3, w = e % 3;
@@ -350,12 +350,14 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
                 }
                 if constexpr (product == 0) mma_bf16(small[j][i], b1[s][j], a3[i]);
                 else if constexpr (product == 1) mma_bf16(small[j][i], b3[j], a1[s][i]);
-                else if constexpr (product == 2) mma_bf16(small[j][i], b2[j], a2[i]);
-                else if constexpr (product == 3) mma_bf16(small[j][i], b2[j], a1[s][i]);
-                else if constexpr (product == 4) mma_bf16(small[j][i], b1[s][j], a2[i]);
+                else if constexpr (product == 2) mma_bf16(small[j][i], b2[j], a3[i]);
+                else if constexpr (product == 3) mma_bf16(small[j][i], b3[j], a2[i]);
+                else if constexpr (product == 4) mma_bf16(small[j][i], b2[j], a2[i]);
+                else if constexpr (product == 5) mma_bf16(small[j][i], b2[j], a1[s][i]);
+                else if constexpr (product == 6) mma_bf16(small[j][i], b1[s][j], a2[i]);
                 else mma_bf16(acc[j][i], b1[s][j], a1[s][i]);
-                // reads for the next K-step: leading parts during the first two products, third parts during the next
-                // two (behind the barrier both during the fifth), second parts during the last
+                // reads for the next K-step: leading parts during the first four products, third parts during the fifth and sixth
+                // (behind the barrier both during the seventh), second parts during the last
                 auto spread = [&](auto slot0, auto slots, auto &&read) __attribute__((always_inline)) {
                     constexpr int z = g - decltype(slot0)::value, n = decltype(slots)::value;
                     if constexpr (z >= 0 && z < n)
@@ -365,14 +367,17 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
                 };
                 using N1 = std::integral_constant<int, SLOTS>;
                 using N2 = std::integral_constant<int, 2 * SLOTS>;
+                using N4 = std::integral_constant<int, 4 * SLOTS>;
+                using Seventh = std::integral_constant<int, 6 * SLOTS>;
+                using Last = std::integral_constant<int, 7 * SLOTS>;
                 if constexpr (s == 0) {
-                    spread(C0{}, N2{}, [&](auto O) { read_first(C1{}, C1{}, cur, O); });
-                    spread(std::integral_constant<int, 2 * SLOTS>{}, N2{}, [&](auto O) { read_third(C1{}, cur, O); });
-                    spread(std::integral_constant<int, 5 * SLOTS>{}, N1{}, [&](auto O) { read_second(C1{}, cur, O); });
+                    spread(C0{}, N4{}, [&](auto O) { read_first(C1{}, C1{}, cur, O); });
+                    spread(N4{}, N2{}, [&](auto O) { read_third(C1{}, cur, O); });
+                    spread(Last{}, N1{}, [&](auto O) { read_second(C1{}, cur, O); });
                 } else {
-                    spread(std::integral_constant<int, 4 * SLOTS>{}, N1{}, [&](auto O) { read_first(C0{}, C0{}, nxt, O); });
-                    spread(std::integral_constant<int, 4 * SLOTS>{}, N1{}, [&](auto O) { read_third(C0{}, nxt, O); });
-                    spread(std::integral_constant<int, 5 * SLOTS>{}, N1{}, [&](auto O) { read_second(C0{}, nxt, O); });
+                    spread(Seventh{}, N1{}, [&](auto O) { read_first(C0{}, C0{}, nxt, O); });
+                    spread(Seventh{}, N1{}, [&](auto O) { read_third(C0{}, nxt, O); });
+                    spread(Last{}, N1{}, [&](auto O) { read_second(C0{}, nxt, O); });
                 }
                 if constexpr (tile_slot < BARRIER_SLOT) {
                     static_for<share_begin(tile_slot + 1, EVENTS, BARRIER_SLOT) - share_begin(tile_slot, EVENTS, BARRIER_SLOT)>([&](auto R) {
@@ -461,318 +466,6 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
                                                              [&](int t_, __amdgpu_buffer_rsrc_t &a, __amdgpu_buffer_rsrc_t &b) { aim_tile(t_); a = aim_a; b = aim_b; });
     }
     tile_epilogue<float, 32, FM, FN, WTM, WTN, EDGE>(acc, args, lds, m0, n0, last_wm, last_wn, last_wave, thread % 64);
-}
-
-// 64 x 64 tiles of grids that leave a compute unit one or two of them: no barrier in the K loop.  Each of the eight
-// wavefronts holds the whole tile and takes every eighth slice of 16 values of k, so that no element is loaded or split
-// twice; a slice goes from memory through registers to the wavefront's own part of LDS (coalesced 16-byte pieces in, MFMA operand layout
-// out: operands along k loaded in that layout directly cost a clock per lane), is read a fragment at a time, split, and multiplied while the next
-// one is split.  The eight sums meet in LDS at the end.  (The tile cut among wavefronts that share their fragments
-// reads 9 fragments from LDS for 6 MFMAs, this one 12 for 24.)  One set of accumulators: an eighth of the sum each, and the products
-// of a slice added smallest first, still round less than FP32 instructions do.
-template <bool KCONTIG, bool EDGE> struct SliceLoader {
-    static constexpr int PIECES = 4;                   // 16-byte pieces per lane and slice (64 rows x 16 values of k)
-    static constexpr int BYTES = 4096;
-    using Set = u32x4[PIECES];
-    Set regs;
-    uint32_t goff[PIECES];
-    uint32_t keep[4];              // EDGE, along the rows: all ones where element e of this lane's pieces is a row that exists
-    int slot[2], at[2];            // LDS: where pieces 0, 1 | 2, 3 go, where the values of fragment 0 | 1 are
-    u32x4 raw[2][2];               // fragments read back, two at a time: 8 values each
-    bool tiny;                     // see split_pair
-
-    __device__ __forceinline__ void prepare(int64_t ld, int rows, int lane, int offset)
-    {
-        tiny = false;
-        static_for<PIECES>([&](auto Qc) {
-            constexpr int q = decltype(Qc)::value;
-            if constexpr (KCONTIG) goff[q] = static_cast<uint32_t>(((16 * q + lane / 4) * ld + lane % 4 * 4) * 4);
-            else goff[q] = !EDGE || lane % 16 * 4 < rows ? static_cast<uint32_t>(((4 * q + lane / 16) * ld + lane % 16 * 4) * 4) : 0x80000000u;
-        });
-#pragma unroll
-        for (int e = 0; e < 4; ++e) keep[e] = !EDGE || KCONTIG || lane % 16 * 4 + e < rows ? ~0u : 0u;
-        if constexpr (KCONTIG) {
-            slot[0] = slot[1] = offset + ldsmap::split_row_slot(lane / 4, lane % 4);
-            at[0] = offset + ldsmap::split_row_slot(lane % 32, 2 * (lane / 32));
-            at[1] = at[0] ^ 16;                        // (the other half of the lane's 8 values)
-        } else {
-            slot[0] = offset + ldsmap::slice_line_slot(lane / 16, lane % 16);
-            slot[1] = offset + ldsmap::slice_line_slot(8 + lane / 16, lane % 16) - 2048;
-            at[0] = offset + ldsmap::slice_line_slot(8 * (lane / 32), lane % 32 / 4) + lane % 4 * 4;
-            at[1] = offset + ldsmap::slice_line_slot(8 * (lane / 32), 8 + lane % 32 / 4) + lane % 4 * 4;
-        }
-    }
-    // ks <= 16 values of k from l0 on (ks <= 0: zeros, no access); the descriptor ends with the last element that exists
-    __device__ __forceinline__ static __amdgpu_buffer_rsrc_t aim(const float *X, int64_t ld, int64_t r0, int64_t l0, int rows, int ks)
-    {
-        const float *base = KCONTIG ? X + r0 * ld + l0 : X + r0 + l0 * ld;
-        if (ks > 16) ks = 16;
-        const int64_t extent = KCONTIG ? (rows - 1) * ld + ks : (ks - 1) * ld + rows;
-        const int range = static_cast<int>(extent * 4) & -static_cast<int>(ks > 0);      // (no branch: it would cut the K loop's schedule)
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(base), 0, range, 0x00020000);
-    }
-    template <int Q> __device__ __forceinline__ void load(Set &set, __amdgpu_buffer_rsrc_t rsrc) const
-    {
-        set[Q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[Q], 0, 0);
-    }
-    // operand along k: values beyond the sum are the next row's
-    __device__ __forceinline__ void cut(int ks, int lane)
-    {
-        if constexpr (KCONTIG)
-            static_for<16>([&](auto X) {
-                constexpr int q = decltype(X)::value / 4, e = decltype(X)::value % 4;
-                regs[q][e] = lane % 4 * 4 + e < ks ? regs[q][e] : 0u;
-            });
-    }
-    template <int Q> __device__ __forceinline__ void store(const Set &set, char *buffer) const
-    {
-        u32x4 v = set[Q];
-        if constexpr (EDGE && !KCONTIG) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] &= keep[e];
-        }
-        *reinterpret_cast<u32x4 *>(buffer + slot[Q / 2] + Q * 1024) = v;
-    }
-    // fragment F of the slice in `buffer` -> raw[F]
-    template <int F> __device__ __forceinline__ void read(const char *buffer)
-    {
-        if constexpr (KCONTIG) {
-            raw[F][0] = *reinterpret_cast<const u32x4 *>(buffer + at[0] + F * 2048);
-            raw[F][1] = *reinterpret_cast<const u32x4 *>(buffer + at[1] + F * 2048);
-        } else {
-            static_for<8>([&](auto E) {
-                constexpr int e = decltype(E)::value;
-                raw[F][e / 4][e % 4] = *reinterpret_cast<const uint32_t *>(buffer + at[F] + e * 256);
-            });
-        }
-    }
-    // values 2 PAIR and 2 PAIR + 1 of fragment F -> their three parts
-    template <int F, int PAIR> __device__ __forceinline__ void split(u32x4 (&part)[3])
-    {
-        const uint32_t x = raw[F][PAIR / 2][2 * (PAIR % 2)], y = raw[F][PAIR / 2][2 * (PAIR % 2) + 1];
-        const SplitPair s = split_pair(__builtin_bit_cast(float, x), __builtin_bit_cast(float, y), tiny);
-        part[0][PAIR] = s.part[0];
-        part[1][PAIR] = s.part[1];
-        part[2][PAIR] = s.part[2];
-    }
-};
-
-template <bool A_KCONTIG, bool B_KCONTIG, bool EDGE>
-__global__ __launch_bounds__(512, 2) void mfma_split_slices_kernel(const MfmaArgs args)
-{
-    constexpr int BM = 64, BN = 64, WAVES = 8, NT = 512, SLICE = 16;
-    constexpr int ROWB = BM * 4 + 16, REGION = BN * ROWB;      // one wavefront's sums: [column][row] floats
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-
-    if constexpr (EDGE) {                              // grid layers behind the K slices: the fringe rows and columns (fringe.h)
-        if (static_cast<int>(blockIdx.z) >= args.slices) {
-            const int g = (static_cast<int>(blockIdx.z) - args.slices) * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
-            if (g < args.fringe_groups * args.slices)
-                fringe_group<NT, A_KCONTIG, B_KCONTIG>(args, g % args.fringe_groups, g / args.fringe_groups, lds);
-            return;
-        }
-    }
-    int tm, tn;
-    if (args.shape == 0) tile_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, tm, tn);
-    else tile_coords_balanced(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, args.reversed != 0, args.shape == MG_SHAPE_C_UPPER, tm, tn);
-    const int64_t m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
-    int kb = blockIdx.z * args.k_per_split;
-    int ke = (kb + args.k_per_split < args.k) ? kb + args.k_per_split : args.k;
-    if (!narrow_to_shape<BM, BN, 32>(args.shape, m0, n0, kb, ke)) return;
-
-    const float *__restrict__ A = static_cast<const float *>(args.A);
-    const float *__restrict__ B = static_cast<const float *>(args.B);
-    const int rows_a = static_cast<int>(args.m_main - m0 < BM ? args.m_main - m0 : BM);
-    const int rows_b = static_cast<int>(args.n_main - n0 < BN ? args.n_main - n0 : BN);
-    const int lane = threadIdx.x % 64, wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-
-    floatx16 acc[2][2];
-    static_for<4>([&](auto X) { acc[decltype(X)::value / 2][decltype(X)::value % 2] = floatx16{}; });
-    SliceLoader<A_KCONTIG, EDGE> la;
-    SliceLoader<B_KCONTIG, EDGE> lb;
-    constexpr int BUFFER = SliceLoader<A_KCONTIG, EDGE>::BYTES + SliceLoader<B_KCONTIG, EDGE>::BYTES;     // one slice
-    static_assert(2 * BUFFER * WAVES <= WAVES * REGION, "two slices per wavefront");
-    la.prepare(args.lda, rows_a, lane, wave * 2 * BUFFER);
-    lb.prepare(args.ldb, rows_b, lane, wave * 2 * BUFFER + SliceLoader<A_KCONTIG, EDGE>::BYTES);
-
-    // rounds of eight slices, the last (which may lack values of k, or whole slices) first
-    const int rounds = (ke - kb + WAVES * SLICE - 1) / (WAVES * SLICE);
-    __amdgpu_buffer_rsrc_t aim_a, aim_b;
-    auto aim_round = [&](int u) __attribute__((always_inline)) {
-        const int l0 = kb + ((rounds - 1 - u) * WAVES + wave) * SLICE, ks = u < rounds ? ke - l0 : 0;
-        aim_a = la.aim(A, args.lda, m0, l0, rows_a, ks);
-        aim_b = lb.aim(B, args.ldb, n0, l0, rows_b, ks);
-    };
-    u32x4 a[2][2][3], b[2][2][3];                      // buffer, fragment, part
-    // fragments in the order a0 b0 a1 b1: F of the slice in LDS buffer BUF -> raw registers; four pairs each -> parts
-    auto read = [&](auto F, auto BUF) __attribute__((always_inline)) {
-        constexpr int f = decltype(F)::value;
-        const char *buffer = lds + decltype(BUF)::value * BUFFER;
-        if constexpr (f % 2 == 0) la.template read<f / 2>(buffer);
-        else lb.template read<f / 2>(buffer);
-    };
-    auto split = [&](auto E, auto BUF) __attribute__((always_inline)) {
-        constexpr int e = decltype(E)::value, f = e / 8, pair = e % 4, buf = decltype(BUF)::value;
-        if constexpr (e / 4 % 2 == 0) la.template split<f, pair>(a[buf][f]);
-        else lb.template split<f, pair>(b[buf][f]);
-    };
-    // piece Q (0 .. 7) of a staged slice -> LDS buffer BUF, and its registers loaded again
-    auto store = [&](auto Q, auto BUF) __attribute__((always_inline)) {
-        constexpr int q = decltype(Q)::value / 2;
-        char *buffer = lds + decltype(BUF)::value * BUFFER;
-        if constexpr (decltype(Q)::value % 2 == 0) { la.template store<q>(la.regs, buffer); la.template load<q>(la.regs, aim_a); }
-        else { lb.template store<q>(lb.regs, buffer); lb.template load<q>(lb.regs, aim_b); }
-    };
-    // Slice u from fragment buffer BUF, the smallest products first.  MORE: meanwhile slice u + 1 is split into the other buffer (its first
-    // fragment has been read, the others are read six MFMAs ahead), slice u + 2 goes to LDS, u + 3 is asked for.
-    auto multiply = [&](auto BUF, auto MORE) __attribute__((always_inline)) {
-        constexpr int buf = decltype(BUF)::value;
-        using Mine = std::integral_constant<int, buf>;
-        using Other = std::integral_constant<int, 1 - buf>;
-        constexpr int pb[6] = {0, 2, 1, 1, 0, 0}, pa[6] = {2, 0, 1, 0, 1, 0};
-        static_for<24>([&](auto X) __attribute__((always_inline)) {
-            constexpr int x = decltype(X)::value, p = x / 4, i = x % 2, j = x / 2 % 2;
-            mma_bf16(acc[j][i], b[buf][j][pb[p]], a[buf][i][pa[p]]);
-            if constexpr (decltype(MORE)::value) {
-                if constexpr (x % 6 == 0 && x < 18) read(std::integral_constant<int, x / 6 + 1>{}, Other{});
-                if constexpr (x == 18) read(std::integral_constant<int, 0>{}, Mine{});
-                if constexpr (x % 2 == 0 && x < 16) store(std::integral_constant<int, x / 2>{}, Mine{});
-                static_for<share_begin(x + 1, 16, 24) - share_begin(x, 16, 24)>([&](auto R) __attribute__((always_inline)) {
-                    split(std::integral_constant<int, share_begin(x, 16, 24) + decltype(R)::value>{}, Other{});
-                });
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        });
-    };
-    // eight columns of C per wavefront, four at a time: four consecutive rows of a column per lane; the old values of whole pieces
-    // are asked for before the sum
-    const int row = lane % 16 * 4, col = wave * 8 + lane / 16;
-    const bool held = args.beta != 0.f && args.partial == nullptr && args.mask == 0;
-    floatx4 old[2];
-    auto piece_left = [&](int pass) __attribute__((always_inline)) {
-        const int64_t left = args.m_main - m0 - row;
-        return n0 + col + 4 * pass >= args.n_main || left <= 0 ? 0 : (left < 4 ? static_cast<int>(left) : 4);
-    };
-    static_for<2>([&](auto P) {
-        constexpr int pass = decltype(P)::value;
-        old[pass] = floatx4{};
-        if (held && piece_left(pass) == 4) {
-            const auto v = *reinterpret_cast<const Pack<float, 4> *>(static_cast<const float *>(args.C) + m0 + row + (n0 + col + 4 * pass) * args.ldc);
-            old[pass] = floatx4{v.v[0], v.v[1], v.v[2], v.v[3]};
-        }
-    });
-    using C0 = std::integral_constant<int, 0>;
-    using C1 = std::integral_constant<int, 1>;
-    if (rounds > 0) {
-        typename SliceLoader<A_KCONTIG, EDGE>::Set second_a;
-        typename SliceLoader<B_KCONTIG, EDGE>::Set second_b;
-        aim_round(0);
-        static_for<4>([&](auto Q) { la.template load<decltype(Q)::value>(la.regs, aim_a); lb.template load<decltype(Q)::value>(lb.regs, aim_b); });
-        aim_round(1);
-        static_for<4>([&](auto Q) { la.template load<decltype(Q)::value>(second_a, aim_a); lb.template load<decltype(Q)::value>(second_b, aim_b); });
-        aim_round(2);
-        const int ks = ke - (kb + ((rounds - 1) * WAVES + wave) * SLICE);
-        la.cut(ks, lane);
-        lb.cut(ks, lane);
-        static_for<8>([&](auto Q) { store(Q, C0{}); });
-        static_for<4>([&](auto F) { read(F, C0{}); });
-        static_for<16>([&](auto E) { split(E, C0{}); });
-        static_for<4>([&](auto Q) { la.template store<decltype(Q)::value>(second_a, lds + BUFFER); lb.template store<decltype(Q)::value>(second_b, lds + BUFFER); });
-        read(C0{}, C1{});
-        int u = 0;
-        for (; u + 2 < rounds; u += 2) {
-            aim_round(u + 3);
-            multiply(C0{}, std::true_type{});
-            aim_round(u + 4);
-            multiply(C1{}, std::true_type{});
-        }
-        if (u + 1 < rounds) {
-            aim_round(rounds);
-            multiply(C0{}, std::true_type{});
-            multiply(C1{}, std::false_type{});
-        } else {
-            multiply(C0{}, std::false_type{});
-        }
-    }
-    __syncthreads();                                   // the sums take the place of the slices
-
-    char *mine = lds + wave * REGION;
-    auto put = [&](char *region, const floatx16 &v, int row, int col) __attribute__((always_inline)) {
-        static_for<4>([&](auto Q) {
-            constexpr int q = decltype(Q)::value;
-            *reinterpret_cast<floatx4 *>(region + (col + lane % 32) * ROWB + (row + 8 * q + 4 * (lane / 32)) * 4) =
-                floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-        });
-    };
-    static_for<4>([&](auto X) {
-        constexpr int i = decltype(X)::value % 2, j = decltype(X)::value / 2;
-        put(mine, acc[j][i], 32 * i, 32 * j);
-    });
-    __syncthreads();
-    floatx4 sum[2];
-    float watch = 0.f;                                 // becomes NaN when a sum is Inf or NaN
-    auto gather = [&](int regions) __attribute__((always_inline)) {
-        static_for<2>([&](auto P) {
-            constexpr int pass = decltype(P)::value;
-            const char *p = lds + (col + 4 * pass) * ROWB + row * 4;
-            sum[pass] = *reinterpret_cast<const floatx4 *>(p);
-            for (int w = 1; w < regions; ++w) sum[pass] += *reinterpret_cast<const floatx4 *>(p + w * REGION);
-        });
-    };
-    gather(WAVES);
-    static_for<8>([&](auto E) { watch = fmaf(sum[decltype(E)::value / 4][decltype(E)::value % 4], 0.f, watch); });
-    if (__syncthreads_or(la.tiny || lb.tiny || watch != 0.f)) {
-        floatx16 exact[1][1];
-        SplitLoader<BM, NT, A_KCONTIG, EDGE, 1> ea;
-        SplitLoader<BN, NT, B_KCONTIG, EDGE, 1> eb;
-        ea.prepare(args.lda, rows_a, threadIdx.x);
-        eb.prepare(args.ldb, rows_b, threadIdx.x);
-        const int ktiles = (ke - kb + 31) / 32, whole = (ktiles - 1) * 32;
-        exact_tile<BM, BN, NT, 1, 1, A_KCONTIG, B_KCONTIG>(exact, ea, eb, lds, ktiles, ke - kb - whole, wave % 2 * 32, wave / 2 % 2 * 32, threadIdx.x,
-                                                           [&](int t, __amdgpu_buffer_rsrc_t &x, __amdgpu_buffer_rsrc_t &y) {
-                                                               const int l0 = t == 0 ? kb + whole : kb + (t - 1) * 32, ks = t < ktiles ? ke - l0 : 0;
-                                                               x = ea.aim(A, args.lda, m0, l0, rows_a, ks);
-                                                               y = eb.aim(B, args.ldb, n0, l0, rows_b, ks);
-                                                           }, wave < 4);
-        if (wave < 4) put(lds, exact[0][0], wave % 2 * 32, wave / 2 * 32);
-        __syncthreads();
-        gather(1);
-    }
-    static_for<2>([&](auto P) {
-        constexpr int pass = decltype(P)::value;
-        const int64_t gm = m0 + row, gn = n0 + col + 4 * pass;
-        int first = 0, valid = piece_left(pass);
-        if (args.mask != 0) {                          // as tile_epilogue: the wanted triangle of C
-            const int64_t d = gn - gm;
-            if (args.shape == MG_SHAPE_C_LOWER) first = d > 0 ? (d < 4 ? static_cast<int>(d) : 4) : 0;
-            else valid = d + 1 < valid ? (d + 1 > 0 ? static_cast<int>(d + 1) : 0) : valid;
-        }
-        const bool raw = args.partial != nullptr;
-        float *p = raw ? args.partial + (static_cast<int64_t>(blockIdx.z) * args.n + gn) * args.m + gm : static_cast<float *>(args.C) + gm + gn * args.ldc;
-        const float alpha = raw ? 1.f : args.alpha, beta = raw ? 0.f : args.beta;
-        if (first == 0 && valid == 4) {
-            Pack<float, 4> o;
-            if (beta != 0.f) {
-                if (!held) {
-                    const Pack<float, 4> c = *reinterpret_cast<const Pack<float, 4> *>(p);
-                    old[pass] = floatx4{c.v[0], c.v[1], c.v[2], c.v[3]};
-                }
-                static_for<4>([&](auto E) { o.v[decltype(E)::value] = fmaf(beta, old[pass][decltype(E)::value], alpha * sum[pass][decltype(E)::value]); });
-            } else {
-                static_for<4>([&](auto E) { o.v[decltype(E)::value] = alpha * sum[pass][decltype(E)::value]; });
-            }
-            *reinterpret_cast<Pack<float, 4> *>(p) = o;
-        } else {
-            static_for<4>([&](auto E) {
-                constexpr int e = decltype(E)::value;
-                if (e >= first && e < valid) {
-                    float o = alpha * sum[pass][e];
-                    if (beta != 0.f) o = fmaf(beta, p[e], o);
-                    p[e] = o;
-                }
-            });
-        }
-    });
 }
 
 }  // namespace mg

@@ -295,18 +295,22 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                {"smfma_128x64x32_w2x2", 128, 64, 32, 0.582f, 0.54f, 3},
                                                {"smfma_64x64x32_w2x2", 64, 64, 32, 0.571f, 0.565f, 5},
                                                {"ssplit_256x128x32_w4x2", 256, 128, 32, 0.f, 0.f, 1},
-                                               {"ssplit_128x128x32_w2x4", 128, 128, 32, 0.f, 0.f, 1},
-                                               {"ssplit_slices_64x64", 64, 64, 32, 0.f, 0.f, 1}};
+                                               {"ssplit_128x128x32_w2x4", 128, 128, 32, 0.f, 0.f, 1}};
         constexpr int kSplit = 5;           // index of the first kernel on the bf16 matrix pipes
-        // Their time in us: turns of one tile per compute unit, each a fixed part and, per K-tile of 32, a part that grows with the
-        // share of the chip that is busy (the power limit); and the traffic of C per MB.
+        // Their time in us: turns of one tile per compute unit, each a fixed part and, per K-tile of 32, a part that grows with the square of
+        // the share of the chip that is busy (the power limit); and the traffic of C per MB.  Fitted to both tiles with 1 to 8 slices on 13
+        // sizes in two orders, one turn and several: 256 x 128 tiles take 2.0 us per K-tile on up to 128 compute units, 2.5 on 224, 2.7 on
+        // all (512^3 40.2 us, 1000^3 73.0, 2048^3 141, (1673, 4032, 554) 57, (8192, 1024, 512) 56, 4096^3 735); 128 x 128 tiles 1.07 on
+        // 64, 1.12 on 144, 1.35 on three turns of 192, 1.48 on all (512^3 23.5, 1000^3 40.8, 1500^3 60, 3000^3 405, 2048^3 104, 4096^3 788).
+        // These are for both operands along k; an operand along its rows takes two transposing reads per fragment (128 x 128 tiles,
+        // kk / mk / mn / kn: (4096, 256, 4096) 149 / 162 / 164 / 158, (3072, 3072, 1536) 217 / 227 / 227 / 223; 256 x 128 250 / 252 / 258 / 253)
         struct SplitCost {
             double turn, ktile, ktile_load, c_mb;
         };
-        static const SplitCost split_costs[3] = {{7.9, 1.58, 0.49, 0.18}, {5.0, 1.01, 0.25, 0.16}, {4.4, 0.30, 0.09, 0.15}};
+        static const SplitCost split_costs[2] = {{8.2, 1.95, 0.75, 0.18}, {5.8, 1.06, 0.41, 0.16}};
         static const double f32_round_cost[5] = {0.0, 0.0, 1.0e6, 2.0e6, 1.8e6};
         const TileChoice *tiles = f32 ? f32_tiles : f16_tiles;
-        const int count = f32 ? 8 : 9;
+        const int count = f32 ? 7 : 9;
         const int smallest = f32 ? 4 : 7;
         bool tried[9] = {false, false, false, false, false, false, false, false, false};
         // work-groups that do something: of a product whose C is a triangle, the tiles that touch it (as the kernels skip the others)
@@ -357,12 +361,17 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             double time;
             if (f32 && i >= kSplit) {
                 const SplitCost &cost = split_costs[i - kSplit];
-                double turns = static_cast<double>(ceil_div(blocks, kComputeUnits));
-                if (narrowed) turns = turns > 1.0 ? std::max(1.0, 0.55 * static_cast<double>(blocks) / kComputeUnits + 0.2) : 1.0;
-                const double load = static_cast<double>(blocks) / (turns * kComputeUnits);
-                const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, tiles[i].bk), slices));
-                time = 1.0e6 * (turns * (cost.turn + ktiles * (cost.ktile + cost.ktile_load * load)) +
-                                cost.c_mb * 4.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0));
+                const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, tiles[i].bk), slices)) * (p.a_trans && !p.b_trans ? 1.0 : 1.05);
+                auto turn = [&](double load) { return cost.turn + ktiles * (cost.ktile + cost.ktile_load * load * load); };
+                const double turns = static_cast<double>(blocks) / kComputeUnits;
+                double us;
+                if (narrowed) {
+                    // (sums of half the length on average, the longest first; TRMM 3000 on 128 x 128 tiles 208 us, 4096 421, 8192 2970)
+                    us = turns > 1.0 ? std::max(1.0, 0.5 * turns + 0.2) * turn(1.0) : turn(turns);
+                } else {
+                    us = floor(turns) * turn(1.0) + (turns > floor(turns) ? turn(turns - floor(turns)) : 0.0);
+                }
+                time = 1.0e6 * (us + cost.c_mb * 4.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0));
             } else if (f32) {
                 // work-groups take turns on a compute unit: ceil(blocks / 256) turns of one tile each, whether the
                 // compute units hold them all at once or are refilled as work-groups retire (squares of 1024 to 6144
@@ -430,7 +439,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             time += ends;
             // split-K: the partial sums are written and read back (8 bytes per slice and output at ~4 TB/s) by
             // a second launch (2.5 us; 4 us behind the bounds-checked FP32 flavour, fitted with the rates above)
-            if (slices > 1) time += 1.0e6 * ((f32 && i >= kSplit ? 6.0 : (f32 && ragged ? 4.0 : 2.5)) + (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) / 4.0e6);
+            // (FP32: half of that traffic where only a triangle is written; SYRK 4096 on 256 x 128 tiles in 4 slices 494 us, 641 unsliced, 555 on
+            // the FP32 pipes)
+            const double sums = (4.0 * slices + 8.0) * static_cast<double>(p.m) * static_cast<double>(p.n) * (f32 && triangle ? 0.5 : 1.0);
+            if (slices > 1) time += 1.0e6 * ((f32 && i >= kSplit ? 6.0 : (f32 && ragged ? 4.0 : 2.5)) + sums / 4.0e6);
+            // (what a call takes beside its turns, in the constants of the others: 512^3 on 64 x 64 tiles 10.9 us, 9.1 without, 1024^3 19.7, 16.5)
             if (f32 && i < kSplit) time += 1.0e6;
             return time;
         };
@@ -443,12 +456,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         int free_slices = 0;
         const bool in_place = p.clip_m != 0 || p.clip_n != 0;
         for (int i = 0; i < count; ++i) {
-            if (f32 && i >= kSplit && p.k < 4) continue;             // (a sum of one or two products: rounded once more than on the FP32 pipes)
+            // (short sums are the traffic of C, which the small tiles overlap better: (3870, 5248, 64) 45.7 / 40.0 us on the 64 x 64 tile of the
+            // FP32 pipes, (2303, 2721, 64) 18.1 / 17.7, (6000, 700, 129) 20.7 / 21.5, (4096, 4096, 256) 63.4 / 73.4)
+            if (f32 && i >= kSplit && p.k < 128) continue;
             // FP32 work-groups take turns on a compute unit, so unequal tiles (skipped ones, narrowed K ranges) only pay off where a compute
             // unit gets many of them: of the kernels on the FP32 pipes the smallest (SYRK 4096: 974 / 923 / 695 / 618 us from the 256 x 256
-            // to the 64 x 64 tile, TRMM 950 / 614 / 596 / 541).  Those on the bf16 pipes are ranked beside it (us, FP32 pipes 64 x 64 / 256 x 128 /
-            // 128 x 128 / 64 x 64 slices: SYRK 1146 x 1056 38.5 / 68 / 46 / 21, 2048 118 / 121 / 77 / 88, 3072 265 / 183 / 236 / 221, 4096 560 /
-            // 519 / 479 / 523; TRMM 1000 31 / 71 / 49 / 26, 3000 244 / 201 / 189 / 266, 4096 546 / 376 / 379 / 527)
+            // to the 64 x 64 tile, TRMM 950 / 614 / 596 / 541).  Those on the bf16 pipes are ranked beside it (us, unsliced, FP32 pipes 64 x 64 /
+            // bf16 pipes 256 x 128 / 128 x 128: SYRK 1146 x 1056 39 / 82 / 51, 2048 120 / 147 / 86, 3072 255 / 223 / 268, 4096 555 / 641 / 558,
+            // 8192 4140 (128 x 64: 4102) / 3620 / 3757; TRMM 1000 31 / 82 / 53, 3000 241 / 239 / 208, 4096 527 / 450 / 421, 8192 3914 / 2741 / 2970)
             if (f32 && p.shape != MG_SHAPE_GENERAL && i < kSplit - 1) continue;
             if (in_place && i > 2 && i != kDeep) continue;           // (no other tile has the flavour, and it is not sliced)
             // FP32 with a short K is bound by the traffic of C, which the large tiles overlap worst (one epilogue per
@@ -485,7 +500,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 if (sl < 1 || (o > 0 && sl == 1)) continue;
                 // (a fringe work-group takes a compute unit of its own beside these kernels' tiles: only behind two turns of tiles and more;
                 // (513, 515, 2000) 19.4 / 24.7 us, (4097, 129, 4095) 51 / 63, 1025^3 27.6 / 31.4, but 4097^3 1021 / 693)
-                if (f32 && i >= kSplit && (p.fringe_m != 0 || p.fringe_n != 0) && (i == kSplit + 2 || sl > 1 || blocks <= kComputeUnits)) continue;
+                if (f32 && i >= kSplit && (p.fringe_m != 0 || p.fringe_n != 0) && (sl > 1 || blocks <= kComputeUnits)) continue;
                 // (an unsliced triangular operand runs below its estimate, most of its sums being shorter: TRMM FP16 3000 x 300 33 us, 38 in slices)
                 const double time = estimate(i, sl) * (narrowed && sl > 1 ? 1.25 : 1.0);
                 if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
