@@ -9,11 +9,12 @@
 // sums see one rounding per four values of k (v_mfma_f32_32x32x16_bf16) where v_mfma_f32_32x32x2_f32 rounds for each.  Eight bf16
 // instructions of 32 cycles take the place of eight FP32 ones of 64 (16 values of k).
 //
-// The sums differ from FP32 arithmetic where a part cannot hold its share: elements below 2^-110 (but not 0), whose last bits lie
-// below bf16's smallest value, and elements or products near the end of the range, which leave Inf or NaN in an
-// accumulator.  The kernel watches for both (the rest that the third part rounds is 0 or at least 2^(e - 23) for an element of exponent e and at most
-// 2^(e - 17): subnormal whenever bits are lost; a test of the sums) and a work-group that meets either computes its
-// tile again with the FP32 instructions.
+// Elements are multiplied by 2^20 on their way into the parts, so that the last bit of any FP32 value, 2^-149, lies above bf16's
+// smallest one, 2^-133: no part loses bits, subnormal elements included.  (2^16 would do for that, but the pipes align products of subnormal
+// factors by their exponents: elements around 2^-140 0.62 units in the last place.)  The sums are 2^40 times too large until the end.  What they
+// cannot hold, elements from 2^107 and sums from 2^88 on, Inf and NaN, leaves Inf or NaN in a rest or an accumulator: a work-group that finds
+// one computes its tile again with the FP32 instructions.  (While elements were taken as they are, one below 2^-110 in a tile's operands cost
+// it the second computation: 4096^3 of values around 1e-36 1219 us, now 749, 2048^3 216, now 128; values near one 738 -> 752 us, 106 -> 108.)
 //
 // Structure: global -> registers -> (split) -> LDS, two LDS stages of 32 values of k, DEPTH K-tiles in flight in staging
 // registers; one barrier per K-tile; issue order pinned slot by slot, one MFMA per slot.
@@ -29,7 +30,8 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 
-// two elements -> their three parts, packed
+// two elements, scaled -> their three parts, packed
+constexpr float SPLIT_SCALE = 0x1p20f, SPLIT_UNSCALE = 0x1p-40f;
 struct SplitPair {
     uint32_t part[3];
 };
@@ -37,10 +39,13 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b)
 {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{a, b}), bf16x2));
 }
-// (tiny: set when bits may have been lost below bf16's range, the rest that the third part rounds being subnormal)
-__device__ __forceinline__ SplitPair split_pair(float a, float b, bool &tiny)
+// (beyond: set when an element is Inf, NaN or too large for its leading part.  Two instructions of the accumulators' test would do
+// instead, but without this one the compiler moves the splits out of their slots and spills 30 registers: 4096^3 800 us.)
+__device__ __forceinline__ SplitPair split_pair(float a, float b, bool &beyond)
 {
     SplitPair s;
+    a *= SPLIT_SCALE;
+    b *= SPLIT_SCALE;
     s.part[0] = bf16_pair(a, b);
     a -= __builtin_bit_cast(float, s.part[0] << 16);
     b -= __builtin_bit_cast(float, s.part[0] & 0xffff0000u);
@@ -48,8 +53,8 @@ __device__ __forceinline__ SplitPair split_pair(float a, float b, bool &tiny)
     a -= __builtin_bit_cast(float, s.part[1] << 16);
     b -= __builtin_bit_cast(float, s.part[1] & 0xffff0000u);
     s.part[2] = bf16_pair(a, b);
-    constexpr int SUBNORMAL = 0x90;
-    tiny |= __builtin_amdgcn_classf(a, SUBNORMAL) | __builtin_amdgcn_classf(b, SUBNORMAL);
+    constexpr int NOT_FINITE = 0x207;
+    beyond |= __builtin_amdgcn_classf(a, NOT_FINITE) | __builtin_amdgcn_classf(b, NOT_FINITE);
     return s;
 }
 // ---- one operand tile: ROWS rows x 32 values of k ---------------------------------------------------
@@ -68,12 +73,12 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
     uint32_t goff[LOADS];
     int slot[LOADS];                // LDS byte offset of each piece inside a plane
     bool keep[4];                   // EDGE, along the rows: element e of this lane's pieces is a row that exists
-    bool tiny;                      // see split_pair
+    bool beyond;                    // see split_pair
     SplitPair made[2];              // the piece being split
 
     __device__ __forceinline__ void prepare(int64_t ld, int rows, int t)
     {
-        tiny = false;
+        beyond = false;
         static_for<LOADS>([&](auto Qc) {
             constexpr int Q = decltype(Qc)::value;
             const int idx = t + Q * NT;
@@ -125,7 +130,7 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
             if constexpr (EDGE && !KCONTIG) bits = keep[2 * HALF + e] ? bits : 0u;
             v[e] = __builtin_bit_cast(float, bits);
         }
-        made[HALF] = split_pair(v[0], v[1], tiny);
+        made[HALF] = split_pair(v[0], v[1], beyond);
     }
     // the staged floats themselves -> LDS, and a fragment (4 values of k per lane of K-step `step`) of them, as in mfma_kernel.h
     __device__ __forceinline__ void store_floats(char *stage, int t) const
@@ -425,19 +430,19 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
         static_for<FRAGS>([&](auto O) { read_second(C0{}, 0, O); });
     }
     constexpr int UNROLL = DEPTH > 2 ? DEPTH : 2;
-    // Every 32 K-tiles the wavefronts agree whether one of them has met an element that the parts cannot hold: the rest of the
-    // sum would be for nothing.
+    // After 8 K-tiles of a long sum and every 32 the wavefronts agree whether one of them has met an element that the parts cannot hold:
+    // the rest of the sum would be for nothing (4096^3 of NaN 1596 -> 1084 us, FP32 pipes 916).
     bool given_up = false;
     int t = 0;
     for (;;) {
-        const int stop = t + 32 < ktiles ? t + 32 : ktiles;
+        const int next = t == 0 && ktiles > 32 ? 8 : t + 32, stop = next < ktiles ? next : ktiles;
         for (; t + UNROLL <= stop; t += UNROLL)
             static_for<UNROLL>([&](auto U) __attribute__((always_inline)) {
                 constexpr int u = decltype(U)::value;
                 tile_body(std::integral_constant<int, u % 2>{}, std::integral_constant<int, (u + 1) % DEPTH>{}, t + u);
             });
         if (t + UNROLL > ktiles) break;
-        given_up = __syncthreads_or(la.tiny || lb.tiny);
+        given_up = __syncthreads_or(la.beyond || lb.beyond);
         if (given_up) break;
     }
     if (!given_up)
@@ -446,13 +451,15 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void mfma_split_kernel(const MfmaAr
             if (t + u < ktiles) tile_body(std::integral_constant<int, u % 2>{}, std::integral_constant<int, (u + 1) % DEPTH>{}, t + u);
         });
 
+    static_for<SLOTS>([&](auto X) { acc[decltype(X)::value / FM][decltype(X)::value % FM] += small[decltype(X)::value / FM][decltype(X)::value % FM]; });
     float watch = 0.f;                                 // becomes NaN when a sum is Inf or NaN
-    static_for<SLOTS>([&](auto X) {
-        constexpr int i = decltype(X)::value % FM, j = decltype(X)::value / FM;
-        acc[j][i] += small[j][i];
-        static_for<16>([&](auto R) { watch = fmaf(acc[j][i][decltype(R)::value], 0.f, watch); });
-    });
-    const bool redo = given_up || la.tiny || lb.tiny || watch != 0.f;
+    if (!given_up)
+        static_for<16 * SLOTS>([&](auto X) {
+            constexpr int i = decltype(X)::value / 16 % FM, j = decltype(X)::value / 16 / FM;
+            watch = fmaf(acc[j][i][decltype(X)::value % 16], 0.f, watch);
+        });
+    const bool redo = given_up || watch != 0.f;        // (an element beyond the parts leaves Inf or NaN in its sums)
+    static_for<SLOTS>([&](auto X) { acc[decltype(X)::value / FM][decltype(X)::value % FM] *= SPLIT_UNSCALE; });
     // (what follows derives its lane numbers anew: kept through the K loop they would cost it registers)
     int thread = threadIdx.x;
     asm volatile("" : "+v"(thread));

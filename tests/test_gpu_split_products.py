@@ -53,12 +53,20 @@ def product(A, B, m, n, k, ta=T, tb=N):
 
 @pytest.mark.parametrize("ta,tb", [(T, N), (N, N), (N, T), (T, T)])
 @pytest.mark.parametrize("m,n,k", [(256, 128, 64), (131, 257, 75)])
-def test_a_sum_that_one_product_dominates(ta, tb, m, n, k):
-    """one element that is not zero in each row of op(A) (rows scaled and picked): products of 24-bit elements, nothing else"""
+@pytest.mark.parametrize("exponents", ["one", "all"])
+def test_a_sum_that_one_product_dominates(ta, tb, m, n, k, exponents):
+    """one element that is not zero in each row of op(A) (rows scaled and picked): products of 24-bit elements, nothing else; also with
+    elements of every exponent, subnormal ones among them, and products between 2^-100 and 2^87"""
     rng = np.random.default_rng(m + k)
+    at = rng.integers(0, k, m)
     A = np.zeros((m, k), np.float32)
-    A[np.arange(m), rng.integers(0, k, m)] = rng.uniform(1, 2, m)
+    A[np.arange(m), at] = rng.uniform(1, 2, m)
     B = rng.uniform(1, 2, (n, k)).astype(np.float32)
+    if exponents == "all":
+        ea = np.linspace(-149, 105, k).astype(int)
+        eb = np.clip(rng.integers(-100, 85, k) - ea, -120, 105)
+        A = np.ldexp(A, ea[None, :]).astype(np.float32)
+        B = np.ldexp(B, eb[None, :]).astype(np.float32)
     exact = B.astype(np.float64) @ A.astype(np.float64).T
     outs = []
     assert forced("ssplit", lambda: outs.append(product(A, B, m, n, k, ta, tb))) >= 2
@@ -129,3 +137,35 @@ def test_no_less_precise_than_the_fp32_pipes(k, spread):
         error[prefix] = max(np.linalg.norm(o - exact) / np.linalg.norm(exact) for o in outs)
     # (where a few products dominate the sum, both are the rounding of those: half a unit in the last place)
     assert error["ssplit"] <= (error["smfma_64x64"] if spread == "uniform" else max(error["smfma_64x64"], 2.0 ** -24))
+
+
+def call_time(A, B, n, k):
+    """microseconds of one n x n x k product, of several in a row"""
+    import torch
+    out = torch.empty(n * n, device="cuda")
+    times = []
+    for _ in range(6):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        for _ in range(10):
+            G.mg_sgemm(C, T, N, n, n, k, 1.0, A, k, B, k, 0.0, out, n)
+        end.record()
+        end.synchronize()
+        times.append(begin.elapsed_time(end) * 100)
+    return sorted(times[1:])[2]
+
+
+def test_time_does_not_depend_on_small_elements():
+    """elements below 2^-110 are products like others (a tile with one of them used to be computed twice: 1.8 times), and NaN ends the
+    sum on the bf16 pipes early (2.3 times; now 1.4, the FP32 pipes' share)"""
+    import torch
+    n, k = 2048, 8192
+    A, B = (torch.empty(n, k, device="cuda").uniform_(-1, 1) for _ in range(2))
+    assert "ssplit" in G.mg_kernel_name(G.mg_query_selected(G.MG_F32, C, T, N, n, n, k, k, k, n)["kernel_id"])
+    usual = call_time(A, B, n, k)
+    some = A.clone()
+    some[:, 17] = 1.0e-36
+    assert call_time(some, B, n, k) < 1.25 * usual
+    assert call_time(A * 1.0e-41, B, n, k) < 1.25 * usual
+    some[:, 17] = float("nan")
+    assert call_time(some, B, n, k) < 1.8 * usual
