@@ -859,9 +859,16 @@ extern "C" {
 mg_status mg_sgemm_static(int layout, int ta, int tb, int64_t m, int64_t n, int64_t k, float alpha, const float *A,
                           int64_t lda, const float *B, int64_t ldb, float beta, float *C, int64_t ldc, void *stream)
 {
-    // what the preferred route of this problem would use (0 for invalid arguments: run_gemm names the error)
-    if (mg_gemm_workspace_bytes(MG_F32, layout, ta, tb, m, n, k, lda, ldb, ldc) > MG_STATIC_SCRATCH_BYTES)
-        return MG_ERR_WORKSPACE;
+    // Refused is what is slow without more scratch, a long sum over a C that leaves the chip idle: the problems whose configuration on the
+    // FP32 pipes wants it too.  Slices of the kernels on the bf16 pipes may only round off a last turn ((3200, 2752, 3840) would ask for
+    // 141 MB): such problems take what fits.  (0 for invalid arguments: run_gemm names the error.)
+    if (mg_gemm_workspace_bytes(MG_F32, layout, ta, tb, m, n, k, lda, ldb, ldc) > MG_STATIC_SCRATCH_BYTES) {
+        Problem p = canonical(MG_F32, layout, ta, tb, m, n, k, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr);
+        p.fp32_pipes = true;
+        int32_t kernel = -1, split = 1;
+        if (choose(p, 256, ~size_t(0), &kernel, &split) == MG_OK && table()[kernel].workspace(p, split) > MG_STATIC_SCRATCH_BYTES)
+            return MG_ERR_WORKSPACE;
+    }
     void *ws = nullptr;
     const mg_status s = static_scratch(&ws);
     if (s != MG_OK) return s;

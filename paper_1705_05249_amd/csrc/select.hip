@@ -458,7 +458,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         for (int i = 0; i < count; ++i) {
             // (short sums are the traffic of C, which the small tiles overlap better: (3870, 5248, 64) 45.7 / 40.0 us on the 64 x 64 tile of the
             // FP32 pipes, (2303, 2721, 64) 18.1 / 17.7, (6000, 700, 129) 20.7 / 21.5, (4096, 4096, 256) 63.4 / 73.4)
-            if (f32 && i >= kSplit && p.k < 128) continue;
+            if (f32 && i >= kSplit && (p.k < 128 || p.fp32_pipes)) continue;
             // FP32 work-groups take turns on a compute unit, so unequal tiles (skipped ones, narrowed K ranges) only pay off where a compute
             // unit gets many of them: of the kernels on the FP32 pipes the smallest (SYRK 4096: 974 / 923 / 695 / 618 us from the 256 x 256
             // to the 64 x 64 tile, TRMM 950 / 614 / 596 / 541).  Those on the bf16 pipes are ranked beside it (us, unsliced, FP32 pipes 64 x 64 /

@@ -151,3 +151,23 @@ print(fastest(900), fastest(1500), fastest(2050))
     assert run.returncode == 0, run.stderr
     direct, *weighed = map(float, run.stdout.split())
     assert max(weighed) < 2.0 * direct, (direct, weighed)              # microseconds
+
+
+def test_static_scratch_takes_what_the_fp32_pipes_take():
+    """problems whose sums are sliced on the bf16 pipes alone are not refused for the room of the slices (no device: the launch fails)"""
+    program = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import torch
+assert torch.cuda.device_count() == 0
+from paper_1705_05249_amd import gemm as G
+N, T = G.MG_NO_TRANS, G.MG_TRANS
+for m, n, k, ta, tb in ((1024, 896, 8448, T, N), (3200, 2752, 3840, T, N), (1443, 3497, 5168, T, N), (5248, 2176, 8640, N, T), (7968, 158, 3184, T, N),
+                        (1536, 1024, 32768, N, N)):
+    lda, ldb = (m if ta == N else k), (k if tb == N else n)
+    print(G.lib().mg_sgemm_static(G.MG_COL_MAJOR, ta, tb, m, n, k, 1.0, 4096, lda, 4096, ldb, 0.0, 4096, m, None))
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    run = subprocess.run([sys.executable, "-c", program, ROOT], capture_output=True, text=True, timeout=300, env=env)
+    assert run.returncode == 0, run.stderr
+    assert run.stdout.split() == ["-12"] * 5 + ["-10"]                 # the last one in eight slices on any pipes: 48 MB
