@@ -151,6 +151,21 @@ mg_status choose(Problem &p, int64_t alignment, size_t workspace_bytes, int32_t 
 
 size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
 
+// What the configuration chosen with all the workspace there is needs, without pointers; the larger of what it needs with beta == 0 and with any
+// other (FP32 ranks its tiles by the traffic of C too, and sums of up to 512 terms choose among fewer of them with beta != 0)
+size_t preferred_bytes(Problem p)
+{
+    size_t most = 0;
+    for (const float beta : {0.f, 1.f}) {
+        int32_t kernel = -1, split = 1;
+        p.beta = beta;
+        if (choose(p, 256, ~size_t(0), &kernel, &split) != MG_OK) continue;
+        const size_t need = table()[kernel].workspace(p, split);
+        if (need > most) most = need;
+    }
+    return most;
+}
+
 // Indirect GEMM, the paper's Section 3.2 route for problems that break the fast kernel's assumptions: copy the
 // operands into zero-padded, aligned buffers whose sizes are whole tiles and run the fast kernel there.  FP16 needs it:
 // ragged or unaligned FP16 problems otherwise run the bounds-checked register-staged kernels at 0.2-0.6 of the
@@ -1052,15 +1067,12 @@ size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m,
 {
     if (dtype != MG_F32 && dtype != MG_F16) return 0;
     if (check_shape(layout, ta, tb, m, n, k, lda, ldb, ldc) != MG_OK || m == 0 || n == 0) return 0;
-    // (the scale-only path of alpha == 0 needs none; FP32 sums of 193 to 512 terms choose among fewer tiles with beta != 0 than
-    // without: of 60000 shapes none needs more with beta == 0)
+    // (the scale-only path of alpha == 0 needs none)
     Problem p = canonical(dtype, layout, ta, tb, m, n, k, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc,
                           nullptr, 0, nullptr);
     IndirectPlan plan;
     if (indirect_plan(p, false, &plan)) return plan.total();      // (room for slices beside the copies is the caller's choice)
-    int32_t kernel = -1, split = 1;
-    if (choose(p, 256, ~size_t(0), &kernel, &split) != MG_OK) return 0;
-    return table()[kernel].workspace(p, split);
+    return preferred_bytes(p);
 }
 
 #define MG_CONV_SHAPE_ARGS                                                                                      \

@@ -171,3 +171,18 @@ for m, n, k, ta, tb in ((1024, 896, 8448, T, N), (3200, 2752, 3840, T, N), (1443
     run = subprocess.run([sys.executable, "-c", program, ROOT], capture_output=True, text=True, timeout=300, env=env)
     assert run.returncode == 0, run.stderr
     assert run.stdout.split() == ["-12"] * 5 + ["-10"]                 # the last one in eight slices on any pipes: 48 MB
+
+
+def test_the_workspace_query_covers_every_beta():
+    """what the query returns holds the slices of the configuration that would be chosen with all the workspace there is"""
+    import random
+    T, rng = G.MG_TRANS, random.Random(3)
+    shapes = [(704, 3072, 2560, N, T), (4544, 1920, 2432, N, N), (256, 1856, 4160, T, N)]
+    shapes += [tuple(64 * rng.randint(1, 80) for _ in range(3)) + (rng.choice((N, T)), rng.choice((N, T))) for _ in range(3000)]
+    shapes += [tuple(rng.randint(1, 5000) for _ in range(3)) + (rng.choice((N, T)), rng.choice((N, T))) for _ in range(1500)]
+    for m, n, k, ta, tb in shapes:
+        lda, ldb = (m if ta == N else k), (k if tb == N else n)
+        room = G.mg_gemm_workspace_bytes(G.MG_F32, C, ta, tb, m, n, k, lda, ldb, m)
+        for beta in (0.0, 1.0):
+            slices = G.mg_query_selected(G.MG_F32, C, ta, tb, m, n, k, lda, ldb, m, 1.0, beta)["split_k"]
+            assert slices == 1 or 4 * slices * m * n <= room, (m, n, k, ta, tb, beta)
