@@ -1020,13 +1020,25 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
     if (m < 0 || n < 0 || k < 0 || m >= lim || n >= lim || k >= lim) return 0;
     const size_t elem = dtype == MG_F32 ? 4 : 2;
     const int64_t lead = layout == MG_COL_MAJOR ? m : n;
+    // the product's own scratch: what the same product without a triangle wants and what this one does (kernels for small problems,
+    // which need none, skip no triangle: such products run on tiles, in slices where those are few)
+    auto product = [&](int ta, int tb, int64_t kk, int64_t lda, int64_t ldb, int64_t ldc, int lower, int upper) {
+        size_t most = mg_gemm_workspace_bytes(dtype, layout, ta, tb, m, n, kk, lda, ldb, ldc);
+        if (check_shape(layout, ta, tb, m, n, kk, lda, ldb, ldc) != MG_OK) return most;
+        for (const int shape : {lower, upper}) {
+            Problem p = canonical(dtype, layout, ta, tb, m, n, kk, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr, shape);
+            p.mask_c = routine == MG_ROUTINE_SYRK;
+            const size_t need = preferred_bytes(p);
+            if (need > most) most = need;
+        }
+        return most;
+    };
     if (routine == MG_ROUTINE_SYRK) {
         if (!valid_trans(trans) || n == 0) return 0;
         const bool nt = trans == MG_NO_TRANS;
-        const int64_t la = (layout == MG_COL_MAJOR) == nt ? n : k;
+        const int64_t la = (layout == MG_COL_MAJOR) == nt ? n : (k > 1 ? k : 1);
         return round_up_256(static_cast<size_t>(n) * n * elem) +
-               mg_gemm_workspace_bytes(dtype, layout, nt ? MG_NO_TRANS : MG_TRANS, nt ? MG_TRANS : MG_NO_TRANS, n, n, k,
-                                       la > 1 ? la : 1, la > 1 ? la : 1, n);
+               product(nt ? MG_NO_TRANS : MG_TRANS, nt ? MG_TRANS : MG_NO_TRANS, k, la, la, n, MG_SHAPE_C_LOWER, MG_SHAPE_C_UPPER);
     }
     if (!valid_side(side) || m == 0 || n == 0) return 0;
     const int64_t ka = side == MG_LEFT ? m : n;
@@ -1040,8 +1052,10 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
     }
     if (routine == MG_ROUTINE_TRMM) {
         if (!valid_trans(trans)) return 0;
-        const size_t gemm = side == MG_LEFT ? mg_gemm_workspace_bytes(dtype, layout, trans, MG_NO_TRANS, m, n, m, ldf, ldk, lead)
-                                            : mg_gemm_workspace_bytes(dtype, layout, MG_NO_TRANS, trans, m, n, n, ldk, ldf, lead);
+        const bool tri_is_a = (side == MG_LEFT) == (layout == MG_COL_MAJOR);
+        const int lower = tri_is_a ? MG_SHAPE_A_LOWER : MG_SHAPE_B_LOWER, upper = tri_is_a ? MG_SHAPE_A_UPPER : MG_SHAPE_B_UPPER;
+        const size_t gemm = side == MG_LEFT ? product(trans, MG_NO_TRANS, m, ldf, ldk, lead, lower, upper)
+                                            : product(MG_NO_TRANS, trans, n, ldk, ldf, lead, lower, upper);
         return dense + round_up_256(static_cast<size_t>(major) * ldk * elem) + gemm;
     }
     return 0;

@@ -490,7 +490,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             int n_options = 1;
             // (a triangular operand already leaves half of the work-groups short sums: slices only where tiles are few; TRMM FP16 3968 x 1181
             // 55 us unsliced, 76 in two slices, 1797 x 221 73 / 37)
-            if (!in_place && !(narrowed && blocks > kComputeUnits / 4)) {
+            // (FP16 triangles of C below 10 us: what slices gain the second launch takes; unsliced / in 4 slices, us on the device | calls in a
+            // row: 200 x 1000 T 7.5 / 8.2 | 8.3 / 10.9, 256 x 2048 T 9.7 / 8.4 | 9.7 / 10.0, 256 x 4096 T 15.9 / 9.8 | 15.9 / 10.3)
+            const double unsliced = estimate(i, 1);
+            const bool short_triangle = !f32 && triangle && unsliced < 10.0e6;
+            if (!in_place && !short_triangle && !(narrowed && blocks > kComputeUnits / 4)) {
                 if (last) options[n_options++] = pick_split(blocks, ktiles);
                 if (blocks < 2 * kComputeUnits)
                     for (int sl = 2; sl <= 16 && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
@@ -502,7 +506,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // (513, 515, 2000) 19.4 / 24.7 us, (4097, 129, 4095) 51 / 63, 1025^3 27.6 / 31.4, but 4097^3 1021 / 693)
                 if (f32 && i >= kSplit && (p.fringe_m != 0 || p.fringe_n != 0) && (sl > 1 || blocks <= kComputeUnits)) continue;
                 // (an unsliced triangular operand runs below its estimate, most of its sums being shorter: TRMM FP16 3000 x 300 33 us, 38 in slices)
-                const double time = estimate(i, sl) * (narrowed && sl > 1 ? 1.25 : 1.0);
+                const double time = sl == 1 ? unsliced : estimate(i, sl) * (narrowed ? 1.25 : 1.0);
                 if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
                 if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
                 if (ranked[i].slices == 0 || time < ranked[i].time) ranked[i] = Ranked{sl, time};

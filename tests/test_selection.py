@@ -186,3 +186,13 @@ def test_the_workspace_query_covers_every_beta():
         for beta in (0.0, 1.0):
             slices = G.mg_query_selected(G.MG_F32, C, ta, tb, m, n, k, lda, ldb, m, 1.0, beta)["split_k"]
             assert slices == 1 or 4 * slices * m * n <= room, (m, n, k, ta, tb, beta)
+
+
+@pytest.mark.parametrize("dtype,n,k,trans", [
+    (G.MG_F16, 256, 2048, N), (G.MG_F16, 256, 3000, G.MG_TRANS), (G.MG_F16, 512, 2500, G.MG_TRANS), (G.MG_F16, 200, 2200, G.MG_TRANS),
+    (G.MG_F32, 512, 1024, N), (G.MG_F32, 256, 768, G.MG_TRANS), (G.MG_F32, 200, 700, N)])
+def test_syrk_query_has_room_for_slices(dtype, n, k, trans):
+    """few tiles with a long sum: the product of the same size without a triangle takes a kernel that needs no workspace"""
+    dense = -(-n * n * (4 if dtype == G.MG_F32 else 2) // 256) * 256
+    for layout in (G.MG_COL_MAJOR, G.MG_ROW_MAJOR):
+        assert G.mg_syrk_workspace_bytes(dtype, layout, trans, n, k) >= dense + 2 * 4 * n * n
