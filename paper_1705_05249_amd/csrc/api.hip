@@ -581,16 +581,13 @@ mg_status run_conv2d_fused(int dtype, const ConvShape &s, int64_t filters, int64
         // filters are one tile column.
         if (k > 256 || filters > 64) return MG_ERR_CONFIG;
         int32_t plain = -1;
+        p.fp32_pipes = true;               // (no variant that gathers exists for the others)
         select_config(t, p, 256, ws_bytes, &plain, &split);
         if (plain < 0) return MG_ERR_CONFIG;
         const std::string name = t[plain].name;
         const char *fused = nullptr;
         if (name == "hmfma_64x64x64_w2x2_mk" || name == "hmfma_64x64x64_w2x2_mk_edge") fused = "hconv_64x64x64_w2x2";
         else if (name == "smfma_64x64x32_w2x2_mk" || name == "smfma_64x64x32_w2x2_mk_edge") fused = "sconv_64x64x32_w2x2";
-        else if (name.compare(0, 6, "ssplit") == 0) {                        // (no such variant: the FP32 pipes' kernel, unsliced)
-            fused = "sconv_64x64x32_w2x2";
-            split = 1;
-        }
         if (fused == nullptr) return MG_ERR_CONFIG;
         for (size_t i = 0; i < t.size(); ++i)
             if (std::string(t[i].name) == fused) kernel = static_cast<int32_t>(i);
