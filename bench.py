@@ -1,15 +1,15 @@
 """Benchmark of the GEMM hot path on one MI355X.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--only GROUP] [--no-cpu-baseline]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--only GROUP] [--no-cpu-baseline] [--details FILE]
 
 One "step" is one mg_hgemm call on the headline workload: FP16 storage / FP32 accumulation, column-major,
 op(A)=A, op(B)=B, m=n=k=4096, alpha=1, beta=0, entries N(0, K^-1/2) rounded to FP16 (seeded, synthetic).  Inputs are
 resident in HBM before the timed region; W warm-up steps, then exactly K steps between two device
 synchronisations.  Prints ONE JSON line: GFLOPS = 2mnk/t, the MFMA roofline of the kernel, the CPU oracle timed on
 a bounded sample of the same workload (cpu_baseline), and under "workloads" every other workload of the five
-configurations (each with the roofline that bounds it), the cold (HBM-real) variants of the small ones, the
-launch floor, the rate of the matrix pipes alone, where the headline kernel's time goes ("accounting"), and the
-paper's own figures for context ("paper_context").
+configurations as [ms, GFLOPS, what bounds it, fraction of that].  --details FILE gets everything as JSON: each workload's kernel,
+roofline, traffic and notes, the cold (HBM-real) variants of the small ones, the launch floor, the rate of the matrix pipes alone,
+where the headline kernel's time goes ("accounting"), and the paper's own figures for context ("paper_context").
 """
 import argparse
 import json
@@ -21,7 +21,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-PEAK_TFLOPS = {"f16": 2500.0, "f32": 157.3}     # MI355X dense MFMA peaks
+# MI355X dense MFMA peaks; ssplit: FP32 products as eight bf16 ones (csrc/mfma_split_kernel.h)
+PEAK_TFLOPS = {"f16": 2500.0, "f32": 157.3, "ssplit": 2500.0 / 8}
 PEAK_HBM_GBS = 8000.0
 GROUPS = ("hgemm", "probes", "config1", "config2", "sgemm", "config3", "config4", "batched", "config5", "conv", "gemv",
           "level3", "copy")
@@ -56,6 +57,7 @@ def main():
     ap.add_argument("--warmup", type=int, default=20)
     ap.add_argument("--no-cpu-baseline", action="store_true", help="skip the oracle timing (profiling runs)")
     ap.add_argument("--no-probes", action="store_true", help="skip the measuring aids (profiling runs of a single kernel)")
+    ap.add_argument("--details", default=None, help="file for everything measured, as JSON (the printed line is kept short)")
     ap.add_argument("--only", default=None, help=" | ".join(GROUPS) + ": run a single group (profiling runs)")
     args = ap.parse_args()
     if args.gpus != 1:
@@ -119,7 +121,7 @@ def main():
             dev, _ = M.timed(call_on(A, B, C), reps or max(5, steps // 5), max(1, warmup // 4))
         entry["gflops"] = round(case.flops / dev / 1e9, 1)
         entry["ms"] = round(dev * 1e3, 5)
-        peak = PEAK_TFLOPS[case.dtype] if bound == "mfma" else PEAK_HBM_GBS
+        peak = PEAK_TFLOPS["ssplit" if sel["name"].startswith("ssplit") else case.dtype] if bound == "mfma" else PEAK_HBM_GBS
         work = case.flops if bound == "mfma" else case.algorithmic_bytes
         entry["roofline"] = roofline(bound, work, dev, peak, key or label)
         nbytes = A.numel() * A.element_size() + B.numel() * B.element_size() + C.numel() * C.element_size()
@@ -459,11 +461,14 @@ def main():
                    "ms_fastest_single_call": round(head["fastest"] * 1e3, 5)},
         "roofline": roofline("mfma", case.flops, dev, PEAK_TFLOPS["f16"], "hgemm_f16_4096x4096x4096_colmajor_NN_alpha1_beta0"),
         "cpu_baseline": head["cpu"],
-        "probes": probes,
-        "traffic_measured_at_commit": traffic.get("measured_at_commit"),
-        "paper_context": PAPER_CONTEXT,
-        "workloads": extra,
+        "launch_floor_us": probes.get("launch_floor", {}).get("us_back_to_back_in_a_graph"),
+        "workloads": {e["workload"].split(" (")[0]: [e["ms"], e["gflops"]] + [e["roofline"][x] for x in ("bound", "frac") if "roofline" in e]
+                      for e in extra},
     }
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(dict(line, workloads=extra, probes=probes, traffic_measured_at_commit=traffic.get("measured_at_commit"),
+                           paper_context=PAPER_CONTEXT), f, indent=1)
     print(json.dumps(line))
 
 

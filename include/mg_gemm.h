@@ -24,7 +24,12 @@
  *     `workspace` (device memory, 256-byte aligned, at least mg_gemm_workspace_bytes()).
  *     A call may write any part of the workspace it is given and expects nothing in it; two
  *     calls that can run at the same time (different streams) need different workspaces.
- *   - Arithmetic: products are accumulated in FP32 (also for FP16 storage); the result
+ *   - Arithmetic: products are accumulated in FP32 (also for FP16 storage).  Larger FP32
+ *     products run on the bf16 matrix pipes: every FP32 element is cut into three bf16 parts,
+ *     whose sum it is exactly, and all products of parts but the smallest (at most 2^-34 of the
+ *     element product) are accumulated in FP32, which is no less precise than the FP32 pipes;
+ *     elements or sums beyond the parts' range (2^107, 2^88), Inf and NaN take the FP32 pipes.
+ *     mg_query_selected() names the kernel (ssplit_*).  The result
  *     alpha*acc + beta*C_old is formed in FP32 and rounded once (round-to-nearest-even) to
  *     the storage type.  beta == 0 means C is not read (NaN/Inf in it do not propagate);
  *     alpha == 0 or k == 0 means A and B are not read.
@@ -390,6 +395,15 @@ int32_t mg_lds_read_offset(int32_t k_contiguous, int32_t fragment_rows, int32_t 
 int32_t mg_lds_f32_store_offset(int32_t k_contiguous, int32_t tile_rows, int32_t row, int32_t k);
 int32_t mg_lds_f32_read_offset(int32_t k_contiguous, int32_t tile_rows, int32_t wave_row,
                                int32_t lane, int32_t fragment, int32_t k_step, int32_t element);
+
+/* The same for one of the three bf16 planes of an FP32 operand on the bf16 pipes: tile_rows rows
+ * (128 or 256) and 32 values of k, fragments of 32 rows, K-steps of 16 values of k.  k_contiguous
+ * != 0: one 16-byte read (half is ignored), else the transposing 8-byte reads of
+ * mg_lds_read_offset.  The lane then holds k = 16 * k_step + 8 * (lane / 32) [+ 4 * half] + 0..
+ * of row wave_row + 32 * fragment + lane % 32; wave_row is a multiple of 32. */
+int32_t mg_lds_split_store_offset(int32_t k_contiguous, int32_t tile_rows, int32_t row, int32_t k);
+int32_t mg_lds_split_read_offset(int32_t k_contiguous, int32_t tile_rows, int32_t wave_row,
+                                 int32_t lane, int32_t fragment, int32_t k_step, int32_t half);
 
 /* ---- measuring aids (paper Section 4.1: how the numbers are taken) --------------------------
  * Three launches that let a benchmark measure, in its own run, what its roofline fractions are

@@ -1188,6 +1188,23 @@ int32_t mg_lds_f32_read_offset(int32_t k_contiguous, int32_t tile_rows, int32_t 
     return mg::ldsmap::native_base(tile_rows, lane, wave_row, fragment) + (8 * k_step + element) * 4 * tile_rows;
 }
 
+int32_t mg_lds_split_store_offset(int32_t k_contiguous, int32_t tile_rows, int32_t row, int32_t k)
+{
+    if ((tile_rows != 128 && tile_rows != 256) || row < 0 || row >= tile_rows || k < 0 || k >= 32) return -1;
+    if (k_contiguous) return mg::ldsmap::split_row_slot(row, k / 8) + 2 * (k % 8);
+    return mg::ldsmap::transposed_slot(tile_rows, k, row / 8) + 2 * (row % 8);
+}
+
+int32_t mg_lds_split_read_offset(int32_t k_contiguous, int32_t tile_rows, int32_t wave_row, int32_t lane, int32_t fragment,
+                                 int32_t k_step, int32_t half)
+{
+    if ((tile_rows != 128 && tile_rows != 256) || half < 0 || half > 1) return -1;
+    if (wave_row < 0 || wave_row % 32 != 0 || lane < 0 || lane > 63 || fragment < 0 || k_step < 0 || k_step > 1) return -1;
+    if (wave_row + 32 * (fragment + 1) > tile_rows) return -1;
+    if (k_contiguous) return mg::ldsmap::split_row_slot(wave_row + lane % 32, 2 * k_step + lane / 32) + fragment * 32 * 64;
+    return mg::ldsmap::split_line_base(tile_rows, lane, wave_row + 32 * fragment) + (16 * k_step + 4 * half) * 2 * tile_rows;
+}
+
 const char *mg_kernel_name(int32_t kernel_id)
 {
     if (kernel_id < 0 || kernel_id >= mg_kernel_count()) return "?";

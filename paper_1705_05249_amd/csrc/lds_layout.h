@@ -86,18 +86,13 @@ MG_HD constexpr int native_base(int rows, int lane, int wrow, int f)
 // lane l to row l % 32, chunk 2 s + l / 32; the 16 lanes of a pass are 16 rows of one chunk, four of them at each
 // quarter of a bank row, told apart by bits 2 and 3 of the row.
 MG_HD constexpr int split_row_slot(int row, int chunk) { return row * 64 + ((chunk ^ ((row >> 2) & 3)) << 4); }
-// [k][row] plane (operand along its rows): 128 rows and more as transposed_slot; with 64 rows a line is half a bank row, and the four
-// lines of a transposing read (32 rows each) meet in pairs: those two lines apart take different halves of it.
-MG_HD constexpr int split_line_slot(int rows, int k, int chunk)
-{
-    return rows >= 128 ? transposed_slot(rows, k, chunk) : k * 2 * rows + ((chunk ^ (4 * ((k >> 1) & 1))) << 4);
-}
-// first of the two reads of the fragment that starts at row wrow, K-step 0; the second is 4 lines on, a K-step 16 lines
+// [k][row] plane (operand along its rows, 128 and more): transposed_slot.  First of the two reads of the fragment that starts at row wrow,
+// K-step 0; the second is 4 lines on, a K-step 16 lines
 MG_HD constexpr int split_line_base(int rows, int lane, int wrow)
 {
     const int i = lane % 16, g = lane / 16, k = 8 * (g / 2) + i / 4;
     const int row = wrow + 16 * (g % 2) + 4 * (i % 4);
-    return split_line_slot(rows, k, row / 8) + 8 * ((row / 4) % 2);
+    return transposed_slot(rows, k, row / 8) + 8 * ((row / 4) % 2);
 }
 
 }  // namespace ldsmap

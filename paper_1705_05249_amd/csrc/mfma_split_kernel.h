@@ -67,6 +67,7 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
     static constexpr int STAGE = 3 * PLANE;
     static constexpr int RCH = ROWS / 4;                                 // pieces per line of an operand along its rows
     static_assert(LOADS >= 1 && ROWS * BK / 4 % NT == 0, "whole pieces per thread");
+    static_assert(ROWS >= 128, "the [k][row] planes' lines are whole bank rows");
     static constexpr uint32_t OUT_OF_RANGE = 0x80000000u;
 
     u32x4 regs[DEPTH][LOADS];
@@ -89,7 +90,7 @@ template <int ROWS, int NT, bool KCONTIG, bool EDGE, int DEPTH> struct SplitLoad
             } else {
                 const int mc = idx % RCH, l = idx / RCH;
                 goff[Q] = !EDGE || mc * 4 < rows ? static_cast<uint32_t>((mc * 4 + l * ld) * 4) : OUT_OF_RANGE;
-                slot[Q] = ldsmap::split_line_slot(ROWS, l, mc / 2) + 8 * (mc % 2);
+                slot[Q] = ldsmap::transposed_slot(ROWS, l, mc / 2) + 8 * (mc % 2);
             }
         });
         // (pieces of a thread are whole lines apart: the same rows)

@@ -113,6 +113,29 @@ def test_fp32_loader_stores_are_conflict_free(tile_rows, threads):
         assert cycles(by_k, 16, PASSES_16B) == 4 and cycles(by_row, 16, PASSES_16B) == 4, (tile_rows, first)
 
 
+@pytest.mark.parametrize("tile_rows", [128, 256])
+def test_bf16_planes_of_fp32_operands(tile_rows):
+    """reads fetch the right elements, reads and stores without conflicts, every element has its own place"""
+    for k_contiguous in (True, False):
+        place = {(row, k): G.mg_lds_split_store_offset(k_contiguous, tile_rows, row, k) for row in range(tile_rows) for k in range(32)}
+        assert sorted(place.values()) == list(range(0, tile_rows * 64, 2))
+        for wave_row in range(0, tile_rows, 32):
+            for f, s, half in itertools.product(range((tile_rows - wave_row) // 32), range(2), range(1 if k_contiguous else 2)):
+                addr = [G.mg_lds_split_read_offset(k_contiguous, tile_rows, wave_row, lane, f, s, half) for lane in range(64)]
+                for lane in range(64):
+                    row, k0 = wave_row + 32 * f + lane % 32, 16 * s + 8 * (lane // 32) + 4 * half
+                    if k_contiguous:
+                        assert all(place[row, k0 + e] == addr[lane] + 2 * e for e in range(8))
+                    else:                                 # (as the transposing reads of the FP16 tiles above)
+                        g, a, b = lane // 16, (lane % 16) // 4, lane % 4
+                        assert all(place[row, k0 + j] == addr[16 * g + a + 4 * j] + 2 * b for j in range(4))
+                assert cycles(addr, *((16, PASSES_16B) if k_contiguous else (8, PASSES_8B))) == (4 if k_contiguous else 2)
+        # stores: 8 bytes per part and piece, a wavefront's 64 pieces in a row
+        for first in range(0, tile_rows * 8, 64):
+            pieces = [(idx // 8, 4 * (idx % 8)) if k_contiguous else (4 * (idx % (tile_rows // 4)), idx // (tile_rows // 4)) for idx in range(first, first + 64)]
+            assert cycles([place[p] for p in pieces], 8, PASSES_8B) == 2
+
+
 def test_fp32_every_element_has_its_own_place():
     for k_contiguous, tile_rows in itertools.product((True, False), (64, 128, 256)):
         seen = {G.mg_lds_f32_store_offset(k_contiguous, tile_rows, row, k) for row in range(tile_rows) for k in range(32)}
@@ -162,3 +185,7 @@ def test_invalid_arguments():
     assert G.mg_lds_f32_read_offset(False, 64, 32, 0, 1, 0, 0) == -1
     assert G.mg_lds_f32_read_offset(False, 64, 16, 0, 0, 0, 0) == -1
     assert G.mg_lds_f32_read_offset(True, 64, 0, 0, 0, 4, 0) == -1
+    assert G.mg_lds_split_store_offset(False, 64, 0, 0) == -1
+    assert G.mg_lds_split_store_offset(True, 128, 0, 32) == -1
+    assert G.mg_lds_split_read_offset(False, 128, 96, 0, 1, 0) == -1
+    assert G.mg_lds_split_read_offset(True, 128, 0, 0, 0, 2) == -1
