@@ -217,13 +217,14 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
         // 1030, 2050) - | 62 / 76, (4100, 4100, 512) 53 / 54 | -.
         const double moved = static_cast<double>(p.m) * p.k + static_cast<double>(p.k) * p.n + static_cast<double>(p.m) * p.n;
         // Rows that start at odd elements cost the direct route a little more: 1801^3 29.9 / 26.7, (2671, 1061, 1265) 35.3 / 29.0
-        // at estimates 1.17 apart, (8201, 1031, 2051) 64 / 75 at 1.29, (1031, 1031, 8001) 56 / 63 at 1.65.  Their sums of fewer than
-        // 1536 terms always take the copies: short ones gain ((4001, 4001, 501) 43 / 40), around 1300 terms they lose (1301^3
-        // 20.3 / 25.8), but the tests of the staged kernels' remainders count on this route there.
+        // at estimates 1.17 apart, (8201, 1031, 2051) 64 / 75 at 1.29, (1031, 1031, 8001) 56 / 63 at 1.65.  Short sums run further
+        // above their estimate (the tiles' checked ends weigh more): of 55 products of 447 to 1515 terms in four orders the direct route won
+        // all 10 that were 1.4 apart and more (1301^3 18.7 / 22.5, (1345, 1409, 1081) 14.2 / 19.7, (1973, 1395, 925) 21.9 / 22.6) and
+        // lost 30 of the 45 others ((4445, 1835, 1487) 63.3 / 52.8 at 1.26, (3901, 1165, 995) 34.0 / 30.2 at 1.36).
         const bool dword_rows = p.lda % 2 == 0 && p.ldb % 2 == 0 && (!pointers_known || (pointer_alignment(p.A) >= 4 && pointer_alignment(p.B) >= 4));
         if (work < 350.0 * moved) return false;
-        compare = work < 900.0 * moved && (dword_rows || p.k >= 1536);
-        odds = dword_rows ? 1.15 : 1.2;
+        compare = work < 900.0 * moved;
+        odds = dword_rows ? 1.15 : (p.k >= 1536 ? 1.2 : 1.4);
         tile = p.m >= 2048 && p.n >= 2048 ? 256 : 128;
         ktile = 64;
     } else {

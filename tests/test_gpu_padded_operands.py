@@ -35,7 +35,7 @@ def _kernels(case):
 
 
 @pytest.mark.parametrize("ta,tb", [(N, N), (T, N), (N, T), (T, T)])
-@pytest.mark.parametrize("m,n,tile,ktiles", [(1345, 1409, "128, 128, 2, 4", t) for t in (17, 18, 19, 20)] +
+@pytest.mark.parametrize("m,n,tile,ktiles", [(1995, 1611, "128, 128, 2, 4", t) for t in (17, 18, 19, 20)] +
                          [(2177, 2051, "256, 128, 4, 2", t) for t in (12, 13, 14)])
 def test_every_remainder_of_the_staged_loops(oracle, ta, tb, m, n, tile, ktiles):
     """every number of K-tiles modulo three and modulo four, on the kernel with three (256 x 128) or four (128 x 128) stages"""
