@@ -363,7 +363,12 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 const SplitCost &cost = split_costs[i - kSplit];
                 const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, tiles[i].bk), slices)) * (p.a_trans && !p.b_trans ? 1.0 : 1.05);
                 auto turn = [&](double load) { return cost.turn + ktiles * (cost.ktile + cost.ktile_load * load * load); };
-                const double turns = static_cast<double>(blocks) / kComputeUnits;
+                // (a triangle's tiles: those of the shader engine that gets most.  SYRK, us, while all counted as equal / now: (3840, 458) 100 / 76,
+                // (2660, 1088) upper 101 / 73, (3728, 2310) 338 / 294, (5520, 576) 193 / 169; 3 us of host time at the most)
+                int64_t share = blocks;
+                if (triangle && blocks <= (slices == 1 ? 4 : 2) * kComputeUnits)
+                    share = busiest_engine_tiles(p.shape == MG_SHAPE_C_LOWER, ceil_div(tm, tiles[i].bm), ceil_div(tn, tiles[i].bn), tiles[i].bm, tiles[i].bn, slices);
+                const double turns = static_cast<double>(share) / kComputeUnits;
                 double us;
                 if (narrowed) {
                     // (sums of half the length on average, the longest first; TRMM 3000 on 128 x 128 tiles 208 us, 4096 421, 8192 2970)

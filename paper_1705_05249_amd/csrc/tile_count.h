@@ -19,4 +19,33 @@ inline int64_t triangle_tiles(bool lower, int64_t across_m, int64_t across_n, in
     return rows * across_n - r * (rows * (rows - 1) / 2);
 }
 
+// Such a launch hands its work-groups to the eight dies in turn and each die to its four shader engines of eight compute units in turn, and
+// tile_coords_balanced (mfma_kernel.h; groups of eight tile rows) says which tile each takes: the wanted tiles of the engine that gets most,
+// times 32, i.e. what the launch costs as if evenly spread.  Work-groups that skip their tile count in the turns, so 15 x 30 tiles of 256 x 128,
+// 240 of them wanted, leave one engine ten for its eight compute units, and 231 of 21 x 21 tiles nine.  `slices` of the sum are as many
+// such grids one behind the other.
+inline int64_t busiest_engine_tiles(bool lower, int64_t across_m, int64_t across_n, int bm, int bn, int slices)
+{
+    constexpr int64_t GROUP = 8;
+    int64_t wanted[32] = {0}, wg = 0;
+    for (int z = 0; z < slices; ++z)
+        for (int64_t first = 0; first < across_m; first += GROUP) {
+            const int64_t size = across_m - first < GROUP ? across_m - first : GROUP;
+            const bool odd = (first / GROUP) % 2 != 0;
+            int64_t shift = lower ? 0 : 1 % size;
+            for (int64_t tn = 0; tn < across_n; ++tn) {
+                for (int64_t r = 0; r < size; ++r, ++wg) {
+                    int64_t row = (odd ? size - 1 - r : r) + shift;
+                    if (row >= size) row -= size;
+                    const int64_t m0 = (first + row) * bm, n0 = tn * bn;
+                    wanted[wg % 32] += lower ? n0 < m0 + bm : m0 < n0 + bn;
+                }
+                if (++shift == size) shift = 0;
+            }
+        }
+    int64_t most = 0;
+    for (const int64_t w : wanted) most = w > most ? w : most;
+    return 32 * most;
+}
+
 }  // namespace mg

@@ -99,6 +99,38 @@ def test_tiles_of_a_triangle(tmp_path):
     assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout == ""
 
 
+def test_tiles_of_the_busiest_shader_engine(tmp_path):
+    """against the kernels' walk (tile_coords_balanced) taken work-group by work-group, ids in turn over eight dies and their four engines"""
+    src, exe = tmp_path / "engines.cpp", tmp_path / "engines"
+    src.write_text("""
+        #include <cstdio>
+        #include "tile_count.h"
+        int main()
+        {
+            const int tiles[][2] = {{256, 128}, {128, 128}};
+            for (const auto &t : tiles)
+                for (int upper = 0; upper < 2; ++upper)
+                    for (int n = 1; n < 5000; n += 37) {
+                        const int across_m = (n + t[0] - 1) / t[0], across_n = (n + t[1] - 1) / t[1];
+                        int engine[32] = {0}, most = 0, slices = 1 + n % 3;
+                        for (int id = 0; id < slices * across_m * across_n; ++id) {
+                            const int wg = id % (across_m * across_n);
+                            const int group = wg / (8 * across_n), first = 8 * group, size = across_m - first < 8 ? across_m - first : 8;
+                            const int r = wg % (8 * across_n) % size, tn = wg % (8 * across_n) / size;
+                            const int tm = first + ((group & 1 ? size - 1 - r : r) + tn + upper) % size;
+                            engine[id % 32] += upper ? tm * t[0] < (tn + 1) * t[1] : tn * t[1] < (tm + 1) * t[0];
+                        }
+                        for (int d : engine) most = d > most ? d : most;
+                        if (mg::busiest_engine_tiles(!upper, across_m, across_n, t[0], t[1], slices) != 32 * most)
+                            printf("%d x %d, n = %d, upper %d\\n", t[0], t[1], n, upper);
+                    }
+            printf("%d %d\\n", (int)mg::busiest_engine_tiles(true, 15, 30, 256, 128, 1), (int)mg::busiest_engine_tiles(false, 21, 21, 128, 128, 1));
+        }""")
+    csrc = os.path.join(ROOT, "paper_1705_05249_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout == "320 288\n"
+
+
 def test_selection_time_does_not_grow_with_the_matrix():
     """a rank-64 update of 2^20 x 2^20 is ranked in the time that one of 2048 x 2048 takes (no device: the launch fails)"""
     program = """
