@@ -377,6 +377,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                     us = floor(turns) * turn(1.0) + (turns > floor(turns) ? turn(turns - floor(turns)) : 0.0);
                 }
                 time = 1.0e6 * (us + cost.c_mb * 4.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0));
+                // (nothing that the FP32 pipes do as fast: the estimates are within about 7 % of each other's truth.  us, FP32 pipes /
+                // bf16 pipes at estimates less than that apart: (2656, 3207, 1150) 167 / 184, (560, 1920, 3746) 82 / 86, (5602, 5340, 266) 159 /
+                // 157, (280, 4504, 3032) 78 / 77, SYRK 1024 x 1408 28.0 / 30.8, 5792 x 384 123 / 133, 3345 x 3792 376 / 405)
+                if (!narrowed) time *= 1.07;
             } else if (f32) {
                 // work-groups take turns on a compute unit: ceil(blocks / 256) turns of one tile each, whether the
                 // compute units hold them all at once or are refilled as work-groups retire (squares of 1024 to 6144
@@ -511,7 +515,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // (513, 515, 2000) 19.4 / 24.7 us, (4097, 129, 4095) 51 / 63, 1025^3 27.6 / 31.4, but 4097^3 1021 / 693)
                 if (f32 && i >= kSplit && (p.fringe_m != 0 || p.fringe_n != 0) && (sl > 1 || blocks <= kComputeUnits)) continue;
                 // (an unsliced triangular operand runs below its estimate, most of its sums being shorter: TRMM FP16 3000 x 300 33 us, 38 in slices)
-                const double time = sl == 1 ? unsliced : estimate(i, sl) * (narrowed ? 1.25 : 1.0);
+                // (FP32 triangles: two slices run 10-25 % above their estimate, us unsliced on the FP32 pipes / in two slices: 3264 x 2941 271 / 303, 2688 x
+                // 2803 178 / 205, 3345 x 3792 372 / 407, 954 x 728 18.9 / 22.4, 785 x 1056 23.5 / 25.6; more slices on the FP32 pipes for more than 7 %)
+                const double sliced = narrowed ? 1.25 : (f32 && triangle ? (sl == 2 ? 1.2 : (i < kSplit ? 1.07 : 1.0)) : 1.0);
+                const double time = sl == 1 ? unsliced : estimate(i, sl) * sliced;
                 if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
                 if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
                 if (ranked[i].slices == 0 || time < ranked[i].time) ranked[i] = Ranked{sl, time};
