@@ -379,8 +379,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 time = 1.0e6 * (us + cost.c_mb * 4.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0));
                 // (nothing that the FP32 pipes do as fast: the estimates are within about 7 % of each other's truth.  us, FP32 pipes /
                 // bf16 pipes at estimates less than that apart: (2656, 3207, 1150) 167 / 184, (560, 1920, 3746) 82 / 86, (5602, 5340, 266) 159 /
-                // 157, (280, 4504, 3032) 78 / 77, SYRK 1024 x 1408 28.0 / 30.8, 5792 x 384 123 / 133, 3345 x 3792 376 / 405)
-                if (!narrowed) time *= 1.07;
+                // 157, (280, 4504, 3032) 78 / 77.  A triangle's tiles win at such estimates: SYRK 2048 118 / 86, 4096 554 / 499, 2194 x 2873 180 / 128)
+                if (p.shape == MG_SHAPE_GENERAL) time *= 1.07;
             } else if (f32) {
                 // work-groups take turns on a compute unit: ceil(blocks / 256) turns of one tile each, whether the
                 // compute units hold them all at once or are refilled as work-groups retire (squares of 1024 to 6144
