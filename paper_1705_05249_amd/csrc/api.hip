@@ -151,15 +151,16 @@ mg_status choose(Problem &p, int64_t alignment, size_t workspace_bytes, int32_t 
 
 size_t round_up_256(size_t v) { return (v + 255) / 256 * 256; }
 
-// What the configuration chosen with all the workspace there is needs, without pointers; the larger of what it needs with beta == 0 and with any
-// other (FP32 ranks its tiles by the traffic of C too, and sums of up to 512 terms choose among fewer of them with beta != 0)
-size_t preferred_bytes(Problem p)
+// What the configuration chosen with all the workspace there is needs, without pointers (taken to lie on `alignment` bytes); the larger of what it
+// needs with beta == 0 and with any other (FP32 ranks its tiles by the traffic of C too, and sums of up to 512 terms choose among fewer of
+// them with beta != 0)
+size_t preferred_bytes(Problem p, int64_t alignment = 256)
 {
     size_t most = 0;
     for (const float beta : {0.f, 1.f}) {
         int32_t kernel = -1, split = 1;
         p.beta = beta;
-        if (choose(p, 256, ~size_t(0), &kernel, &split) != MG_OK) continue;
+        if (choose(p, alignment, ~size_t(0), &kernel, &split) != MG_OK) continue;
         const size_t need = table()[kernel].workspace(p, split);
         if (need > most) most = need;
     }
@@ -210,6 +211,7 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
         const bool aligned = p.lda % 8 == 0 && p.ldb % 8 == 0 &&
                              (!pointers_known || (pointer_alignment(p.A) >= 16 && pointer_alignment(p.B) >= 16));
         if (whole && aligned) return false;                            // the fast kernels take it directly
+        if (pointers_known && dma_ragged_operands(p, 16) && dma_offsets_fit(p, 192, 64)) return false;       // so do those for sizes that end inside a tile
         // The bounds-checked kernels run their whole K-tiles on the fast flavour's schedule: up to about 900 multiply-adds per
         // element moved the two routes' estimates are compared; beyond, the copies always pay.  Even leading dimensions, us
         // direct / through the copies of A and B (A along m | along k): 1300^3 21.6 / 25.1 | 19.2 / 25.1, 1500^3 37 / 27 | 33 /
@@ -1026,8 +1028,12 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
         for (const int shape : {lower, upper}) {
             Problem p = canonical(dtype, layout, ta, tb, m, n, kk, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr, shape);
             p.mask_c = routine == MG_ROUTINE_SYRK;
-            const size_t need = preferred_bytes(p);
-            if (need > most) most = need;
+            // (FP16 operands off 16 bytes take other kernels, which slice more)
+            for (const int64_t alignment : {int64_t(256), int64_t(8)}) {
+                if (alignment < 16 && !dma_ragged_operands(p, 256)) continue;
+                const size_t need = preferred_bytes(p, alignment);
+                if (need > most) most = need;
+            }
         }
         return most;
     };
@@ -1083,8 +1089,10 @@ size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m,
     Problem p = canonical(dtype, layout, ta, tb, m, n, k, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc,
                           nullptr, 0, nullptr);
     IndirectPlan plan;
-    if (indirect_plan(p, false, &plan)) return plan.total();      // (room for slices beside the copies is the caller's choice)
-    return preferred_bytes(p);
+    // (room for slices beside the copies is the caller's choice; where aligned pointers would spare the copies, for what the call then prefers)
+    if (!indirect_plan(p, false, &plan)) return preferred_bytes(p);
+    const size_t direct = dma_ragged_operands(p, 16) ? preferred_bytes(p) : 0;
+    return direct > plan.total() ? direct : plan.total();
 }
 
 #define MG_CONV_SHAPE_ARGS                                                                                      \

@@ -130,6 +130,30 @@ struct PadCopy {
 };
 hipError_t launch_pad_matrices(int dtype, const PadCopy *copies, int count, hipStream_t stream);
 
+inline int64_t pointer_alignment(const void *p)
+{
+    uintptr_t v = reinterpret_cast<uintptr_t>(p);
+    if (v == 0) return 256;
+    int64_t a = static_cast<int64_t>(v & (~v + 1));
+    return a > 256 ? 256 : a;
+}
+
+// Operands that the direct-to-LDS kernels for sizes ending inside a tile take: every 16-byte piece starts on 16 bytes and lies wholly inside
+// its operand or wholly outside.  alignment: of the pointers, where they are not known.
+inline bool dma_ragged_operands(const Problem &p, int64_t alignment)
+{
+    if (p.dtype != MG_F16 || p.lda % 8 || p.ldb % 8) return false;
+    if (pointer_alignment(p.A) < 16 || pointer_alignment(p.B) < 16 || (p.A == nullptr && alignment < 16)) return false;
+    return (p.a_trans ? p.k : p.m) % 8 == 0 && (p.b_trans ? p.n : p.k) % 8 == 0;
+}
+
+// Their lane offsets inside a tile, which count from 3 KB before it, stay below 2^31
+inline bool dma_offsets_fit(const Problem &p, int64_t tile_rows, int64_t tile_k)
+{
+    const int64_t lines = tile_rows > tile_k ? tile_rows : tile_k;
+    return (p.lda > p.ldb ? p.lda : p.ldb) * lines * static_cast<int64_t>(p.elem()) < (int64_t(1) << 31) - 4096;
+}
+
 // One compiled kernel (or kernel family instance) in the configuration table.
 struct KernelEntry {
     const char *name;
@@ -151,13 +175,5 @@ void register_batched(std::vector<KernelEntry> &table);
 void register_batched_tile(std::vector<KernelEntry> &table);
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
-
-inline int64_t pointer_alignment(const void *p)
-{
-    uintptr_t v = reinterpret_cast<uintptr_t>(p);
-    if (v == 0) return 256;
-    int64_t a = static_cast<int64_t>(v & (~v + 1));
-    return a > 256 ? 256 : a;
-}
 
 }  // namespace mg

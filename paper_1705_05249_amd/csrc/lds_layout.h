@@ -52,10 +52,15 @@ template <int RB> MG_HD constexpr int kcontig_xor(int f, int s)
 // line of `rows` halves per k; the 16-byte chunk c of line k sits at slot c ^ line_swizzle(k).  An MFMA operand is
 // two transposing 8-byte reads (ds_read_b64_tr_b16): in each group of 16 lanes, lane 4a + b receives element b of
 // what lanes a, a + 4, a + 8, a + 12 fetched, so lanes a + 4j (j = 0..3) fetch the same four rows at four consecutive k.
-MG_HD constexpr int line_swizzle(int k) { return 4 * (k & 3) + 2 * ((k >> 3) & 1); }
-MG_HD constexpr int transposed_slot(int rows, int k, int chunk) { return k * 2 * rows + ((chunk ^ line_swizzle(k)) << 4); }
-// First of the two reads of fragment 0, K-step 0; the second is 4 lines on; fragment f: base ^ (2 RB f); K-step s:
-// + s * (512 / RB) lines.  Lane l: i = l % 16 fetches rows 4 (i % 4) .. + 3 of its group's 16 rows at line i / 4;
+// Lines of an odd number of 128-byte pieces (64 or 192 rows): successive lines already start half a bank row apart, and a line is closed
+// under XORs inside its groups of eight slots only: line k's chunks are moved by 2 * (k / 2 % 2) + 4 * (k / 8 % 2).
+MG_HD constexpr int line_swizzle(int rows, int k)
+{
+    return rows % 128 == 0 ? 4 * (k & 3) + 2 * ((k >> 3) & 1) : 2 * ((k >> 1) & 1) + 4 * ((k >> 3) & 1);
+}
+MG_HD constexpr int transposed_slot(int rows, int k, int chunk) { return k * 2 * rows + ((chunk ^ line_swizzle(rows, k)) << 4); }
+// First of the two reads of the fragment that starts at row wrow, K-step 0; the second is 4 lines on; K-step s: + s * (512 / RB) lines;
+// fragment f of a wavefront tile that starts at a multiple of its power of two of rows: base ^ (2 RB f).  Lane l: i = l % 16 fetches rows 4 (i % 4) .. + 3 of its group's 16 rows at line i / 4;
 // 32-row fragments: groups 2c, 2c + 1 are the row halves of k chunk c; 16-row fragments: group g is k chunk g.
 template <int RB> MG_HD constexpr int transposed_base(int lane, int wrow, int rows)
 {

@@ -46,6 +46,40 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int RB = 32, bool C
     }
 };
 
+// The flavour for sizes that end inside a tile (VARIANT DMA_RAGGED): operands whose rows start on 16 bytes, any m and n along whose
+// operand the memory does not run, else (and for k) multiples of the eight elements of a 16-byte piece.
+template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int STAGES> struct MfmaRaggedConfig {
+    using Checked = MfmaConfig<_Float16, BM, BN, 64, WM, WN, AK, BKC, true>;   // same legality and split-K rules
+    static constexpr int NT = WM * WN * 64;
+    static constexpr int STAGE_BYTES = (BM + BN) * 128;
+    static constexpr int LDS = STAGES * STAGE_BYTES > Checked::EPILOGUE_LDS ? STAGES * STAGE_BYTES : Checked::EPILOGUE_LDS;
+    static_assert(LDS <= 160 * 1024, "LDS of a compute unit");
+
+    static bool legal(const Problem &p, int split, int64_t alignment)
+    {
+        if (!dma_ragged_operands(p, alignment)) return false;
+        // (a grid of the wanted tiles of a triangle wants a square C)
+        if (p.shape >= MG_SHAPE_C_LOWER && p.m != p.n) return false;
+        if (!dma_offsets_fit(p, BM > BN ? BM : BN, 64)) return false;
+        return Checked::legal(p, split, alignment);
+    }
+
+    static hipError_t launch(const Problem &p, int split)
+    {
+        static bool attr_set = false;   // raising the dynamic LDS limit is idempotent; races are harmless
+        return launch_tile_kernel<_Float16>(hgemm_dma_kernel<BM, BN, WM, WN, AK, BKC, 16, DMA_RAGGED, false, STAGES>, &attr_set, LDS, NT, BM, BN,
+                                            Checked::k_per_split(p, split), p, split, 0, BM == BN);
+    }
+
+    static KernelEntry entry(const char *name)
+    {
+        KernelEntry e = Checked::entry(name, launch);
+        e.cfg.lds_bytes = LDS;
+        e.legal = legal;
+        return e;
+    }
+};
+
 // The kernel whose wavefronts take turns (mfma_pp_kernel.h): 256 x 256 tiles, 2 x 4 wavefronts, 16x16x32 blocks,
 // B contiguous along k.  Same legality as the direct-to-LDS kernels; 1 KB more LDS (the dump area).
 template <bool AK, bool CLIP = false> struct MfmaPpConfig {

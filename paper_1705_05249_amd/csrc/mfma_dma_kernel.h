@@ -45,17 +45,28 @@ typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
 
+constexpr int DMA_RAGGED = 8;      // of a kernel's VARIANT
+
 // One operand tile (ROWS rows x 64 k, FP16): global -> LDS.  A wavefront owns COUNT consecutive 1 KB blocks.
-template <int ROWS, int NT, bool KCONTIG, int RB = 32> struct DmaLoader {
+// RAGGED: rows and values of k may end inside the tile, on whole chunks: lanes whose chunk does not exist name an offset outside the
+// descriptor's range, for which the hardware writes zeros to LDS without touching memory.
+template <int ROWS, int NT, bool KCONTIG, int RB = 32, bool RAGGED = false> struct DmaLoader {
     static constexpr int LDS_BYTES = ROWS * 128;
     static constexpr int COUNT = LDS_BYTES / (NT * 16);
-    static_assert(COUNT >= 1 && COUNT * NT * 16 == LDS_BYTES && (COUNT % 4 == 0 || COUNT < 4), "tile / work-group size");
+    static constexpr uint32_t MISSING = 0x80000000u;
+    static_assert(COUNT >= 1 && COUNT * NT * 16 == LDS_BYTES, "tile / work-group size");
     static constexpr int imm(int q) { return (q % 4) * 1024; }      // the 12-bit immediate reaches four blocks
 
-    uint32_t goff[COUNT];      // lane's global byte offset inside the tile, less the immediate
+    static constexpr int LEAD = RAGGED ? imm(3) : 0;      // RAGGED (rows shorter than a tile's): the descriptor starts this far before the tile,
+                                                          // so that no offset is negative
+
+    uint32_t goff[COUNT];      // lane's global byte offset inside the tile, plus LEAD, less the immediate
+    int kpos[RAGGED ? COUNT : 1];       // the chunk's first value of k inside the K-tile
+    int kleft;                 // RAGGED: values of k from the tile aimed at to the end of the sum (none: the tile is zero)
     __amdgpu_buffer_rsrc_t rsrc;
 
-    __device__ inline void prepare(int64_t ld, int wave, int lane)
+    // rows_left: RAGGED, rows of the operand from the tile's first one on
+    __device__ inline void prepare(int64_t ld, int wave, int lane, int rows_left = ROWS)
     {
         static_for<COUNT>([&](auto Qc) {
             constexpr int Q = decltype(Qc)::value;
@@ -64,25 +75,35 @@ template <int ROWS, int NT, bool KCONTIG, int RB = 32> struct DmaLoader {
             if constexpr (KCONTIG) {
                 const int r = o / 128, slot = (o / 16) % 8;
                 g = r * ld * 2 + ((slot ^ ldsmap::swizzle<RB>(r)) << 4);
+                if constexpr (RAGGED) {
+                    kpos[Q] = (slot ^ ldsmap::swizzle<RB>(r)) * 8;
+                    if (r >= rows_left) kpos[Q] = 1 << 30;
+                }
             } else {
                 const int kl = o / (2 * ROWS), slot = (o / 16) % (ROWS / 8);
-                g = kl * ld * 2 + ((slot ^ ldsmap::line_swizzle(kl)) << 4);
+                g = kl * ld * 2 + ((slot ^ ldsmap::line_swizzle(ROWS, kl)) << 4);
+                if constexpr (RAGGED) {
+                    kpos[Q] = kl;
+                    if ((slot ^ ldsmap::line_swizzle(ROWS, kl)) * 8 >= rows_left) kpos[Q] = 1 << 30;
+                }
             }
-            goff[Q] = static_cast<uint32_t>(g - imm(Q));
+            goff[Q] = static_cast<uint32_t>(g + LEAD - imm(Q));
         });
     }
 
-    __device__ inline void aim(const _Float16 *X, int64_t ld, int64_t r0, int64_t l0)
+    __device__ inline void aim(const _Float16 *X, int64_t ld, int64_t r0, int64_t l0, int left = 0)
     {
+        kleft = left;
         const _Float16 *base = KCONTIG ? X + r0 * ld + l0 : X + r0 + l0 * ld;
-        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(base), 0, 0x7fffffff, 0x00020000);
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(base - LEAD / 2), 0, 0x7fffffff, 0x00020000);
     }
 
     // mine: this wavefront's first block in the destination stage (wave-uniform)
     template <int Q> __device__ inline void issue(lds_char *mine) const
     {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, reinterpret_cast<lds_void *>(mine + (Q / 4) * 4096), 16, goff[Q], 0,
-                                                 imm(Q), 0);
+        uint32_t at = goff[Q];
+        if constexpr (RAGGED) at = kpos[Q] < kleft ? at : MISSING;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, reinterpret_cast<lds_void *>(mine + (Q / 4) * 4096), 16, at, 0, imm(Q), 0);
     }
 };
 
@@ -142,23 +163,25 @@ template <int N> __device__ inline void hold_registers(const u32x4 (&f)[N])
     for (int i = 0; i < N; ++i) asm volatile("" ::"v"(f[i]));
 }
 
-template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int PROBE = 0, bool CLIP = false, int STAGES = 2>
+template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int VARIANT = 0, bool CLIP = false, int STAGES = 2>
 __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs args)
 {
 #if defined(__HIP_DEVICE_COMPILE__)      // the host pass needs the kernel's symbol only (LDS address-space code is device code)
     using T = _Float16;
+    // VARIANT: the diagnostic builds' switches (PROBE, 0 in every registered kernel) and 8: sizes that end inside a tile
+    constexpr int PROBE = VARIANT & 7;
+    constexpr bool RAGGED = (VARIANT & DMA_RAGGED) != 0;
     constexpr int BK = 64, NT = WM * WN * 64;
     constexpr int WTM = BM / WM, WTN = BN / WN;
     constexpr int FM = WTM / RB, FN = WTN / RB;
     constexpr int KSTEPS = BK / ((64 / RB) * 8);
-    static_assert(WTM % (2 * RB) == 0 && WTN % (2 * RB) == 0, "wavefront tile: an even number of fragments per side");
+    static_assert(WTM % RB == 0 && WTN % RB == 0, "wavefront tile: whole fragments");
     // the reads issued behind the barrier (next tile, step 0) go to fragment buffer 0 while the MFMAs of the last
     // step still read their operands: that must be buffer 1
     static_assert(KSTEPS % 2 == 0, "fragment double buffering needs an even number of K-steps");
-    // the [k][row] layout XORs slot numbers up to 14 into a line of ROWS / 8 slots
-    static_assert((A_KCONTIG || BM >= 128) && (B_KCONTIG || BN >= 128), "an operand that is not contiguous along k needs 128 rows");
-    using LoadA = DmaLoader<BM, NT, A_KCONTIG, RB>;
-    using LoadB = DmaLoader<BN, NT, B_KCONTIG, RB>;
+    static_assert(BM % 64 == 0 && BN % 64 == 0, "lines of whole 128-byte pieces");
+    using LoadA = DmaLoader<BM, NT, A_KCONTIG, RB, RAGGED>;
+    using LoadB = DmaLoader<BN, NT, B_KCONTIG, RB, RAGGED>;
     constexpr int A_BYTES = LoadA::LDS_BYTES, B_BYTES = LoadB::LDS_BYTES;   // LDS: [A stage 0][A stage 1] ... [B stage 0][B stage 1] ...
     constexpr int SLOTS = FM * FN, FRAGS = FM + FN;
     constexpr int PIECES = LoadA::COUNT + LoadB::COUNT;
@@ -168,6 +191,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
 
     int tm, tn;
     if (args.shape == 0) tile_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, tm, tn);
+    else if (RAGGED && BM == BN && args.shape >= MG_SHAPE_C_LOWER) tile_coords_triangle(blockIdx.x, args.tiles_m, args.shape == MG_SHAPE_C_UPPER, tm, tn);
     else tile_coords_balanced(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, args.reversed != 0, args.shape == MG_SHAPE_C_UPPER, tm, tn);
     const int64_t m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
     int kb = blockIdx.z * args.k_per_split;
@@ -189,8 +213,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
             for (int kx = 0; kx < 4; ++kx) frag[kx] = p ^ (32 * kx);
             for (int kx = 4; kx < 8; ++kx) frag[kx] = 0;
         } else {
-            const int p = operand_base + ldsmap::transposed_base<RB>(lane, wrow, rows);
-            for (int f = 0; f < 8; ++f) frag[f] = p ^ ldsmap::transposed_xor<RB>(f);
+            for (int f = 0; f < 8; ++f) frag[f] = operand_base + ldsmap::transposed_base<RB>(lane, wrow + RB * f, rows);
         }
     };
     frag_setup(A_KCONTIG, wm * WTM, 0, BM, frag_a);
@@ -207,14 +230,15 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
 
     LoadA la;
     LoadB lb;
-    la.prepare(args.lda, wave, lane);
-    lb.prepare(args.ldb, wave, lane);
-    const int ktiles = (ke - kb) / BK;
+    la.prepare(args.lda, wave, lane, args.m - static_cast<int>(m0));
+    lb.prepare(args.ldb, wave, lane, args.n - static_cast<int>(n0));
+    const int ktiles = RAGGED ? (ke - kb + BK - 1) / BK : (ke - kb) / BK;
     auto aim_tile = [&](int t) {
         int l0 = kb + t * BK;
-        l0 = l0 < ke ? l0 : ke - BK;            // past the end: reload the last tile into a stage nobody reads
-        la.aim(A, args.lda, m0, l0);
-        lb.aim(B, args.ldb, n0, l0);
+        const int left = ke - l0;               // (RAGGED: past the end nothing is fetched)
+        if (!RAGGED || left <= 0) l0 = l0 < ke ? l0 : ke - BK;            // past the end: reload the last tile into a stage nobody reads
+        la.aim(A, args.lda, m0, l0, left);
+        lb.aim(B, args.ldb, n0, l0, left);
     };
     lds_char *const mine_a = lds3 + wave_u * (LoadA::COUNT * 1024);
     lds_char *const mine_b = lds3 + STAGES * A_BYTES + wave_u * (LoadB::COUNT * 1024);
@@ -278,7 +302,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
     constexpr int TAIL_READ_SLOTS = TAIL >= 4 ? TAIL * 3 / 4 : TAIL;
     static_assert(PIECES * MG_DMA_SPACING <= BARRIER_SLOT, "loads must be issued before the barrier");
 
-    // PROBE (diagnostic builds only; 0 in every registered kernel): 1 = no global loads in the K loop, 2 = no
+    // PROBE: 1 = no global loads in the K loop, 2 = no
     // fragment reads in the K loop, 4 = cycle stamps around the per-tile wait and barrier, written to args.partial
     constexpr bool STAMPS = (PROBE & 4) != 0;
     uint64_t stamp_a = 0, stamp_b = 0, stamp_c = 0, sum_wait = 0, sum_barrier = 0, t_begin = 0, rt_begin = 0;
@@ -365,7 +389,7 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
             out[7] = __builtin_amdgcn_s_getreg(4 | (0 << 6) | (31 << 11));     // HW_ID
         }
     } else {
-        tile_epilogue<T, RB, FM, FN, WTM, WTN, CLIP>(acc, args, lds, m0, n0, wm, wn, wave, lane);       // CLIP: C may end inside the tile
+        tile_epilogue<T, RB, FM, FN, WTM, WTN, (CLIP || RAGGED)>(acc, args, lds, m0, n0, wm, wn, wave, lane);       // CLIP: C may end inside the tile
     }
 #else
     (void)args;

@@ -22,7 +22,7 @@ inline ConvGeom conv_geometry(const ConvShape &s)
 
 template <typename T, typename Kernel>
 hipError_t launch_tile_kernel(Kernel kernel, bool *attr_set, int lds_bytes, int threads, int bm, int bn, int k_per_split,
-                              const Problem &p, int split, int64_t fringe_groups = 0)
+                              const Problem &p, int split, int64_t fringe_groups = 0, bool triangle_grid = false)
 {
     if (!*attr_set) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
@@ -51,12 +51,14 @@ hipError_t launch_tile_kernel(Kernel kernel, bool *attr_set, int lds_bytes, int 
     a.slices = split;
     a.fringe_groups = static_cast<int>(fringe_groups);
     // (the fringe work-groups of all slices fill whole grid layers behind the tiles')
-    const int64_t tiles = static_cast<int64_t>(a.tiles_m) * a.tiles_n;
+    // (triangle_grid: the kernel's tiles are square and it takes a grid of those that touch a triangular C, see tile_coords_triangle)
+    const int triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER ? p.shape : 0;
+    const int64_t tiles = triangle_grid && triangle != 0 ? static_cast<int64_t>(a.tiles_m) * (a.tiles_m + 1) / 2
+                                                         : static_cast<int64_t>(a.tiles_m) * a.tiles_n;
     const unsigned layers = static_cast<unsigned>(split + ceil_div(fringe_groups * split, tiles));
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(tiles), 1, layers), dim3(threads), lds_bytes, p.stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split == 1) return e;
-    const int triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER ? p.shape : 0;
     const int64_t total = p.m * p.n;
     const bool wide = p.m % 4 == 0 && reinterpret_cast<uintptr_t>(a.partial) % 16 == 0;
     const int64_t groups = wide ? total / 4 : total;

@@ -40,6 +40,7 @@
 
 #include "internal.h"
 #include "lds_layout.h"
+#include "tile_count.h"
 #include "fringe.h"
 
 #ifndef MG_TAIL_SIXTEENTHS
@@ -576,6 +577,15 @@ __device__ inline void tile_coords_balanced(int wg, int tiles_m, int tiles_n, in
     tm = first + (((group & 1) ? size - 1 - r : r) + tn + (upper ? 1 : 0)) % size;
 }
 
+// Square tiles of a triangular C, with a work-group for each wanted tile and none for the others (triangle_tile in tile_count.h): the
+// ids of one XCD made consecutive as in tile_coords
+__device__ inline void tile_coords_triangle(int wg, int tiles, bool upper, int &tm, int &tn)
+{
+    const int total = gridDim.x;
+    const int xcd = wg % 8, q = total / 8, rem = total % 8;
+    triangle_tile(xcd * q + (xcd < rem ? xcd : rem) + wg / 8, tiles, upper, tm, tn);
+}
+
 template <int BM, int BN, int BK> __device__ inline bool narrow_to_shape(int shape, int64_t m0, int64_t n0, int &kb, int &ke)
 {
     if (shape == 0) return true;
@@ -633,7 +643,9 @@ template <typename T, int RB, int FM, int FN, int WTM, int WTN, bool EDGE, typen
 __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM], const MfmaArgs &args, char *lds,
                                      int64_t m0, int64_t n0, int wm, int wn, int wave, int lane, const Early &early = {})
 {
-    constexpr int NBLK = WTN / 32;                     // 32-column blocks of the wavefront tile
+    constexpr int BC = WTN % 32 == 0 ? 32 : 16;        // columns of a block
+    constexpr int NBLK = WTN / BC;                     // blocks of the wavefront tile
+    static_assert(RB == 16 || BC == 32, "16-column blocks need 16-column fragments");
     const int wm_u = __builtin_amdgcn_readfirstlane(wm), wn_u = __builtin_amdgcn_readfirstlane(wn);
     const int64_t gm0 = m0 + wm_u * WTM, gn0 = n0 + wn_u * WTN;     // wave-uniform corner of the wavefront tile
     const float alpha = args.alpha, beta = args.beta;
@@ -657,11 +669,11 @@ __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM],
                 }
         } else {
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
+            for (int jj = 0; jj < BC / 16; ++jj)
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
                     *reinterpret_cast<floatx4 *>(region + (16 * jj + lane % 16) * ROWB + (i * 16 + 4 * (lane / 16)) * 4) =
-                        acc[2 * j + jj][i];
+                        acc[BC / 16 * j + jj][i];
         }
         wave_fence();
     };
@@ -670,13 +682,11 @@ __device__ inline void tile_epilogue(typename BlockAcc<RB>::type (&acc)[FN][FM],
         using U = std::remove_pointer_t<decltype(base)>;
         constexpr int PER = 16 / static_cast<int>(sizeof(U));
         constexpr int CPRW = WTM / PER;                // pieces per column
-        constexpr int COLS = 64 / CPRW;                // columns per wavefront instruction
-        static_assert(CPRW <= 64 && 64 % CPRW == 0, "wavefront tile rows");
-        const int c = lane % CPRW, r0 = lane / CPRW;
+        static_assert(BC * CPRW % 64 == 0, "whole wavefront instructions");
 #pragma unroll
-        for (int pass = 0; pass < 32 / COLS; ++pass) {
-            const int r = r0 + pass * COLS;            // column inside the 32-column block
-            const int64_t gn = gn0 + j * 32 + r, gm = gm0 + c * PER;
+        for (int pass = 0; pass < BC * CPRW / 64; ++pass) {
+            const int c = (lane + 64 * pass) % CPRW, r = (lane + 64 * pass) / CPRW;        // piece, column inside the block
+            const int64_t gn = gn0 + j * BC + r, gm = gm0 + c * PER;
             int valid = PER, first = 0;          // elements first .. valid - 1 of the piece are written
             if constexpr (EDGE) {
                 const int64_t left = args.m_main - gm;

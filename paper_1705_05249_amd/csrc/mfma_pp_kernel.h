@@ -71,7 +71,7 @@ template <int ROWS, bool KCONTIG> struct DmaLoaderHalf {
                 g = r * ld * 2 + ((slot ^ ldsmap::swizzle<16>(r)) << 4);
             } else {
                 const int kl = o / (2 * ROWS), slot = (o / 16) % (ROWS / 8);
-                g = kl * ld * 2 + ((slot ^ ldsmap::line_swizzle(kl)) << 4);
+                g = kl * ld * 2 + ((slot ^ ldsmap::line_swizzle(ROWS, kl)) << 4);
             }
             goff[q] = static_cast<uint32_t>(g);
         }

@@ -265,8 +265,28 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                {"hmfma_128x128x64_w2x2", 128, 128, 64, 3.61f, 3.0f, 2},
                                                {"hmfma_128x64x64_w2x2", 128, 64, 64, 2.85f, 1.87f, 3},
                                                {"hmfma_64x64x64_w2x2", 64, 64, 64, 2.30f, 1.65f, 5},
-                                               {"hdeep16_128x128x64_w2x4", 128, 128, 64, 4.0f, 4.0f, 1}};
-        constexpr int kDeep = 8;            // index of the last one
+                                               {"hdeep16_128x128x64_w2x4", 128, 128, 64, 4.0f, 4.0f, 1},
+                                               {"hdma16r_192x192x64_w2x4", 192, 192, 64, 0.f, 0.f, 1},
+                                               {"hdma16r_192x128x64_w2x4", 192, 128, 64, 0.f, 0.f, 1},
+                                               {"hdma16r_128x128x64_w2x4", 128, 128, 64, 0.f, 0.f, 1},
+                                               {"hdma16r_128x64x64_w4x2", 128, 64, 64, 0.f, 0.f, 1},
+                                               {"hdma16r_64x64x64_w2x2", 64, 64, 64, 0.f, 0.f, 2}};
+        constexpr int kDeep = 8;            // index of the one with four stages
+        constexpr int kRagged = 9, kRaggedSmallest = 13;      // indices of the direct-to-LDS kernels for sizes that end inside a tile
+        // Their time in us, fitted to every tile with 1 to 8 slices on 310 sizes of 64 to 6000 in the four operand orders (residuals 5 to 8 %
+        // rms): turns of one tile per compute unit, each a fixed part and, per K-tile, a part that grows with the square of the share of
+        // the chip that is busy (the power limit) and the part of a second resident work-group; both operands along k / neither / A along m and B
+        // along k; rows of an operand along k that are no multiple of 128 bytes apart (each 128-byte piece of a row touches two
+        // lines); the traffic of C and of the partial sums.
+        struct RaggedCost {
+            double turn, ktile, ktile_load, second, both_k, neither_k, one_k, stray_rows, c, sums;
+        };
+        static const RaggedCost ragged_costs[5] = {{2.5, 0.607, 0.283, 0.0, 0.95, 1.05, 1.01, 0.08, 0.59, 0.86},
+                                                   {2.1, 0.442, 0.237, 0.0, 0.94, 1.09, 1.04, 0.10, 0.69, 0.95},
+                                                   {1.0, 0.308, 0.180, 0.0, 0.96, 1.11, 1.06, 0.12, 1.14, 0.99},
+                                                   {1.2, 0.205, 0.116, 0.0, 0.94, 1.13, 1.04, 0.12, 0.84, 0.82},
+                                                   {1.2, 0.163, 0.025, 0.179, 0.95, 1.12, 1.05, 0.12, 0.49, 0.64}};
+        const bool ragged_family = !f32 && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 && dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
         // LDS; the smaller the tile, the more that shows.  Measured rates relative to the (m, k) order (A along m,
         // B along k; tiles up to 128 x 64 / up to 256 x 128 / 256 x 256): both operands along k 1.10 / 1.06 / 1.02,
@@ -310,9 +330,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         static const SplitCost split_costs[2] = {{8.2, 1.95, 0.75, 0.18}, {5.8, 1.06, 0.41, 0.16}};
         static const double f32_round_cost[5] = {0.0, 0.0, 1.0e6, 2.0e6, 1.8e6};
         const TileChoice *tiles = f32 ? f32_tiles : f16_tiles;
-        const int count = f32 ? 7 : 9;
-        const int smallest = f32 ? 4 : 7;
-        bool tried[9] = {false, false, false, false, false, false, false, false, false};
+        const int count = f32 ? 7 : (ragged_family ? 14 : 9);
+        const int smallest = f32 ? 4 : (ragged_family ? kRaggedSmallest : 7);
+        bool tried[14] = {false};
         // work-groups that do something: of a product whose C is a triangle, the tiles that touch it (as the kernels skip the others)
         const bool triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
         // a triangular operand: tiles with sums of every length up to k, on average half (FP32; see the end of the ranking for FP16)
@@ -359,6 +379,24 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 return tiles[i].ceiling * (1.0 - pow(idle, static_cast<double>(u)));
             };
             double time;
+            if (!f32 && i >= kRagged) {
+                const RaggedCost &cost = ragged_costs[i - kRagged];
+                double each = p.a_trans ? (p.b_trans ? 1.0 : cost.both_k) : (p.b_trans ? cost.neither_k : cost.one_k);
+                if (p.a_trans && p.lda % 64) each *= 1.0 + cost.stray_rows;
+                else if (!p.b_trans && p.ldb % 64) each *= 1.0 + 0.5 * cost.stray_rows;
+                const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, 64), slices)) * each;
+                auto turn = [&](double load) {
+                    return load <= 1.0 ? cost.turn + ktiles * (cost.ktile + cost.ktile_load * load * load)
+                                       : cost.turn + ktiles * (cost.ktile + cost.ktile_load + cost.second);
+                };
+                const int64_t whole = blocks / full, rest = blocks % full;
+                double us = 0.5 + static_cast<double>(whole) * turn(tiles[i].resident) +
+                            (rest > 0 ? turn(static_cast<double>(rest) / kComputeUnits) : 0.0);
+                us += cost.c * 2.0 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0) * (triangle ? 0.5 : 1.0) / 4.5e6;
+                if (slices > 1)
+                    us += 3.0 + 0.2 * slices + cost.sums * (4.0 * slices + 6.0) * static_cast<double>(p.m) * static_cast<double>(p.n) * (triangle ? 0.5 : 1.0) / 4.0e6;
+                return us * 1.0e6;
+            }
             if (f32 && i >= kSplit) {
                 const SplitCost &cost = split_costs[i - kSplit];
                 const double ktiles = static_cast<double>(ceil_div(ceil_div(p.k, tiles[i].bk), slices)) * (p.a_trans && !p.b_trans ? 1.0 : 1.05);
@@ -460,7 +498,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         struct Ranked {
             int slices;                      // 0: not a candidate
             double time;
-        } ranked[9] = {};
+        } ranked[14] = {};
         double free_time = 0.0;              // best estimate with all the workspace one could wish for, and its slices
         int free_slices = 0;
         const bool in_place = p.clip_m != 0 || p.clip_n != 0;
@@ -490,6 +528,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 const bool wide = whole ? p.m * p.n > 25000000 : p.k > 128 && turns64 >= 6 && 2 * turns128 <= turns64;
                 if (tiles[i].bm * tiles[i].bn > (wide ? 128 * 64 : 64 * 64)) continue;
             }
+            // (where these take the operands the register-staged kernels are nowhere faster by more than 2 %, 190 sizes)
+            if (ragged_family && i > 2 && i < kDeep) continue;
+            // (tiles of a triangle are counted for heights that are multiples of the width)
+            if (!f32 && triangle && i >= kRagged && tiles[i].bm % tiles[i].bn != 0) continue;
             const bool last = i == smallest;
             const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
             const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn);
@@ -504,9 +546,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             const double unsliced = estimate(i, 1);
             const bool short_triangle = !f32 && triangle && unsliced < 10.0e6;
             if (!in_place && !short_triangle && !(narrowed && blocks > kComputeUnits / 4)) {
-                if (last) options[n_options++] = pick_split(blocks, ktiles);
-                if (blocks < 2 * kComputeUnits)
-                    for (int sl = 2; sl <= 16 && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
+                if (last && !ragged_family) options[n_options++] = pick_split(blocks, ktiles);
+                if (blocks < 2 * kComputeUnits && (!ragged_family || i >= kRagged))
+                    for (int sl = 2; sl <= (ragged_family ? 8 : 16) && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
             }
             for (int o = 0; o < n_options; ++o) {
                 const int sl = options[o];

@@ -8,6 +8,8 @@ bytes; lanes that read the same address share one access; an 8-byte read is serv
 time; a 16-byte access 16 lanes at a time, namely lanes {0-3, 12-15, 20-27}, then {4-11, 16-19, 28-31}, and the
 same in the upper half of the wavefront; a 4-byte read all 64 lanes at once."""
 import itertools
+import os
+import subprocess
 
 import pytest
 
@@ -189,3 +191,55 @@ def test_invalid_arguments():
     assert G.mg_lds_split_store_offset(True, 128, 0, 32) == -1
     assert G.mg_lds_split_read_offset(False, 128, 96, 0, 1, 0) == -1
     assert G.mg_lds_split_read_offset(True, 128, 0, 0, 0, 2) == -1
+
+
+def test_fragments_of_the_tiles_that_sizes_may_end_in(tmp_path):
+    """wavefront tiles of 32 to 96 rows on 16-row fragments, lines of an odd number of 128-byte pieces (64 and 192 rows) among them: the right
+    elements, no conflicts, and no two 16-byte pieces of a tile at one place"""
+    src, exe = tmp_path / "places.cpp", tmp_path / "places"
+    src.write_text("""
+        #include <cstdio>
+        #include "lds_layout.h"
+        using namespace mg::ldsmap;
+        int main()
+        {
+            const int tiles[][2] = {{192, 96}, {192, 48}, {192, 64}, {128, 32}, {64, 32}};
+            for (const auto &t : tiles) {
+                for (int row = 0; row < t[0]; ++row)
+                    for (int c = 0; c < 8; ++c) printf("k %d %d %d %d\\n", t[0], row, 8 * c, kcontig_slot<16>(row, c));
+                for (int k = 0; k < 64; ++k)
+                    for (int c = 0; c < t[0] / 8; ++c) printf("t %d %d %d %d\\n", t[0], 8 * c, k, transposed_slot(t[0], k, c));
+                for (int wrow = 0; wrow < t[0]; wrow += t[1])
+                    for (int f = 0; f < t[1] / 16; ++f)
+                        for (int s = 0; s < 2; ++s) {
+                            printf("K %d %d %d", t[0], wrow + 16 * f, s);
+                            for (int l = 0; l < 64; ++l) printf(" %d", (kcontig_base<16>(l, wrow) ^ kcontig_xor<16>(f, s)) + f * 16 * 128);
+                            printf("\\nT %d %d %d", t[0], wrow + 16 * f, s);
+                            for (int l = 0; l < 64; ++l) printf(" %d", transposed_base<16>(l, wrow + 16 * f, t[0]) + s * 32 * 2 * t[0]);
+                            printf("\\n");
+                        }
+            }
+        }""")
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1705_05249_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    lines = [line.split() for line in subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n") if line]
+    stored = {}                                    # (layout, tile) -> (row, k) of the piece's first element -> place
+    for kind, tile, row, k, at in (line for line in lines if line[0] in "kt"):
+        stored.setdefault((kind, int(tile)), {})[int(row), int(k)] = int(at)
+    assert len(stored) == 6
+    for (_, tile), places in stored.items():
+        assert set(places.values()) == set(range(0, tile * 128, 16))
+    for line in (line for line in lines if line[0] in "KT"):
+        tile, first, s = (int(v) for v in line[1:4])
+        addr = [int(v) for v in line[4:]]
+        places = stored[line[0].lower(), tile]
+        for half in (0,) if line[0] == "K" else (0, 1):
+            here = [a + half * 4 * 2 * tile for a in addr]
+            for lane in range(64):
+                row, k0 = first + lane % 16, 8 * (4 * s + lane // 16) + 4 * half
+                if line[0] == "K":
+                    assert places[row, k0] == here[lane]
+                else:
+                    a, b = (lane % 16) // 4, lane % 4
+                    assert all(places[row // 8 * 8, k0 + j] + 2 * (row % 8) == here[16 * (lane // 16) + a + 4 * j] + 2 * b for j in range(4))
+            assert cycles(here, 16 if line[0] == "K" else 8, PASSES_16B if line[0] == "K" else PASSES_8B) == (4 if line[0] == "K" else 2)

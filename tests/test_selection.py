@@ -99,6 +99,30 @@ def test_tiles_of_a_triangle(tmp_path):
     assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout == ""
 
 
+def test_every_tile_of_a_triangle_has_one_work_group(tmp_path):
+    src, exe = tmp_path / "walk.cpp", tmp_path / "walk"
+    src.write_text("""
+        #include <cstdio>
+        #include <vector>
+        #include "tile_count.h"
+        int main()
+        {
+            for (int tiles = 1; tiles < 1200; tiles += tiles < 100 ? 1 : 97)
+                for (int upper = 0; upper < 2; ++upper) {
+                    std::vector<int> seen(tiles * tiles);
+                    for (int id = 0; id < tiles * (tiles + 1) / 2; ++id) {
+                        int tm = -1, tn = -1;
+                        mg::triangle_tile(id, tiles, upper != 0, tm, tn);
+                        if (tm < 0 || tn < 0 || tm >= tiles || tn >= tiles || (upper ? tn < tm : tn > tm) || seen[tm * tiles + tn]++)
+                            printf("%d tiles, id %d: %d %d\\n", tiles, id, tm, tn);
+                    }
+                }
+        }""")
+    csrc = os.path.join(ROOT, "paper_1705_05249_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, str(src), "-o", str(exe)], check=True)
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout == ""
+
+
 def test_tiles_of_the_busiest_shader_engine(tmp_path):
     """against the kernels' walk (tile_coords_balanced) taken work-group by work-group, ids in turn over eight dies and their four engines"""
     src, exe = tmp_path / "engines.cpp", tmp_path / "engines"
