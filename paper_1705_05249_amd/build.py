@@ -1,4 +1,4 @@
-"""Compile the HIP sources under csrc/ into libmg_gemm.so (gfx950 only), in-tree.
+"""Compile the HIP sources under csrc/ into libmg_gemm.so (gfx950 only) and the Python calls into _mg_call.so, in-tree.
 
 hipcc cross-compiles without a GPU.  Objects are rebuilt when a source or header is newer.
 """
@@ -7,11 +7,13 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmg_gemm.so")
+CALL = os.path.join(HERE, "_mg_call.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
@@ -47,6 +49,10 @@ def build(force: bool = True, verbose: bool = False, extra_flags=()) -> str:
     if jobs or not os.path.exists(LIB):
         cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
         subprocess.run(cmd, check=True)
+    source = os.path.join(CSRC, "python_call.cpp")
+    if force or not os.path.exists(CALL) or os.path.getmtime(CALL) < max(os.path.getmtime(source), newest_header):
+        subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", sysconfig.get_paths()["include"],
+                        source, "-o", CALL], check=True)
     return LIB
 
 

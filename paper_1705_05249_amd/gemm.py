@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libmg_gemm.so: same names and argument order as include/mg_gemm.h.
+"""Thin binding of libmg_gemm.so: same names and argument order as include/mg_gemm.h.  Calls that launch work go through a small
+extension module (csrc/python_call.cpp), queries through ctypes.
 
 Argument marshalling only -- every step of the computation runs in the HIP kernels.  Matrix
 arguments may be torch tensors on the GPU (their data_ptr() is passed) or raw integer device
@@ -49,6 +50,26 @@ class MgError(RuntimeError):
 
 
 _lib = None
+_call = None            # csrc/python_call.cpp, bound to the library's entry points
+
+
+def _stream_calls():
+    """torch's functions for the current device and for its current stream's address"""
+    import torch
+    torch.cuda.current_stream()                   # (initialises torch's GPU state; raises where there is no GPU)
+    return torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
+def _native():
+    """the entry points with arguments taken as they are"""
+    global _call
+    if _call is None:
+        L = lib()
+        from . import _mg_call
+        names = [name for name in EXPORTS if hasattr(_mg_call, name)]
+        _mg_call.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in names}, _stream_calls)
+        _call = _mg_call
+    return _call
 
 
 def lib():
@@ -178,21 +199,13 @@ def _stream(stream):
     return torch.cuda.current_stream().cuda_stream
 
 
-def _ws(workspace):
-    if workspace is None:
-        return None, 0
-    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
-
-
 def status_string(status: int) -> str:
     return lib().mg_status_string(status).decode()
 
 
 def mg_sgemm(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, workspace=None, stream=None,
              check=True) -> int:
-    ws, ws_bytes = _ws(workspace)
-    st = lib().mg_sgemm(layout, trans_a, trans_b, m, n, k, alpha, _addr(A), lda, _addr(B), ldb, beta, _addr(C),
-                        ldc, ws, ws_bytes, _stream(stream))
+    st = (_call or _native()).mg_sgemm(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_sgemm")
     return st
@@ -203,8 +216,7 @@ MG_FRINGE_AUTO, MG_FRINGE_OFF, MG_FRINGE_ON = 0, 1, 2
 
 
 def mg_sgemm_static(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, stream=None, check=True) -> int:
-    st = lib().mg_sgemm_static(layout, trans_a, trans_b, m, n, k, alpha, _addr(A), lda, _addr(B), ldb, beta, _addr(C),
-                               ldc, _stream(stream))
+    st = (_call or _native()).mg_sgemm_static(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_sgemm_static")
     return st
@@ -212,9 +224,7 @@ def mg_sgemm_static(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, be
 
 def mg_hgemm(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, workspace=None, stream=None,
              check=True) -> int:
-    ws, ws_bytes = _ws(workspace)
-    st = lib().mg_hgemm(layout, trans_a, trans_b, m, n, k, alpha, _addr(A), lda, _addr(B), ldb, beta, _addr(C),
-                        ldc, ws, ws_bytes, _stream(stream))
+    st = (_call or _native()).mg_hgemm(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_hgemm")
     return st
@@ -222,9 +232,7 @@ def mg_hgemm(layout, trans_a, trans_b, m, n, k, alpha, A, lda, B, ldb, beta, C, 
 
 def mg_sgemv(layout, trans_a, m, n, alpha, A, lda, x, incx, beta, y, incy, workspace=None, stream=None,
              check=True) -> int:
-    ws, ws_bytes = _ws(workspace)
-    st = lib().mg_sgemv(layout, trans_a, m, n, alpha, _addr(A), lda, _addr(x), incx, beta, _addr(y), incy, ws, ws_bytes,
-                        _stream(stream))
+    st = (_call or _native()).mg_sgemv(layout, trans_a, m, n, alpha, A, lda, x, incx, beta, y, incy, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_sgemv")
     return st
@@ -232,18 +240,14 @@ def mg_sgemv(layout, trans_a, m, n, alpha, A, lda, x, incx, beta, y, incy, works
 
 def mg_hgemv(layout, trans_a, m, n, alpha, A, lda, x, incx, beta, y, incy, workspace=None, stream=None,
              check=True) -> int:
-    ws, ws_bytes = _ws(workspace)
-    st = lib().mg_hgemv(layout, trans_a, m, n, alpha, _addr(A), lda, _addr(x), incx, beta, _addr(y), incy, ws, ws_bytes,
-                        _stream(stream))
+    st = (_call or _native()).mg_hgemv(layout, trans_a, m, n, alpha, A, lda, x, incx, beta, y, incy, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_hgemv")
     return st
 
 
 def _symm(name, layout, side, uplo, m, n, alpha, A, lda, B, ldb, beta, C, ldc, workspace, stream, check):
-    ws, ws_bytes = _ws(workspace)
-    st = getattr(lib(), name)(layout, side, uplo, m, n, alpha, _addr(A), lda, _addr(B), ldb, beta, _addr(C), ldc, ws,
-                              ws_bytes, _stream(stream))
+    st = getattr(_call or _native(), name)(layout, side, uplo, m, n, alpha, A, lda, B, ldb, beta, C, ldc, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, name)
     return st
@@ -258,9 +262,7 @@ def mg_hsymm(layout, side, uplo, m, n, alpha, A, lda, B, ldb, beta, C, ldc, work
 
 
 def _syrk(name, layout, uplo, trans, n, k, alpha, A, lda, beta, C, ldc, workspace, stream, check):
-    ws, ws_bytes = _ws(workspace)
-    st = getattr(lib(), name)(layout, uplo, trans, n, k, alpha, _addr(A), lda, beta, _addr(C), ldc, ws, ws_bytes,
-                              _stream(stream))
+    st = getattr(_call or _native(), name)(layout, uplo, trans, n, k, alpha, A, lda, beta, C, ldc, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, name)
     return st
@@ -275,9 +277,7 @@ def mg_hsyrk(layout, uplo, trans, n, k, alpha, A, lda, beta, C, ldc, workspace=N
 
 
 def _trmm(name, layout, side, uplo, trans_a, diag, m, n, alpha, A, lda, B, ldb, workspace, stream, check):
-    ws, ws_bytes = _ws(workspace)
-    st = getattr(lib(), name)(layout, side, uplo, trans_a, diag, m, n, alpha, _addr(A), lda, _addr(B), ldb, ws, ws_bytes,
-                              _stream(stream))
+    st = getattr(_call or _native(), name)(layout, side, uplo, trans_a, diag, m, n, alpha, A, lda, B, ldb, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, name)
     return st
@@ -309,9 +309,8 @@ def mg_gemv_workspace_bytes(dtype, layout, trans_a, m, n, lda) -> int:
 
 def mg_sgemm_batched(layout, trans_a, trans_b, m, n, k, alphas, A, a_offsets, lda, B, b_offsets, ldb, betas, C,
                      c_offsets, ldc, batch_count, stream=None, check=True) -> int:
-    st = lib().mg_sgemm_batched(layout, trans_a, trans_b, m, n, k, _addr(alphas), _addr(A), _addr(a_offsets), lda,
-                                _addr(B), _addr(b_offsets), ldb, _addr(betas), _addr(C), _addr(c_offsets), ldc,
-                                batch_count, _stream(stream))
+    st = (_call or _native()).mg_sgemm_batched(layout, trans_a, trans_b, m, n, k, alphas, A, a_offsets, lda, B, b_offsets, ldb, betas, C,
+                                                c_offsets, ldc, batch_count, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_sgemm_batched")
     return st
@@ -319,9 +318,8 @@ def mg_sgemm_batched(layout, trans_a, trans_b, m, n, k, alphas, A, a_offsets, ld
 
 def mg_hgemm_batched(layout, trans_a, trans_b, m, n, k, alphas, A, a_offsets, lda, B, b_offsets, ldb, betas, C,
                      c_offsets, ldc, batch_count, stream=None, check=True) -> int:
-    st = lib().mg_hgemm_batched(layout, trans_a, trans_b, m, n, k, _addr(alphas), _addr(A), _addr(a_offsets), lda,
-                                _addr(B), _addr(b_offsets), ldb, _addr(betas), _addr(C), _addr(c_offsets), ldc,
-                                batch_count, _stream(stream))
+    st = (_call or _native()).mg_hgemm_batched(layout, trans_a, trans_b, m, n, k, alphas, A, a_offsets, lda, B, b_offsets, ldb, betas, C,
+                                                c_offsets, ldc, batch_count, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_hgemm_batched")
     return st
@@ -329,8 +327,8 @@ def mg_hgemm_batched(layout, trans_a, trans_b, m, n, k, alphas, A, a_offsets, ld
 
 def mg_hgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, A, lda, stride_a, B, ldb, stride_b, beta, C,
                              ldc, stride_c, batch_count, stream=None, check=True) -> int:
-    st = lib().mg_hgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, _addr(A), lda, stride_a, _addr(B),
-                                        ldb, stride_b, beta, _addr(C), ldc, stride_c, batch_count, _stream(stream))
+    st = (_call or _native()).mg_hgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, A, lda, stride_a, B, ldb, stride_b,
+                                                        beta, C, ldc, stride_c, batch_count, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_hgemm_strided_batched")
     return st
@@ -338,8 +336,8 @@ def mg_hgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, A, lda, s
 
 def mg_sgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, A, lda, stride_a, B, ldb, stride_b, beta, C,
                              ldc, stride_c, batch_count, stream=None, check=True) -> int:
-    st = lib().mg_sgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, _addr(A), lda, stride_a, _addr(B),
-                                        ldb, stride_b, beta, _addr(C), ldc, stride_c, batch_count, _stream(stream))
+    st = (_call or _native()).mg_sgemm_strided_batched(layout, trans_a, trans_b, m, n, k, alpha, A, lda, stride_a, B, ldb, stride_b,
+                                                        beta, C, ldc, stride_c, batch_count, stream)
     if check and st != MG_OK:
         raise MgError(st, "mg_sgemm_strided_batched")
     return st
@@ -350,8 +348,7 @@ def _geometry(channels, height, width, kernel, pad, stride, dilation):
 
 
 def _im2col(name, channels, height, width, kernel, pad, stride, dilation, im, col, stream, check):
-    st = getattr(lib(), name)(*_geometry(channels, height, width, kernel, pad, stride, dilation), _addr(im), _addr(col),
-                              _stream(stream))
+    st = getattr(_call or _native(), name)(*_geometry(channels, height, width, kernel, pad, stride, dilation), im, col, stream)
     if check and st != MG_OK:
         raise MgError(st, name)
     return st
@@ -368,9 +365,8 @@ def mg_him2col(channels, height, width, kernel, pad, stride, dilation, im, col, 
 
 def _conv2d(name, channels, height, width, kernel, pad, stride, dilation, filters, alpha, im, weights, beta, out,
             workspace, stream, check):
-    ws, ws_bytes = _ws(workspace)
-    st = getattr(lib(), name)(*_geometry(channels, height, width, kernel, pad, stride, dilation), filters, alpha,
-                              _addr(im), _addr(weights), beta, _addr(out), ws, ws_bytes, _stream(stream))
+    st = getattr(_call or _native(), name)(*_geometry(channels, height, width, kernel, pad, stride, dilation), filters, alpha,
+                                           im, weights, beta, out, workspace, stream)
     if check and st != MG_OK:
         raise MgError(st, name)
     return st
