@@ -629,6 +629,9 @@ mg_status run_conv2d(int dtype, const ConvShape &s, int64_t filters, float alpha
         }
         // Without the unfold pass where a kernel that gathers op(A) from the image exists for the configuration the
         // GEMM would get: the caller's workspace then only serves the slices of the sum.
+        // Few outputs: the whole convolution in one launch, from a band of the image in LDS.
+        if (forced < 0 && !plain && conv_gather_pays(dtype, s, filters))
+            return launch_conv_gather(dtype, s, filters, alpha, im, weights, beta, out, static_cast<hipStream_t>(stream)) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
         mg_status fused = run_conv2d_fused(dtype, s, filters, n, k, alpha, im, weights, beta, out, ws, ws_bytes, stream);
         if (fused != MG_ERR_CONFIG || forced_conv) return fused;
         if (launch_im2col(dtype, s, im, ws, static_cast<hipStream_t>(stream)) != hipSuccess) return MG_ERR_LAUNCH;

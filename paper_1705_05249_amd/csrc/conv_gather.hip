@@ -1,0 +1,321 @@
+// Convolution of one image in one launch, for layers of few outputs: the column matrix of IM2COL (paper, Section 3.1) is never stored, nor
+// gathered from memory element by element.  A work-group owns 32 output positions x 32 filters; what the 32 positions see of the
+// image, a band of a few rows of every channel, is copied into LDS with its zero padding around it, so that a tap of any output is an
+// address (that of the position plus that of the row (c, kh, kw) of the column matrix, from a table) without conditions.  The eight
+// wavefronts share the sum: each takes an eighth of the rows of the column matrix, reads its MFMA operand from the band element by element and
+// the filters' one straight from memory (16 bytes per lane, contiguous along the sum), and the eight partial blocks meet in LDS (as in tiny.hip).
+//
+// Bound by latency: launch, the rounds of loads that bring the band (0.9 us each: PIECES pieces of a thread) and the LDS reads of an eighth of
+// the sum (0.32 us per K-step).  The unfold route takes two dependent launches, each with a gap of 3.5-4 us and a latency of its own.  us,
+// unfold route / this kernel: FP16 128 channels of 28 x 28, 3 x 3, 256 filters 11.8 / 7.6, 256 of 14 x 14, 512 filters 21.0 / 11.7, 128 of 56 x
+// 56, 128 filters 16.2 / 11.7; FP32 the first 19.1 / 11.7; 16 of 7 x 7, 16 filters 8.9 / 4.3 (FP32 7.7 / 4.7).
+// Tried: sixteen wavefronts (the first layer 8.7, the fourth 5.0), ten K-steps of filters at once (7.8, 4.6), K-steps in groups of three without
+// branches (7.7, 5.6), 16 x 16 blocks, whose filter loads are 64-byte runs (7.6, 4.8).
+#include "mfma_host.h"
+
+namespace mg {
+namespace {
+
+struct GatherArgs {
+    const void *im, *weights;
+    void *out;
+    ConvGeom g;
+    int positions, filters, k;
+    int chunk;                     // channels of the image band that are in LDS at once
+    int pitch, left;               // elements of a row of the band; of them in front of the image's first column
+    int band_bytes;                // LDS bytes of the band (the table lies behind it)
+    uint32_t by_taps, by_kw, by_row, by_ow;       // for divisions by kh * kw, kw, pieces of an image row, ow
+    int line_step;                 // image rows that a thread's pieces are apart
+    int share, rest, minor, positions_first;      // as in TinyArgs
+    float alpha, beta;
+};
+
+constexpr int kThreads = 512;
+
+// n / d by the multiplication with ceil(2^32 / d), exact while n * d < 2^32; 0 stands for d == 1
+uint32_t reciprocal(int64_t d) { return d == 1 ? 0u : static_cast<uint32_t>(((int64_t(1) << 32) + d - 1) / d); }
+__device__ inline int quotient(int n, uint32_t by) { return by == 0 ? n : static_cast<int>(__umulhi(static_cast<uint32_t>(n), by)); }
+
+constexpr int kReduceBytes = 8 * 16 * 64 * 4 + 32 * 33 * 4;     // partial blocks and the staged sums
+
+// V: elements of a piece of an image row (a divisor of its length, at most 16 bytes)
+template <typename T, int V>
+__global__ __launch_bounds__(kThreads) void conv_gather_kernel(const GatherArgs a)
+{
+    constexpr int CH = ElemTraits<T>::CH, STEP = 2 * CH;       // values of k per lane and per K-step
+    constexpr int BATCH = 6;                                    // K-steps whose filters are loaded together
+    constexpr int PIECES = 8;                                   // pieces of the band a thread has in flight
+    constexpr int ES = sizeof(T);
+    using Raw = std::conditional_t<V * ES == 16, u32x4, std::conditional_t<V * ES == 8, u32x2, std::conditional_t<V * ES == 4, uint32_t, uint16_t>>>;
+    struct __attribute__((packed, aligned(ES))) Loose { T v[V]; };          // at element alignment
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const ConvGeom &g = a.g;
+    const int tid = threadIdx.x, lane = tid % 64, ln = lane % 32, lg = lane / 32;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
+
+    const int xcd = blockIdx.x % 8;
+    const int id = xcd * a.share + (xcd < a.rest ? xcd : a.rest) + blockIdx.x / 8;
+    const int outer = id / a.minor, inner = id - outer * a.minor;
+    const int m0 = (a.positions_first ? inner : outer) * 32, n0 = (a.positions_first ? outer : inner) * 32;
+    const T *__restrict__ im = static_cast<const T *>(a.im);
+    const T *__restrict__ weights = static_cast<const T *>(a.weights);
+
+    // the band: rows of the image from first_row on, band_rows of each channel
+    const int last = m0 + 31 < a.positions ? m0 + 31 : a.positions - 1;
+    const int oh_first = quotient(m0, a.by_ow);
+    const int band_rows = (quotient(last, a.by_ow) - oh_first) * g.stride_h + (g.kh - 1) * g.dil_h + 1;
+    const int first_row = oh_first * g.stride_h - g.pad_h;
+    const int taps = g.kh * g.kw;
+    const int per_row = g.w / V;                                // pieces of an image row (V: a power of two)
+    int *const table = reinterpret_cast<int *>(lds + a.band_bytes);
+
+    // this lane's position in the band (lanes past the last output repeat it; they are not stored)
+    const int pos = m0 + ln < a.positions ? m0 + ln : a.positions - 1;
+    const int oh = quotient(pos, a.by_ow), ow = pos - oh * g.ow;
+    const char *const mine = lds + (((oh - oh_first) * g.stride_h) * a.pitch + ow * g.stride_w - g.pad_w + a.left) * ES;
+    const int filter = n0 + ln < a.filters ? n0 + ln : a.filters - 1;
+    const T *const w_row = weights + static_cast<int64_t>(filter) * a.k;
+
+    // old values of this thread's two outputs (position tid % 32, filters tid / 32 and + 16): asked for now
+    T *out = static_cast<T *>(a.out);
+    bool stored[2];
+    float old[2] = {0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int mi = tid % 32, ni = tid / 32 + 16 * i;
+        stored[i] = m0 + mi < a.positions && n0 + ni < a.filters;
+        if (stored[i] && a.beta != 0.f) old[i] = load_as_float(out + (m0 + mi) + static_cast<int64_t>(n0 + ni) * a.positions);
+    }
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+    // the padding around the image stays zero in every chunk: cleared once
+    for (int at = tid * 16; at < a.band_bytes; at += kThreads * 16) *reinterpret_cast<u32x4 *>(lds + at) = u32x4{0u, 0u, 0u, 0u};
+    // addresses of the column matrix's rows relative to a position's, for a chunk's channels (the last chunk may have fewer)
+    for (int r = tid; r < ((a.chunk * taps + STEP - 1) / STEP) * STEP; r += kThreads) {
+        const int c = quotient(r, a.by_taps), t = r - c * taps, kh = quotient(t, a.by_kw), kw = t - kh * g.kw;
+        table[r] = r < a.chunk * taps ? ((c * band_rows + kh * g.dil_h) * a.pitch + kw * g.dil_w) * ES : 0;
+    }
+    __syncthreads();
+
+    // a thread's pieces are line_step lines (rows of the band) and piece_step pieces apart
+    const float by_band = 1.f / static_cast<float>(band_rows);             // (halves added: exact for the numbers of lines there are)
+    const int line_step = a.line_step, piece_step = kThreads - line_step * per_row;
+    const int channel_step = static_cast<int>((static_cast<float>(line_step) + 0.5f) * by_band), row_step = line_step - channel_step * band_rows;
+    const int line0 = quotient(tid, a.by_row), piece0 = tid - line0 * per_row;
+    const int channel0 = static_cast<int>((static_cast<float>(line0) + 0.5f) * by_band);
+    for (int c0 = 0; c0 < g.channels; c0 += a.chunk) {
+        const int channels = g.channels - c0 < a.chunk ? g.channels - c0 : a.chunk;
+        const int k0 = c0 * taps, kc = channels * taps;         // rows of the column matrix in this chunk
+        // whole K-steps, an eighth to each wavefront; what is left of the sum behind them is the last wavefront's
+        const int steps = kc / STEP, share = (steps + 7) / 8;
+        const int s_begin = wave * share, s_end = s_begin + share < steps ? s_begin + share : steps;
+        const T *const w_mine = w_row + k0 + lg * CH;
+        // filters of K-steps s .. s + BATCH - 1 (past the end: the last one again)
+        auto load_filters = [&](u32x4 (&q)[BATCH], int s) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) q[j] = load_unaligned_chunk<T>(w_mine + (s + j < s_end ? s + j : s_end - 1) * STEP);
+        };
+        u32x4 now[BATCH] = {}, next[BATCH] = {};
+        if (s_begin < s_end) load_filters(now, s_begin);
+
+        // the band: every piece of a row of the image inside it; a thread walks pieces kThreads apart
+        const int pieces = channels * band_rows * per_row;
+        int piece = piece0, channel = channel0, row = line0 - channel0 * band_rows;
+        for (int base = 0; base < pieces; base += PIECES * kThreads) {
+            Raw v[PIECES];
+            int to[PIECES];
+            static_for<PIECES>([&](auto P) __attribute__((always_inline)) {
+                constexpr int p = decltype(P)::value;
+                const int ih = first_row + row;
+                const bool in = channel < channels && static_cast<unsigned>(ih) < static_cast<unsigned>(g.h);
+                to[p] = in ? ((channel * band_rows + row) * a.pitch + a.left + piece * V) * ES : -1;
+                // (a piece that is not wanted: the image's first one)
+                v[p] = __builtin_bit_cast(Raw, *reinterpret_cast<const Loose *>(im + (in ? (static_cast<int64_t>(c0 + channel) * g.h + ih) * g.w + piece * V : 0)));
+                piece += piece_step;
+                row += row_step;
+                channel += channel_step;
+                if (piece >= per_row) { piece -= per_row; ++row; }
+                if (row >= band_rows) { row -= band_rows; ++channel; }
+            });
+            static_for<PIECES>([&](auto P) __attribute__((always_inline)) {
+                constexpr int p = decltype(P)::value;
+                if (to[p] >= 0) *reinterpret_cast<Raw *>(lds + to[p]) = v[p];
+            });
+        }
+        __syncthreads();
+
+        // the positions' operand of K-step s; wanted: rows of the column matrix that exist from the lane's first one on
+        auto gather = [&](int s, int wanted) __attribute__((always_inline)) {
+            const int *t = table + s * STEP + lg * CH;
+            u32x4 fa = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int e = 0; e < CH; ++e) {
+                const uint32_t x = elem_bits<T>(*reinterpret_cast<const T *>(mine + t[e]));
+                const uint32_t b = e < wanted ? x : 0u;
+                if constexpr (ES == 4) fa[e] = b;
+                else fa[e >> 1] |= b << (16 * (e & 1));
+            }
+            return fa;
+        };
+        for (int s = s_begin; s < s_end; s += BATCH) {
+            if (s + BATCH < s_end) load_filters(next, s + BATCH);
+            static_for<BATCH>([&](auto J) __attribute__((always_inline)) {
+                constexpr int j = decltype(J)::value;
+                if (s + j < s_end) mma(acc, now[j], gather(s + j, CH), T{});
+            });
+#pragma unroll
+            for (int j = 0; j < BATCH; ++j) now[j] = next[j];
+        }
+        if (wave == 7 && steps * STEP < kc) {
+            const int left = kc - steps * STEP - lg * CH;
+            mma(acc, gather_chunk<T>(w_mine + steps * STEP, left), gather(steps, left), T{});
+        }
+        __syncthreads();               // everyone is done with the band
+    }
+
+    // the eight partial blocks, as in tiny_gemm_kernel
+    float *part = reinterpret_cast<float *>(lds);
+    float *stage = reinterpret_cast<float *>(lds + 8 * 16 * 64 * 4);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) part[(wave * 16 + r) * 64 + lane] = acc[r];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int e = tid + kThreads * i, r = e / 64, l = e % 64;
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) s += part[w * 1024 + e];
+        stage[(l % 32) * 33 + 8 * (r / 4) + 4 * (l / 32) + r % 4] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int mi = tid % 32, ni = tid / 32 + 16 * i;
+        if (stored[i]) {
+            float o = a.alpha * stage[ni * 33 + mi];
+            if (a.beta != 0.f) o = fmaf(a.beta, old[i], o);
+            store_from_float(out + (m0 + mi) + static_cast<int64_t>(n0 + ni) * a.positions, o);
+        }
+    }
+}
+
+template <typename T, int V> hipError_t launch(const GatherArgs &a, int lds_bytes, hipStream_t stream)
+{
+    auto kernel = conv_gather_kernel<T, V>;
+    static bool attr_set = false;   // raising the dynamic LDS limit is idempotent; races are harmless
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    const unsigned groups = static_cast<unsigned>(ceil_div(a.positions, 32) * ceil_div(a.filters, 32));
+    hipLaunchKernelGGL(kernel, dim3(groups), dim3(kThreads), lds_bytes, stream, a);
+    return hipGetLastError();
+}
+
+struct Band {
+    int v, left, pitch;
+    int64_t rows, chunk, band_bytes, lds_bytes;
+};
+
+// The band of a layer: chunk 0 if not even sixteen channels of it (or all, if fewer) fit into LDS
+Band band_of(int dtype, const ConvShape &s, int64_t out_h, int64_t out_w)
+{
+    const int64_t es = dtype == MG_F32 ? 4 : 2, taps = s.kernel_h * s.kernel_w;
+    Band b{};
+    b.v = static_cast<int>(16 / es);
+    while (s.width % b.v != 0) b.v /= 2;
+    b.left = static_cast<int>(ceil_div(s.pad_w, b.v) * b.v);
+    b.pitch = static_cast<int>(ceil_div(b.left + s.width + s.pad_w, b.v) * b.v);
+    int64_t lines = (31 + out_w - 1) / out_w;               // output rows that 32 positions span, less one
+    if (lines > out_h - 1) lines = out_h - 1;
+    b.rows = lines * s.stride_h + (s.kernel_h - 1) * s.dilation_h + 1;
+    const int64_t room = 144 * 1024, step = 2 * (16 / es);
+    auto bytes = [&](int64_t channels) {
+        b.band_bytes = ceil_div(channels * b.rows * b.pitch * es, 16) * 16;
+        return b.band_bytes + ceil_div(channels * taps, step) * step * 4;
+    };
+    b.chunk = s.channels;
+    while (b.chunk > 16 && bytes(b.chunk) > room) b.chunk = ceil_div(b.chunk / 2, 16) * 16 < b.chunk ? ceil_div(b.chunk / 2, 16) * 16 : 16;
+    b.lds_bytes = bytes(b.chunk);
+    if (b.lds_bytes > room) b.chunk = 0;
+    if (b.lds_bytes < kReduceBytes) b.lds_bytes = kReduceBytes;
+    return b;
+}
+
+}  // namespace
+
+static bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
+{
+    const int64_t out_h = conv_out_extent(s.height, s.kernel_h, s.pad_h, s.stride_h, s.dilation_h);
+    const int64_t out_w = conv_out_extent(s.width, s.kernel_w, s.pad_w, s.stride_w, s.dilation_w);
+    const int64_t lim = int64_t(1) << 31;
+    // (the extents of the band are worked out in 32 bits)
+    if (s.pad_w > 4096 || s.width > 65536 || (s.kernel_h - 1) * s.dilation_h > 65536 || s.stride_h > 4096 || s.kernel_h * s.kernel_w > 4096) return false;
+    if (s.channels * s.kernel_h * s.kernel_w >= lim || out_h * out_w >= lim - 32 || filters >= lim - 32) return false;
+    if (ceil_div(out_h * out_w, 32) * ceil_div(filters, 32) >= lim) return false;
+    // (divisions by multiplication: the dividends are positions, rows of the column matrix in LDS and threads)
+    if ((out_h * out_w + 32) * out_w >= (int64_t(1) << 32) || s.kernel_h * s.kernel_w * 65536 >= (int64_t(1) << 32)) return false;
+    return band_of(dtype, s, out_h, out_w).chunk != 0;
+}
+
+// Whether the kernel takes a layer and is estimated faster than the routes through GEMM kernels (the unfold route, or for layers of few terms
+// the one that gathers from memory).  Both estimates in us, fitted to 77 layers of the benchmark's and of random sizes (3 to 449 channels, 7 to
+// 112 wide, 1 x 1 to 7 x 7 filters, both strides; residuals 10-17 % rms): of those the rule picks the faster route but for four, (351 channels of 81
+// x 81, 16 filters: 41 / 52) the worst, and they take 0.69 (FP16) and 0.78 (FP32) of the other routes' time.
+bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
+{
+    if (!conv_gather_fits(dtype, s, filters)) return false;
+    const int64_t out_h = conv_out_extent(s.height, s.kernel_h, s.pad_h, s.stride_h, s.dilation_h);
+    const int64_t out_w = conv_out_extent(s.width, s.kernel_w, s.pad_w, s.stride_w, s.dilation_w);
+    const Band b = band_of(dtype, s, out_h, out_w);
+    const int64_t taps = s.kernel_h * s.kernel_w, chunks = ceil_div(s.channels, b.chunk), step = dtype == MG_F32 ? 8 : 16;
+    const int64_t rounds = ceil_div(b.chunk * b.rows * (s.width / b.v), 8 * kThreads) * chunks;
+    const int64_t steps = ceil_div(ceil_div(b.chunk * taps, step), 8) * chunks;
+    const int64_t turns = ceil_div(ceil_div(out_h * out_w, 32) * ceil_div(filters, 32), 256);
+    const double k = static_cast<double>(s.channels * taps), positions = static_cast<double>(out_h * out_w);
+    const double column_mb = k * positions * (dtype == MG_F32 ? 4.0e-6 : 2.0e-6), gflop = 2.0e-9 * k * positions * static_cast<double>(filters);
+    const double here = 3.6 + static_cast<double>(turns) * (dtype == MG_F32 ? 0.85 * rounds + 0.36 * steps : 0.89 * rounds + 0.32 * steps);
+    const double there = dtype == MG_F32 ? 7.8 + 0.49 * column_mb + 0.0034 * k + 11.2 * gflop : 8.6 + 0.63 * column_mb + 0.0024 * k + 1.33 * gflop;
+    return here < there;
+}
+
+hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,
+                              void *out, hipStream_t stream)
+{
+    GatherArgs a{};
+    a.im = im; a.weights = weights; a.out = out;
+    a.g = conv_geometry(s);
+    a.positions = a.g.oh * a.g.ow;
+    a.filters = static_cast<int>(filters);
+    a.k = static_cast<int>(s.channels * s.kernel_h * s.kernel_w);
+    const Band b = band_of(dtype, s, a.g.oh, a.g.ow);
+    if (b.chunk == 0) return hipErrorInvalidValue;
+    a.chunk = static_cast<int>(b.chunk);
+    a.pitch = b.pitch;
+    a.left = b.left;
+    a.band_bytes = static_cast<int>(b.band_bytes);
+    a.alpha = alpha; a.beta = beta;
+    a.by_taps = reciprocal(s.kernel_h * s.kernel_w);
+    a.by_kw = reciprocal(s.kernel_w);
+    a.by_row = reciprocal(s.width / b.v);
+    a.by_ow = reciprocal(a.g.ow);
+    a.line_step = static_cast<int>(kThreads / (s.width / b.v));
+    const int64_t across_m = ceil_div(a.positions, 32), across_n = ceil_div(filters, 32), groups = across_m * across_n;
+    a.share = static_cast<int>(groups / 8);
+    a.rest = static_cast<int>(groups % 8);
+    a.positions_first = across_m <= across_n ? 1 : 0;
+    a.minor = static_cast<int>(a.positions_first ? across_m : across_n);
+    const int lds = static_cast<int>(b.lds_bytes);
+    if (dtype == MG_F32) {
+        if (b.v == 4) return launch<float, 4>(a, lds, stream);
+        return b.v == 2 ? launch<float, 2>(a, lds, stream) : launch<float, 1>(a, lds, stream);
+    }
+    if (b.v == 8) return launch<_Float16, 8>(a, lds, stream);
+    if (b.v == 4) return launch<_Float16, 4>(a, lds, stream);
+    return b.v == 2 ? launch<_Float16, 2>(a, lds, stream) : launch<_Float16, 1>(a, lds, stream);
+}
+
+}  // namespace mg

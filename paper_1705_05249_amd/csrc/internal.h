@@ -100,6 +100,11 @@ int64_t conv_out_extent(int64_t size, int64_t kernel, int64_t pad, int64_t strid
 // dtype: mg_dtype.  The column matrix must have fewer than 2^31 elements.
 hipError_t launch_im2col(int dtype, const ConvShape &s, const void *im, void *col, hipStream_t stream);
 
+// The whole convolution in one launch (conv_gather.hip): positions x filters outputs, out (filters x positions, row-major) = alpha * ... + beta * out
+bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters);
+hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,
+                              void *out, hipStream_t stream);
+
 // Support kernels of the GEMM-derived level-3 routines.  Matrices are seen in the column-major view of
 // their bytes (element (i, j) at p[i + j*ld]); dtype: mg_dtype.  What lies between the columns of a destination may be written.
 // dst <- the whole symmetric n x n matrix from its stored lower (i >= j) or upper triangle

@@ -1,0 +1,75 @@
+"""Convolutions in one launch from a band of the image in LDS (csrc/conv_gather.hip): output positions and filters beside the 32 x 32 blocks, every
+width of the band's pieces, sums that end inside a K-step, bands in several chunks of channels, padding, stride and dilation, against the CPU
+oracle, bit for bit on integers; the calls that keep their former routes."""
+import pytest
+
+import helpers as H
+from paper_1705_05249_amd import gemm as G
+from paper_1705_05249_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def CO():
+    from oracle import conv_oracle
+    return conv_oracle
+
+
+def kernels(dtype, *geo, beta=0.0):
+    """names of the kernels that one call launches"""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    case = W.conv_case(dtype, *geo, beta=beta)
+    im, w, out = H.to_gpu(case.im), H.to_gpu(case.weights), H.to_gpu(case.out)
+    code = G.MG_F32 if dtype == "f32" else G.MG_F16
+    args = (case.channels, case.height, case.width, case.kernel, case.pad, case.stride, case.dilation)
+    ws = torch.empty(max(256, G.mg_conv2d_workspace_bytes(code, *args, case.filters)), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as record:
+        (G.mg_sconv2d if dtype == "f32" else G.mg_hconv2d)(*args, case.filters, case.alpha, im, w, case.beta, out, ws)
+        torch.cuda.synchronize()
+    return [e.name for e in record.events() if "mg::" in e.name or "_ZN2mg" in e.name]
+
+
+GEO = [
+    # channels, height, width, kernel, pad, stride, dilation, filters
+    (16, 8, 8, (3, 3), (1, 1), (1, 1), (1, 1), 32),         # 64 positions; pieces of eight (FP16), four (FP32)
+    (16, 5, 12, (3, 3), (1, 1), (1, 1), (1, 1), 33),        # 60 positions, 33 filters; pieces of four
+    (7, 9, 14, (3, 3), (1, 1), (2, 2), (1, 1), 31),         # 35 positions, 63 terms; pieces of two, stride
+    (3, 7, 7, (7, 7), (3, 3), (2, 2), (1, 1), 5),           # single elements, wide padding, 147 terms
+    (1, 1, 1, (1, 1), (1, 1), (1, 1), (1, 1), 1),           # one term, nine positions, eight of them padding
+    (2, 33, 3, (3, 1), (1, 0), (1, 1), (2, 1), 40),         # three positions a row: the band of a block is a dozen rows; dilation down
+    (5, 6, 40, (2, 5), (0, 4), (3, 2), (1, 2), 64),         # dilation across, padding wider than the filter's half
+    (65, 7, 7, (3, 3), (1, 1), (1, 1), (1, 1), 32),         # 585 terms: the last K-step is partial
+    (9, 2, 136, (3, 3), (1, 1), (1, 1), (1, 1), 16),        # most blocks begin and end inside a row
+    (182, 19, 8, (1, 1), (2, 1), (4, 4), (1, 1), 33),       # the band comes in two chunks of channels, the second one smaller
+]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("geo", GEO)
+def test_blocks_bands_and_sums(CO, dtype, geo):
+    for integer in (True, False):
+        case = W.conv_case(dtype, *geo, alpha=1.0 if integer else 0.75, beta=1.0 if integer else -0.5, case=11, integer=integer)
+        H.check_conv(case, CO, "auto")
+    ran = kernels(dtype, *geo)
+    assert len(ran) == 1 and "conv_gather" in ran[0], ran
+
+
+def test_infinite_pixels_stay_where_they_are(CO):
+    """an infinite pixel reaches the outputs that see it, no other: nothing multiplies zeros from outside the sum with it"""
+    import numpy as np
+    case = W.conv_case("f32", 3, 9, 9, (3, 3), (1, 1), (1, 1), (1, 1), 4, beta=0.0, case=2)
+    case.im.reshape(3, 9, 9)[1, 4, 4] = np.inf
+    out = H.run_conv(case, "auto").reshape(4, 9, 9)
+    seen = np.zeros((9, 9), bool)
+    seen[3:6, 3:6] = True
+    assert np.isinf(out[:, seen]).all() and np.isfinite(out[:, ~seen]).all()
+
+
+@pytest.mark.parametrize("dtype,geo", [("f16", (64, 93, 93, (3, 3), (1, 1), (1, 1), (1, 1), 261)), ("f32", (16, 63, 63, (3, 3), (1, 1), (1, 1), (1, 1), 448)),
+                                       ("f16", (512, 7, 7, (3, 3), (1, 1), (1, 1), (1, 1), 512))])
+def test_larger_layers_keep_the_unfold_route(dtype, geo):
+    """22 / 65, 15 / 21 and 17.6 / 20.8 us"""
+    assert any("im2col" in name for name in kernels(dtype, *geo))
