@@ -226,26 +226,20 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         }
         if (*kernel >= 0) return;
     }
-    // Problems of at most one 32 x 32 block per compute unit and a short sum: the kernel whose eight wavefronts share
-    // the sum of one block (tiny.hip) beats the macro tiles' software pipeline, which never fills, and saves the
-    // second launch of a sliced sum.  Measured, shared-sum kernel against the best macro tile (with slices), us:
-    // FP32 256^3 4.8 / 6.8, 512^3 7.0 / 9.7, (256 | 384 | 512)^2 x 768: 8.9 / 9.2 | 10.0 | 10.8, x 1024: 11.3 / 10.0 |
-    // 13.8 | 11.8, x 1536: 15.3 / 11.4 | 15.3 | 14.2; FP16 with B along k, (256^2 | 384^2 | 512^2 | 512 x 196 |
-    // 256 x 784) x 1024: 5.8 / 6.7 | 5.8 / 6.6 | 6.1 / 6.7 | 5.8 | 5.9, x 2048: 8.7 / 9.0 | 8.8 / 8.9 | 9.6 / 9.7 |
-    // 8.7 / 10.7 | 8.8 / 12.9, x 3072: 11.6 / 10.3 | 11.6 / 13.1 | 12.4 / 11.2 | 11.6 / 11.5 | 13.7 / 14.2.
+    // Problems of at most one 32 x 32 block per compute unit: the kernel whose eight wavefronts share the sum of one block (tiny.hip) beats the
+    // macro tiles' software pipeline, which never fills, and saves the second launch of a sliced sum, until its eight shares grow longer
+    // than those of slices.  Its time over that of the best macro tile with any slices, geometric means over 260 problems of up to 256 blocks in
+    // all orders: FP32 of up to 128 terms 0.75, 256 0.62, 512 0.61, 768 0.69, 1024 0.80, 1536 0.90 (2048 1.12 on up to 64 blocks, 0.84 on
+    // more; 2560 1.10); FP16 0.98 up to 256, 512 0.94, 768 0.85, 1024 0.78, 1536 0.82, 2048 0.81, 2560 0.84 (3072 0.93, 4096 0.94, beyond
+    // 1.2), where the time of ranking the tiles, 0.5 us, comes on top.  More blocks than compute units: 1.2 to 1.8.
     // (with fringe rows / columns taken off, the tiles cover tm x tn of C)
     const int64_t tm = p.m - p.fringe_m, tn = p.n - p.fringe_n;
     const int64_t blocks32 = ceil_div(p.m, 32) * ceil_div(p.n, 32);
     const char *order_tag = p.a_trans ? (p.b_trans ? "kn" : "kk") : (p.b_trans ? "mn" : "mk");
     const bool few_blocks = p.shape == MG_SHAPE_GENERAL && blocks32 <= kComputeUnits && p.m > 1 && p.n > 1;
-    if (f32 && few_blocks && p.k >= 64 && p.k <= (blocks32 > 64 ? 1024 : 768)) {
+    if (few_blocks && p.k >= 48 && p.k <= (f32 ? (blocks32 > 64 ? 2048 : 1536) : 2560)) {
         char name[48];
-        snprintf(name, sizeof name, "stiny_32x32_%s", order_tag);
-        if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
-    }
-    if (!f32 && few_blocks && !p.b_trans && p.k >= 768 && p.k <= 2560) {
-        char name[48];
-        snprintf(name, sizeof name, "htiny_32x32_%s", order_tag);
+        snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
     }
     if (p.m >= 16 && p.n >= 16) {
@@ -499,8 +493,6 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             int slices;                      // 0: not a candidate
             double time;
         } ranked[14] = {};
-        double free_time = 0.0;              // best estimate with all the workspace one could wish for, and its slices
-        int free_slices = 0;
         const bool in_place = p.clip_m != 0 || p.clip_n != 0;
         for (int i = 0; i < count; ++i) {
             // (short sums are the traffic of C, which the small tiles overlap better: (3870, 5248, 64) 45.7 / 40.0 us on the 64 x 64 tile of the
@@ -561,7 +553,6 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // 2803 178 / 205, 3345 x 3792 372 / 407, 954 x 728 18.9 / 22.4, 785 x 1056 23.5 / 25.6; more slices on the FP32 pipes for more than 7 %)
                 const double sliced = narrowed ? 1.25 : (f32 && triangle ? (sl == 2 ? 1.2 : (i < kSplit ? 1.07 : 1.0)) : 1.0);
                 const double time = sl == 1 ? unsliced : estimate(i, sl) * sliced;
-                if (free_slices == 0 || time < free_time) { free_slices = sl; free_time = time; }
                 if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
                 if (ranked[i].slices == 0 || time < ranked[i].time) ranked[i] = Ranked{sl, time};
             }
@@ -573,14 +564,6 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (best < 0) break;
             const int want = ranked[best].slices;
             const double best_time = ranked[best].time;
-            // FP16, other orders and shorter sums: where the macro tiles would cut a sum of at most three 512-wide chunks
-            // into slices (a second launch that adds the partial sums), the shared-sum kernel does it in one
-            // (whether or not the caller brought the workspace for the slices)
-            if (!f32 && attempt == 0 && free_slices > 1 && p.shape == MG_SHAPE_GENERAL && blocks32 <= kComputeUnits && p.k <= 1536) {
-                char name[48];
-                snprintf(name, sizeof name, "htiny_32x32_%s", order_tag);
-                if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
-            }
             // FP16 products with a triangular C are ranked by the tiles that touch it (us, ranked as all of C / now: 2048^3 25 / 17,
             // 2560^3 36 / 24, 3584 x 1024 33 / 20, 4096^3 84 both).  A triangular operand (unequal K ranges) is ranked like
             // the general problem (TRMM, us, before the kernels with three and four stages / with them: 1536 25.5 / 21.4, 2048 30.5 /

@@ -3,18 +3,26 @@
 // what it costs on the macro-tile kernel is one wavefront's chain of dependent MFMAs over all of K (32 cycles per
 // k: 4 us at k = 256) behind a software pipeline that needs several K-tiles to fill.
 //
-// Here a work-group owns one 32 x 32 block of C and its eight wavefronts share the sum: the whole K range of both
-// operand panels (in chunks of 1 KB per row: 256 floats / 512 halves) is brought into LDS with every thread loading,
-// wavefront w takes K-steps w, w + 8, ... of it, and the eight partial blocks are added through LDS by all 512
-// threads, which also apply alpha and beta and write C.  One launch, no workspace, any shape and alignment (rows
-// and k values outside the matrices are zero in LDS; stores are masked); four times as many work-groups as 64 x 64
-// tiles would give, each with an eighth of the dependent chain.
+// Here a work-group owns one 32 x 32 block of C and its eight wavefronts share the sum: each takes an eighth of it, asks for all of its
+// operands at once, turns them into MFMA operands through a part of LDS of its own (no barrier: the LDS executes a wavefront's operations in
+// order), and the eight partial blocks are added through LDS by all 512 threads, which also apply alpha and beta and write C.  One
+// launch, no workspace, any shape and alignment; four times as many work-groups as 64 x 64 tiles would give, each with
+// an eighth of the dependent chain.
 //
-// LDS: [A rows 0..31][B rows 0..31], 1 KB per row, the 16-byte chunk c of row r at slot c ^ (r % 16) (a fragment
-// read is 16 rows at one chunk per pass: 16 different slots).  An operand that is not contiguous along k: FP32 stays
-// as in memory ([k][row], 128 bytes per k) and a fragment is four 4-byte reads; FP16 is turned in registers on its
-// way into LDS (a thread loads four k lines of eight rows and stores eight 8-byte pieces [row][4 k]).  Up to three
-// chunks are on their way from memory at once.
+// Bound by latency, and for long sums by what a compute unit's L1 passes on (64 bytes a clock: 1.9 us for a block of (512, 196, 2304)).  Before,
+// the work-group brought 1 KB of every row at a time into LDS, three chunks on their way and two barriers for each.  us, before / now (A along
+// m and B along k): FP32 256^3 4.7 / 4.3, 512^3 7.1 / 6.1, 384 x 384 x 1024 11.4 / 8.9, (33, 65, 999) 12.1 / 9.1; FP16 (512, 196, 2304) 10.0 / 6.9
+// (both along k 8.7 / 6.2, neither 16.8 / 8.2), (256, 784, 1152) 7.0 / 5.4, 512 x 512 x 1536 8.0 / 6.2, 64 x 320 x 2560 9.9 / 6.7.
+//
+// The sum is cut into pairs of K-steps, 128 bytes of a row (64 halves, 32 floats).  MFMA blocks are 16 x 16, four to a wavefront.  A pair of an operand:
+//   * along k: 32 rows of 128 bytes, eight lanes on a row: whole cache lines (16 rows of 64 bytes at a time, straight into operand registers,
+//     took FP32 384 x 384 x 1024 from 10.7 to 14.3 us, both operands along k); LDS [row][k], chunk c of row r at slot c ^ swizzle16(r);
+//   * FP16 along its rows: 64 lines of 64 bytes; LDS as in memory, chunk c of line k at slot c ^ 2 (k / 8 % 2), read by two transposing reads
+//     per block (the 32 lanes of a pass hit 64 different banks);
+//   * FP32 along its rows: four 4-byte loads per block and K-step, runs of 64 bytes, straight into the operand registers.
+// Rows past the last one repeat it (they end in outputs that C does not have).  Behind the whole pairs is a partial one with loads that are
+// checked piece by piece; it also takes the last line of an operand along its rows whose last piece would run past the operand's end.
+#include "mfma_dma_kernel.h"
 #include "mfma_host.h"
 
 namespace mg {
@@ -30,16 +38,142 @@ struct TinyArgs {
     float alpha, beta;
 };
 
-constexpr int kRowBytes = 1024;
-constexpr int kPanelBytes = 32 * kRowBytes;
+constexpr int kPairBytes = 32 * 128;                     // LDS bytes of a pair of K-steps of one operand
+constexpr int kWaves = 8;
+
+template <typename T, bool KCONTIG> struct TinySide {
+    static constexpr int CH = ElemTraits<T>::CH;            // elements per 16-byte piece
+    static constexpr int STEP = 4 * CH, PAIR = 2 * STEP;    // values of k per K-step and pair
+    static constexpr bool HALF = sizeof(T) == 2;
+    static constexpr bool TURNED = KCONTIG || HALF;         // through LDS
+    static constexpr int PIECES = 4;                        // 16-byte pieces of a pair per lane
+
+    // Addresses are a wave-uniform part (64 bits, scalar) and a lane's byte offset that is the same for every pair.
+    const char *base;           // the block's first row at pair 0 of this wavefront
+    int64_t ld;                 // bytes
+    int rows_left;              // rows of the operand behind the block's first one
+    int row, k;                 // of this lane's first piece or element: row of the block and value of k inside the pair
+    uint32_t at[KCONTIG ? PIECES : (HALF ? 1 : 2)];
+
+    // lane's piece i of a pair: along k, row lane / 8 + 8 i, chunk lane % 8; else line lane / 4 + 16 i, chunk lane % 4
+    __device__ inline void prepare(const void *data, int64_t ld_, int rows, int row0, int64_t k0, int lane)
+    {
+        ld = ld_ * static_cast<int64_t>(sizeof(T));
+        rows_left = rows - 1 - row0;
+        base = static_cast<const char *>(data) + (KCONTIG ? row0 * ld + k0 * static_cast<int64_t>(sizeof(T)) : row0 * static_cast<int64_t>(sizeof(T)) + k0 * ld);
+        if constexpr (KCONTIG) {
+            row = lane / 8;
+            k = lane % 8 * CH;
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) at[i] = static_cast<uint32_t>(existing(row + 8 * i) * ld + k * static_cast<int>(sizeof(T)));
+        } else if constexpr (HALF) {
+            row = lane % 4 * CH;
+            row = row <= rows_left ? row : 0;          // (a piece without rows: the first one again)
+            k = lane / 4;
+            at[0] = static_cast<uint32_t>(row * 2 + k * ld);
+        } else {
+            row = lane % 16;
+            k = lane / 16 * 4;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) at[b] = static_cast<uint32_t>(existing(row + 16 * b) * 4 + k * ld);
+        }
+    }
+    __device__ inline int existing(int r) const { return r < rows_left ? r : rows_left; }
+
+    // wave-uniform address of pair number `pair` of this wavefront, `l` values of k on
+    __device__ inline const char *line(int pair, int l) const
+    {
+        const int64_t from = static_cast<int64_t>(pair) * PAIR + l;
+        return base + (KCONTIG ? from * static_cast<int64_t>(sizeof(T)) : from * ld);
+    }
+    __device__ static inline const T *element(const char *uniform, uint32_t lane_offset) { return reinterpret_cast<const T *>(uniform + lane_offset); }
+
+    // FP32 along its rows: the pairs from `pair` on by buffer loads, whose scalar offsets take the place of 64-bit addresses in vector registers
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ inline void aim(int pair)
+    {
+        if constexpr (!TURNED) rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(line(pair, 0)), 0, 0x7fffffff, 0x00020000);
+    }
+
+    // pair number `pair` of this wavefront, the J-th behind the one aimed at
+    template <int J> __device__ inline void fetch(u32x4 (&f)[PIECES], int pair) const
+    {
+        if constexpr (KCONTIG) {
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) f[i] = load_unaligned_chunk<T>(element(line(pair, 0), at[i]));
+        } else if constexpr (HALF) {
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) f[i] = load_unaligned_chunk<T>(element(line(pair, 16 * i), at[0]));
+        } else {
+            // operand 2 s + b: K-step s, block b
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    f[i][e] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at[i % 2], static_cast<uint32_t>(ld) * (J * PAIR + i / 2 * STEP + e), 0);
+        }
+    }
+
+    // the partial pair behind `pair` pairs of this wavefront, with `left` values of k
+    __device__ inline void fetch_rest(u32x4 (&f)[PIECES], int pair, int left) const
+    {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if constexpr (KCONTIG) {
+                const T *p = element(line(pair, 0), at[i]);
+                if (left - k >= CH) v = load_unaligned_chunk<T>(p);
+                else if (left - k > 0) v = gather_chunk<T>(p, left - k);
+            } else if constexpr (HALF) {
+                const T *p = element(line(pair, 16 * i), at[0]);
+                const int valid = rows_left + 1 - row;
+                if (k + 16 * i < left) v = valid >= CH ? load_unaligned_chunk<T>(p) : gather_chunk<T>(p, valid);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (i / 2 * STEP + k + e < left) v[e] = elem_bits<T>(*element(line(pair, i / 2 * STEP + e), at[i % 2]));
+            }
+            f[i] = v;
+        }
+    }
+
+    // pieces -> operands: f[2 s + b] becomes K-step s of block b
+    __device__ inline void turn(u32x4 (&f)[PIECES], lds_char *mine, int lane) const
+    {
+        if constexpr (TURNED) {
+            using lds_u32x4 = __attribute__((address_space(3))) u32x4;
+            const int ln = lane % 16, lg = lane / 16;
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) {
+                const int to = KCONTIG ? ldsmap::kcontig_slot<16>(lane / 8 + 8 * i, lane % 8)
+                                       : (lane / 4 + 16 * i) * 64 + (((lane % 4) ^ (2 * (((lane / 4) >> 3) & 1))) << 4);
+                *(lds_u32x4 *)(mine + to) = f[i];
+            }
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) {
+                const int s = i / 2, b = i % 2;
+                if constexpr (KCONTIG) {
+                    f[i] = *(lds_u32x4 *)(mine + ldsmap::kcontig_slot<16>(16 * b + ln, 4 * s + lg));
+                } else {
+                    const int quad = ln % 4, line = 32 * s + 8 * lg + ln / 4;
+                    lds_char *const p = mine + line * 64 + (((2 * b + quad / 2) ^ (2 * (lg & 1))) << 4) + 8 * (quad % 2);
+                    const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)p);
+                    const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(p + 4 * 64));
+                    f[i] = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                }
+            }
+        }
+    }
+};
 
 template <typename T, bool A_KCONTIG, bool B_KCONTIG>
-__global__ __launch_bounds__(512) void tiny_gemm_kernel(const TinyArgs a)
+__global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a)
 {
-    constexpr int CH = ElemTraits<T>::CH;                  // elements per 16-byte chunk
-    constexpr int KC = kRowBytes / static_cast<int>(sizeof(T));     // k values per chunk of the K range
-    constexpr int STEPS = KC / (2 * CH);                   // K-steps per chunk: 32
-    constexpr int LOADS = 2 * kPanelBytes / 16 / 512;     // 16-byte pieces per thread and chunk: 8
+#if defined(__HIP_DEVICE_COMPILE__)      // the host pass needs the kernel's symbol only (LDS address-space code is device code)
+    using SideA = TinySide<T, A_KCONTIG>;
+    using SideB = TinySide<T, B_KCONTIG>;
+    constexpr int PAIR = SideA::PAIR;
+    constexpr int NP = sizeof(T) == 4 ? 4 : 5;          // pairs whose loads are in flight together: FP32 sums up to 1024, FP16 up to 2560
     extern __shared__ __attribute__((aligned(16))) char lds[];
 
     const int tid = threadIdx.x, lane = tid % 64;
@@ -50,81 +184,19 @@ __global__ __launch_bounds__(512) void tiny_gemm_kernel(const TinyArgs a)
     const int xcd = blockIdx.x % 8;
     const int id = xcd * a.share + (xcd < a.rest ? xcd : a.rest) + blockIdx.x / 8;
     const int outer = id / a.minor, inner = id - outer * a.minor;
-    const int64_t m0 = static_cast<int64_t>(a.n_first ? outer : inner) * 32, n0 = static_cast<int64_t>(a.n_first ? inner : outer) * 32;
-    const T *A = static_cast<const T *>(a.A);
-    const T *B = static_cast<const T *>(a.B);
+    const int m0 = (a.n_first ? outer : inner) * 32, n0 = (a.n_first ? inner : outer) * 32;
 
-    // piece q = tid + 512 i of a chunk (i = 0 .. 7): operand q / 2048; k-contiguous operand: row (q % 2048) / 64, chunk q % 64;
-    // else line (q % 2048) / CPL of k, row chunk q % CPL (CPL = 32 rows / CH per line)
-    // up to DEPTH chunks are on their way at once (the whole K range of most problems this kernel is selected for:
-    // one memory latency instead of one per chunk)
-    constexpr int DEPTH = 3;
-    u32x4 regs[DEPTH][LOADS];
-    auto load_chunk = [&](auto SLOT, int k0) __attribute__((always_inline)) {
-        constexpr int slot = decltype(SLOT)::value;
-        static_for<LOADS>([&](auto I) __attribute__((always_inline)) {
-            constexpr int i = decltype(I)::value;
-            constexpr bool is_b = i >= LOADS / 2;              // pieces 0 .. 2047 are A's, the rest B's
-            const int rem = tid + 512 * (i % (LOADS / 2));
-            constexpr bool kcontig = is_b ? B_KCONTIG : A_KCONTIG;
-            const T *X = is_b ? B : A;
-            const int64_t row0 = is_b ? n0 : m0;
-            const int rows = is_b ? a.n : a.m;
-            const int64_t s_row = is_b ? a.b_sn : a.a_sm, s_k = is_b ? a.b_sk : a.a_sk;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if constexpr (kcontig) {
-                const int r = rem / 64, c = rem % 64;
-                const int64_t row = row0 + r;
-                const int kv = a.k - (k0 + c * CH);
-                if (row < rows && kv > 0) {
-                    const T *p = X + row * s_row + (k0 + c * CH);
-                    v = kv >= CH ? load_unaligned_chunk<T>(p) : gather_chunk<T>(p, kv);
-                }
-            } else {
-                constexpr int CPL = 32 / CH;
-                // FP16: the four pieces of a thread are four consecutive k lines of the same eight rows, so that the
-                // thread can turn them in registers (store_chunk); FP32: piece rem of the panel as it lies in memory
-                const int line = sizeof(T) == 2 ? 4 * (tid / CPL) + i % (LOADS / 2) : rem / CPL;
-                const int c = sizeof(T) == 2 ? tid % CPL : rem % CPL;
-                const int64_t row = row0 + c * CH;
-                const int rv = static_cast<int>(rows - row);
-                if (k0 + line < a.k && rv > 0) {
-                    const T *p = X + row + static_cast<int64_t>(k0 + line) * s_k;
-                    v = rv >= CH ? load_unaligned_chunk<T>(p) : gather_chunk<T>(p, rv);
-                }
-            }
-            regs[slot][i] = v;
-        });
-    };
-    auto store_chunk = [&](auto SLOT) __attribute__((always_inline)) {
-        constexpr int slot = decltype(SLOT)::value;
-        static_for<LOADS>([&](auto I) __attribute__((always_inline)) {
-            constexpr int i = decltype(I)::value;
-            constexpr bool is_b = i >= LOADS / 2;
-            const int rem = tid + 512 * (i % (LOADS / 2));
-            constexpr bool kcontig = is_b ? B_KCONTIG : A_KCONTIG;
-            char *panel = lds + (is_b ? kPanelBytes : 0);
-            if constexpr (kcontig) {
-                const int r = rem / 64, c = rem % 64;
-                *reinterpret_cast<u32x4 *>(panel + r * kRowBytes + ((c ^ (r & 15)) << 4)) = regs[slot][i];
-            } else if constexpr (sizeof(T) == 4) {
-                // FP32: the panel stays as in memory, [k][row] in lines of 128 bytes (piece rem is simply at rem * 16);
-                // the fragment reads gather their four k values (each a conflict-free read of 32 consecutive rows)
-                *reinterpret_cast<u32x4 *>(panel + rem * 16) = regs[slot][i];
-            } else if constexpr (i % (LOADS / 2) == 0) {
-                // FP16 along m / n: this thread holds k lines 4 g .. 4 g + 3 of rows 8 c .. 8 c + 7 (pieces i .. i + 3);
-                // turned in registers they are eight 8-byte pieces [row][4 k]
-                constexpr int CPL = 32 / CH;
-                const int g = tid / CPL, c = tid % CPL;
-                static_for<CH>([&](auto J) {
-                    constexpr int j = decltype(J)::value;
-                    const u32x4 t = transposed_row<j, 4>(&regs[slot][i], T{});
-                    const int r = c * CH + j;
-                    *reinterpret_cast<uint2 *>(panel + r * kRowBytes + (((g / 2) ^ (r & 15)) << 4) + (g % 2) * 8) = uint2{t[0], t[1]};
-                });
-            }
-        });
-    };
+    // whole pairs, an eighth to each wavefront; the partial one is the last wavefront's
+    const bool runs_over = (!A_KCONTIG && SideA::HALF && a.m % SideA::CH != 0) || (!B_KCONTIG && SideB::HALF && a.n % SideB::CH != 0);
+    const int pairs = (a.k - (runs_over ? 1 : 0)) / PAIR, share = (pairs + kWaves - 1) / kWaves;
+    const int begin = wave * share < pairs ? wave * share : pairs, count = begin + share < pairs ? share : pairs - begin;
+    const int left = wave == kWaves - 1 ? a.k - pairs * PAIR : 0;
+    SideA sa;
+    SideB sb;
+    sa.prepare(a.A, A_KCONTIG ? a.a_sm : a.a_sk, a.m, m0, static_cast<int64_t>(begin) * PAIR, lane);
+    sb.prepare(a.B, B_KCONTIG ? a.b_sn : a.b_sk, a.n, n0, static_cast<int64_t>(begin) * PAIR, lane);
+    lds_char *const mine_a = (lds_char *)lds + wave * (SideA::TURNED + SideB::TURNED) * kPairBytes;
+    lds_char *const mine_b = mine_a + SideA::TURNED * kPairBytes;
 
     // this thread's two elements of C (row tid % 32, columns tid / 32 and + 16): the old values are asked for now
     T *C = static_cast<T *>(a.C);
@@ -136,66 +208,74 @@ __global__ __launch_bounds__(512) void tiny_gemm_kernel(const TinyArgs a)
         mine[i] = m0 + mi < a.m && n0 + ni < a.n;
         if (mine[i] && a.beta != 0.f) old[i] = load_as_float(C + (m0 + mi) + (n0 + ni) * a.ldc);
     }
-    floatx16 acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const int ln = lane % 32, lg = lane / 32;
-    const int chunks = (a.k + KC - 1) / KC;
-    static_for<DEPTH>([&](auto D) {
-        if (decltype(D)::value < chunks) load_chunk(D, decltype(D)::value * KC);
-    });
-    for (int base = 0; base < chunks; base += DEPTH) {
-        static_for<DEPTH>([&](auto D) {
-            const int ch = base + decltype(D)::value;
-            if (ch >= chunks) return;
-            if (ch > 0) __syncthreads();                       // everyone is done with the chunk before
-            store_chunk(D);
-            __syncthreads();
-            if (ch + DEPTH < chunks) load_chunk(D, (ch + DEPTH) * KC);
-            const int left = a.k - ch * KC;
-            const int steps = left >= KC ? STEPS : (left + 2 * CH - 1) / (2 * CH);
-            // this wavefront's K-steps of the chunk: all fragments first (one LDS latency), then the chain of MFMAs
-            u32x4 fa[STEPS / 8], fb[STEPS / 8];
-#pragma unroll
-            for (int j = 0; j < STEPS / 8; ++j) {
-                const int s = wave + 8 * j;
-                const int c = 2 * s + lg;
-                const int off = ln * kRowBytes + ((c ^ (ln & 15)) << 4);
-                if (s < steps) {
-                    auto fragment = [&](auto KCONTIG, const char *panel) {
-                        if constexpr (decltype(KCONTIG)::value || sizeof(T) != 4) {
-                            return *reinterpret_cast<const u32x4 *>(panel + off);
-                        } else {
-                            const uint32_t *line = reinterpret_cast<const uint32_t *>(panel + (c * 4) * 128 + ln * 4);
-                            return u32x4{line[0], line[32], line[64], line[96]};
-                        }
-                    };
-                    fa[j] = fragment(std::integral_constant<bool, A_KCONTIG>{}, lds);
-                    fb[j] = fragment(std::integral_constant<bool, B_KCONTIG>{}, lds + kPanelBytes);
-                }
+    floatx4 acc[2][2] = {};             // [n][m]
+    auto multiply = [&](u32x4 (&x)[4], u32x4 (&y)[4]) __attribute__((always_inline)) {
+        sa.turn(x, mine_a, lane);
+        sb.turn(y, mine_b, lane);
+        static_for<2>([&](auto S) __attribute__((always_inline)) {
+            constexpr int s = 2 * decltype(S)::value;
+            if constexpr (sizeof(T) == 2) {
+                mma(acc[0][0], y[s], x[s], T{});
+                mma(acc[0][1], y[s], x[s + 1], T{});
+                mma(acc[1][0], y[s + 1], x[s], T{});
+                mma(acc[1][1], y[s + 1], x[s + 1], T{});
+            } else {
+                // (whole-vector casts and named components, see mma; the four blocks in turn: an instruction does not wait for the one before)
+                const floatx4 u0 = __builtin_bit_cast(floatx4, x[s]), u1 = __builtin_bit_cast(floatx4, x[s + 1]);
+                const floatx4 v0 = __builtin_bit_cast(floatx4, y[s]), v1 = __builtin_bit_cast(floatx4, y[s + 1]);
+                auto blocks = [&](float p, float q, float r, float t) __attribute__((always_inline)) {
+                    acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(p, r, acc[0][0], 0, 0, 0);
+                    acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(q, r, acc[0][1], 0, 0, 0);
+                    acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(p, t, acc[1][0], 0, 0, 0);
+                    acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(q, t, acc[1][1], 0, 0, 0);
+                };
+                blocks(u0.x, u1.x, v0.x, v1.x);
+                blocks(u0.y, u1.y, v0.y, v1.y);
+                blocks(u0.z, u1.z, v0.z, v1.z);
+                blocks(u0.w, u1.w, v0.w, v1.w);
             }
-#pragma unroll
-            for (int j = 0; j < STEPS / 8; ++j)
-                if (wave + 8 * j < steps) mma(acc, fb[j], fa[j], T{});
+        });
+    };
+    for (int done = 0; done < count; done += NP) {
+        u32x4 fa[NP][4], fb[NP][4];
+        sa.aim(done);
+        sb.aim(done);
+        static_for<NP>([&](auto J) __attribute__((always_inline)) {
+            constexpr int j = decltype(J)::value;
+            if (done + j < count) {
+                sa.template fetch<j>(fa[j], done + j);
+                sb.template fetch<j>(fb[j], done + j);
+            }
+        });
+        asm volatile("" ::: "memory");             // all loads first: merged with the products they would wait for each other
+        static_for<NP>([&](auto J) __attribute__((always_inline)) {
+            constexpr int j = decltype(J)::value;
+            if (done + j < count) multiply(fa[j], fb[j]);
         });
     }
-    // The eight partial blocks -> LDS as [wavefront][register][lane] (register 4 q + i of lane l is
-    // C(8 q + 4 (l / 32) + i, l % 32)); every thread adds the eight values of two (register, lane) pairs, hands the
+    if (left > 0) {
+        u32x4 x[4], y[4];
+        sa.fetch_rest(x, count, left);
+        sb.fetch_rest(y, count, left);
+        multiply(x, y);
+    }
+    // The eight partial blocks -> LDS as [wavefront][register][lane] (register 8 j + 4 i + r of lane l is
+    // C(16 i + 4 (l / 16) + r, 16 j + l % 16)); every thread adds the eight values of two (register, lane) pairs, hands the
     // sums on through a [column][row] staging area (33 floats per column: no bank conflicts either way), and writes
     // two elements of C, consecutive threads consecutive rows.
     __syncthreads();
     float *part = reinterpret_cast<float *>(lds);
-    float *stage = reinterpret_cast<float *>(lds + 8 * 16 * 64 * 4);
+    float *stage = reinterpret_cast<float *>(lds + kWaves * 16 * 64 * 4);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) part[(wave * 16 + r) * 64 + lane] = acc[r];
+    for (int r = 0; r < 16; ++r) part[(wave * 16 + r) * 64 + lane] = acc[r / 8][r / 4 % 2][r % 4];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int e = tid + 512 * i, r = e / 64, l = e % 64;
-        float s = 0.f;
+        float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) s += part[w * 1024 + e];
-        stage[(l % 32) * 33 + 8 * (r / 4) + 4 * (l / 32) + r % 4] = s;
+        for (int w = 0; w < kWaves; ++w) sum += part[w * 1024 + e];
+        stage[(16 * (r / 8) + l % 16) * 33 + 16 * (r / 4 % 2) + 4 * (l / 16) + r % 4] = sum;
     }
     __syncthreads();
 #pragma unroll
@@ -207,11 +287,16 @@ __global__ __launch_bounds__(512) void tiny_gemm_kernel(const TinyArgs a)
             store_from_float(C + (m0 + mi) + (n0 + ni) * a.ldc, o);
         }
     }
+#else
+    (void)a;
+#endif
 }
 
 template <typename T, bool AK, bool BKC> struct TinyConfig {
     static constexpr int DTYPE = sizeof(T) == 4 ? MG_F32 : MG_F16;
-    static constexpr int LDS = 2 * kPanelBytes;
+    static constexpr int SUMS = kWaves * 16 * 64 * 4 + 32 * 33 * 4;
+    static constexpr int PAIRS = kWaves * (TinySide<T, AK>::TURNED + TinySide<T, BKC>::TURNED) * kPairBytes;
+    static constexpr int LDS = PAIRS > SUMS ? PAIRS : SUMS;
 
     static bool legal(const Problem &p, int split, int64_t alignment)
     {
@@ -220,6 +305,8 @@ template <typename T, bool AK, bool BKC> struct TinyConfig {
         if (p.conv != nullptr || p.fringe_m != 0 || p.fringe_n != 0 || p.clip_m != 0 || p.clip_n != 0) return false;
         if (p.alpha == 0.f || p.k == 0 || p.shape != MG_SHAPE_GENERAL) return false;
         if (p.m >= (int64_t(1) << 31) || p.n >= (int64_t(1) << 31) || p.k >= (int64_t(1) << 31)) return false;
+        // (offsets inside the pairs of K-steps that are loaded together)
+        if ((p.lda > p.ldb ? p.lda : p.ldb) * 192 * static_cast<int64_t>(sizeof(T)) >= (int64_t(1) << 31)) return false;
         return ceil_div(p.m, 32) * ceil_div(p.n, 32) < (int64_t(1) << 31);
     }
 
@@ -253,7 +340,7 @@ template <typename T, bool AK, bool BKC> struct TinyConfig {
         mg_config c{};
         c.family = MG_FAMILY_MFMA;
         c.dtype = DTYPE;
-        c.tile_m = 32; c.tile_n = 32; c.tile_k = kRowBytes / static_cast<int>(sizeof(T));
+        c.tile_m = 32; c.tile_n = 32; c.tile_k = TinySide<T, AK>::PAIR;
         c.waves_m = 1; c.waves_n = 1;
         c.split_k = 1;
         c.threads = 512;

@@ -1,0 +1,48 @@
+"""The kernel whose eight wavefronts share the sum of one 32 x 32 block (csrc/tiny.hip): sums beside its pairs of K-steps and beside eight of them, blocks
+that end anywhere, pieces that would run past an operand's last line, all operand orders and alignments, against the CPU oracle, bit for bit on
+integers."""
+import pytest
+
+import helpers as H
+from paper_1705_05249_amd import gemm as G
+from paper_1705_05249_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+C, N, T = W.COL_MAJOR, W.NO_TRANS, W.TRANS
+ORDERS = {"mk": (N, N), "kk": (T, N), "mn": (N, T), "kn": (T, T)}
+
+
+@pytest.mark.parametrize("order", sorted(ORDERS))
+@pytest.mark.parametrize("dtype,pair", [("f32", 32), ("f16", 64)])
+@pytest.mark.parametrize("m,n,pairs,over,pad", [(32, 32, 1, 0, 0), (35, 29, 1, 0, 0), (3, 5, 0, 1, 0), (33, 64, 1, -1, 1), (64, 31, 8, 1, 3), (40, 48, 9, 0, 8),
+                                                (7, 100, 7, 5, 1), (65, 33, 41, -7, 0), (16, 70, 16, 0, 2)])
+def test_blocks_and_pairs(oracle, dtype, pair, order, m, n, pairs, over, pad):
+    ta, tb = ORDERS[order]
+    k = pairs * pair + over
+    lds = dict(lda=W.tight_ld(C, ta, m, k) + pad, ldb=W.tight_ld(C, tb, k, n) + pad, ldc=m + pad)
+    make = W.skinny_case if dtype == "f32" else W.hgemm_case
+    if dtype == "f32":
+        case = make(m, n, k, case=31, integer=True, ta=ta, tb=tb, alpha=1.0, beta=1.0)
+    else:
+        case = make(m, n, k, case=31, layout=C, ta=ta, tb=tb, beta=1.0, integer=True, **lds)
+    try:
+        G.mg_override_config(G.kernel_id(("s" if dtype == "f32" else "h") + "tiny_32x32_" + order), 1)
+        H.check_case(case, oracle)
+    finally:
+        G.mg_clear_override()
+
+
+@pytest.mark.parametrize("order", sorted(ORDERS))
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_beta_zero_leaves_nan_behind(oracle, dtype, order):
+    import numpy as np
+    ta, tb = ORDERS[order]
+    case = (W.skinny_case(45, 50, 201, case=3, integer=True, ta=ta, tb=tb, alpha=2.0, beta=0.0) if dtype == "f32"
+            else W.hgemm_case(45, 50, 201, case=3, ta=ta, tb=tb, beta=0.0, integer=True))
+    case.C[:] = np.nan
+    try:
+        G.mg_override_config(G.kernel_id(("s" if dtype == "f32" else "h") + "tiny_32x32_" + order), 1)
+        H.check_case(case, oracle)
+    finally:
+        G.mg_clear_override()
