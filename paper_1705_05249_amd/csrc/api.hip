@@ -472,6 +472,7 @@ mg_status run_batched(BatchedProblem &p, int layout, int ta, int tb, int64_t m, 
         if (!e.legal_batched || !e.legal_batched(p)) return MG_ERR_CONFIG;
         kernel = forced;
     } else {
+        if (batched_dma_pays(p)) return launch_batched_dma(p) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
         kernel = select_batched(t, p);
         if (kernel < 0) return MG_ERR_CONFIG;
     }

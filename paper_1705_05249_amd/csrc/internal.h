@@ -159,6 +159,10 @@ inline bool dma_offsets_fit(const Problem &p, int64_t tile_rows, int64_t tile_k)
     return (p.lda > p.ldb ? p.lda : p.ldb) * lines * static_cast<int64_t>(p.elem()) < (int64_t(1) << 31) - 4096;
 }
 
+// Strided batches of FP16 instances on the direct-to-LDS tiles (batched_dma.hip)
+bool batched_dma_pays(const BatchedProblem &p);
+hipError_t launch_batched_dma(const BatchedProblem &p);
+
 // One compiled kernel (or kernel family instance) in the configuration table.
 struct KernelEntry {
     const char *name;

@@ -163,10 +163,11 @@ template <int N> __device__ inline void hold_registers(const u32x4 (&f)[N])
     for (int i = 0; i < N; ++i) asm volatile("" ::"v"(f[i]));
 }
 
-template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int VARIANT = 0, bool CLIP = false, int STAGES = 2>
-__global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs args)
+#if defined(__HIP_DEVICE_COMPILE__)      // (LDS address-space code is device code: the host pass needs the kernels' symbols only)
+// The tile at (m0, n0) over the values kb .. ke of k.
+template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB, int VARIANT, bool CLIP, int STAGES>
+__device__ __forceinline__ void hgemm_dma_tile(const MfmaArgs &args, int64_t m0, int64_t n0, int kb, int ke)
 {
-#if defined(__HIP_DEVICE_COMPILE__)      // the host pass needs the kernel's symbol only (LDS address-space code is device code)
     using T = _Float16;
     // VARIANT: the diagnostic builds' switches (PROBE, 0 in every registered kernel) and 8: sizes that end inside a tile
     constexpr int PROBE = VARIANT & 7;
@@ -189,14 +190,6 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
     extern __shared__ __attribute__((aligned(16))) char lds[];
     lds_char *const lds3 = (lds_char *)lds;
 
-    int tm, tn;
-    if (args.shape == 0) tile_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, tm, tn);
-    else if (RAGGED && BM == BN && args.shape >= MG_SHAPE_C_LOWER) tile_coords_triangle(blockIdx.x, args.tiles_m, args.shape == MG_SHAPE_C_UPPER, tm, tn);
-    else tile_coords_balanced(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, args.reversed != 0, args.shape == MG_SHAPE_C_UPPER, tm, tn);
-    const int64_t m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
-    int kb = blockIdx.z * args.k_per_split;
-    int ke = (kb + args.k_per_split < args.k) ? kb + args.k_per_split : args.k;
-    if (!narrow_to_shape<BM, BN, BK>(args.shape, m0, n0, kb, ke)) return;
     const T *__restrict__ A = static_cast<const T *>(args.A);
     const T *__restrict__ B = static_cast<const T *>(args.B);
 
@@ -391,6 +384,24 @@ __global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs a
     } else {
         tile_epilogue<T, RB, FM, FN, WTM, WTN, (CLIP || RAGGED)>(acc, args, lds, m0, n0, wm, wn, wave, lane);       // CLIP: C may end inside the tile
     }
+}
+#endif
+
+template <int BM, int BN, int WM, int WN, bool A_KCONTIG, bool B_KCONTIG, int RB = 32, int VARIANT = 0, bool CLIP = false, int STAGES = 2>
+__global__ __launch_bounds__(WM *WN * 64) void hgemm_dma_kernel(const MfmaArgs args)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BK = 64;
+    constexpr bool RAGGED = (VARIANT & DMA_RAGGED) != 0;
+    int tm, tn;
+    if (args.shape == 0) tile_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, tm, tn);
+    else if (RAGGED && BM == BN && args.shape >= MG_SHAPE_C_LOWER) tile_coords_triangle(blockIdx.x, args.tiles_m, args.shape == MG_SHAPE_C_UPPER, tm, tn);
+    else tile_coords_balanced(blockIdx.x, args.tiles_m, args.tiles_n, args.group_m, args.reversed != 0, args.shape == MG_SHAPE_C_UPPER, tm, tn);
+    const int64_t m0 = static_cast<int64_t>(tm) * BM, n0 = static_cast<int64_t>(tn) * BN;
+    int kb = blockIdx.z * args.k_per_split;
+    int ke = (kb + args.k_per_split < args.k) ? kb + args.k_per_split : args.k;
+    if (!narrow_to_shape<BM, BN, BK>(args.shape, m0, n0, kb, ke)) return;
+    hgemm_dma_tile<BM, BN, WM, WN, A_KCONTIG, B_KCONTIG, RB, VARIANT, CLIP, STAGES>(args, m0, n0, kb, ke);
 #else
     (void)args;
 #endif
