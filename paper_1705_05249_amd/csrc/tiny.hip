@@ -11,7 +11,7 @@
 //
 // Bound by latency, and for long sums by what a compute unit's L1 passes on (64 bytes a clock: 1.9 us for a block of (512, 196, 2304)).  Before,
 // the work-group brought 1 KB of every row at a time into LDS, three chunks on their way and two barriers for each.  us, before / now (A along
-// m and B along k): FP32 256^3 4.7 / 4.3, 512^3 7.1 / 6.1, 384 x 384 x 1024 11.4 / 8.9, (33, 65, 999) 12.1 / 9.1; FP16 (512, 196, 2304) 10.0 / 6.9
+// m and B along k): FP32 256^3 4.7 / 4.3, 512^3 7.1 / 6.2, 384 x 384 x 1024 11.3 / 8.9, (33, 65, 999) 12.0 / 9.2, 128 x 128 x 500 6.7 both; FP16 (512, 196, 2304) 10.0 / 6.9
 // (both along k 8.7 / 6.2, neither 16.8 / 8.2), (256, 784, 1152) 7.0 / 5.4, 512 x 512 x 1536 8.0 / 6.2, 64 x 320 x 2560 9.9 / 6.7.
 //
 // The sum is cut into pairs of K-steps, 128 bytes of a row (64 halves, 32 floats).  MFMA blocks are 16 x 16, four to a wavefront.  A pair of an operand:
@@ -208,31 +208,34 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
         mine[i] = m0 + mi < a.m && n0 + ni < a.n;
         if (mine[i] && a.beta != 0.f) old[i] = load_as_float(C + (m0 + mi) + (n0 + ni) * a.ldc);
     }
-    floatx4 acc[2][2] = {};             // [n][m]
+    // [n][m]; FP32: four sets, by value of k modulo 4 of a lane's piece, added pairwise at the end.  A wavefront's share is whole pairs, so with one
+    // set a short sum would be chains of 32 terms on few wavefronts, and its error against 64 bits 1.4 times that of an eighth for each (k = 64).
+    constexpr int SETS = sizeof(T) == 4 ? 4 : 1;
+    floatx4 acc[SETS][2][2] = {};
     auto multiply = [&](u32x4 (&x)[4], u32x4 (&y)[4]) __attribute__((always_inline)) {
         sa.turn(x, mine_a, lane);
         sb.turn(y, mine_b, lane);
         static_for<2>([&](auto S) __attribute__((always_inline)) {
             constexpr int s = 2 * decltype(S)::value;
             if constexpr (sizeof(T) == 2) {
-                mma(acc[0][0], y[s], x[s], T{});
-                mma(acc[0][1], y[s], x[s + 1], T{});
-                mma(acc[1][0], y[s + 1], x[s], T{});
-                mma(acc[1][1], y[s + 1], x[s + 1], T{});
+                mma(acc[0][0][0], y[s], x[s], T{});
+                mma(acc[0][0][1], y[s], x[s + 1], T{});
+                mma(acc[0][1][0], y[s + 1], x[s], T{});
+                mma(acc[0][1][1], y[s + 1], x[s + 1], T{});
             } else {
                 // (whole-vector casts and named components, see mma; the four blocks in turn: an instruction does not wait for the one before)
                 const floatx4 u0 = __builtin_bit_cast(floatx4, x[s]), u1 = __builtin_bit_cast(floatx4, x[s + 1]);
                 const floatx4 v0 = __builtin_bit_cast(floatx4, y[s]), v1 = __builtin_bit_cast(floatx4, y[s + 1]);
-                auto blocks = [&](float p, float q, float r, float t) __attribute__((always_inline)) {
-                    acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(p, r, acc[0][0], 0, 0, 0);
-                    acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(q, r, acc[0][1], 0, 0, 0);
-                    acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(p, t, acc[1][0], 0, 0, 0);
-                    acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(q, t, acc[1][1], 0, 0, 0);
+                auto blocks = [&](floatx4 (&c)[2][2], float p, float q, float r, float t) __attribute__((always_inline)) {
+                    c[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(p, r, c[0][0], 0, 0, 0);
+                    c[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(q, r, c[0][1], 0, 0, 0);
+                    c[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(p, t, c[1][0], 0, 0, 0);
+                    c[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(q, t, c[1][1], 0, 0, 0);
                 };
-                blocks(u0.x, u1.x, v0.x, v1.x);
-                blocks(u0.y, u1.y, v0.y, v1.y);
-                blocks(u0.z, u1.z, v0.z, v1.z);
-                blocks(u0.w, u1.w, v0.w, v1.w);
+                blocks(acc[0], u0.x, u1.x, v0.x, v1.x);
+                blocks(acc[1], u0.y, u1.y, v0.y, v1.y);
+                blocks(acc[2], u0.z, u1.z, v0.z, v1.z);
+                blocks(acc[3], u0.w, u1.w, v0.w, v1.w);
             }
         });
     };
@@ -259,6 +262,12 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
         sb.fetch_rest(y, count, left);
         multiply(x, y);
     }
+    if constexpr (SETS == 4) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc[0][j][i] = (acc[0][j][i] + acc[1][j][i]) + (acc[2][j][i] + acc[3][j][i]);
+    }
     // The eight partial blocks -> LDS as [wavefront][register][lane] (register 8 j + 4 i + r of lane l is
     // C(16 i + 4 (l / 16) + r, 16 j + l % 16)); every thread adds the eight values of two (register, lane) pairs, hands the
     // sums on through a [column][row] staging area (33 floats per column: no bank conflicts either way), and writes
@@ -267,7 +276,7 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
     float *part = reinterpret_cast<float *>(lds);
     float *stage = reinterpret_cast<float *>(lds + kWaves * 16 * 64 * 4);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) part[(wave * 16 + r) * 64 + lane] = acc[r / 8][r / 4 % 2][r % 4];
+    for (int r = 0; r < 16; ++r) part[(wave * 16 + r) * 64 + lane] = acc[0][r / 8][r / 4 % 2][r % 4];
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {

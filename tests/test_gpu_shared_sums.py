@@ -46,3 +46,35 @@ def test_beta_zero_leaves_nan_behind(oracle, dtype, order):
         H.check_case(case, oracle)
     finally:
         G.mg_clear_override()
+
+
+@pytest.mark.parametrize("order", sorted(ORDERS))
+@pytest.mark.parametrize("k", [64, 96, 160, 288])
+def test_error_of_a_sum_shared_by_eight(order, k):
+    """FP32 error against 64 bits: at most that of eight equal parts of the sum, each added up term by term, and then each other's sums.
+
+    The parts are added up here with one rounding per term; the tenth on top is for another order of the terms.  Chains of 32 terms, on
+    as few wavefronts as that takes, have 1.36 times this error at k = 64 and 1.21 times at 288."""
+    import numpy as np
+    import torch
+    ta, tb = ORDERS[order]
+    rng = np.random.default_rng(7)
+    a = (rng.random((256, k)) * 2 - 1).astype(np.float32)
+    b = (rng.random((k, 256)) * 2 - 1).astype(np.float32)
+    exact = a.astype(np.float64) @ b.astype(np.float64)
+    total = np.zeros((256, 256), np.float32)
+    for part in np.array_split(np.arange(k), 8):
+        s = np.zeros((256, 256), np.float32)
+        for l in part:
+            s = (s.astype(np.float64) + np.outer(a[:, l].astype(np.float64), b[l].astype(np.float64))).astype(np.float32)
+        total += s
+    stored_a = torch.from_numpy(np.ascontiguousarray(a if ta == T else a.T)).cuda()
+    stored_b = torch.from_numpy(np.ascontiguousarray(b if tb == T else b.T)).cuda()
+    c = torch.zeros(256, 256, device="cuda")
+    try:
+        G.mg_override_config(G.kernel_id("stiny_32x32_" + order), 1)
+        G.mg_sgemm(C, ta, tb, 256, 256, k, 1.0, stored_a, k if ta == T else 256, stored_b, 256 if tb == T else k, 0.0, c, 256, None)
+    finally:
+        G.mg_clear_override()
+    error = lambda x: np.linalg.norm(x.astype(np.float64) - exact) / np.linalg.norm(exact)
+    assert error(c.cpu().numpy().T) <= 1.1 * error(total)
