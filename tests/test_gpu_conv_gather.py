@@ -73,3 +73,34 @@ def test_infinite_pixels_stay_where_they_are(CO):
 def test_larger_layers_keep_the_unfold_route(dtype, geo):
     """22 / 65, 15 / 21 and 17.6 / 20.8 us"""
     assert any("im2col" in name for name in kernels(dtype, *geo))
+
+
+def test_error_of_an_evenly_shared_sum():
+    """FP32, 200 terms: an error against 64 bits of at most that of 25 K-steps of eight terms dealt to the eight wavefronts in turn, term by term.
+
+    3 % on top for another order of the terms.  Shares rounded up to four K-steps, on seven wavefronts, have 1.06 times this error, equal ones
+    0.99 times."""
+    import numpy as np
+    import torch
+    channels, size, filters, k = 8, 30, 100, 200
+    out = size - 4
+    rng = np.random.default_rng(5)
+    im = (rng.random((channels, size, size)) * 2 - 1).astype(np.float32)
+    weights = (rng.random((filters, k)) * 2 - 1).astype(np.float32)
+    windows = np.lib.stride_tricks.sliding_window_view(im, (5, 5), axis=(1, 2))
+    columns = windows.transpose(0, 3, 4, 1, 2).reshape(k, out * out)
+    exact = weights.astype(np.float64) @ columns.astype(np.float64)
+    total = np.zeros_like(exact, dtype=np.float32)
+    for wave in range(8):
+        s = np.zeros_like(total)
+        for l in range(k):
+            if l // 8 % 8 == wave:
+                s = (s.astype(np.float64) + np.outer(weights[:, l].astype(np.float64), columns[l].astype(np.float64))).astype(np.float32)
+        total += s
+    assert any("conv_gather" in n for n in kernels("f32", channels, size, size, (5, 5), (0, 0), (1, 1), (1, 1), filters))
+    geometry = (channels, size, size, (5, 5), (0, 0), (1, 1), (1, 1))
+    ws = torch.empty(max(256, G.mg_conv2d_workspace_bytes(G.MG_F32, *geometry, filters)), dtype=torch.uint8, device="cuda")
+    got = torch.zeros(filters, out * out, device="cuda")
+    G.mg_sconv2d(*geometry, filters, 1.0, torch.from_numpy(im).cuda(), torch.from_numpy(weights).cuda(), 0.0, got, ws)
+    error = lambda x: np.linalg.norm(x.astype(np.float64) - exact) / np.linalg.norm(exact)
+    assert error(got.cpu().numpy()) <= 1.03 * error(total)
