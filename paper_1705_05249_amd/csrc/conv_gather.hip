@@ -264,9 +264,12 @@ static bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
 }
 
 // Whether the kernel takes a layer and is estimated faster than the routes through GEMM kernels (the unfold route, or for layers of few terms
-// the one that gathers from memory).  Both estimates in us, fitted to 77 layers of the benchmark's and of random sizes (3 to 449 channels, 7 to
-// 112 wide, 1 x 1 to 7 x 7 filters, both strides; residuals 10-17 % rms): of those the rule picks the faster route but for four, (351 channels of 81
-// x 81, 16 filters: 41 / 52) the worst, and they take 0.69 (FP16) and 0.78 (FP32) of the other routes' time.
+// the one that gathers from memory).  Both estimates in us, fitted to 420 random layers (3 to 512 channels, 7 to 112 wide, 1 x 1 to 7 x 7 filters,
+// both strides, 16 to 512 filters; residuals 5-14 % rms here, 9 % there).  Where the grid takes several turns, the band several chunks or a band more
+// than four rounds, loads compete for the caches and the time runs away from the estimate, so that more is asked: without that,
+// 447 channels of 98 x 98, 32 filters in FP16 took 114 us instead of 62, and 306 of 84 x 84, 104 filters in FP32 126 instead of 80.  On 400 other
+// random layers calls are 1.84 (FP16) and 1.56 (FP32) times as fast, those of the other routes included; five are slower by 3 to 10 % (317
+// channels of 20 x 20, 16 filters in FP16 the worst: 14.9 / 16.6).
 bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
 {
     if (!conv_gather_fits(dtype, s, filters)) return false;
@@ -277,11 +280,17 @@ bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
     const int64_t rounds = ceil_div(b.chunk * b.rows * (s.width / b.v), 8 * kThreads) * chunks;
     const int64_t steps = ceil_div(ceil_div(b.chunk * taps, step), 8) * chunks;
     const int64_t turns = ceil_div(ceil_div(out_h * out_w, 32) * ceil_div(filters, 32), 256);
+    const bool f32 = dtype == MG_F32;
     const double k = static_cast<double>(s.channels * taps), positions = static_cast<double>(out_h * out_w);
-    const double column_mb = k * positions * (dtype == MG_F32 ? 4.0e-6 : 2.0e-6), gflop = 2.0e-9 * k * positions * static_cast<double>(filters);
-    const double here = 3.6 + static_cast<double>(turns) * (dtype == MG_F32 ? 0.85 * rounds + 0.36 * steps : 0.89 * rounds + 0.32 * steps);
-    const double there = dtype == MG_F32 ? 7.8 + 0.49 * column_mb + 0.0034 * k + 11.2 * gflop : 8.6 + 0.63 * column_mb + 0.0024 * k + 1.33 * gflop;
-    return here < there;
+    const double column_mb = k * positions * (f32 ? 4.0e-6 : 2.0e-6), gflop = 2.0e-9 * k * positions * static_cast<double>(filters);
+    const double tiles = static_cast<double>(ceil_div(out_h * out_w, 64) * ceil_div(filters, 64)) / 256.0;      // of 64 x 64, for a compute unit
+    const double per_round = f32 ? 0.986 + (b.v == 2 ? 0.092 : 0.0) : 1.047 + (b.v == 2 ? 0.1 : 0.0);
+    const double turn = per_round * static_cast<double>(rounds) + (f32 ? 0.377 : 0.261) * static_cast<double>(steps) + (f32 ? 0.823 : 0.188) * static_cast<double>(chunks - 1);
+    const double here = (f32 ? 3.1 : 3.4) + static_cast<double>(turns) * turn + (f32 ? 0.37 * static_cast<double>(turns - 1) : 0.0);
+    const double there = f32 ? 10.66 + 0.396 * column_mb + 0.00237 * k + 9.34 * gflop + (tiles > 1.0 ? 0.449 * (tiles - 1.0) : 0.0)
+                             : 11.32 + 0.584 * column_mb + 0.00135 * k + 1.96 * gflop;
+    const double wanted = turns > 1 || chunks > 1 || rounds > 4 ? 1.4 : 1.1;
+    return wanted * here < there;
 }
 
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,

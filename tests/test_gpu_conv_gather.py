@@ -69,9 +69,11 @@ def test_infinite_pixels_stay_where_they_are(CO):
 
 
 @pytest.mark.parametrize("dtype,geo", [("f16", (64, 93, 93, (3, 3), (1, 1), (1, 1), (1, 1), 261)), ("f32", (16, 63, 63, (3, 3), (1, 1), (1, 1), (1, 1), 448)),
-                                       ("f16", (512, 7, 7, (3, 3), (1, 1), (1, 1), (1, 1), 512))])
+                                       ("f16", (512, 7, 7, (3, 3), (1, 1), (1, 1), (1, 1), 512)),
+                                       ("f16", (447, 98, 98, (3, 3), (1, 1), (1, 1), (1, 1), 32)), ("f32", (306, 84, 84, (3, 3), (1, 1), (1, 1), (1, 1), 104)),
+                                       ("f32", (64, 85, 85, (7, 7), (3, 3), (1, 1), (1, 1), 80)), ("f32", (16, 106, 106, (3, 3), (1, 1), (1, 1), (1, 1), 115))])
 def test_larger_layers_keep_the_unfold_route(dtype, geo):
-    """22 / 65, 15 / 21 and 17.6 / 20.8 us"""
+    """22 / 65, 15 / 21, 17.6 / 20.8, 62 / 114, 80 / 126, 87 / 102 and 17.5 / 20.1 us"""
     assert any("im2col" in name for name in kernels(dtype, *geo))
 
 
