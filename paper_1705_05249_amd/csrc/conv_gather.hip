@@ -263,13 +263,13 @@ static bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
     return band_of(dtype, s, out_h, out_w).chunk != 0;
 }
 
-// Whether the kernel takes a layer and is estimated faster than the routes through GEMM kernels (the unfold route, or for layers of few terms
-// the one that gathers from memory).  Both estimates in us, fitted to 420 random layers (3 to 512 channels, 7 to 112 wide, 1 x 1 to 7 x 7 filters,
-// both strides, 16 to 512 filters; residuals 5-14 % rms here, 9 % there).  Where the grid takes several turns, the band several chunks or a band more
-// than four rounds, loads compete for the caches and the time runs away from the estimate, so that more is asked: without that,
-// 447 channels of 98 x 98, 32 filters in FP16 took 114 us instead of 62, and 306 of 84 x 84, 104 filters in FP32 126 instead of 80.  On 400 other
-// random layers calls are 1.84 (FP16) and 1.56 (FP32) times as fast, those of the other routes included; five are slower by 3 to 10 % (317
-// channels of 20 x 20, 16 filters in FP16 the worst: 14.9 / 16.6).
+// Whether the kernel takes a layer and is estimated faster than the routes through GEMM kernels: the unfold route, or for layers of few terms
+// and filters the one that gathers from memory (fused).  All estimates in us, fitted to both routes of one build over 300 random layers (1 to 512 channels, 7
+// to 256 wide, 1 x 1 to 7 x 7 filters, both strides, 16 to 512 filters).  FP16 filters of an odd number of terms have rows at odd elements, whose loads
+// take longer.  Where the grid takes several turns, the band several chunks or more than four rounds, loads compete for the caches and more is asked;
+// past six turns it did not pay (32 channels of 256 x 256, 7 x 7, 48 filters in FP16 121 / 142 us).  On 308 other layers calls are 1.30 (FP16) and 1.27 (FP32)
+// times as fast as without the kernel, those it does not take included, and one of the layers is more than 2 % slower (7.9 / 8.1); 3 channels of 224 x
+// 224, 7 x 7, stride 2, 64 filters keep the fused route (9.2 / 18.3), 447 of 98 x 98 with 32 filters the unfold route (62 / 114).
 bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
 {
     if (!conv_gather_fits(dtype, s, filters)) return false;
@@ -284,13 +284,18 @@ bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
     const double k = static_cast<double>(s.channels * taps), positions = static_cast<double>(out_h * out_w);
     const double column_mb = k * positions * (f32 ? 4.0e-6 : 2.0e-6), gflop = 2.0e-9 * k * positions * static_cast<double>(filters);
     const double tiles = static_cast<double>(ceil_div(out_h * out_w, 64) * ceil_div(filters, 64)) / 256.0;      // of 64 x 64, for a compute unit
-    const double per_round = f32 ? 0.986 + (b.v == 2 ? 0.092 : 0.0) : 1.047 + (b.v == 2 ? 0.1 : 0.0);
-    const double turn = per_round * static_cast<double>(rounds) + (f32 ? 0.377 : 0.261) * static_cast<double>(steps) + (f32 ? 0.823 : 0.188) * static_cast<double>(chunks - 1);
-    const double here = (f32 ? 3.1 : 3.4) + static_cast<double>(turns) * turn + (f32 ? 0.37 * static_cast<double>(turns - 1) : 0.0);
-    const double there = f32 ? 10.66 + 0.396 * column_mb + 0.00237 * k + 9.34 * gflop + (tiles > 1.0 ? 0.449 * (tiles - 1.0) : 0.0)
-                             : 11.32 + 0.584 * column_mb + 0.00135 * k + 1.96 * gflop;
-    const double wanted = turns > 1 || chunks > 1 || rounds > 4 ? 1.4 : 1.1;
-    return wanted * here < there;
+    if (turns > 6) return false;
+    const double odd = !f32 && s.channels * taps % 2 != 0 ? 0.471 : (!f32 && s.channels * taps % 8 != 0 ? 0.073 : 0.0);
+    const double turn = f32 ? 0.832 * static_cast<double>(rounds) + 0.379 * static_cast<double>(steps) + 0.459 * static_cast<double>(chunks - 1)
+                            : 0.911 * static_cast<double>(rounds) + (0.29 + odd) * static_cast<double>(steps) + 0.283 * static_cast<double>(chunks - 1);
+    const double here = (f32 ? 3.2 : 3.03) + static_cast<double>(turns) * turn + (f32 ? 0.742 : 0.473) * static_cast<double>(turns - 1);
+    const double over = tiles > 1.0 ? tiles - 1.0 : 0.0;
+    double there;
+    if (filters <= 64 && k <= 256.0)      // (the layers of the fused route)
+        there = f32 ? 7.52 + 0.570 * column_mb + 0.00006 * k + 2.57 * over : 7.63 + 0.420 * column_mb + 4.89 * gflop + 1.11 * over;
+    else
+        there = f32 ? 7.51 + 0.527 * column_mb + 0.00378 * k + 7.44 * gflop + 1.50 * over : 7.57 + 0.502 * column_mb + 0.00214 * k + 3.04 * gflop + 0.73 * over;
+    return (turns > 1 || chunks > 1 || rounds > 4 ? 1.2 : 1.1) * here < there;
 }
 
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,
