@@ -98,10 +98,12 @@ bool batched_dma_pays(const BatchedProblem &p)
     // whole 64^3 with A along m and B along k have a kernel of their own (10000 of them 36.7 us, here 38.0)
     if (p.m == 64 && p.n == 64 && p.k == 64 && !p.a_trans && !p.b_trans) return false;
     // Thin instances and streams from memory lose more to the tiles' empty part than the loads gain.  us, batched_tile.hip / here: 3000 x (40, 128, 128)
-    // 25.4 / 30.1, 9000 x (56, 160, 32) (286 MB) 70 / 94, 7000 x (160, 80, 72) (421 MB) 121 / 171; of 41 sizes, two thirds of which this
-    // rule takes, none is slower and the mean is 1.17 times as fast.
+    // 25.4 / 30.1, 9000 x (56, 160, 32) (286 MB) 70 / 94, 7000 x (160, 80, 72) (421 MB) 121 / 171.  So do 64 x 64 tiles in large batches, and sooner where
+    // neither operand runs along k: 1621 x 136^3 (180 MB) 61 / 68, 2000 x (56, 120, 176) (151 MB) 24 / 27.  Over 440 sizes, routes timed in one build,
+    // calls are 1.19 times as fast as without these kernels, those they do not take included; of the 344 they take 6 are 2 to 8 % slower.
     const double mb = 2.0e-6 * static_cast<double>(p.batch) * static_cast<double>(p.m * p.k + p.k * p.n + p.m * p.n);
     const int64_t thin = p.m < p.n ? p.m : p.n;
+    if (tile_of(p) == 2 && mb > (!p.a_trans && p.b_trans ? 40.0 : 80.0)) return false;
     return (thin >= 40 && mb <= 60.0) || (thin > 48 && mb <= 250.0);
 }
 
