@@ -387,6 +387,12 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 double us = 0.5 + static_cast<double>(whole) * turn(tiles[i].resident) +
                             (rest > 0 ? turn(static_cast<double>(rest) / kComputeUnits) : 0.0);
                 us += cost.c * 2.0 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0) * (triangle ? 0.5 : 1.0) / 4.5e6;
+                // (the masked stores of a triangle, which fetch the old C tile by tile: what a turn takes longer than on 64 x 64 tiles, without / with
+                // beta, 105 SYRK of 64 to 2800; (2824, 256) with beta 22.3 us on 192 x 192 tiles, 13.6 on 64 x 64, (72, 64) 5.6 on 128 x 128, 4.1)
+                static const double masked[2][5] = {{2.6, 1.5, 0.9, 0.3, 0.0}, {8.7, 5.0, 3.1, 0.3, 0.0}};
+                if (triangle && slices == 1) us += masked[p.beta != 0.f][i - kRagged] * static_cast<double>(whole + (rest > 0 ? 1 : 0));
+                // (few tiles: a K-tile is a load's latency; (72, 2224) 13.2 us unsliced, 9.0 in slices)
+                if (triangle && blocks <= kComputeUnits / 4) us += 0.1 * ktiles;
                 if (slices > 1)
                     us += 3.0 + 0.2 * slices + cost.sums * (4.0 * slices + 6.0) * static_cast<double>(p.m) * static_cast<double>(p.n) * (triangle ? 0.5 : 1.0) / 4.0e6;
                 return us * 1.0e6;
@@ -536,7 +542,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // (FP16 triangles of C below 10 us: what slices gain the second launch takes; unsliced / in 4 slices, us on the device | calls in a
             // row: 200 x 1000 T 7.5 / 8.2 | 8.3 / 10.9, 256 x 2048 T 9.7 / 8.4 | 9.7 / 10.0, 256 x 4096 T 15.9 / 9.8 | 15.9 / 10.3)
             const double unsliced = estimate(i, 1);
-            const bool short_triangle = !f32 && triangle && unsliced < 10.0e6;
+            const bool short_triangle = !f32 && triangle && unsliced < (i >= kRagged ? 5.0e6 : 10.0e6);
             if (!in_place && !short_triangle && !(narrowed && blocks > kComputeUnits / 4)) {
                 if (last && !ragged_family) options[n_options++] = pick_split(blocks, ktiles);
                 if (blocks < 2 * kComputeUnits && (!ragged_family || i >= kRagged))
