@@ -309,10 +309,11 @@ mg_status mg_him2col(MG_CONV_GEOMETRY, const uint16_t *im, uint16_t *col, void *
 /* Convolution = IM2COL into the workspace, then the GEMM of this library on it.  The
  * workspace (device, 256-byte aligned) must hold mg_conv2d_workspace_bytes(); a 1x1 filter
  * with unit stride and no padding needs no column matrix (the image is the matrix).  Layers
- * with few rows in the column matrix and at most 64 filters run as one launch of a GEMM
- * kernel that gathers the column matrix from the image (kernels of the family
- * MG_FAMILY_CONV; same result, the workspace is required all the same); forcing such a
- * kernel with mg_override_config takes that route for any layer, forcing a GEMM kernel the
+ * of few outputs run as one launch of a kernel that reads the image itself, and layers with
+ * few rows in the column matrix and at most 64 filters as one launch of a GEMM kernel that
+ * gathers it from the image (kernels of the family MG_FAMILY_CONV); same result, the
+ * workspace is required all the same.  Forcing a kernel of that family with
+ * mg_override_config takes its route for any layer, forcing a GEMM kernel the
  * IM2COL route. */
 mg_status mg_sconv2d(MG_CONV_GEOMETRY, int64_t filters, float alpha, const float *im,
                      const float *weights, float beta, float *out,
