@@ -20,10 +20,12 @@
 //   * FP16 along its rows: 64 lines of 64 bytes; LDS as in memory, chunk c of line k at slot c ^ 2 (k / 8 % 2), read by two transposing reads
 //     per block (the 32 lanes of a pass hit 64 different banks);
 //   * FP32 along its rows: four 4-byte loads per block and K-step, runs of 64 bytes, straight into the operand registers.
-// Rows past the last one repeat it (they end in outputs that C does not have).  Behind the whole pairs is a partial one with loads that are
-// checked piece by piece; it also takes the last line of an operand along its rows whose last piece would run past the operand's end.
+// Rows past the last one repeat it (they end in outputs that C does not have).  Behind the whole pairs are the values that do not fill one, with
+// loads that are checked piece by piece; they include the last lines of an FP16 operand along its rows whose pieces would run past the operand's
+// end (shared_sum.h), so that operands of one to three rows may leave a few values more than a pair.
 #include "mfma_dma_kernel.h"
 #include "mfma_host.h"
+#include "shared_sum.h"
 
 namespace mg {
 namespace {
@@ -35,6 +37,7 @@ struct TinyArgs {
     int m, n, k;
     int share, rest;                         // work-groups per XCD, and how many XCDs have one more
     int minor, n_first;                      // blocks side by side along the shorter side of C, which is n if n_first
+    int kept;                                // values of k at the end of the sum that are not in whole pairs
     float alpha, beta;
 };
 
@@ -114,7 +117,7 @@ template <typename T, bool KCONTIG> struct TinySide {
         }
     }
 
-    // the partial pair behind `pair` pairs of this wavefront, with `left` values of k
+    // pair number `pair` of this wavefront, of which `left` values of k exist (or all)
     __device__ inline void fetch_rest(u32x4 (&f)[PIECES], int pair, int left) const
     {
 #pragma unroll
@@ -189,9 +192,8 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
     const int outer = id / a.minor, inner = id - outer * a.minor;
     const int m0 = (a.n_first ? outer : inner) * 32, n0 = (a.n_first ? inner : outer) * 32;
 
-    // whole pairs, an eighth to each wavefront; the partial one is the last wavefront's
-    const bool runs_over = (!A_KCONTIG && SideA::HALF && a.m % SideA::CH != 0) || (!B_KCONTIG && SideB::HALF && a.n % SideB::CH != 0);
-    const int pairs = (a.k - (runs_over ? 1 : 0)) / PAIR, share = (pairs + kWaves - 1) / kWaves;
+    // whole pairs, an eighth to each wavefront; what is left is the last wavefront's
+    const int pairs = whole_pairs(a.k, a.kept, PAIR), share = (pairs + kWaves - 1) / kWaves;
     const int begin = wave * share < pairs ? wave * share : pairs, count = begin + share < pairs ? share : pairs - begin;
     const int left = wave == kWaves - 1 ? a.k - pairs * PAIR : 0;
     SideA sa;
@@ -259,10 +261,11 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
             if (done + j < count) multiply(fa[j], fb[j]);
         });
     }
-    if (left > 0) {
+    // (twice only for an FP16 operand of one to three rows)
+    for (int rest = left, pair = count; rest > 0; rest -= PAIR, ++pair) {
         u32x4 x[4], y[4];
-        sa.fetch_rest(x, count, left);
-        sb.fetch_rest(y, count, left);
+        sa.fetch_rest(x, pair, rest);
+        sb.fetch_rest(y, pair, rest);
         multiply(x, y);
     }
     if constexpr (SETS == 4) {
@@ -343,6 +346,9 @@ template <typename T, bool AK, bool BKC> struct TinyConfig {
         a.rest = static_cast<int>(groups % 8);
         a.n_first = p.m >= p.n ? 1 : 0;
         a.minor = static_cast<int>(ceil_div(a.n_first ? p.n : p.m, 32));
+        const int piece = sizeof(T) == 2 ? 8 : 1;            // (FP32 operands along their rows come in single elements)
+        const int kept_a = AK ? 0 : lines_kept_back(p.m, p.lda, piece), kept_b = BKC ? 0 : lines_kept_back(p.n, p.ldb, piece);
+        a.kept = kept_a > kept_b ? kept_a : kept_b;
         hipLaunchKernelGGL(kernel, dim3(groups), dim3(512), LDS, p.stream, a);
         return hipGetLastError();
     }

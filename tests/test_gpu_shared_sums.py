@@ -78,3 +78,22 @@ def test_error_of_a_sum_shared_by_eight(order, k):
         G.mg_clear_override()
     error = lambda x: np.linalg.norm(x.astype(np.float64) - exact) / np.linalg.norm(exact)
     assert error(c.cpu().numpy().T) <= 1.1 * error(total)
+
+
+@pytest.mark.parametrize("order", ["mk", "mn", "kn"])
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("m,n", [(1, 33), (2, 40), (3, 5), (4, 2), (40, 3), (33, 1)])
+@pytest.mark.parametrize("k,pad", [(64, 0), (65, 0), (66, 0), (70, 1), (129, 0), (577, 0), (130, 2)])
+def test_lines_shorter_than_a_piece(oracle, dtype, order, m, n, k, pad):
+    """operands along their rows of one to four rows, with next to nothing between the lines: the values that are left fill a pair and more"""
+    import numpy as np
+    ta, tb = ORDERS[order]
+    rng = np.random.default_rng(m * 131 + n * 17 + k)
+    draw = lambda *shape: rng.integers(-2, 3, shape)                # noqa: E731
+    case = W.make_case(f"short_lines_{m}x{n}x{k}", dtype, C, ta, tb, draw(m, k), draw(k, n), draw(m, n), 1.0, 1.0,
+                       W.tight_ld(C, ta, m, k) + pad, W.tight_ld(C, tb, k, n) + pad, m + pad, exact=True)
+    try:
+        G.mg_override_config(G.kernel_id(("s" if dtype == "f32" else "h") + "tiny_32x32_" + order), 1)
+        H.check_case(case, oracle)
+    finally:
+        G.mg_clear_override()
