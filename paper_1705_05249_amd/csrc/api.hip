@@ -167,6 +167,23 @@ size_t preferred_bytes(Problem p, int64_t alignment = 256)
     return most;
 }
 
+// The same wherever the operands lie: FP16 operands off 16 bytes take other kernels than aligned ones, which slice more ((424, 808, 2280): none / 8
+// slices).  Room for these where what fits into the aligned call's leaves a call off 16 bytes estimated slower by more than worth_us.
+size_t preferred_bytes_anywhere(Problem p, double worth_us)
+{
+    size_t most = preferred_bytes(p);
+    if (!dma_ragged_operands(p, 256)) return most;
+    for (const float beta : {0.f, 1.f}) {
+        int32_t kernel = -1, split = 1;
+        double free_us = 0.0, us = 0.0;
+        p.beta = beta;
+        if (choose(p, 8, most, &kernel, &split, &us) != MG_OK || choose(p, 8, ~size_t(0), &kernel, &split, &free_us) != MG_OK) continue;
+        const size_t need = table()[kernel].workspace(p, split);
+        if (need > most && us > free_us + worth_us) most = need;
+    }
+    return most;
+}
+
 // Indirect GEMM, the paper's Section 3.2 route for problems that break the fast kernel's assumptions: copy the
 // operands into zero-padded, aligned buffers whose sizes are whole tiles and run the fast kernel there.  FP16 needs it:
 // ragged or unaligned FP16 problems otherwise run the bounds-checked register-staged kernels at 0.2-0.6 of the
@@ -1032,12 +1049,8 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
         for (const int shape : {lower, upper}) {
             Problem p = canonical(dtype, layout, ta, tb, m, n, kk, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr, shape);
             p.mask_c = routine == MG_ROUTINE_SYRK;
-            // (FP16 operands off 16 bytes take other kernels, which slice more)
-            for (const int64_t alignment : {int64_t(256), int64_t(8)}) {
-                if (alignment < 16 && !dma_ragged_operands(p, 256)) continue;
-                const size_t need = preferred_bytes(p, alignment);
-                if (need > most) most = need;
-            }
+            const size_t need = preferred_bytes_anywhere(p, 0.0);
+            if (need > most) most = need;
         }
         return most;
     };
@@ -1094,8 +1107,11 @@ size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m,
                           nullptr, 0, nullptr);
     IndirectPlan plan;
     // (room for slices beside the copies is the caller's choice; where aligned pointers would spare the copies, for what the call then prefers)
-    if (!indirect_plan(p, false, &plan)) return preferred_bytes(p);
-    const size_t direct = dma_ragged_operands(p, 16) ? preferred_bytes(p) : 0;
+    // Off 16 bytes, of 440 calls 20 get less than they prefer, one of them for more than 1 % ((640, 640, 4096) 20.3 -> 22.3 us); with the aligned
+    // call's room alone 162 did, up to 1.7 times as slow ((1032, 976, 5896) 48.9 -> 82.8 us).
+    const double worth_us = 1.0;
+    if (!indirect_plan(p, false, &plan)) return preferred_bytes_anywhere(p, worth_us);
+    const size_t direct = dma_ragged_operands(p, 16) ? preferred_bytes_anywhere(p, worth_us) : 0;
     return direct > plan.total() ? direct : plan.total();
 }
 

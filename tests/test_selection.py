@@ -8,7 +8,7 @@ import pytest
 from paper_1705_05249_amd import gemm as G
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-C, N = G.MG_COL_MAJOR, G.MG_NO_TRANS
+C, N, T = G.MG_COL_MAJOR, G.MG_NO_TRANS, G.MG_TRANS
 
 
 def matvec(dtype, outputs, length, ld):
@@ -252,3 +252,26 @@ def test_syrk_query_has_room_for_slices(dtype, n, k, trans):
     dense = -(-n * n * (4 if dtype == G.MG_F32 else 2) // 256) * 256
     for layout in (G.MG_COL_MAJOR, G.MG_ROW_MAJOR):
         assert G.mg_syrk_workspace_bytes(dtype, layout, trans, n, k) >= dense + 2 * 4 * n * n
+
+
+def wanted_off_16_bytes(m, n, k, ta, tb):
+    """(bytes that the query names, bytes of the slices that a tight FP16 call off 16 bytes prefers)"""
+    args = (G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m)
+    slices = [G.mg_query_selected(*args, 1.0, beta, alignment)["split_k"] for alignment in (8, 2) for beta in (0.0, 1.0)]
+    return G.mg_gemm_workspace_bytes(*args), max(s * m * n * 4 if s > 1 else 0 for s in slices)
+
+
+@pytest.mark.parametrize("m,n,k,ta,tb", [(424, 808, 2280, N, N), (1672, 560, 3264, N, T), (448, 608, 2744, T, T), (1000, 1000, 4096, N, N),
+                                         (256, 2048, 4096, N, N), (1032, 976, 5896, T, N), (512, 1256, 5216, N, T), (304, 1368, 4160, T, T)])
+def test_workspace_query_covers_operands_off_16_bytes(m, n, k, ta, tb):
+    """us with the room that aligned operands ask for / with this: (1032, 976, 5896) 82.8 / 48.9, (304, 1368, 4160) 21.0 / 18.0"""
+    room, wanted = wanted_off_16_bytes(m, n, k, ta, tb)
+    assert room >= wanted > 0
+
+
+def test_workspace_query_covers_most_operands_off_16_bytes():
+    """the others gain less than a microsecond by their estimates"""
+    import random
+    rng = random.Random(1)
+    sizes = [(rng.randrange(8, 188) * 8, rng.randrange(8, 188) * 8, rng.randrange(32, 1000) * 8, rng.choice((N, T)), rng.choice((N, T))) for _ in range(300)]
+    assert sum(room < wanted for room, wanted in (wanted_off_16_bytes(*size) for size in sizes)) <= 30
