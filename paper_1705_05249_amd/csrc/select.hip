@@ -237,7 +237,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
     const int64_t blocks32 = ceil_div(p.m, 32) * ceil_div(p.n, 32);
     const char *order_tag = p.a_trans ? (p.b_trans ? "kn" : "kk") : (p.b_trans ? "mn" : "mk");
     const bool few_blocks = p.shape == MG_SHAPE_GENERAL && blocks32 <= kComputeUnits && p.m > 1 && p.n > 1;
-    if (few_blocks && p.k >= 48 && p.k <= (f32 ? (blocks32 > 64 ? 2048 : 1536) : 2560)) {
+    // FP16 products of whole 64 x 64 tiles (aligned operands) and few K-tiles of 64 are ranked with the tiles, below: the register-staged ones without
+    // checks start their products after one load, five work-groups to a compute unit.
+    const bool whole64 = !f32 && p.conv == nullptr && p.m % 64 == 0 && p.n % 64 == 0 && p.k % 64 == 0 && dma_ragged_operands(p, alignment);
+    const bool whole_short = whole64 && p.shape == MG_SHAPE_GENERAL && (p.k <= 256 || (p.k <= 384 && p.m / 64 * (p.n / 64) <= kComputeUnits));
+    if (few_blocks && !whole_short && p.k >= 48 && p.k <= (f32 ? (blocks32 > 64 ? 2048 : 1536) : 2560)) {
         char name[48];
         snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
@@ -280,7 +284,40 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                    {1.0, 0.308, 0.180, 0.0, 0.96, 1.11, 1.06, 0.12, 1.14, 0.99},
                                                    {1.2, 0.205, 0.116, 0.0, 0.94, 1.13, 1.04, 0.12, 0.84, 0.82},
                                                    {1.2, 0.163, 0.025, 0.179, 0.95, 1.12, 1.05, 0.12, 0.49, 0.64}};
-        const bool ragged_family = !f32 && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 && dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
+        // Of sums of up to four K-tiles these are up to 40 % off, since a turn is then its first load and its epilogue, and the register-staged
+        // kernels have their place: whole tiles, and checked ones for several turns of single K-tiles ((560, 6952, 64) with
+        // beta 64 x 64 7.2 us, 64 x 64 / 128 x 128 direct-to-LDS 9.1 / 10.5).  Their times in us, fitted to half of 600 sizes of 64 to 8192 and of 670 whole
+        // ones (3 to 7 % rms): a fixed part; turns of one tile per compute unit; and what a busier chip takes longer.  Half of the sizes, the other half
+        // chosen for, these rules over the kernels without the direct-to-LDS tiles for any size: 0.875 of the time (whole ones 0.98), 3 of 148 (9 of
+        // 334) more than 3 % slower; the costs above, without these, 0.90 (1.03), 20 (147).
+        struct ShortCost {
+            double fixed, turn, turn_beta, ktile, busy;
+        };
+        static const ShortCost short_costs[2][14] = {{{}, {}, {}, {}, {}, {},
+                                                      {4.33, 0.46, 0.74, 0.33, 0.37},
+                                                      {3.73, 0.36, 0.31, 0.20, 0.18},
+                                                      {},
+                                                      {2.43, 3.03, 1.84, 0.62, 3.42},
+                                                      {1.85, 3.44, 1.38, 0.48, 1.98},
+                                                      {1.73, 2.58, 1.01, 0.35, 1.31},
+                                                      {1.57, 2.03, 0.54, 0.26, 0.61},
+                                                      {2.66, 0.68, 0.43, 0.19, 0.24}},
+                                                     {{}, {},
+                                                      {3.07, 0.85, 0.60, 0.40, 1.18},
+                                                      {}, {}, {},
+                                                      {3.45, 0.39, 0.47, 0.30, 0.48},
+                                                      {3.09, 0.14, 0.18, 0.18, 0.37},
+                                                      {},
+                                                      {1.79, 3.61, 1.14, 0.62, 3.11},
+                                                      {1.66, 3.59, 0.87, 0.46, 1.94},
+                                                      {1.58, 2.68, 0.57, 0.34, 1.28},
+                                                      {1.59, 1.97, 0.33, 0.25, 0.67},
+                                                      {2.53, 0.74, 0.23, 0.17, 0.29}}};
+        // (triangles of C have costs of their own; whole ones of up to three K-tiles stay with the register-staged tiles: SYRK (640, 64) 4.1 us, 4.5)
+        const bool triangular_c = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
+        const bool short_sum = !triangular_c && (whole_short || p.k <= 256);
+        const bool ragged_family = !f32 && !(whole64 && p.shape != MG_SHAPE_GENERAL && p.k <= 192) && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 &&
+                                   dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
         // LDS; the smaller the tile, the more that shows.  Measured rates relative to the (m, k) order (A along m,
         // B along k; tiles up to 128 x 64 / up to 256 x 128 / 256 x 256): both operands along k 1.10 / 1.06 / 1.02,
@@ -373,6 +410,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 return tiles[i].ceiling * (1.0 - pow(idle, static_cast<double>(u)));
             };
             double time;
+            if (ragged_family && short_sum) {
+                const ShortCost &cost = short_costs[whole_short][i];
+                const double x = static_cast<double>(blocks) / kComputeUnits, ktiles = static_cast<double>(ceil_div(p.k, 64)) * (p.b_trans ? 1.12 : 1.0);
+                return 1.0e6 * (cost.fixed + ceil(x) * (cost.turn + (p.beta != 0.f ? cost.turn_beta : 0.0) + cost.ktile * ktiles) + x * cost.busy);
+            }
             if (!f32 && i >= kRagged) {
                 const RaggedCost &cost = ragged_costs[i - kRagged];
                 double each = p.a_trans ? (p.b_trans ? 1.0 : cost.both_k) : (p.b_trans ? cost.neither_k : cost.one_k);
@@ -526,8 +568,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 const bool wide = whole ? p.m * p.n > 25000000 : p.k > 128 && turns64 >= 6 && 2 * turns128 <= turns64;
                 if (tiles[i].bm * tiles[i].bn > (wide ? 128 * 64 : 64 * 64)) continue;
             }
-            // (where these take the operands the register-staged kernels are nowhere faster by more than 2 %, 190 sizes)
-            if (ragged_family && i > 2 && i < kDeep) continue;
+            if (ragged_family && short_sum) {
+                // (the whole tiles' costs are for tiles that divide C)
+                if (short_costs[whole_short][i].fixed == 0.0 || (i < kRagged && whole_short && (p.m % tiles[i].bm != 0 || p.n % tiles[i].bn != 0))) continue;
+            } else if (ragged_family && i > 2 && i < kDeep) {
+                continue;            // (beside these the register-staged kernels have next to nothing to gain from longer sums)
+            }
+            // (a single turn of two stages and a few K-tiles: (7936, 256, 320) 6.8 us, 5.8 on other tiles)
+            if (ragged_family && !short_sum && i == 2 && p.k <= 512 && wanted_tiles(128, 128) <= kComputeUnits) continue;
             // (tiles of a triangle are counted for heights that are multiples of the width)
             if (!f32 && triangle && i >= kRagged && tiles[i].bm % tiles[i].bn != 0) continue;
             const bool last = i == smallest;
@@ -561,6 +609,20 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 const double time = sl == 1 ? unsliced : estimate(i, sl) * sliced;
                 if (sl > 1 && static_cast<size_t>(sl) * p.m * p.n * sizeof(float) > workspace_bytes) continue;
                 if (ranked[i].slices == 0 || time < ranked[i].time) ranked[i] = Ranked{sl, time};
+            }
+        }
+        // The shared-sum kernel among them, in the same way (4 % rms): (64, 64, 256) both along k 3.2 us, 64 x 64 tiles
+        // 3.7, but (704, 128, 64) neither along k 4.7, 3.6
+        if (few_blocks && whole_short) {
+            double best_us = 1.0e30;
+            for (int i = 0; i < count; ++i)
+                if (ranked[i].slices != 0 && ranked[i].time * 1.0e-6 < best_us) best_us = ranked[i].time * 1.0e-6;
+            const double ktile = p.a_trans ? (p.b_trans ? 0.14 : 0.07) : (p.b_trans ? 0.17 : 0.10), first = p.a_trans ? (p.b_trans ? 0.36 : 0.0) : (p.b_trans ? 0.78 : 0.43);
+            const double us = 3.0 + first + (p.beta != 0.f ? 0.44 : 0.0) + ktile * static_cast<double>(p.k / 64) + 0.23 * static_cast<double>(blocks32) / kComputeUnits;
+            if (1.03 * us < best_us) {
+                char name[48];
+                snprintf(name, sizeof name, "htiny_32x32_%s", order_tag);
+                if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
             }
         }
         for (int attempt = 0; attempt < count; ++attempt) {

@@ -275,3 +275,20 @@ def test_workspace_query_covers_most_operands_off_16_bytes():
     rng = random.Random(1)
     sizes = [(rng.randrange(8, 188) * 8, rng.randrange(8, 188) * 8, rng.randrange(32, 1000) * 8, rng.choice((N, T)), rng.choice((N, T))) for _ in range(300)]
     assert sum(room < wanted for room, wanted in (wanted_off_16_bytes(*size) for size in sizes)) <= 30
+
+
+@pytest.mark.parametrize("m,n,k,ta,tb,beta,slow", [
+    (704, 128, 64, N, T, 0.5, "htiny"), (64, 128, 64, N, T, 0.0, "htiny"), (2432, 256, 64, N, N, 0.5, "hdma"), (2240, 1856, 64, N, N, 0.5, "hdma"),
+    (896, 1024, 128, T, T, 0.0, "hdma16_"), (560, 6952, 64, T, N, 0.5, "hdma"), (232, 168, 16, T, N, 0.5, "hdma16r_128x128"),
+    (136, 368, 40, T, T, 0.5, "hdma16r_128x128"), (128, 960, 320, N, T, 0.5, "htiny")])
+def test_short_fp16_sums(m, n, k, ta, tb, beta, slow):
+    """a few K-tiles of 64: not the kernels that a turn's first load and epilogue make slower there, by 1.14 to 1.34 times"""
+    name = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, beta)["name"]
+    assert not name.startswith(slow), name
+
+
+def test_long_and_few_fp16_sums_keep_their_kernels():
+    for m, n, k, ta, tb, name in ((512, 196, 2304, N, N, "htiny"), (128, 128, 512, T, N, "htiny"), (64, 64, 256, T, N, "htiny"), (3000, 3000, 3000, N, N, "hdma16r_192x192"),
+                                  (848, 496, 200, N, T, "hdma16r_64x64"), (40, 40, 48, N, N, "htiny")):
+        chosen = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, 0.0)["name"]
+        assert chosen.startswith(name), (m, n, k, chosen)
