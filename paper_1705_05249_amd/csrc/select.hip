@@ -316,6 +316,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         // (triangles of C have costs of their own; whole ones of up to three K-tiles stay with the register-staged tiles: SYRK (640, 64) 4.1 us, 4.5)
         const bool triangular_c = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
         const bool short_sum = !triangular_c && (whole_short || p.k <= 256);
+        // The checked register-staged 256 x 256 tile beside them, in the same form (147 sizes of 640 to 7000 terms, 5 % rms), where 192 x 192 tiles
+        // leave a nearly empty turn: (5416, 5112, 2456) 192 x 192 159 us, this 142, (3280, 3600, 2600) 86.2, 67.6; SYRK (4600, 2896) 128 x 128 88.2, this
+        // 72.8.  Of 250 products of 900 to 8000 it takes 12, 0.93 of the time, one 2 % slower.
+        constexpr int kStagedLargest = 3;
+        static const RaggedCost staged_largest = {6.9, 0.98, 0.44, 0.0, 0.94, 1.10, 1.03, 0.08, 1.0, 1.0};
         const bool ragged_family = !f32 && !(whole64 && p.shape != MG_SHAPE_GENERAL && p.k <= 192) && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 &&
                                    dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
@@ -415,8 +420,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 const double x = static_cast<double>(blocks) / kComputeUnits, ktiles = static_cast<double>(ceil_div(p.k, 64)) * (p.b_trans ? 1.12 : 1.0);
                 return 1.0e6 * (cost.fixed + ceil(x) * (cost.turn + (p.beta != 0.f ? cost.turn_beta : 0.0) + cost.ktile * ktiles) + x * cost.busy);
             }
-            if (!f32 && i >= kRagged) {
-                const RaggedCost &cost = ragged_costs[i - kRagged];
+            const bool large_staged = ragged_family && i == kStagedLargest;
+            if (!f32 && (i >= kRagged || large_staged)) {
+                const RaggedCost &cost = large_staged ? staged_largest : ragged_costs[i - kRagged];
                 double each = p.a_trans ? (p.b_trans ? 1.0 : cost.both_k) : (p.b_trans ? cost.neither_k : cost.one_k);
                 if (p.a_trans && p.lda % 64) each *= 1.0 + cost.stray_rows;
                 else if (!p.b_trans && p.ldb % 64) each *= 1.0 + 0.5 * cost.stray_rows;
@@ -426,13 +432,16 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                        : cost.turn + ktiles * (cost.ktile + cost.ktile_load + cost.second);
                 };
                 const int64_t whole = blocks / full, rest = blocks % full;
-                double us = 0.5 + static_cast<double>(whole) * turn(tiles[i].resident) +
+                double us = (large_staged ? 3.4 : 0.5) + static_cast<double>(whole) * turn(tiles[i].resident) +
                             (rest > 0 ? turn(static_cast<double>(rest) / kComputeUnits) : 0.0);
                 us += cost.c * 2.0 * static_cast<double>(p.m) * static_cast<double>(p.n) * (p.beta != 0.f ? 2.0 : 1.0) * (triangle ? 0.5 : 1.0) / 4.5e6;
                 // (the masked stores of a triangle, which fetch the old C tile by tile: what a turn takes longer than on 64 x 64 tiles, without / with
                 // beta, 105 SYRK of 64 to 2800; (2824, 256) with beta 22.3 us on 192 x 192 tiles, 13.6 on 64 x 64, (72, 64) 5.6 on 128 x 128, 4.1)
                 static const double masked[2][5] = {{2.6, 1.5, 0.9, 0.3, 0.0}, {8.7, 5.0, 3.1, 0.3, 0.0}};
-                if (triangle && slices == 1) us += masked[p.beta != 0.f][i - kRagged] * static_cast<double>(whole + (rest > 0 ? 1 : 0));
+                // (64-wide tiles: half a microsecond for each turn behind the first, without beta too; (4784, 16) 64 x 64 20.8, 128 x 128 16.1)
+                const double turns = static_cast<double>(whole + (rest > 0 ? 1 : 0));
+                if (triangle && slices == 1 && !large_staged) us += masked[p.beta != 0.f][i - kRagged] * turns + (i >= kRagged + 3 ? 0.5 * (turns - 1.0) : 0.0);
+                if (triangle && large_staged) us *= 1.1;
                 // (few tiles: a K-tile is a load's latency; (72, 2224) 13.2 us unsliced, 9.0 in slices)
                 if (triangle && blocks <= kComputeUnits / 4) us += 0.1 * ktiles;
                 if (slices > 1)
@@ -571,11 +580,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (ragged_family && short_sum) {
                 // (the whole tiles' costs are for tiles that divide C)
                 if (short_costs[whole_short][i].fixed == 0.0 || (i < kRagged && whole_short && (p.m % tiles[i].bm != 0 || p.n % tiles[i].bn != 0))) continue;
-            } else if (ragged_family && i > 2 && i < kDeep) {
-                continue;            // (beside these the register-staged kernels have next to nothing to gain from longer sums)
+            } else if (ragged_family && i > 3 && i < kDeep) {
+                continue;            // (beside these the smaller register-staged kernels have nothing to gain from longer sums)
             }
             // (a single turn of two stages and a few K-tiles: (7936, 256, 320) 6.8 us, 5.8 on other tiles)
             if (ragged_family && !short_sum && i == 2 && p.k <= 512 && wanted_tiles(128, 128) <= kComputeUnits) continue;
+            // (the checked 256 x 256 tile only where there is no whole one, all its sums are as long, and no masked stores fetch the old C: SYRK (5344,
+            // 2384) with beta 147 us, 88 on 192 x 192)
+            if (ragged_family && i == kStagedLargest && (narrowed || (triangle && p.beta != 0.f) || (p.m % 256 == 0 && p.n % 256 == 0 && p.k % 64 == 0))) continue;
             // (tiles of a triangle are counted for heights that are multiples of the width)
             if (!f32 && triangle && i >= kRagged && tiles[i].bm % tiles[i].bn != 0) continue;
             const bool last = i == smallest;

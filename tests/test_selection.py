@@ -292,3 +292,9 @@ def test_long_and_few_fp16_sums_keep_their_kernels():
                                   (848, 496, 200, N, T, "hdma16r_64x64"), (40, 40, 48, N, N, "htiny")):
         chosen = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, 0.0)["name"]
         assert chosen.startswith(name), (m, n, k, chosen)
+
+
+@pytest.mark.parametrize("m,n,k,ta,tb", [(3280, 3600, 2600, T, N), (5416, 5112, 2456, N, N)])
+def test_checked_256_tiles_where_192_leave_a_turn_empty(m, n, k, ta, tb):
+    """us, 192 x 192 / 256 x 256: 86 / 68 and 159 / 142"""
+    assert G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, 0.0)["name"].startswith("hmfma_256x256")
