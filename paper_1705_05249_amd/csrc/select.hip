@@ -241,6 +241,14 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
     // checks start their products after one load, five work-groups to a compute unit.
     const bool whole64 = !f32 && p.conv == nullptr && p.m % 64 == 0 && p.n % 64 == 0 && p.k % 64 == 0 && dma_ragged_operands(p, alignment);
     const bool whole_short = whole64 && p.shape == MG_SHAPE_GENERAL && (p.k <= 256 || (p.k <= 384 && p.m / 64 * (p.n / 64) <= kComputeUnits));
+    // (of a triangle of C they always are: over 123 SYRK of up to four K-tiles 64 x 64 ones take 0.93 of the time of what was chosen before the direct-to-LDS tiles
+    // for any size, at most 1.01, and within 1 % of the fastest of all; (640, 64) 4.1 us, 4.5 on those tiles)
+    const bool triangular_c = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
+    if (triangular_c && whole64 && p.k <= 256) {
+        char name[48];
+        snprintf(name, sizeof name, "hmfma_64x64x64_w2x2_%s", order_tag);
+        if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
+    }
     if (few_blocks && !whole_short && p.k >= 48 && p.k <= (f32 ? (blocks32 > 64 ? 2048 : 1536) : 2560)) {
         char name[48];
         snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
@@ -291,9 +299,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         // chosen for, these rules over the kernels without the direct-to-LDS tiles for any size: 0.875 of the time (whole ones 0.98), 3 of 148 (9 of
         // 334) more than 3 % slower; the costs above, without these, 0.90 (1.03), 20 (147).
         struct ShortCost {
-            double fixed, turn, turn_beta, ktile, busy;
+            double fixed, turn, turn_beta, ktile, busy, fixed_beta = 0.0, busy_beta = 0.0;
         };
-        static const ShortCost short_costs[2][14] = {{{}, {}, {}, {}, {}, {},
+        // general products | of whole tiles | triangles of C (400 sizes of 64 to 6200; 5 of 204 held out more than 3 % slower, without 16, up to 29 %;
+        // (4416, 120) with beta 24.5 us on 64 x 64 direct-to-LDS tiles, 18.6)
+        static const ShortCost short_costs[3][14] = {{{}, {}, {}, {}, {}, {},
                                                       {4.33, 0.46, 0.74, 0.33, 0.37},
                                                       {3.73, 0.36, 0.31, 0.20, 0.18},
                                                       {},
@@ -312,16 +322,23 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                       {1.66, 3.59, 0.87, 0.46, 1.94},
                                                       {1.58, 2.68, 0.57, 0.34, 1.28},
                                                       {1.59, 1.97, 0.33, 0.25, 0.67},
-                                                      {2.53, 0.74, 0.23, 0.17, 0.29}}};
-        // (triangles of C have costs of their own; whole ones of up to three K-tiles stay with the register-staged tiles: SYRK (640, 64) 4.1 us, 4.5)
-        const bool triangular_c = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
-        const bool short_sum = !triangular_c && (whole_short || p.k <= 256);
+                                                      {2.53, 0.74, 0.23, 0.17, 0.29}},
+                                                     {{}, {}, {}, {}, {}, {}, {},
+                                                      {4.53, 0.01, 0.08, 0.20, 0.90, 2.14, 0.25},
+                                                      {},
+                                                      {4.99, 3.53, 0.00, 0.65, 2.90, 8.19, 2.31},
+                                                      {},
+                                                      {3.10, 2.62, 0.16, 0.36, 1.41, 3.99, 0.46},
+                                                      {2.75, 1.27, 0.05, 0.27, 2.07, 1.99, 0.82},
+                                                      {3.24, 0.90, 0.13, 0.18, 0.32, 2.02, 0.00}}};
+        const bool short_sum = whole_short || p.k <= 256;
+        const ShortCost *short_cost = short_costs[whole_short ? 1 : (triangular_c ? 2 : 0)];
         // The checked register-staged 256 x 256 tile beside them, in the same form (147 sizes of 640 to 7000 terms, 5 % rms), where 192 x 192 tiles
         // leave a nearly empty turn: (5416, 5112, 2456) 192 x 192 159 us, this 142, (3280, 3600, 2600) 86.2, 67.6; SYRK (4600, 2896) 128 x 128 88.2, this
         // 72.8.  Of 250 products of 900 to 8000 it takes 12, 0.93 of the time, one 2 % slower.
         constexpr int kStagedLargest = 3;
         static const RaggedCost staged_largest = {6.9, 0.98, 0.44, 0.0, 0.94, 1.10, 1.03, 0.08, 1.0, 1.0};
-        const bool ragged_family = !f32 && !(whole64 && p.shape != MG_SHAPE_GENERAL && p.k <= 192) && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 &&
+        const bool ragged_family = !f32 && !(whole64 && p.shape != MG_SHAPE_GENERAL && !triangular_c && p.k <= 192) && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 &&
                                    dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
         // LDS; the smaller the tile, the more that shows.  Measured rates relative to the (m, k) order (A along m,
@@ -416,9 +433,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             };
             double time;
             if (ragged_family && short_sum) {
-                const ShortCost &cost = short_costs[whole_short][i];
+                const ShortCost &cost = short_cost[i];
                 const double x = static_cast<double>(blocks) / kComputeUnits, ktiles = static_cast<double>(ceil_div(p.k, 64)) * (p.b_trans ? 1.12 : 1.0);
-                return 1.0e6 * (cost.fixed + ceil(x) * (cost.turn + (p.beta != 0.f ? cost.turn_beta : 0.0) + cost.ktile * ktiles) + x * cost.busy);
+                const double updates = p.beta != 0.f ? cost.fixed_beta + ceil(x) * cost.turn_beta + x * cost.busy_beta : 0.0;
+                return 1.0e6 * (cost.fixed + ceil(x) * (cost.turn + cost.ktile * ktiles) + x * cost.busy + updates);
             }
             const bool large_staged = ragged_family && i == kStagedLargest;
             if (!f32 && (i >= kRagged || large_staged)) {
@@ -438,9 +456,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // (the masked stores of a triangle, which fetch the old C tile by tile: what a turn takes longer than on 64 x 64 tiles, without / with
                 // beta, 105 SYRK of 64 to 2800; (2824, 256) with beta 22.3 us on 192 x 192 tiles, 13.6 on 64 x 64, (72, 64) 5.6 on 128 x 128, 4.1)
                 static const double masked[2][5] = {{2.6, 1.5, 0.9, 0.3, 0.0}, {8.7, 5.0, 3.1, 0.3, 0.0}};
-                // (64-wide tiles: half a microsecond for each turn behind the first, without beta too; (4784, 16) 64 x 64 20.8, 128 x 128 16.1)
-                const double turns = static_cast<double>(whole + (rest > 0 ? 1 : 0));
-                if (triangle && slices == 1 && !large_staged) us += masked[p.beta != 0.f][i - kRagged] * turns + (i >= kRagged + 3 ? 0.5 * (turns - 1.0) : 0.0);
+                if (triangle && slices == 1 && !large_staged) us += masked[p.beta != 0.f][i - kRagged] * static_cast<double>(whole + (rest > 0 ? 1 : 0));
                 if (triangle && large_staged) us *= 1.1;
                 // (few tiles: a K-tile is a load's latency; (72, 2224) 13.2 us unsliced, 9.0 in slices)
                 if (triangle && blocks <= kComputeUnits / 4) us += 0.1 * ktiles;
@@ -579,15 +595,16 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             }
             if (ragged_family && short_sum) {
                 // (the whole tiles' costs are for tiles that divide C)
-                if (short_costs[whole_short][i].fixed == 0.0 || (i < kRagged && whole_short && (p.m % tiles[i].bm != 0 || p.n % tiles[i].bn != 0))) continue;
+                if (short_cost[i].fixed == 0.0 || (i < kRagged && whole_short && (p.m % tiles[i].bm != 0 || p.n % tiles[i].bn != 0))) continue;
             } else if (ragged_family && i > 3 && i < kDeep) {
                 continue;            // (beside these the smaller register-staged kernels have nothing to gain from longer sums)
             }
             // (a single turn of two stages and a few K-tiles: (7936, 256, 320) 6.8 us, 5.8 on other tiles)
             if (ragged_family && !short_sum && i == 2 && p.k <= 512 && wanted_tiles(128, 128) <= kComputeUnits) continue;
-            // (the checked 256 x 256 tile only where there is no whole one, all its sums are as long, and no masked stores fetch the old C: SYRK (5344,
-            // 2384) with beta 147 us, 88 on 192 x 192)
-            if (ragged_family && i == kStagedLargest && (narrowed || (triangle && p.beta != 0.f) || (p.m % 256 == 0 && p.n % 256 == 0 && p.k % 64 == 0))) continue;
+            // (the checked 256 x 256 tile only where there is no whole one and all its sums are as long; for triangles of C if no masked stores fetch
+            // the old C, SYRK (5344, 2384) with beta 147 us, 88 on 192 x 192, and few tiles, whose grid holds the others too: (5512, 4032), 253 of 484,
+            // 175 us, 114)
+            if (ragged_family && i == kStagedLargest && (narrowed || (triangle && (p.beta != 0.f || wanted_tiles(256, 256) > kComputeUnits * 3 / 4)) || (p.m % 256 == 0 && p.n % 256 == 0 && p.k % 64 == 0))) continue;
             // (tiles of a triangle are counted for heights that are multiples of the width)
             if (!f32 && triangle && i >= kRagged && tiles[i].bm % tiles[i].bn != 0) continue;
             const bool last = i == smallest;
