@@ -288,8 +288,10 @@ static bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
 // to 256 wide, 1 x 1 to 7 x 7 filters, both strides, 16 to 512 filters).  FP16 filters of an odd number of terms have rows at odd elements, whose loads
 // take longer.  Where the grid takes several turns, the band several chunks or more than four rounds, loads compete for the caches and more is asked;
 // past six turns it did not pay (32 channels of 256 x 256, 7 x 7, 48 filters in FP16 121 / 142 us).  On 308 other layers calls are 1.30 (FP16) and 1.27 (FP32)
-// times as fast as without the kernel, those it does not take included, and one of the layers is more than 2 % slower (7.9 / 8.1); 3 channels of 224 x
-// 224, 7 x 7, stride 2, 64 filters keep the fused route (9.2 / 18.3), 447 of 98 x 98 with 32 filters the unfold route (62 / 114).
+// times as fast as without the kernel, those it does not take included; 3 channels of 224 x 224, 7 x 7, stride 2, 64 filters keep the fused
+// route (9.2 / 18.3), 447 of 98 x 98 with 32 filters the unfold route (62 / 114).  Of 690 other FP32 layers that the estimates alone would give it, 7 of the
+// 22 with several chunks or more than three turns and a gain of less than 1.4 lost up to a fifth (480 of 64 x 64, 5 x 5, stride 2, 249 filters
+// 80 / 96): these stay out; of the rest 2 are more than 3 % slower (68 of 17 x 17, 1 x 1, stride 2, 171 filters 6.7 / 7.4).
 bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
 {
     if (!conv_gather_fits(dtype, s, filters)) return false;
@@ -315,7 +317,7 @@ bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
         there = f32 ? 7.52 + 0.570 * column_mb + 0.00006 * k + 2.57 * over : 7.63 + 0.420 * column_mb + 4.89 * gflop + 1.11 * over;
     else
         there = f32 ? 7.51 + 0.527 * column_mb + 0.00378 * k + 7.44 * gflop + 1.50 * over : 7.57 + 0.502 * column_mb + 0.00214 * k + 3.04 * gflop + 0.73 * over;
-    return (turns > 1 || chunks > 1 || rounds > 4 ? 1.2 : 1.1) * here < there;
+    return (f32 && (chunks > 1 || turns > 3) ? 1.4 : (turns > 1 || rounds > 4 ? 1.2 : 1.1)) * here < there;
 }
 
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,

@@ -88,6 +88,13 @@ def test_larger_layers_keep_the_unfold_route(dtype, geo):
     assert any("im2col" in name for name in kernels(dtype, *geo))
 
 
+@pytest.mark.parametrize("geo", [(480, 64, 64, (5, 5), (2, 2), (2, 2), (1, 1), 249), (185, 43, 43, (7, 7), (3, 3), (1, 1), (1, 1), 113),
+                                 (42, 198, 198, (3, 3), (1, 1), (1, 1), (1, 1), 29)])
+def test_layers_of_many_loads_and_little_gain_keep_the_unfold_route(geo):
+    """FP32, bands in several chunks and grids of several turns: 80 / 96, 66 / 74 and 44 / 50 us"""
+    assert any("im2col" in name for name in kernels("f32", *geo))
+
+
 def test_error_of_an_evenly_shared_sum():
     """FP32, 200 terms: an error against 64 bits of at most that of 25 K-steps of eight terms dealt to the eight wavefronts in turn, term by term.
 
