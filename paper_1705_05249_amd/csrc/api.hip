@@ -398,7 +398,7 @@ mg_status run_canonical(Problem p)
 // shape: a ProblemShape hint in terms of the canonical (column-major) problem, see canonical()
 mg_status run_gemm(int dtype, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k, float alpha,
                    const void *A, int64_t lda, const void *B, int64_t ldb, float beta, void *C, int64_t ldc,
-                   void *ws, size_t ws_bytes, void *stream, int shape = MG_SHAPE_GENERAL)
+                   void *ws, size_t ws_bytes, void *stream, int shape = MG_SHAPE_GENERAL, bool unfolded = false)
 {
     mg_status s = check_shape(layout, ta, tb, m, n, k, lda, ldb, ldc);
     if (s != MG_OK) return s;
@@ -406,6 +406,7 @@ mg_status run_gemm(int dtype, int layout, int ta, int tb, int64_t m, int64_t n, 
     const bool reads_ab = alpha != 0.f && k != 0;
     if (C == nullptr || (reads_ab && (A == nullptr || B == nullptr))) return MG_ERR_NULL;
     Problem p = canonical(dtype, layout, ta, tb, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, ws, ws_bytes, stream, shape);
+    p.unfolded = unfolded;
     return run_canonical(p);
 }
 
@@ -645,11 +646,11 @@ mg_status run_conv2d(int dtype, const ConvShape &s, int64_t filters, float alpha
             col_bytes = round_up_256(static_cast<size_t>(k) * n * elem);
             if (ws == nullptr || pointer_alignment(ws) < 256 || ws_bytes < col_bytes) return MG_ERR_WORKSPACE;
         }
-        // Without the unfold pass where a kernel that gathers op(A) from the image exists for the configuration the
-        // GEMM would get: the caller's workspace then only serves the slices of the sum.
         // Few outputs: the whole convolution in one launch, from a band of the image in LDS.
         if (forced < 0 && !plain && conv_gather_pays(dtype, s, filters))
             return launch_conv_gather(dtype, s, filters, alpha, im, weights, beta, out, static_cast<hipStream_t>(stream)) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
+        // Without the unfold pass where a kernel that gathers op(A) from the image exists for the configuration the
+        // GEMM would get: the caller's workspace then only serves the slices of the sum.
         mg_status fused = run_conv2d_fused(dtype, s, filters, n, k, alpha, im, weights, beta, out, ws, ws_bytes, stream);
         if (fused != MG_ERR_CONFIG || forced_conv) return fused;
         if (launch_im2col(dtype, s, im, ws, static_cast<hipStream_t>(stream)) != hipSuccess) return MG_ERR_LAUNCH;
@@ -658,7 +659,7 @@ mg_status run_conv2d(int dtype, const ConvShape &s, int64_t filters, float alpha
     void *rest = ws == nullptr ? nullptr : static_cast<char *>(ws) + col_bytes;
     const size_t rest_bytes = ws_bytes > col_bytes ? ws_bytes - col_bytes : 0;
     return run_gemm(dtype, MG_ROW_MAJOR, MG_NO_TRANS, MG_NO_TRANS, filters, n, k, alpha, weights, k, col, n, beta, out,
-                    n, rest_bytes ? rest : nullptr, rest_bytes, stream);
+                    n, rest_bytes ? rest : nullptr, rest_bytes, stream, MG_SHAPE_GENERAL, col_bytes != 0);
 }
 
 // ---- GEMM-derived level-3 routines: a support kernel makes the special operand general (or sets the
@@ -1097,14 +1098,14 @@ size_t mg_trmm_workspace_bytes(int dtype, int layout, int side, int trans_a, int
     return level3_workspace_bytes(MG_ROUTINE_TRMM, dtype, layout, side, trans_a, m, n, 0);
 }
 
-size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k,
-                               int64_t lda, int64_t ldb, int64_t ldc)
+static size_t gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k, int64_t lda, int64_t ldb, int64_t ldc, bool unfolded)
 {
     if (dtype != MG_F32 && dtype != MG_F16) return 0;
     if (check_shape(layout, ta, tb, m, n, k, lda, ldb, ldc) != MG_OK || m == 0 || n == 0) return 0;
     // (the scale-only path of alpha == 0 needs none)
     Problem p = canonical(dtype, layout, ta, tb, m, n, k, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc,
                           nullptr, 0, nullptr);
+    p.unfolded = unfolded;
     IndirectPlan plan;
     // (room for slices beside the copies is the caller's choice; where aligned pointers would spare the copies, for what the call then prefers)
     // Off 16 bytes, of 440 calls 20 get less than they prefer, one of them for more than 1 % ((640, 640, 4096) 20.3 -> 22.3 us); with the aligned
@@ -1113,6 +1114,12 @@ size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m,
     if (!indirect_plan(p, false, &plan)) return preferred_bytes_anywhere(p, worth_us);
     const size_t direct = dma_ragged_operands(p, 16) ? preferred_bytes_anywhere(p, worth_us) : 0;
     return direct > plan.total() ? direct : plan.total();
+}
+
+size_t mg_gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k,
+                               int64_t lda, int64_t ldb, int64_t ldc)
+{
+    return gemm_workspace_bytes(dtype, layout, ta, tb, m, n, k, lda, ldb, ldc, false);
 }
 
 #define MG_CONV_SHAPE_ARGS                                                                                      \
@@ -1151,7 +1158,7 @@ size_t mg_conv2d_workspace_bytes(int dtype, MG_CONV_SHAPE_ARGS, int64_t filters)
     if (check_conv(s, filters, &out_h, &out_w, &k) != MG_OK || filters == 0 || out_h * out_w == 0) return 0;
     const int64_t n = out_h * out_w;
     const size_t col = conv_is_plain_gemm(s) ? 0 : round_up_256(static_cast<size_t>(k) * n * (dtype == MG_F32 ? 4 : 2));
-    return col + mg_gemm_workspace_bytes(dtype, MG_ROW_MAJOR, MG_NO_TRANS, MG_NO_TRANS, filters, n, k, k, n, n);
+    return col + gemm_workspace_bytes(dtype, MG_ROW_MAJOR, MG_NO_TRANS, MG_NO_TRANS, filters, n, k, k, n, n, col != 0);
 }
 
 int64_t mg_conv2d_out_extent(int64_t size, int64_t kernel, int64_t pad, int64_t stride, int64_t dilation)

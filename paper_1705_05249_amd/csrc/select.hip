@@ -249,7 +249,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         snprintf(name, sizeof name, "hmfma_64x64x64_w2x2_%s", order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
     }
-    if (few_blocks && !whole_short && p.k >= 48 && p.k <= (f32 ? (blocks32 > 64 ? 2048 : 1536) : 2560)) {
+    // (FP32 behind the unfold pass, 51 layers of 1281 to 2048 terms: up to 64 blocks 1.08 up to 1536 terms, more 0.98 up to 1536, 0.98 with two of nine
+    // up to 1.11 beyond; where there is room for slices)
+    const bool unfolded = p.unfolded && workspace_bytes / 8 >= static_cast<size_t>(p.m) * static_cast<size_t>(p.n);
+    const int64_t most_f32 = unfolded ? (blocks32 > 64 ? 1536 : 1280) : (blocks32 > 64 ? 2048 : 1536);
+    if (few_blocks && !whole_short && p.k >= 48 && p.k <= (f32 ? most_f32 : 2560)) {
         char name[48];
         snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;

@@ -298,3 +298,14 @@ def test_long_and_few_fp16_sums_keep_their_kernels():
 def test_checked_256_tiles_where_192_leave_a_turn_empty(m, n, k, ta, tb):
     """us, 192 x 192 / 256 x 256: 86 / 68 and 159 / 142"""
     assert G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, 0.0)["name"].startswith("hmfma_256x256")
+
+
+@pytest.mark.parametrize("channels,size,filters", [(164, 9, 40), (151, 8, 59), (150, 7, 51)])
+def test_fp32_products_behind_the_unfold_pass_are_sliced(channels, size, filters):
+    """few blocks, 1281 to 1536 terms: 14.0 us in slices, 15.8 on the kernel whose wavefronts share the sum; the query names the slices' room"""
+    k, n = 9 * channels, size * size
+    column = -(-4 * k * n // 256) * 256
+    room = G.mg_conv2d_workspace_bytes(G.MG_F32, channels, size, size, (3, 3), (1, 1), (1, 1), (1, 1), filters) - column
+    assert room >= 2 * 4 * n * filters
+    alone = G.mg_query_selected(G.MG_F32, G.MG_ROW_MAJOR, N, N, filters, n, k, k, n, n)
+    assert alone["name"].startswith("stiny")
