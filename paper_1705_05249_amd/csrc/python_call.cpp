@@ -3,6 +3,8 @@
 // In ctypes and Python these conversions were 4 us of the 7.6 that the host took for a small product, 0.9 of 3.8 now: calls one behind the other,
 // FP32 256^3 7.6 -> 4.8 us, which is the kernel's own time, FP16 64 x 64 x 64 7.6 -> 3.8.
 //
+// Arguments of other types (ctypes' own scalars, objects that only ctypes can convert, errors) go to gemm.py, which makes the call through ctypes.
+//
 // The library is not linked: gemm.py loads it and hands over the addresses of its functions (bind).  Conversions follow from the entry points'
 // own types: a size_t stands for the bytes of the workspace in front of it, the last pointer is the stream.
 #define PY_SSIZE_T_CLEAN
@@ -22,6 +24,7 @@ namespace {
 PyObject *s_data_ptr, *s_numel, *s_element_size, *s_cuda_stream;       // interned names
 PyObject *stream_calls;                     // gemm.py's: () -> torch's functions for the current device and for its current stream
 PyObject *get_device, *get_stream;          // these
+PyObject *other_types;                      // gemm.py's: (name, arguments) -> status, through ctypes
 
 // an address: None, an integer, or a tensor
 bool address(PyObject *o, void **out)
@@ -89,9 +92,10 @@ bool workspace_bytes(PyObject *o, size_t *out)
         if (v == nullptr) return false;
         product *= PyLong_AsSize_t(v);
         Py_DECREF(v);
+        if (PyErr_Occurred() != nullptr) return false;
     }
     *out = product;
-    return PyErr_Occurred() == nullptr;
+    return true;
 }
 
 template <typename P> bool convert(PyObject *o, bool last, P *out)
@@ -126,8 +130,23 @@ template <typename... P> constexpr Py_ssize_t arguments_before(size_t i)
     return n;
 }
 
+// what is left of a call that cannot be converted here: the error, or what ctypes makes of it
+PyObject *call_other_types(const char *name, PyObject *const *args, Py_ssize_t count)
+{
+    if (other_types == nullptr || !(PyErr_ExceptionMatches(PyExc_TypeError) || PyErr_ExceptionMatches(PyExc_OverflowError))) return nullptr;
+    PyErr_Clear();
+    PyObject *list = PyTuple_New(count);
+    if (list == nullptr) return nullptr;
+    for (Py_ssize_t i = 0; i < count; ++i) {
+        Py_INCREF(args[i]);
+        PyTuple_SET_ITEM(list, i, args[i]);
+    }
+    PyObject *status = PyObject_CallFunction(other_types, "sN", name, list);
+    return status;
+}
+
 template <typename... P, size_t... I>
-PyObject *invoke(mg_status (*fn)(P...), PyObject *const *args, Py_ssize_t count, std::index_sequence<I...>)
+PyObject *invoke(const char *name, mg_status (*fn)(P...), PyObject *const *args, Py_ssize_t count, std::index_sequence<I...>)
 {
     constexpr Py_ssize_t wanted = arguments_before<P...>(sizeof...(P));
     if (count != wanted || fn == nullptr) {
@@ -136,7 +155,7 @@ PyObject *invoke(mg_status (*fn)(P...), PyObject *const *args, Py_ssize_t count,
     }
     std::tuple<P...> v;
     if (!(convert<P>(args[std::is_same_v<P, size_t> ? arguments_before<P...>(I) - 1 : arguments_before<P...>(I)], I + 1 == sizeof...(P), &std::get<I>(v)) && ...))
-        return nullptr;
+        return call_other_types(name, args, count);
     mg_status status;
     Py_BEGIN_ALLOW_THREADS
     status = fn(std::get<I>(v)...);
@@ -153,17 +172,17 @@ PyObject *invoke(mg_status (*fn)(P...), PyObject *const *args, Py_ssize_t count,
     decltype(&::name) bound_##name;                                                             \
     template <typename... P> PyObject *call_##name(mg_status (*fn)(P...), PyObject *const *args, Py_ssize_t count) \
     {                                                                                           \
-        return invoke(fn, args, count, std::index_sequence_for<P...>{});                        \
+        return invoke(#name, fn, args, count, std::index_sequence_for<P...>{});                 \
     }                                                                                           \
     PyObject *py_##name(PyObject *, PyObject *const *args, Py_ssize_t count) { return call_##name(bound_##name, args, count); }
 MG_ENTRIES(X)
 #undef X
 
-// bind(name -> address, stream_calls)
+// bind(name -> address, stream_calls[, other_types])
 PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t count)
 {
-    if (count != 2 || !PyDict_Check(args[0])) {
-        PyErr_SetString(PyExc_TypeError, "bind(addresses, stream_calls)");
+    if ((count != 2 && count != 3) || !PyDict_Check(args[0])) {
+        PyErr_SetString(PyExc_TypeError, "bind(addresses, stream_calls[, other_types])");
         return nullptr;
     }
     void *at = nullptr;
@@ -176,6 +195,10 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t count)
 #undef X
     Py_INCREF(args[1]);
     Py_XSETREF(stream_calls, args[1]);
+    if (count == 3) {
+        Py_INCREF(args[2]);
+        Py_XSETREF(other_types, args[2]);
+    }
     Py_RETURN_NONE;
 }
 

@@ -11,6 +11,7 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libmg_gemm.so")
+CALL_PATH = os.path.join(HERE, "_mg_call.so")
 
 MG_ROW_MAJOR, MG_COL_MAJOR = 101, 102
 MG_NO_TRANS, MG_TRANS, MG_CONJ_TRANS = 111, 112, 113
@@ -65,11 +66,36 @@ def _native():
     global _call
     if _call is None:
         L = lib()
+        if not os.path.exists(CALL_PATH):
+            raise RuntimeError(f"{CALL_PATH} is missing: build it first "
+                               "(python -c 'import __graft_entry__ as g; g.build()')")
         from . import _mg_call
         names = [name for name in EXPORTS if hasattr(_mg_call, name)]
-        _mg_call.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in names}, _stream_calls)
+        _mg_call.bind({name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in names}, _stream_calls, _by_ctypes)
         _call = _mg_call
     return _call
+
+
+class ArgumentError(ctypes.ArgumentError, TypeError):
+    """an argument that ctypes cannot convert either"""
+
+
+def _by_ctypes(name, args):
+    """a call whose arguments the extension does not convert: ctypes' own scalars and whatever else ctypes takes"""
+    fn, given, values = getattr(lib(), name), iter(args), []
+    for i, t in enumerate(fn.argtypes):
+        if t is ctypes.c_size_t:
+            values.append(0 if last is None else last.numel() * last.element_size())
+            continue
+        last = next(given)
+        if t is ctypes.c_void_p:
+            values.append(_stream(last) if i + 1 == len(fn.argtypes) else _addr(last))
+        else:
+            values.append(last)
+    try:
+        return fn(*values)
+    except ctypes.ArgumentError as e:
+        raise ArgumentError(str(e)) from None
 
 
 def lib():
