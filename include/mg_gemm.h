@@ -309,12 +309,12 @@ mg_status mg_him2col(MG_CONV_GEOMETRY, const uint16_t *im, uint16_t *col, void *
 /* Convolution = IM2COL into the workspace, then the GEMM of this library on it.  The
  * workspace (device, 256-byte aligned) must hold mg_conv2d_workspace_bytes(); a 1x1 filter
  * with unit stride and no padding needs no column matrix (the image is the matrix).  Layers
- * of few outputs run as one launch of a kernel that reads the image itself, and layers with
- * few rows in the column matrix and at most 64 filters as one launch of a GEMM kernel that
- * gathers it from the image (kernels of the family MG_FAMILY_CONV); same result, the
- * workspace is required all the same.  Forcing a kernel of that family with
- * mg_override_config takes its route for any layer, forcing a GEMM kernel the
- * IM2COL route. */
+ * of few outputs run as one launch of a kernel that reads the image itself (not in the table of
+ * kernels: chosen by the library only, see mg_probe_conv_gather), and layers with few rows in
+ * the column matrix and at most 64 filters as one launch of a GEMM kernel that gathers it from
+ * the image (kernels of the family MG_FAMILY_CONV); same result, the workspace is required all
+ * the same.  Forcing a kernel of that family with mg_override_config takes its route for any
+ * layer, forcing a GEMM kernel the IM2COL route. */
 mg_status mg_sconv2d(MG_CONV_GEOMETRY, int64_t filters, float alpha, const float *im,
                      const float *weights, float beta, float *out,
                      void *workspace, size_t workspace_bytes, void *stream);
@@ -348,7 +348,9 @@ mg_status mg_query_selected(int dtype, int layout, int trans_a, int trans_b,
  * dtype.  A call for which the forced kernel is illegal (alignment, shape, workspace)
  * returns MG_ERR_CONFIG / MG_ERR_WORKSPACE instead of falling back silently. */
 mg_status mg_override_config(int32_t kernel_id, int32_t split_k);
-/* Same for the batched routine: kernel_id must be of family MG_FAMILY_BATCHED. */
+/* Same for the batched routine: kernel_id must be of family MG_FAMILY_BATCHED.  (The direct-to-LDS
+ * tiles that strided FP16 batches take by the library's choice are not in the table: they take no
+ * generic batch, whose alignment is on the device.  See mg_probe_hgemm_batched_tile.) */
 mg_status mg_override_batched_config(int32_t kernel_id);
 /* Fringe of ragged FP32 problems (paper Section 4.2: sizes just above a multiple of the tile,
  * the multiples of 129, are where tiled kernels lose most).  When m or n of the column-major view
@@ -408,7 +410,8 @@ int32_t mg_lds_split_read_offset(int32_t k_contiguous, int32_t tile_rows, int32_
 
 /* ---- measuring aids (paper Section 4.1: how the numbers are taken) --------------------------
  * Three launches that let a benchmark measure, in its own run, what its roofline fractions are
- * judged against.  All are asynchronous on `stream` and touch nothing but what is named. */
+ * judged against, and two that run a kernel of the library on problems for which it would not be
+ * chosen.  All are asynchronous on `stream` and touch nothing but what is named. */
 /* One empty kernel (one wavefront): timed back to back it gives the launch floor. */
 mg_status mg_probe_empty_launch(void *stream);
 /* The matrix pipes alone: 256 work-groups of 8 wavefronts (two per SIMD) each issue
@@ -431,6 +434,24 @@ mg_status mg_probe_mfma_only(int32_t rounds, float *sink, void *stream);
 mg_status mg_probe_hgemm_stamps(int64_t m, int64_t n, int64_t k, const uint16_t *A, int64_t lda,
                                 const uint16_t *B, int64_t ldb, uint16_t *C, int64_t ldc,
                                 uint64_t *stamps, void *stream);
+
+/* The convolution of mg_sconv2d / mg_hconv2d on the kernel for layers of few outputs, whatever the
+ * layer.  No workspace; statuses as there, and MG_ERR_CONFIG for a dtype that is none, alpha == 0
+ * and layers that the kernel does not take (sixteen channels of the image rows that 32 outputs see
+ * must fit into local memory). */
+mg_status mg_probe_conv_gather(int dtype, MG_CONV_GEOMETRY, int64_t filters, float alpha,
+                               const void *im, const void *weights, float beta, void *out,
+                               void *stream);
+/* mg_hgemm_strided_batched on direct-to-LDS tiles of 128 x 128 (tile 0), 128 x 64 (1) or 64 x 64
+ * (2), whatever the batch.  Statuses as there, and MG_ERR_CONFIG for another tile, alpha == 0, k == 0
+ * and operands that the kernels do not take: A and B, their strides and leading dimensions on 16
+ * bytes, and eight elements a piece along the direction in which each is contiguous. */
+mg_status mg_probe_hgemm_batched_tile(int32_t tile, int layout, int trans_a, int trans_b,
+                                      int64_t m, int64_t n, int64_t k, float alpha,
+                                      const uint16_t *A, int64_t lda, int64_t stride_a,
+                                      const uint16_t *B, int64_t ldb, int64_t stride_b, float beta,
+                                      uint16_t *C, int64_t ldc, int64_t stride_c,
+                                      int64_t batch_count, void *stream);
 
 const char *mg_status_string(mg_status status);
 /* "major.minor" of this ABI. */

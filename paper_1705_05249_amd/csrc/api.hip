@@ -466,7 +466,7 @@ mg_status run_gemv(int dtype, int layout, int trans, int64_t m, int64_t n, float
 mg_status run_batched(BatchedProblem &p, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k,
                       const void *A, const int64_t *a_off, int64_t stride_a, int64_t lda, const void *B,
                       const int64_t *b_off, int64_t stride_b, int64_t ldb, void *C, const int64_t *c_off,
-                      int64_t stride_c, int64_t ldc, int64_t batch, void *stream)
+                      int64_t stride_c, int64_t ldc, int64_t batch, void *stream, int probe_tile = -1)
 {
     const bool at = ta != MG_NO_TRANS, bt = tb != MG_NO_TRANS;
     p.k = k;
@@ -481,6 +481,10 @@ mg_status run_batched(BatchedProblem &p, int layout, int ta, int tb, int64_t m, 
         p.m = n; p.n = m;
         p.A = B; p.a_off = b_off; p.stride_a = stride_b; p.lda = ldb; p.a_trans = bt;
         p.B = A; p.b_off = a_off; p.stride_b = stride_a; p.ldb = lda; p.b_trans = at;
+    }
+    if (probe_tile >= 0) {
+        if (probe_tile > 2 || !batched_dma_fits(p)) return MG_ERR_CONFIG;
+        return launch_batched_dma(p, probe_tile) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
     }
     const auto &t = table();
     int32_t kernel = -1;
@@ -518,7 +522,7 @@ mg_status generic_batched(int dtype, int layout, int ta, int tb, int64_t m, int6
 
 mg_status strided_batched(int dtype, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k, float alpha,
                           const void *A, int64_t lda, int64_t stride_a, const void *B, int64_t ldb, int64_t stride_b,
-                          float beta, void *C, int64_t ldc, int64_t stride_c, int64_t batch_count, void *stream)
+                          float beta, void *C, int64_t ldc, int64_t stride_c, int64_t batch_count, void *stream, int probe_tile = -1)
 {
     mg_status s = check_shape(layout, ta, tb, m, n, k, lda, ldb, ldc);
     if (s != MG_OK) return s;
@@ -532,7 +536,7 @@ mg_status strided_batched(int dtype, int layout, int ta, int tb, int64_t m, int6
     p.strided = true;
     p.alpha = alpha; p.beta = beta;
     return run_batched(p, layout, ta, tb, m, n, k, A, nullptr, stride_a, lda, B, nullptr, stride_b, ldb, C, nullptr,
-                       stride_c, ldc, batch_count, stream);
+                       stride_c, ldc, batch_count, stream, probe_tile);
 }
 
 // Checks a convolution geometry; fills the output extents and K = channels * kernel_h * kernel_w.
@@ -1148,6 +1152,27 @@ mg_status mg_hconv2d(MG_CONV_SHAPE_ARGS, int64_t filters, float alpha, const uin
                      float beta, uint16_t *out, void *workspace, size_t workspace_bytes, void *stream)
 {
     return run_conv2d(MG_F16, MG_CONV_SHAPE, filters, alpha, im, weights, beta, out, workspace, workspace_bytes, stream);
+}
+
+mg_status mg_probe_conv_gather(int dtype, MG_CONV_SHAPE_ARGS, int64_t filters, float alpha, const void *im, const void *weights, float beta, void *out, void *stream)
+{
+    if (dtype != MG_F32 && dtype != MG_F16) return MG_ERR_CONFIG;
+    const ConvShape s = MG_CONV_SHAPE;
+    int64_t out_h, out_w, k;
+    const mg_status st = check_conv(s, filters, &out_h, &out_w, &k);
+    if (st != MG_OK) return st;
+    if (filters == 0 || out_h * out_w == 0) return MG_OK;
+    if (out == nullptr || (alpha != 0.f && (im == nullptr || weights == nullptr))) return MG_ERR_NULL;
+    if (alpha == 0.f || !conv_gather_fits(dtype, s, filters)) return MG_ERR_CONFIG;
+    return launch_conv_gather(dtype, s, filters, alpha, im, weights, beta, out, static_cast<hipStream_t>(stream)) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
+}
+
+mg_status mg_probe_hgemm_batched_tile(int32_t tile, int layout, int ta, int tb, int64_t m, int64_t n, int64_t k, float alpha, const uint16_t *A, int64_t lda,
+                                      int64_t stride_a, const uint16_t *B, int64_t ldb, int64_t stride_b, float beta, uint16_t *C, int64_t ldc,
+                                      int64_t stride_c, int64_t batch_count, void *stream)
+{
+    if (tile < 0) return MG_ERR_CONFIG;
+    return strided_batched(MG_F16, layout, ta, tb, m, n, k, alpha, A, lda, stride_a, B, ldb, stride_b, beta, C, ldc, stride_c, batch_count, stream, tile);
 }
 
 size_t mg_conv2d_workspace_bytes(int dtype, MG_CONV_SHAPE_ARGS, int64_t filters)

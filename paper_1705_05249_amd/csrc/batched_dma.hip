@@ -75,9 +75,9 @@ int tile_of(const BatchedProblem &p)
     return cost[2] < cost[best] ? 2 : best;
 }
 
-template <bool AK, bool BKC> hipError_t launch_order(const BatchedProblem &p)
+template <bool AK, bool BKC> hipError_t launch_order(const BatchedProblem &p, int tile)
 {
-    switch (tile_of(p)) {
+    switch (tile) {
     case 0: return launch<128, 128, 2, 4, AK, BKC, 2>(p);
     case 1: return launch<128, 64, 4, 2, AK, BKC, 2>(p);
     default: return launch<64, 64, 2, 2, AK, BKC, 2>(p);
@@ -86,7 +86,7 @@ template <bool AK, bool BKC> hipError_t launch_order(const BatchedProblem &p)
 
 }  // namespace
 
-bool batched_dma_pays(const BatchedProblem &p)
+bool batched_dma_fits(const BatchedProblem &p)
 {
     if (!p.strided || p.dtype != MG_F16 || p.alpha == 0.f || p.k == 0) return false;
     const int64_t lim = int64_t(1) << 31;
@@ -94,7 +94,13 @@ bool batched_dma_pays(const BatchedProblem &p)
     if (pointer_alignment(p.A) < 16 || pointer_alignment(p.B) < 16) return false;
     if ((p.a_trans ? p.k : p.m) % 8 || (p.b_trans ? p.n : p.k) % 8) return false;
     if ((p.lda > p.ldb ? p.lda : p.ldb) * 128 * 2 >= lim - 4096) return false;
-    if (ceil_div(p.m, 64) * ceil_div(p.n, 64) * p.batch >= lim) return false;
+    // (the grid of the smallest tiles, in threads)
+    return ceil_div(p.m, 64) * ceil_div(p.n, 64) * p.batch < lim / 128;
+}
+
+bool batched_dma_pays(const BatchedProblem &p)
+{
+    if (!batched_dma_fits(p)) return false;
     // whole 64^3 with A along m and B along k have a kernel of their own (10000 of them 36.7 us, here 38.0)
     if (p.m == 64 && p.n == 64 && p.k == 64 && !p.a_trans && !p.b_trans) return false;
     // Thin instances and streams from memory lose more to the tiles' empty part than the loads gain.  us, batched_tile.hip / here: 3000 x (40, 128, 128)
@@ -107,10 +113,11 @@ bool batched_dma_pays(const BatchedProblem &p)
     return (thin >= 40 && mb <= 60.0) || (thin > 48 && mb <= 250.0);
 }
 
-hipError_t launch_batched_dma(const BatchedProblem &p)
+hipError_t launch_batched_dma(const BatchedProblem &p, int tile)
 {
-    if (p.a_trans) return p.b_trans ? launch_order<true, false>(p) : launch_order<true, true>(p);
-    return p.b_trans ? launch_order<false, false>(p) : launch_order<false, true>(p);
+    if (tile < 0) tile = tile_of(p);
+    if (p.a_trans) return p.b_trans ? launch_order<true, false>(p, tile) : launch_order<true, true>(p, tile);
+    return p.b_trans ? launch_order<false, false>(p, tile) : launch_order<false, true>(p, tile);
 }
 
 }  // namespace mg

@@ -269,7 +269,7 @@ Band band_of(int dtype, const ConvShape &s, int64_t out_h, int64_t out_w)
 
 }  // namespace
 
-static bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
+bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
 {
     const int64_t out_h = conv_out_extent(s.height, s.kernel_h, s.pad_h, s.stride_h, s.dilation_h);
     const int64_t out_w = conv_out_extent(s.width, s.kernel_w, s.pad_w, s.stride_w, s.dilation_w);

@@ -102,6 +102,7 @@ int64_t conv_out_extent(int64_t size, int64_t kernel, int64_t pad, int64_t strid
 hipError_t launch_im2col(int dtype, const ConvShape &s, const void *im, void *col, hipStream_t stream);
 
 // The whole convolution in one launch (conv_gather.hip): positions x filters outputs, out (filters x positions, row-major) = alpha * ... + beta * out
+bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters);
 bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters);
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,
                               void *out, hipStream_t stream);
@@ -160,9 +161,10 @@ inline bool dma_offsets_fit(const Problem &p, int64_t tile_rows, int64_t tile_k)
     return (p.lda > p.ldb ? p.lda : p.ldb) * lines * static_cast<int64_t>(p.elem()) < (int64_t(1) << 31) - 4096;
 }
 
-// Strided batches of FP16 instances on the direct-to-LDS tiles (batched_dma.hip)
+// Strided batches of FP16 instances on the direct-to-LDS tiles (batched_dma.hip).  tile: 0, 1, 2 for 128 x 128, 128 x 64, 64 x 64; -1: the kernel's choice
+bool batched_dma_fits(const BatchedProblem &p);
 bool batched_dma_pays(const BatchedProblem &p);
-hipError_t launch_batched_dma(const BatchedProblem &p);
+hipError_t launch_batched_dma(const BatchedProblem &p, int tile = -1);
 
 // One compiled kernel (or kernel family instance) in the configuration table.
 struct KernelEntry {

@@ -31,7 +31,7 @@ EXPORTS = ("mg_sgemm", "mg_hgemm", "mg_sgemm_static", "mg_sgemv", "mg_hgemv", "m
            "mg_kernel_info", "mg_kernel_name", "mg_query_selected", "mg_override_config",
            "mg_override_batched_config", "mg_override_fringe", "mg_clear_override", "mg_lds_store_offset", "mg_lds_read_offset", "mg_lds_f32_store_offset", "mg_lds_f32_read_offset",
            "mg_lds_split_store_offset", "mg_lds_split_read_offset",
-           "mg_probe_empty_launch", "mg_probe_mfma_only", "mg_probe_hgemm_stamps",
+           "mg_probe_empty_launch", "mg_probe_mfma_only", "mg_probe_hgemm_stamps", "mg_probe_conv_gather", "mg_probe_hgemm_batched_tile",
            "mg_status_string", "mg_version")
 
 
@@ -202,6 +202,10 @@ def lib():
         L.mg_probe_mfma_only.restype = i32
         L.mg_probe_hgemm_stamps.argtypes = [i64, i64, i64, vp, i64, vp, i64, vp, i64, vp, vp]
         L.mg_probe_hgemm_stamps.restype = i32
+        L.mg_probe_conv_gather.argtypes = [i32] + geometry + [i64, f32, vp, vp, f32, vp, vp]
+        L.mg_probe_conv_gather.restype = i32
+        L.mg_probe_hgemm_batched_tile.argtypes = [ctypes.c_int32] + L.mg_hgemm_strided_batched.argtypes
+        L.mg_probe_hgemm_batched_tile.restype = i32
         L.mg_status_string.argtypes = [i32]
         L.mg_status_string.restype = ctypes.c_char_p
         L.mg_version.argtypes = []
@@ -482,6 +486,20 @@ def mg_probe_mfma_only(rounds, sink, stream=None, check=True) -> int:
 def mg_probe_hgemm_stamps(m, n, k, A, lda, B, ldb, C, ldc, stamps, stream=None, check=True) -> int:
     return _checked(lib().mg_probe_hgemm_stamps(m, n, k, _addr(A), lda, _addr(B), ldb, _addr(C), ldc, _addr(stamps),
                                                 _stream(stream)), "mg_probe_hgemm_stamps", check)
+
+
+def mg_probe_conv_gather(dtype, channels, height, width, kernel, pad, stride, dilation, filters, alpha, im, weights, beta, out, stream=None,
+                         check=True) -> int:
+    st = lib().mg_probe_conv_gather(dtype, *_geometry(channels, height, width, kernel, pad, stride, dilation), filters, alpha, _addr(im),
+                                    _addr(weights), beta, _addr(out), _stream(stream))
+    return _checked(st, "mg_probe_conv_gather", check)
+
+
+def mg_probe_hgemm_batched_tile(tile, layout, trans_a, trans_b, m, n, k, alpha, A, lda, stride_a, B, ldb, stride_b, beta, C, ldc, stride_c,
+                                batch_count, stream=None, check=True) -> int:
+    st = lib().mg_probe_hgemm_batched_tile(tile, layout, trans_a, trans_b, m, n, k, alpha, _addr(A), lda, stride_a, _addr(B), ldb, stride_b,
+                                           beta, _addr(C), ldc, stride_c, batch_count, _stream(stream))
+    return _checked(st, "mg_probe_hgemm_batched_tile", check)
 
 
 def mg_query_selected(dtype, layout, trans_a, trans_b, m, n, k, lda, ldb, ldc, alpha=1.0, beta=0.0,

@@ -54,9 +54,48 @@ def test_blocks_bands_and_sums(CO, dtype, geo):
         case = W.conv_case(dtype, *geo, alpha=1.0 if integer else 0.75, beta=1.0 if integer else -0.5, case=11, integer=integer)
         H.check_conv(case, CO, "auto")
     ran = kernels(dtype, *geo)
-    # (182 channels in FP32: the rows outside the image are most of the band, and the unfold route is the better one)
+    # (182 channels in FP32: the rows outside the image are most of the band, and the unfold route is the better one; test_any_layer_on_this_kernel has it)
     if (dtype, geo[0]) != ("f32", 182):
         assert len(ran) == 1 and "conv_gather" in ran[0], ran
+
+
+def odd_layers():
+    """small layers of any geometry: about a third of them with one to three positions, filters or channels"""
+    import random
+    rng = random.Random(6)
+    layers = []
+    while len(layers) < 120:
+        few = lambda most: rng.randint(1, 3) if rng.random() < 0.3 else rng.randint(1, most)       # noqa: E731
+        kernel, dilation = (rng.choice((1, 2, 3, 5, 7)), rng.choice((1, 3, 4))), (rng.choice((1, 1, 2, 3)), rng.choice((1, 1, 2, 3)))
+        pad, stride = (rng.randint(0, 4), rng.randint(0, 9)), (rng.randint(1, 4), rng.randint(1, 4))
+        channels, height, width, filters = few(90), few(40), few(70), few(80)
+        extents = [(size + 2 * p - d * (x - 1) - 1) // s + 1 for size, x, p, s, d in zip((height, width), kernel, pad, stride, dilation)]
+        if min(extents) >= 1 and channels * kernel[0] * kernel[1] * extents[0] * extents[1] * filters < 4e7:
+            layers.append((channels, height, width, kernel, pad, stride, dilation, filters))
+    return layers
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("geo", GEO + odd_layers())
+def test_any_layer_on_this_kernel(CO, dtype, geo):
+    """not the library's choice: every layer that the kernel takes"""
+    import numpy as np
+    case = W.conv_case(dtype, *geo, alpha=1.0, beta=1.0 if geo[0] % 2 else 0.0, case=13, integer=True)
+    if case.beta == 0.0:
+        case.out[:] = np.nan
+    want, _ = CO.conv2d(dtype, *H.conv_geometry(case), case.filters, case.alpha, case.im, case.weights, case.beta, case.out)
+    im, weights, out = H.to_gpu(case.im), H.to_gpu(case.weights), H.to_gpu(case.out)
+    G.mg_probe_conv_gather(G.MG_F32 if dtype == "f32" else G.MG_F16, *H.conv_geometry(case), case.filters, case.alpha, im, weights, case.beta, out)
+    assert np.array_equal(out.cpu().numpy().astype(np.float64), want)
+
+
+def test_layers_whose_rows_do_not_fit_are_refused():
+    """sixteen channels of a band of 7 rows of 1000 elements in FP32"""
+    import torch
+    x = torch.zeros(64 * 7 * 1000, device="cuda")
+    assert G.mg_probe_conv_gather(G.MG_F32, 64, 7, 1000, (7, 7), (3, 3), (1, 1), (1, 1), 1, 1.0, x, x, 0.0, x.clone(), check=False) == -11
+    assert G.mg_probe_conv_gather(G.MG_F32, 64, 7, 100, (3, 3), (1, 1), (1, 1), (1, 1), 1, 0.0, x, x, 0.0, x.clone(), check=False) == -11
+    assert G.mg_probe_conv_gather(7, 64, 7, 100, (3, 3), (1, 1), (1, 1), (1, 1), 1, 1.0, x, x, 0.0, x.clone(), check=False) == -11
 
 
 def test_two_chunks_of_channels_f32(CO):
