@@ -298,24 +298,24 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                    {1.2, 0.163, 0.025, 0.179, 0.95, 1.12, 1.05, 0.12, 0.49, 0.64}};
         // Of sums of up to four K-tiles these are up to 40 % off, since a turn is then its first load and its epilogue, and the register-staged
         // kernels have their place: whole tiles, and checked ones for several turns of single K-tiles ((560, 6952, 64) with
-        // beta 64 x 64 7.2 us, 64 x 64 / 128 x 128 direct-to-LDS 9.1 / 10.5).  Their times in us, fitted to half of 600 sizes of 64 to 8192 and of 670 whole
-        // ones (3 to 7 % rms): a fixed part; turns of one tile per compute unit; and what a busier chip takes longer.  Half of the sizes, the other half
-        // chosen for, these rules over the kernels without the direct-to-LDS tiles for any size: 0.875 of the time (whole ones 0.98), 3 of 148 (9 of
-        // 334) more than 3 % slower; the costs above, without these, 0.90 (1.03), 20 (147).
+        // beta 64 x 64 7.2 us, 64 x 64 / 128 x 128 direct-to-LDS 9.1 / 10.5).  Their times in us, fitted to 820 sizes of 64 to 8192 (the checked tiles' to those of
+        // more than one turn) and to 670 whole ones, 3 to 6 % rms: a fixed part; turns of one tile per compute unit; and what a busier chip takes longer.
+        // Fitted to half of the sizes and chosen for the other half, against the kernels without the direct-to-LDS tiles for any size: 0.886 of the time
+        // (whole ones 0.98), 16 of 777 (9 of 334) more than 3 % slower, at most 10 % (19 %); by the costs above 0.907 (1.03), 91 (147), up to 28 % (43 %).
         struct ShortCost {
             double fixed, turn, turn_beta, ktile, busy, fixed_beta = 0.0, busy_beta = 0.0;
         };
         // general products | of whole tiles | triangles of C (400 sizes of 64 to 6200; 5 of 204 held out more than 3 % slower, without 16, up to 29 %;
         // (4416, 120) with beta 24.5 us on 64 x 64 direct-to-LDS tiles, 18.6)
         static const ShortCost short_costs[3][14] = {{{}, {}, {}, {}, {}, {},
-                                                      {4.33, 0.46, 0.74, 0.33, 0.37},
-                                                      {3.73, 0.36, 0.31, 0.20, 0.18},
+                                                      {3.61, 0.45, 0.48, 0.26, 0.88},
+                                                      {3.50, 0.20, 0.21, 0.15, 0.56},
                                                       {},
-                                                      {2.43, 3.03, 1.84, 0.62, 3.42},
-                                                      {1.85, 3.44, 1.38, 0.48, 1.98},
-                                                      {1.73, 2.58, 1.01, 0.35, 1.31},
-                                                      {1.57, 2.03, 0.54, 0.26, 0.61},
-                                                      {2.66, 0.68, 0.43, 0.19, 0.24}},
+                                                      {2.41, 3.02, 2.12, 0.65, 2.88},
+                                                      {2.03, 3.21, 1.51, 0.50, 1.85},
+                                                      {1.84, 2.42, 1.06, 0.37, 1.28},
+                                                      {1.66, 1.92, 0.54, 0.27, 0.68},
+                                                      {2.62, 0.72, 0.37, 0.17, 0.31}},
                                                      {{}, {},
                                                       {3.07, 0.85, 0.60, 0.40, 1.18},
                                                       {}, {}, {},
