@@ -1,10 +1,10 @@
 // Strided batches of FP16 instances whose rows start on 16 bytes: the direct-to-LDS tiles for sizes that end anywhere (mfma_dma_kernel.h), a grid of
 // the tiles of all instances.  (Only strided batches: the offsets of the others are on the device, their alignment is not known.)
 // Bound by latency for calls that the chip holds at once (launch, one load, the products of a K-tile or two, the turn through LDS and one store:
-// 512 x (128, 128, 64) in 7.4 us of which the traffic of its 33 MB takes 5), else by traffic.  The kernel of batched_tile.hip brings 64 x 64
-// tiles through registers, so that a 128 x 128 instance asks for its operands twice and takes four work-groups.  us, that kernel / this one: 512 x
-// (128, 128, 64) 10.6 / 7.4, 4000 of them (262 MB) 50 / 43, 500 x 128^3 11.9 / 9.3, 1000 x 96^3 17.2 / 14.5, 200 x 160^3 12.4 / 9.6, 200 x (64, 72,
-// 136) 6.6 / 4.1, 3000 x 48^3 11.8 / 10.5.  Two LDS stages; three take a compute unit's second work-group (9.7).
+// 512 x (128, 128, 64) in 8.6 us of which the traffic of its 33 MB takes 5), else by traffic.  The kernel of batched_tile.hip brings 64 x 64
+// tiles through registers, so that a 128 x 128 instance asks for its operands twice and takes four work-groups.  us in a replayed graph (A along m, B along
+// k), that kernel / this one: 512 x (128, 128, 64) 11.5 / 8.6, 4000 of them (262 MB, not taken) 52 / 53, 500 x 128^3 13.0 / 10.5, 1000 x 96^3 18.4 / 15.4, 200 x 160^3
+// 13.4 / 10.7, 200 x (64, 72, 136) 6.9 / 4.7, 3000 x 48^3 12.5 / 11.5.  Two LDS stages; three take a compute unit's second work-group (1.3 times as long).
 #include "batched_walk.h"
 #include "mfma_dma_kernel.h"
 #include "mfma_host.h"
@@ -66,7 +66,7 @@ template <int BM, int BN, int WM, int WN, bool AK, bool BKC, int STAGES> hipErro
 }
 
 // 128 x 128, 128 x 64 or 64 x 64: the tile that computes least beside the instance, the smaller ones at 1.05 and 1.25 times their area (they ask for
-// the operands more often: 128 x 128 x 64 on the three 7.4 / 7.9 / 8.1 us; over 41 sizes any factors of 1.02 to 1.1 and 1.1 to 1.3 give the same)
+// the operands more often: 512 x (128, 128, 64) on the three 8.5 / 8.8 / 9.0 us; over 41 sizes any factors of 1.02 to 1.1 and 1.1 to 1.3 give the same)
 int tile_of(const BatchedProblem &p)
 {
     auto area = [&](int64_t bm, int64_t bn) { return static_cast<double>(ceil_div(p.m, bm) * bm) * static_cast<double>(ceil_div(p.n, bn) * bn); };
@@ -104,9 +104,9 @@ bool batched_dma_pays(const BatchedProblem &p)
     // whole 64^3 with A along m and B along k have a kernel of their own (10000 of them 36.7 us, here 38.0)
     if (p.m == 64 && p.n == 64 && p.k == 64 && !p.a_trans && !p.b_trans) return false;
     // Thin instances and streams from memory lose more to the tiles' empty part than the loads gain.  us, batched_tile.hip / here: 3000 x (40, 128, 128)
-    // 25.4 / 30.1, 9000 x (56, 160, 32) (286 MB) 70 / 94, 7000 x (160, 80, 72) (421 MB) 121 / 171.  So do 64 x 64 tiles in large batches, and sooner where
-    // neither operand runs along k: 1621 x 136^3 (180 MB) 61 / 68, 2000 x (56, 120, 176) (151 MB) 24 / 27.  Over 440 sizes, routes timed in one build,
-    // calls are 1.19 times as fast as without these kernels, those they do not take included; of the 344 they take 6 are 2 to 8 % slower.
+    // 27.7 / 30.3, 9000 x (56, 160, 32) (286 MB) 78 / 93, 7000 x (160, 80, 72) (421 MB) 135 / 168.  So do 64 x 64 tiles in large batches, and sooner where
+    // neither operand runs along k: 1621 x 136^3 (180 MB) 51.5 / 59.2, 2000 x (56, 120, 176) (151 MB) 24.5 / 27.6.  Over 500 random batches calls take 0.86 of
+    // the time without these kernels, those they do not take included; 6 are 3 to 8 % slower.
     const double mb = 2.0e-6 * static_cast<double>(p.batch) * static_cast<double>(p.m * p.k + p.k * p.n + p.m * p.n);
     const int64_t thin = p.m < p.n ? p.m : p.n;
     if (tile_of(p) == 2 && mb > (!p.a_trans && p.b_trans ? 40.0 : 80.0)) return false;

@@ -35,7 +35,7 @@ template <int RB> MG_HD constexpr int swizzle(int row) { return RB == 16 ? swizz
 template <int RB> MG_HD constexpr int kcontig_slot(int row, int chunk) { return row * 128 + ((chunk ^ swizzle<RB>(row)) << 4); }
 
 // Lane's read address (byte offset inside the operand stage) for fragment 0 of K-step 0 of a wavefront tile that
-// starts at row wrow (a multiple of 64); fragment f of K-step s is at (base ^ kcontig_xor(f, s)) + f * RB * 128.
+// starts at row wrow (a multiple of RB, with 32-row fragments of 64); fragment f of K-step s is at (base ^ kcontig_xor(f, s)) + f * RB * 128.
 template <int RB> MG_HD constexpr int kcontig_base(int lane, int wrow)
 {
     return kcontig_slot<RB>(wrow + lane % RB, lane / RB);
@@ -49,7 +49,7 @@ template <int RB> MG_HD constexpr int kcontig_xor(int f, int s)
 }
 
 // ---- [k][row] layout (operand contiguous along its row index: m for A, n for B), FP16 only: as in memory, one
-// line of `rows` halves per k; the 16-byte chunk c of line k sits at slot c ^ line_swizzle(k).  An MFMA operand is
+// line of `rows` halves per k; the 16-byte chunk c of line k sits at slot c ^ line_swizzle(rows, k).  An MFMA operand is
 // two transposing 8-byte reads (ds_read_b64_tr_b16): in each group of 16 lanes, lane 4a + b receives element b of
 // what lanes a, a + 4, a + 8, a + 12 fetched, so lanes a + 4j (j = 0..3) fetch the same four rows at four consecutive k.
 // Lines of an odd number of 128-byte pieces (64 or 192 rows): successive lines already start half a bank row apart, and a line is closed

@@ -1,8 +1,8 @@
 // FP16 macro-tile GEMM kernel for gfx950 whose operand tiles go from global memory straight into LDS
-// (buffer loads with the LDS modifier): no staging registers, no LDS store instructions.  Whole tiles and
-// 16-byte aligned operands only; everything else runs on the register-staged kernel of mfma_kernel.h, whose
-// work-group tile / wavefront tile / K-step structure (the parameterised gemm kernel of the paper's
-// Section 3.2), rasterisation and epilogue this kernel shares.
+// (buffer loads with the LDS modifier): no staging registers, no LDS store instructions.  Operands whose rows start on
+// 16 bytes: whole tiles, or (VARIANT DMA_RAGGED) sizes that end inside a tile on whole 16-byte pieces; everything else runs
+// on the register-staged kernel of mfma_kernel.h, whose work-group tile / wavefront tile / K-step structure (the
+// parameterised gemm kernel of the paper's Section 3.2), rasterisation and epilogue this kernel shares.
 //
 // A direct-to-LDS load writes, per wavefront instruction, 64 x 16 bytes to consecutive LDS addresses (base in
 // M0 + immediate offset + lane * 16) while every lane names its own global address; the immediate offset is
@@ -13,7 +13,8 @@
 //   * contiguous along k: [row][k], 128 bytes per row, chunk c of row r at slot c ^ ((r ^ r/8) % 8) -- the
 //     layout of the register-staged kernel; an MFMA operand is one 16-byte read per lane;
 //   * contiguous along its row index (m for A, n for B): [k][row] as in memory, 2 * ROWS bytes per k, the
-//     16-byte chunk c of line k at slot c ^ (4 * (k % 4) + 2 * (k / 8 % 2)); an MFMA operand is two transposing 8-byte reads
+//     16-byte chunk c of line k at slot c ^ line_swizzle(ROWS, k) (lds_layout.h; for lines of a multiple of 128 rows
+//     4 * (k % 4) + 2 * (k / 8 % 2)); an MFMA operand is two transposing 8-byte reads
 //     (ds_read_b64_tr_b16): in each group of 16 lanes, lane 4a + b receives element b of what lanes a, a + 4,
 //     a + 8, a + 12 fetched, so when those four lanes fetch the same four rows at four consecutive k, lane
 //     4a + b ends up with four consecutive k of row 4a + b.  The LDS serves 256 bytes per clock (64 banks),

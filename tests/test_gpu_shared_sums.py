@@ -18,14 +18,17 @@ ORDERS = {"mk": (N, N), "kk": (T, N), "mn": (N, T), "kn": (T, T)}
 @pytest.mark.parametrize("m,n,pairs,over,pad", [(32, 32, 1, 0, 0), (35, 29, 1, 0, 0), (3, 5, 0, 1, 0), (33, 64, 1, -1, 1), (64, 31, 8, 1, 3), (40, 48, 9, 0, 8),
                                                 (7, 100, 7, 5, 1), (65, 33, 41, -7, 0), (16, 70, 16, 0, 2)])
 def test_blocks_and_pairs(oracle, dtype, pair, order, m, n, pairs, over, pad):
+    """(what lies between and behind the lines of A and B is NaN)"""
     ta, tb = ORDERS[order]
     k = pairs * pair + over
     lds = dict(lda=W.tight_ld(C, ta, m, k) + pad, ldb=W.tight_ld(C, tb, k, n) + pad, ldc=m + pad)
-    make = W.skinny_case if dtype == "f32" else W.hgemm_case
     if dtype == "f32":
-        case = make(m, n, k, case=31, integer=True, ta=ta, tb=tb, alpha=1.0, beta=1.0)
+        import numpy as np
+        g = W.rng_for(5, 31)
+        matrices = (W.small_ints(g, s, 2, np.float32) for s in ((m, k), (k, n), (m, n)))
+        case = W.make_case(f"shared_{m}x{n}x{k}", "f32", C, ta, tb, *matrices, 1.0, 1.0, exact=True, **lds)
     else:
-        case = make(m, n, k, case=31, layout=C, ta=ta, tb=tb, beta=1.0, integer=True, **lds)
+        case = W.hgemm_case(m, n, k, case=31, layout=C, ta=ta, tb=tb, beta=1.0, integer=True, **lds)
     try:
         G.mg_override_config(G.kernel_id(("s" if dtype == "f32" else "h") + "tiny_32x32_" + order), 1)
         H.check_case(case, oracle)
