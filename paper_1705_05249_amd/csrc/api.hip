@@ -5,6 +5,8 @@
 // a machine without a GPU.
 #include <atomic>
 #include <mutex>
+#include <string.h>
+
 #include <string>
 
 #include "internal.h"
@@ -581,10 +583,10 @@ mg_status run_im2col(int dtype, const ConvShape &s, const void *im, void *col, v
     return launch_im2col(dtype, s, im, col, static_cast<hipStream_t>(stream)) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
 }
 
-// The convolution as one GEMM launch whose op(A) is gathered from the image (kernels of the family MG_FAMILY_CONV):
-// the configuration is the one automatic selection gives the GEMM on a stored column matrix, if that is a kernel
-// with such a variant (the 64 x 64 tile "mk" kernels, with their slices of the sum) and the layer is one where the
-// gather pays, or the forced configuration if that is of the family.  MG_ERR_CONFIG: no such kernel, take the unfold route.
+// The convolution as one GEMM launch whose op(A) is gathered from the image (kernels of the family MG_FAMILY_CONV): the 64 x 64 tile where
+// the gather pays, or the forced configuration if that is of the family.  A gathered K-tile takes about 1.5 us against 1.0 us for a stored
+// one (each element is a load of its own behind index arithmetic), and every tile column of filters gathers the same elements again: it pays
+// where the sum is a few K-tiles and the filters are one tile column (conv_route).  MG_ERR_CONFIG: take the unfold route.
 mg_status run_conv2d_fused(int dtype, const ConvShape &s, int64_t filters, int64_t n, int64_t k, float alpha, const void *im,
                            const void *weights, float beta, void *out, void *ws, size_t ws_bytes, void *stream)
 {
@@ -599,24 +601,9 @@ mg_status run_conv2d_fused(int dtype, const ConvShape &s, int64_t filters, int64
         kernel = forced;
         split = g_override_split[dtype];
     } else {
-        // Measured on the four benchmark layers (FP16, us, fused / unfold route): 147 rows of the column matrix and 64
-        // filters 9.4 / 12.2; 576 rows, 128 filters 16.9 / 14.0; 1152 rows, 256 filters 30 (15.5 in four slices) /
-        // 14.9; 2304 rows, 512 filters 55 (20 in four slices) / 17.5.  A gathered K-tile takes about 1.5 us against
-        // 1.0 us for a stored one (each element is a load of its own behind index arithmetic), and every tile column
-        // of filters gathers the same elements again: the fused route pays where the sum is a few K-tiles and the
-        // filters are one tile column.
-        if (k > 256 || filters > 64) return MG_ERR_CONFIG;
-        int32_t plain = -1;
-        p.fp32_pipes = true;               // (no variant that gathers exists for the others)
-        select_config(t, p, 256, ws_bytes, &plain, &split);
-        if (plain < 0) return MG_ERR_CONFIG;
-        const std::string name = t[plain].name;
-        const char *fused = nullptr;
-        if (name == "hmfma_64x64x64_w2x2_mk" || name == "hmfma_64x64x64_w2x2_mk_edge") fused = "hconv_64x64x64_w2x2";
-        else if (name == "smfma_64x64x32_w2x2_mk" || name == "smfma_64x64x32_w2x2_mk_edge") fused = "sconv_64x64x32_w2x2";
-        if (fused == nullptr) return MG_ERR_CONFIG;
+        const char *fused = dtype == MG_F32 ? "sconv_64x64x32_w2x2" : "hconv_64x64x64_w2x2";
         for (size_t i = 0; i < t.size(); ++i)
-            if (std::string(t[i].name) == fused) kernel = static_cast<int32_t>(i);
+            if (strcmp(t[i].name, fused) == 0) kernel = static_cast<int32_t>(i);
         if (kernel < 0) return MG_ERR_CONFIG;
     }
     p.A = im;
@@ -651,11 +638,11 @@ mg_status run_conv2d(int dtype, const ConvShape &s, int64_t filters, float alpha
             if (ws == nullptr || pointer_alignment(ws) < 256 || ws_bytes < col_bytes) return MG_ERR_WORKSPACE;
         }
         // Few outputs: the whole convolution in one launch, from a band of the image in LDS.
-        if (forced < 0 && !plain && conv_gather_pays(dtype, s, filters))
+        const ConvRoute route = forced >= 0 || plain ? ConvRoute::unfold : conv_route(dtype, s, filters);
+        if (route == ConvRoute::gather)
             return launch_conv_gather(dtype, s, filters, alpha, im, weights, beta, out, static_cast<hipStream_t>(stream)) == hipSuccess ? MG_OK : MG_ERR_LAUNCH;
-        // Without the unfold pass where a kernel that gathers op(A) from the image exists for the configuration the
-        // GEMM would get: the caller's workspace then only serves the slices of the sum.
-        mg_status fused = run_conv2d_fused(dtype, s, filters, n, k, alpha, im, weights, beta, out, ws, ws_bytes, stream);
+        // Without the unfold pass, or a forced kernel of that family (whose slices of the sum are all that the workspace then serves).
+        mg_status fused = forced < 0 && route != ConvRoute::fused ? MG_ERR_CONFIG : run_conv2d_fused(dtype, s, filters, n, k, alpha, im, weights, beta, out, ws, ws_bytes, stream);
         if (fused != MG_ERR_CONFIG || forced_conv) return fused;
         if (launch_im2col(dtype, s, im, ws, static_cast<hipStream_t>(stream)) != hipSuccess) return MG_ERR_LAUNCH;
         col = ws;

@@ -283,41 +283,88 @@ bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
     return band_of(dtype, s, out_h, out_w).chunk != 0;
 }
 
-// Whether the kernel takes a layer and is estimated faster than the routes through GEMM kernels: the unfold route, or for layers of few terms
-// and filters the one that gathers from memory (fused).  All estimates in us, fitted to both routes of one build over 300 random layers (1 to 512 channels, 7
-// to 256 wide, 1 x 1 to 7 x 7 filters, both strides, 16 to 512 filters).  FP16 filters of an odd number of terms have rows at odd elements, whose loads
-// take longer.  Where the grid takes several turns, the band several chunks or more than four rounds, loads compete for the caches and more is asked;
-// past six turns it did not pay (32 channels of 256 x 256, 7 x 7, 48 filters in FP16 121 / 142 us).  On 308 other layers calls are 1.30 (FP16) and 1.27 (FP32)
-// times as fast as without the kernel, those it does not take included; 3 channels of 224 x 224, 7 x 7, stride 2, 64 filters keep the fused
-// route (9.2 / 18.3), 447 of 98 x 98 with 32 filters the unfold route (62 / 114).  Of 690 other FP32 layers that the estimates alone would give it, 7 of the
-// 22 with several chunks or more than three turns and a gain of less than 1.4 lost up to a fifth (480 of 64 x 64, 5 x 5, stride 2, 249 filters
-// 80 / 96): these stay out; of the rest 2 are more than 3 % slower (68 of 17 x 17, 1 x 1, stride 2, 171 filters 6.7 / 7.4).
-bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters)
+// The route of a layer: this kernel, the GEMM kernel that gathers the column matrix from memory (up to 256 terms and 64 filters), or the unfold pass and a
+// GEMM.  All estimates in us, fitted to each route forced in one build on 18000 (FP16) and 17000 (FP32) random layers: 1 to 512 channels, 4 to 300 wide, filters of 1 x 1
+// to 7 x 7, strides, paddings and dilations up to 3 and 4, 1 to 512 filters; rms errors: here 6 and 4.5 %, gathering GEMM 7 and 6, unfold 7 and 6.5.  A gain of 3 % is asked for, of
+// 12 % with several turns or chunks, whose estimates are further off; past eight turns it did not pay.  Here: rounds of loads that bring the band and the LDS reads of the
+// sum make a work-group's latency, of which a second work-group on a compute unit hides all but its loads and K-steps; what the grid reads counts beside that.
+// On 16000 other layers calls take 0.70 of the time without this kernel, 41 are more than 3 % slower (at most 1.27 times).  By the rule before (one sum of six terms for
+// the other routes, a gain of 1.4 for FP32 layers of several chunks or turns) 65 of 7300 were, up to 1.38 times; against it 0.93 of the time, 188 of 16000 more than 3 %
+// slower.  us, unfold or gathering GEMM / this: FP32 64 channels of 140 x 140, 3 x 3, 22 filters 40.7 / 25.2, 480 of 64 x 64, 5 x 5, stride 2, 249 filters 80 / 96, 219 of
+// 185 x 6, 7 x 3, 14 filters 689 / 29 (a thin product); FP16 7 of 116 x 116, 3 x 3, 32 filters 6.1 / 8.5, 447 of 98 x 98, 3 x 3, 32 filters 62 / 114.
+ConvRoute conv_route(int dtype, const ConvShape &s, int64_t filters)
 {
-    if (!conv_gather_fits(dtype, s, filters)) return false;
+    const bool f32 = dtype == MG_F32;
     const int64_t out_h = conv_out_extent(s.height, s.kernel_h, s.pad_h, s.stride_h, s.dilation_h);
     const int64_t out_w = conv_out_extent(s.width, s.kernel_w, s.pad_w, s.stride_w, s.dilation_w);
+    const int64_t taps = s.kernel_h * s.kernel_w, terms = s.channels * taps, positions = out_h * out_w, es = f32 ? 4 : 2;
+    const int64_t groups = ceil_div(positions, 32) * ceil_div(filters, 32), thinner = positions < filters ? positions : filters;
+    const double k = static_cast<double>(terms), x = static_cast<double>(groups) / 256.0;
+    const double tiles = static_cast<double>(ceil_div(positions, 64)) * static_cast<double>(ceil_div(filters, 64)) / 256.0;       // of 64 x 64, for a compute unit
+    const double busy = tiles < 1.0 ? tiles : 1.0, over = tiles > 1.0 ? tiles - 1.0 : 0.0, ktiles = static_cast<double>(ceil_div(terms, f32 ? 32 : 64));
+    const double column_mb = 1.0e-6 * k * static_cast<double>(positions) * static_cast<double>(es);
+    const double image_mb = 1.0e-6 * static_cast<double>(s.channels) * static_cast<double>(s.height * s.width) * static_cast<double>(es);
+    const double gflop = 2.0e-9 * k * static_cast<double>(positions) * static_cast<double>(filters);
+    // (FP16: rows of the product's operands, filters and column matrix, off 16 bytes)
+    const double off_f = !f32 && terms % 8 != 0 ? 1.0 : 0.0, off_c = !f32 && positions % 8 != 0 ? 1.0 : 0.0, off = off_f + off_c > 0.0 ? 1.0 : 0.0;
+
+    // the unfold pass and a matrix-vector product, the kernel whose wavefronts share a sum, the one for thin products, or tiles
+    double unfold;
+    const int64_t most_shared = f32 ? (groups > 64 ? 1536 : 1280) + (thinner < 16 ? (groups > 64 ? 512 : 256) : 0) : 2560;
+    const double pass = f32 ? (positions % 8 != 0 ? 0.473 : 0.428) * column_mb + 0.030 * image_mb : (0.511 + 0.098 * off_c) * column_mb + 0.061 * image_mb;
+    if (thinner == 1) {
+        unfold = pass + (f32 ? 5.13 + 0.099 * column_mb + 0.00158 * k : 6.19 + 0.218 * column_mb + 0.00189 * k);
+    } else if (groups <= 256 && terms >= 48 && terms <= most_shared) {
+        unfold = f32 ? pass + 5.57 + 0.00701 * k + 0.937 * x
+                     : 6.01 + 0.778 * column_mb + 0.022 * image_mb + (0.00267 + 0.00045 * off_c) * k + 0.878 * off_f + 0.506 * off_c;
+    } else if (thinner < 16) {
+        unfold = pass + (f32 ? 5.51 + 0.132 * k + 0.32 * column_mb : 5.93 + 0.143 * k + 0.70 * column_mb);
+    } else {
+        const double wide = ktiles * (tiles > 0.05 ? tiles : 0.05);
+        const double sliced = f32 ? 4.31 + 2.44 * sqrt(wide) : 4.69 + 1.59 * sqrt(wide), whole = (f32 ? 0.580 : 0.421) * ktiles, sum = sliced < whole ? sliced : whole;
+        unfold = f32 ? pass + 6.88 + sum + 1.17 * over + 4.05 * gflop + 0.227 * x
+                     : 6.10 + 0.534 * column_mb + 0.063 * image_mb + sum * (1.0 + 0.111 * (off_f + off_c)) + 0.392 * over + (0.042 + 1.07 * off) * gflop + 0.120 * x +
+                           0.597 * off_f + 0.877 * off_c;
+    }
+    ConvRoute route = ConvRoute::unfold;
+    double best = unfold;
+    if (terms <= 256 && filters <= 64) {
+        const double late = tiles > 0.753 ? tiles - 0.753 : 0.0;
+        const double fused = f32 ? 4.61 + 1.277 * ktiles + 1.248 * late * (1.0 + 0.657 * ktiles) + 0.203 * ktiles * busy
+                                 : 4.38 + 1.608 * ktiles + 1.119 * late * (1.0 + 0.439 * ktiles) + 0.098 * ktiles * busy + 0.060 * column_mb;
+        if (1.03 * fused < best) {
+            route = ConvRoute::fused;
+            best = fused;
+        }
+    }
+    if (groups > 8 * 256 || !conv_gather_fits(dtype, s, filters)) return route;
     const Band b = band_of(dtype, s, out_h, out_w);
-    const int64_t taps = s.kernel_h * s.kernel_w, chunks = ceil_div(s.channels, b.chunk), step = dtype == MG_F32 ? 8 : 16;
-    const int64_t rounds = ceil_div(b.chunk * b.rows * (s.width / b.v), 8 * kThreads) * chunks;
-    const int64_t steps = ceil_div(ceil_div(b.chunk * taps, step), 8) * chunks;
-    const int64_t turns = ceil_div(ceil_div(out_h * out_w, 32) * ceil_div(filters, 32), 256);
-    const bool f32 = dtype == MG_F32;
-    const double k = static_cast<double>(s.channels * taps), positions = static_cast<double>(out_h * out_w);
-    const double column_mb = k * positions * (f32 ? 4.0e-6 : 2.0e-6), gflop = 2.0e-9 * k * positions * static_cast<double>(filters);
-    const double tiles = static_cast<double>(ceil_div(out_h * out_w, 64) * ceil_div(filters, 64)) / 256.0;      // of 64 x 64, for a compute unit
-    if (turns > 6) return false;
-    const double odd = !f32 && s.channels * taps % 2 != 0 ? 0.471 : (!f32 && s.channels * taps % 8 != 0 ? 0.073 : 0.0);
-    const double turn = f32 ? 0.832 * static_cast<double>(rounds) + 0.379 * static_cast<double>(steps) + 0.459 * static_cast<double>(chunks - 1)
-                            : 0.911 * static_cast<double>(rounds) + (0.29 + odd) * static_cast<double>(steps) + 0.283 * static_cast<double>(chunks - 1);
-    const double here = (f32 ? 3.2 : 3.03) + static_cast<double>(turns) * turn + (f32 ? 0.742 : 0.473) * static_cast<double>(turns - 1);
-    const double over = tiles > 1.0 ? tiles - 1.0 : 0.0;
-    double there;
-    if (filters <= 64 && k <= 256.0)      // (the layers of the fused route)
-        there = f32 ? 7.52 + 0.570 * column_mb + 0.00006 * k + 2.57 * over : 7.63 + 0.420 * column_mb + 4.89 * gflop + 1.11 * over;
-    else
-        there = f32 ? 7.51 + 0.527 * column_mb + 0.00378 * k + 7.44 * gflop + 1.50 * over : 7.57 + 0.502 * column_mb + 0.00214 * k + 3.04 * gflop + 0.73 * over;
-    return (f32 && (chunks > 1 || turns > 3) ? 1.4 : (turns > 1 || rounds > 4 ? 1.2 : 1.1)) * here < there;
+    // rows of the band of most work-groups (b.rows is the most that any can have)
+    int64_t lines = out_w % 32 == 0 ? 0 : (32 % out_w == 0 ? 32 / out_w - 1 : (30 + out_w) / out_w);
+    if (lines > out_h - 1) lines = out_h - 1;
+    int64_t rows = lines * s.stride_h + (s.kernel_h - 1) * s.dilation_h + 1;
+    if (rows > s.height) rows = s.height;
+    const int64_t step = f32 ? 8 : 16;
+    const int64_t chunks = ceil_div(s.channels, b.chunk), last = s.channels - (chunks - 1) * b.chunk, per_channel = rows * (s.width / b.v);
+    const double rounds = static_cast<double>(ceil_div(b.chunk * per_channel, 8 * kThreads) * (chunks - 1) + ceil_div(last * per_channel, 8 * kThreads));
+    const double loads = static_cast<double>(ceil_div(b.chunk * per_channel, kThreads) * (chunks - 1) + ceil_div(last * per_channel, kThreads));
+    const double steps = static_cast<double>(ceil_div(b.chunk * taps / step, 8) * (chunks - 1) + ceil_div(last * taps / step, 8));
+    const double partial = static_cast<double>((b.chunk * taps % step != 0 ? chunks - 1 : 0) + (last * taps % step != 0 ? 1 : 0));
+    // loads of filters by a wavefront, whole batches of six K-steps on as many wavefronts as have any: from rows at odd elements each takes its time
+    auto batches = [&](int64_t channels) {
+        const int64_t all = channels * taps / step;
+        return static_cast<double>((all < 8 ? all : 8) * ceil_div(ceil_div(all, 8), 6)) * (6.0 / 8.0);
+    };
+    const double fill = static_cast<double>(filters < 32 ? filters : 32) / 32.0;        // distinct rows of filters
+    const double odd = !f32 && terms % 2 != 0 ? fill * (batches(b.chunk) * static_cast<double>(chunks - 1) + batches(last)) : 0.0;
+    const double latency = (f32 ? 0.748 : 0.783) + (f32 ? 0.778 : 0.726) * rounds + (f32 ? 0.0332 : 0.0466) * loads + (f32 ? 2.20 : 0.917) * k / kThreads + 0.353 * odd +
+                           (f32 ? 0.42 : 0.37) * static_cast<double>(chunks - 1) + (f32 ? 0.045 : 0.0) * steps + (f32 ? 0.458 : 0.350) * static_cast<double>(b.lds_bytes) / 65536.0;
+    const double another = (f32 ? 0.891 : 0.966) + (f32 ? 0.0085 : 0.0368) * loads + (f32 ? 0.277 : 0.057) * (steps + partial) + 0.243 * odd;
+    const int64_t resident = b.lds_bytes <= 80 * 1024 ? 2 : 1, full = groups / (resident * 256), rest = groups % (resident * 256);
+    const double reads_kb = (static_cast<double>(s.channels * rows * s.width) + static_cast<double>(filters < 32 ? filters : 32) * k) * static_cast<double>(es) / 1024.0;
+    const double here = (f32 ? 2.58 : 2.71) + static_cast<double>(full) * (latency + static_cast<double>(resident - 1) * another) +
+                        (rest > 0 ? latency + (rest > 256 ? another : 0.0) : 0.0) + (f32 ? 0.0066 : 0.0103) * x * reads_kb;
+    return (groups > 256 || chunks > 1 ? 1.12 : 1.03) * here < best ? ConvRoute::gather : route;
 }
 
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,

@@ -103,7 +103,9 @@ hipError_t launch_im2col(int dtype, const ConvShape &s, const void *im, void *co
 
 // The whole convolution in one launch (conv_gather.hip): positions x filters outputs, out (filters x positions, row-major) = alpha * ... + beta * out
 bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters);
-bool conv_gather_pays(int dtype, const ConvShape &s, int64_t filters);
+// and which of the routes of a convolution is estimated fastest: the unfold pass and a GEMM, a GEMM kernel that gathers, that one launch
+enum class ConvRoute { unfold, fused, gather };
+ConvRoute conv_route(int dtype, const ConvShape &s, int64_t filters);
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,
                               void *out, hipStream_t stream);
 

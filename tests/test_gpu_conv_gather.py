@@ -194,6 +194,18 @@ def test_error_of_a_long_sum(channels, size, kernel, filters):
     assert error(got.cpu().numpy()) <= 1.05 * error(total)
 
 
+@pytest.mark.parametrize("dtype,channels,size,kernel,stride,filters,kernels_in_order", [
+    ("f32", 64, 140, 3, 1, 22, ["conv_gather"]),                                                             # 40.7 / 25.2
+    ("f16", 16, 111, 3, 1, 13, ["conv_gather"]),                                                             # a thin product 31.4 / 8.0
+    ("f16", 7, 116, 3, 1, 32, ["mfma"]), ("f16", 64, 65, 1, 2, 35, ["mfma"]),      # 8.5 / 6.1, 8.0 / 5.9
+    ("f32", 64, 45, 1, 2, 28, ["im2col", "tiny"]), ("f16", 3, 44, 7, 1, 194, ["im2col", "kernel"])])           # 8.4 / 6.4, 11.0 / 8.8
+def test_routes(dtype, channels, size, kernel, stride, filters, kernels_in_order):
+    """us on another route / on this"""
+    pair = lambda v: (v, v)                     # noqa: E731
+    ran = kernels(dtype, channels, size, size, pair(kernel), pair(kernel // 2), pair(stride), (1, 1), filters)
+    assert len(ran) == len(kernels_in_order) and all(part in name for part, name in zip(kernels_in_order, ran)), ran
+
+
 def test_first_layer_keeps_the_fused_route():
     """9.2 / 18.3 us"""
     ran = kernels("f16", 3, 224, 224, (7, 7), (3, 3), (2, 2), (1, 1), 64)
