@@ -11,6 +11,8 @@ namespace mg {
 // launch costs; 0 where another kind of kernel is chosen.
 void select_config(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
                    int32_t *kernel, int32_t *split, double *estimated_us = nullptr);
+// Whether an FP32 product takes no fringe off for the kernel whose wavefronts share the sum of a 32 x 32 block.
+bool shared_without_fringe(const Problem &p);
 // Returns the kernel id for a batched problem, or -1.
 int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProblem &p);
 

@@ -200,7 +200,22 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
     else panel(outputs > 32768 && (f32 || stride % 16 == 0) ? 16 : 8, 1);
 }
 
+// Longest sum that FP32 products of `blocks32` 32 x 32 blocks share among a block's wavefronts.  (Both operands along k, up to 64 blocks: 0.94 up to 1280 terms, 1.05 to 1.15
+// up to 1792, 15 of 16 slower.  Behind the unfold pass, 51 layers of 1281 to 2048 terms: up to 64 blocks 1.08 up to 1536 terms, more 0.98 up to 1536, 0.98
+// with two of nine up to 1.11 beyond; where there is room for slices)
+int64_t most_shared_f32(const Problem &p, int64_t blocks32, bool unfolded)
+{
+    if (blocks32 > 64) return unfolded ? 1536 : 2048;
+    return unfolded || (p.a_trans && !p.b_trans) ? 1280 : 1536;
+}
+
 }  // namespace
+
+bool shared_without_fringe(const Problem &p)
+{
+    const int64_t blocks32 = ceil_div(p.m, 32) * ceil_div(p.n, 32);
+    return blocks32 <= kComputeUnits && p.k <= (blocks32 > 64 ? 1536 : 1280);
+}
 
 void select_config(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
                    int32_t *kernel, int32_t *split, double *estimated_us)
@@ -249,11 +264,12 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         snprintf(name, sizeof name, "hmfma_64x64x64_w2x2_%s", order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
     }
-    // (FP32 behind the unfold pass, 51 layers of 1281 to 2048 terms: up to 64 blocks 1.08 up to 1536 terms, more 0.98 up to 1536, 0.98 with two of nine
-    // up to 1.11 beyond; where there is room for slices)
-    const bool unfolded = p.unfolded && workspace_bytes / 8 >= static_cast<size_t>(p.m) * static_cast<size_t>(p.n);
-    const int64_t most_f32 = unfolded ? (blocks32 > 64 ? 1536 : 1280) : (blocks32 > 64 ? 2048 : 1536);
-    if (few_blocks && !whole_short && p.k >= 48 && p.k <= (f32 ? most_f32 : 2560)) {
+    const int64_t most_f32 = most_shared_f32(p, blocks32, p.unfolded && workspace_bytes / 8 >= static_cast<size_t>(p.m) * static_cast<size_t>(p.n));
+    // (FP16 on 1500 aligned products: neither operand along k, which the tiles read by transposing loads as well, its time over that of the tiles 1.06 to 1.12 up to 640 terms, 250 of
+    // 275 slower, 0.96 from there to 1024; other orders 1.0 down to 0.85 from 65 to 640)
+    const bool aligned16 = !f32 && dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
+    const int64_t least = aligned16 && !p.a_trans && p.b_trans ? 641 : 48, most = f32 ? most_f32 : 2560;
+    if (few_blocks && !whole_short && p.k >= least && p.k <= most) {
         char name[48];
         snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
