@@ -323,7 +323,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         };
         // general products | of whole tiles | triangles of C (400 sizes of 64 to 6200; 5 of 204 held out more than 3 % slower, without 16, up to 29 %;
         // (4416, 120) with beta 24.5 us on 64 x 64 direct-to-LDS tiles, 18.6)
-        static const ShortCost short_costs[3][14] = {{{}, {}, {}, {}, {}, {},
+        // | general products with beta whose rows of C end inside a 16-byte piece, which the large tiles fetch element by element: (4391, 1435, 128) 192 x 192 23.3 us, checked 64 x 64 12.7.
+        // Fitted to half of 1560 such products, on the other half 1.007 times the best tile (by the first row 1.051), 60 instead of 224 of 782 more than 3 % slower, at most
+        // 1.32 instead of 1.81 times
+        static const ShortCost short_costs[4][14] = {{{}, {}, {}, {}, {}, {},
                                                       {3.61, 0.45, 0.48, 0.26, 0.88},
                                                       {3.50, 0.20, 0.21, 0.15, 0.56},
                                                       {},
@@ -350,9 +353,18 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                       {},
                                                       {3.10, 2.62, 0.16, 0.36, 1.41, 3.99, 0.46},
                                                       {2.75, 1.27, 0.05, 0.27, 2.07, 1.99, 0.82},
-                                                      {3.24, 0.90, 0.13, 0.18, 0.32, 2.02, 0.00}}};
+                                                      {3.24, 0.90, 0.13, 0.18, 0.32, 2.02, 0.00}},
+                                                     {{}, {}, {}, {}, {}, {},
+                                                      {6.57, 0.82, 0.0, 0.24, 0.82},
+                                                      {5.09, 0.0, 0.0, 0.14, 0.89},
+                                                      {},
+                                                      {5.77, 6.34, 0.0, 0.62, 3.16},
+                                                      {4.76, 5.00, 0.0, 0.48, 2.39},
+                                                      {3.75, 3.60, 0.0, 0.34, 1.55},
+                                                      {2.58, 2.42, 0.0, 0.26, 0.88},
+                                                      {4.04, 0.26, 0.0, 0.16, 1.18}}};
         const bool short_sum = whole_short || p.k <= 256;
-        const ShortCost *short_cost = short_costs[whole_short ? 1 : (triangular_c ? 2 : 0)];
+        const ShortCost *short_cost = short_costs[whole_short ? 1 : (triangular_c ? 2 : (p.beta != 0.f && p.m % 8 != 0 ? 3 : 0))];
         // The checked register-staged 256 x 256 tile beside them, in the same form (147 sizes of 640 to 7000 terms, 5 % rms), where 192 x 192 tiles
         // leave a nearly empty turn: (5416, 5112, 2456) 192 x 192 159 us, this 142, (3280, 3600, 2600) 86.2, 67.6; SYRK (4600, 2896) 128 x 128 88.2, this
         // 72.8.  Of 250 products of 900 to 8000 it takes 12, 0.93 of the time, one 2 % slower.

@@ -324,3 +324,10 @@ def test_fp16_shared_sums_of_operands_along_their_rows(m, n, k, ta, tb, shared):
     """neither operand along k, rows on 16 bytes: up to 640 terms the tiles, 1.06 to 1.12 times as fast"""
     chosen = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m)["name"]
     assert chosen.startswith("htiny") == shared, chosen
+
+
+@pytest.mark.parametrize("m,n,k,tb,ldc", [(4391, 1435, 128, N, 4391), (5301, 5840, 40, N, 5301), (3767, 4576, 24, T, 3767), (5799, 1208, 16, N, 5800), (893, 5184, 64, N, 893)])
+def test_short_fp16_sums_with_beta_whose_rows_of_c_end_inside_a_piece(m, n, k, tb, ldc):
+    """us, 192 x 192 direct-to-LDS tiles / checked 64 x 64: 23.3 / 12.7, 66.6 / 36.8, 42.1 / 26.2, 20.3 / 13.0"""
+    args = (G.MG_F16, C, T, tb, m, n, k, k, k if tb == N else n, ldc)
+    assert G.mg_query_selected(*args, 1.0, 0.5)["name"].startswith("hmfma_64x64")
