@@ -288,9 +288,9 @@ bool conv_gather_fits(int dtype, const ConvShape &s, int64_t filters)
 // to 7 x 7, strides, paddings and dilations up to 3 and 4, 1 to 512 filters; rms errors: here 6 and 4.5 %, gathering GEMM 7 and 6, unfold 7 and 6.5.  A gain of 3 % is asked for, of
 // 12 % with several turns or chunks, whose estimates are further off; past eight turns it did not pay.  Here: rounds of loads that bring the band and the LDS reads of the
 // sum make a work-group's latency, of which a second work-group on a compute unit hides all but its loads and K-steps; what the grid reads counts beside that.
-// On 16000 other layers calls take 0.70 of the time without this kernel, 41 are more than 3 % slower (at most 1.27 times).  By the rule before (one sum of six terms for
-// the other routes, a gain of 1.4 for FP32 layers of several chunks or turns) 65 of 7300 were, up to 1.38 times; against it 0.93 of the time, 188 of 16000 more than 3 %
-// slower.  us, unfold or gathering GEMM / this: FP32 64 channels of 140 x 140, 3 x 3, 22 filters 40.7 / 25.2, 480 of 64 x 64, 5 x 5, stride 2, 249 filters 80 / 96, 219 of
+// On 16000 other layers calls take 0.67 of the time without this kernel, 41 are more than 3 % slower (at most 1.27 times).  By the rule before (one sum of six terms for
+// the other routes, a gain of 1.4 for FP32 layers of several chunks or turns) 65 of 7300 were, up to 1.38 times; against that rule without the 1.4, 0.93 of the time and
+// 188 of 16000 more than 3 % slower.  us, unfold or gathering GEMM / this: FP32 64 channels of 140 x 140, 3 x 3, 22 filters 40.7 / 25.2, 480 of 64 x 64, 5 x 5, stride 2, 249 filters 80 / 96, 219 of
 // 185 x 6, 7 x 3, 14 filters 689 / 29 (a thin product); FP16 7 of 116 x 116, 3 x 3, 32 filters 6.1 / 8.5, 447 of 98 x 98, 3 x 3, 32 filters 62 / 114.
 ConvRoute conv_route(int dtype, const ConvShape &s, int64_t filters)
 {
