@@ -119,8 +119,8 @@ void plan_fringe(Problem &p, bool forced)
     if (mode == MG_FRINGE_OFF || (forced && mode != MG_FRINGE_ON)) return;
     if (p.dtype != MG_F32 || p.shape != MG_SHAPE_GENERAL || p.mask_c || p.conv != nullptr || p.alpha == 0.f || p.k == 0) return;
     if (p.m < 64 || p.n < 64) return;
-    // Few blocks and a sum of up to 1536 (up to 64 blocks 1280) terms: the kernel whose wavefronts share a sum takes any size as a whole.  1500 products with 1 to 4 rows or
-    // columns beside the tiles 0.71 of the time; beyond 1600 terms up to 1.19, (450, 129, 1928) 15.3 us, 12.9 with the fringe taken off.
+    // Few blocks and a sum of up to 1024 terms: the kernel whose wavefronts share a sum takes any size as a whole.  1010 products with 1 to 4 rows or columns beside the
+    // tiles 0.63 of the time, none slower; 1025 to 1536 terms 0.85, some 1.05; beyond 1600 up to 1.19, (450, 129, 1928) 15.3 us, 12.9 with the fringe taken off.
     if (mode == MG_FRINGE_AUTO && (p.k < 256 || shared_without_fringe(p))) return;
     auto extra = [&](int64_t d) {
         const int64_t r = d % 64;

@@ -214,7 +214,7 @@ int64_t most_shared_f32(const Problem &p, int64_t blocks32, bool unfolded)
 bool shared_without_fringe(const Problem &p)
 {
     const int64_t blocks32 = ceil_div(p.m, 32) * ceil_div(p.n, 32);
-    return blocks32 <= kComputeUnits && p.k <= (blocks32 > 64 ? 1536 : 1280);
+    return blocks32 <= kComputeUnits && p.k <= 1024;
 }
 
 void select_config(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,

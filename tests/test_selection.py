@@ -312,8 +312,8 @@ def test_fp32_products_behind_the_unfold_pass_are_sliced(channels, size, filters
 
 
 @pytest.mark.parametrize("m,n,k,ta,tb,name,fringe", [
-    (676, 323, 369, N, N, "stiny", 0), (129, 513, 1500, T, N, "stiny", 0), (65, 65, 300, N, T, "stiny", 0),      # 8.7 us, 13.9 with the fringe taken off
-    (450, 129, 1928, T, N, "s", 33), (1025, 1025, 600, N, N, "s", 17)])                                          # 15.3 us, 12.9 with it; more blocks than compute units
+    (676, 323, 369, N, N, "stiny", 0), (129, 513, 1000, T, N, "stiny", 0), (65, 65, 300, N, T, "stiny", 0),      # 8.7 us, 13.9 with the fringe taken off
+    (1025, 129, 1030, N, T, "s", 17), (450, 129, 1928, T, N, "s", 33), (1025, 1025, 600, N, N, "s", 17)])                                          # 15.3 us, 12.9 with it; more blocks than compute units
 def test_fringe_of_fp32_products_whose_sum_is_shared(m, n, k, ta, tb, name, fringe):
     chosen = G.mg_query_selected(G.MG_F32, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m)
     assert chosen["name"].startswith(name) and (chosen["fringe"] == 0) == (fringe == 0), chosen
