@@ -364,7 +364,10 @@ ConvRoute conv_route(int dtype, const ConvShape &s, int64_t filters)
     const double reads_kb = (static_cast<double>(s.channels * rows * s.width) + static_cast<double>(filters < 32 ? filters : 32) * k) * static_cast<double>(es) / 1024.0;
     const double here = (f32 ? 2.58 : 2.71) + static_cast<double>(full) * (latency + static_cast<double>(resident - 1) * another) +
                         (rest > 0 ? latency + (rest > 256 ? another : 0.0) : 0.0) + (f32 ? 0.0066 : 0.0103) * x * reads_kb;
-    return (groups > 256 || chunks > 1 ? 1.12 : 1.03) * here < best ? ConvRoute::gather : route;
+    // (FP32: the gathering GEMM kernel adds its terms in one chain, with 1.45 times the error of eight at 27 terms: only for a clear gain)
+    const bool several = groups > 256 || chunks > 1;
+    const double asked = f32 && route == ConvRoute::fused ? (several ? 1.08 : 0.9) : (several ? 1.12 : 1.03);
+    return asked * here < best ? ConvRoute::gather : route;
 }
 
 hipError_t launch_conv_gather(int dtype, const ConvShape &s, int64_t filters, float alpha, const void *im, const void *weights, float beta,

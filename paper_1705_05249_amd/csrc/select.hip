@@ -202,7 +202,7 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
 
 // Longest sum that FP32 products of `blocks32` 32 x 32 blocks share among a block's wavefronts.  (Both operands along k, up to 64 blocks: 0.94 up to 1280 terms, 1.05 to 1.15
 // up to 1792, 15 of 16 slower.  Behind the unfold pass, 51 layers of 1281 to 2048 terms: up to 64 blocks 1.08 up to 1536 terms, more 0.98 up to 1536, 0.98
-// with two of nine up to 1.11 beyond; where there is room for slices)
+// with two of nine up to 1.11 beyond; where there is room for slices, which products thinner than 16 do not take)
 int64_t most_shared_f32(const Problem &p, int64_t blocks32, bool unfolded)
 {
     if (blocks32 > 64) return unfolded ? 1536 : 2048;
@@ -264,7 +264,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         snprintf(name, sizeof name, "hmfma_64x64x64_w2x2_%s", order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
     }
-    const int64_t most_f32 = most_shared_f32(p, blocks32, p.unfolded && workspace_bytes / 8 >= static_cast<size_t>(p.m) * static_cast<size_t>(p.n));
+    const int64_t most_f32 = most_shared_f32(p, blocks32, p.unfolded && p.m >= 16 && p.n >= 16 && workspace_bytes / 8 >= static_cast<size_t>(p.m) * static_cast<size_t>(p.n));
     // (FP16 on 1500 aligned products: neither operand along k, which the tiles read by transposing loads as well, its time over that of the tiles 1.06 to 1.12 up to 640 terms, 250 of
     // 275 slower, 0.96 from there to 1024; other orders 1.0 down to 0.85 from 65 to 640)
     const bool aligned16 = !f32 && dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);

@@ -206,6 +206,17 @@ def test_routes(dtype, channels, size, kernel, stride, filters, kernels_in_order
     assert len(ran) == len(kernels_in_order) and all(part in name for part, name in zip(kernels_in_order, ran)), ran
 
 
+def test_thin_products_behind_the_unfold_pass_with_any_workspace():
+    """FP32, 1600 terms, 5 filters: with room for slices, which so thin a product does not take, the sum is shared all the same (an error of 1.5e-7, one chain 7.1e-7)"""
+    import torch
+    geo, filters = (64, 97, 97, (5, 5), (2, 2), (2, 2), (1, 1)), 5
+    im, w = torch.rand(64, 97, 97, device="cuda") * 2 - 1, torch.rand(filters, 1600, device="cuda") * 2 - 1
+    exact = torch.from_numpy(w.cpu().double().numpy()) @ torch.nn.functional.unfold(im.cpu().double()[None], 5, padding=2, stride=2)[0]
+    got = torch.zeros(filters, 49 * 49, device="cuda")
+    G.mg_sconv2d(*geo, filters, 1.0, im, w, 0.0, got, torch.empty(1 << 26, dtype=torch.uint8, device="cuda"))
+    assert (got.cpu().double() - exact).norm() <= 3.0e-7 * exact.norm()
+
+
 def test_first_layer_keeps_the_fused_route():
     """9.2 / 18.3 us"""
     ran = kernels("f16", 3, 224, 224, (7, 7), (3, 3), (2, 2), (1, 1), 64)
