@@ -171,9 +171,9 @@ size_t preferred_bytes(Problem p, int64_t alignment = 256)
     return most;
 }
 
-// The same wherever the operands lie: FP16 operands off 16 bytes take other kernels than aligned ones, which slice more ((424, 808, 2280): none / 8
-// slices).  Room for these where what fits into the aligned call's leaves a call off 16 bytes estimated slower by more than worth_us.
-size_t preferred_bytes_anywhere(Problem p, double worth_us)
+// The same wherever the operands lie: FP16 operands off 16 bytes take other kernels than aligned ones, with slices where those need none.  (With the
+// aligned call's room alone 162 of 440 calls got less than they prefer, up to 1.7 times as slow: (1032, 976, 5896) 48.9 -> 82.8 us.)
+size_t preferred_bytes_anywhere(Problem p)
 {
     size_t most = preferred_bytes(p);
     if (!dma_ragged_operands(p, 256)) return most;
@@ -183,7 +183,7 @@ size_t preferred_bytes_anywhere(Problem p, double worth_us)
         p.beta = beta;
         if (choose(p, 8, most, &kernel, &split, &us) != MG_OK || choose(p, 8, ~size_t(0), &kernel, &split, &free_us) != MG_OK) continue;
         const size_t need = table()[kernel].workspace(p, split);
-        if (need > most && us > free_us + worth_us) most = need;
+        if (need > most && us > free_us) most = need;
     }
     return most;
 }
@@ -198,8 +198,7 @@ size_t preferred_bytes_anywhere(Problem p, double worth_us)
 struct IndirectPlan {
     int64_t mp, np, kp;
     size_t a_bytes, b_bytes, c_bytes;
-    bool compare;            // take it only if its estimate is below the direct route's times `odds`
-    double odds;
+    bool compare;            // take it only if its estimate is below the direct route's
     size_t total() const { return a_bytes + b_bytes + c_bytes; }
 };
 
@@ -223,7 +222,6 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     const double work = static_cast<double>(p.m) * static_cast<double>(p.n) * static_cast<double>(p.k);
     int64_t tile = 0, ktile = 0;
     bool compare = false;
-    double odds = 1.0;
     if (p.dtype == MG_F16) {
         // a launch in front, its gap and ~10 us of copies at 2051^2 (~33 us at 4096^2): measured a loss at 1000^3 (28 against
         // 22 us), a gain at 2049^3 (56 against 96 us; both while C was copied too)
@@ -239,15 +237,8 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
         // 28, 1800^3 30 / 27 | 29 / 28, 2050^3 45 / 41 | 47 / 40, 2500^3 60 / 49 | 59 / 50, 2700^3 59 / 58 | 60 / 60, (8200,
         // 1030, 2050) - | 62 / 76, (4100, 4100, 512) 53 / 54 | -.
         const double moved = static_cast<double>(p.m) * p.k + static_cast<double>(p.k) * p.n + static_cast<double>(p.m) * p.n;
-        // Rows that start at odd elements cost the direct route a little more: 1801^3 29.9 / 26.7, (2671, 1061, 1265) 35.3 / 29.0
-        // at estimates 1.17 apart, (8201, 1031, 2051) 64 / 75 at 1.29, (1031, 1031, 8001) 56 / 63 at 1.65.  Short sums run further
-        // above their estimate (the tiles' checked ends weigh more): of 55 products of 447 to 1515 terms in four orders the direct route won
-        // all 10 that were 1.4 apart and more (1301^3 18.7 / 22.5, (1345, 1409, 1081) 14.2 / 19.7, (1973, 1395, 925) 21.9 / 22.6) and
-        // lost 30 of the 45 others ((4445, 1835, 1487) 63.3 / 52.8 at 1.26, (3901, 1165, 995) 34.0 / 30.2 at 1.36).
-        const bool dword_rows = p.lda % 2 == 0 && p.ldb % 2 == 0 && (!pointers_known || (pointer_alignment(p.A) >= 4 && pointer_alignment(p.B) >= 4));
         if (work < 350.0 * moved) return false;
         compare = work < 900.0 * moved;
-        odds = dword_rows ? 1.15 : (p.k >= 1536 ? 1.2 : 1.4);
         tile = p.m >= 2048 && p.n >= 2048 ? 256 : 128;
         ktile = 64;
     } else {
@@ -260,7 +251,6 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
     }
     *plan = padded_to(p, tile, tile, ktile);
     plan->compare = compare;
-    plan->odds = odds;
     return true;
 }
 
@@ -336,7 +326,7 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken, 
             double us = 0.0;
             const bool known = choose(direct->p, problem_alignment(p), p.workspace_bytes, &direct->kernel, &direct->split, &us) == MG_OK;
             if (!known) direct->kernel = -1;
-            if (best_kernel < 0 || (known && us > 0.0 && plan.odds * us <= best_us + copies_us)) {
+            if (best_kernel < 0 || (known && us > 0.0 && us <= best_us + copies_us)) {
                 *taken = false;
                 return MG_OK;
             }
@@ -1043,7 +1033,7 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
         for (const int shape : {lower, upper}) {
             Problem p = canonical(dtype, layout, ta, tb, m, n, kk, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr, shape);
             p.mask_c = routine == MG_ROUTINE_SYRK;
-            const size_t need = preferred_bytes_anywhere(p, 0.0);
+            const size_t need = preferred_bytes_anywhere(p);
             if (need > most) most = need;
         }
         return most;
@@ -1101,11 +1091,8 @@ static size_t gemm_workspace_bytes(int dtype, int layout, int ta, int tb, int64_
     p.unfolded = unfolded;
     IndirectPlan plan;
     // (room for slices beside the copies is the caller's choice; where aligned pointers would spare the copies, for what the call then prefers)
-    // Off 16 bytes, of 440 calls 20 get less than they prefer, one of them for more than 1 % ((640, 640, 4096) 20.3 -> 22.3 us); with the aligned
-    // call's room alone 162 did, up to 1.7 times as slow ((1032, 976, 5896) 48.9 -> 82.8 us).
-    const double worth_us = 1.0;
-    if (!indirect_plan(p, false, &plan)) return preferred_bytes_anywhere(p, worth_us);
-    const size_t direct = dma_ragged_operands(p, 16) ? preferred_bytes_anywhere(p, worth_us) : 0;
+    if (!indirect_plan(p, false, &plan)) return preferred_bytes_anywhere(p);
+    const size_t direct = dma_ragged_operands(p, 16) ? preferred_bytes_anywhere(p) : 0;
     return direct > plan.total() ? direct : plan.total();
 }
 

@@ -26,6 +26,7 @@ void register_smfma_64x64x32_w2x2(std::vector<KernelEntry> &table);
 void register_ssplit_256x128x32_w4x2(std::vector<KernelEntry> &table);
 void register_ssplit_128x128x32_w2x4(std::vector<KernelEntry> &table);
 void register_hdma16r(std::vector<KernelEntry> &table);
+void register_hany16(std::vector<KernelEntry> &table);
 
 void register_mfma(std::vector<KernelEntry> &table)
 {
@@ -53,5 +54,6 @@ void register_mfma(std::vector<KernelEntry> &table)
     register_ssplit_256x128x32_w4x2(table);
     register_ssplit_128x128x32_w2x4(table);
     register_hdma16r(table);
+    register_hany16(table);
 }
 }  // namespace mg

@@ -372,6 +372,46 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         static const RaggedCost staged_largest = {6.9, 0.98, 0.44, 0.0, 0.94, 1.10, 1.03, 0.08, 1.0, 1.0};
         const bool ragged_family = !f32 && !(whole64 && p.shape != MG_SHAPE_GENERAL && !triangular_c && p.k <= 192) && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 &&
                                    dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
+        // FP16 operands that the direct-to-LDS kernels do not take (rows off 16 bytes, sizes that end inside a piece): the tiles whose pieces come from any
+        // element (mfma_any_kernel.h), with 1, 2, 4 or 8 slices; for sums of up to 320 terms beside the checked register-staged ones, unsliced, which start
+        // sooner and whose wavefronts write their parts of C one by one ((512, 1664, 128) 4.1 us on 64 x 64 of these, 5.2 of those, (1402, 6146, 64)
+        // 11.9 us, 18.5 on 192 x 128; (143, 5204, 475) with beta 8.7, 7.5); up to 1024 beside the register-staged 256 x 256 tile ((4997, 5466, 896) 68 us, 79 on 256 x 128).
+        // Their time in us: a fixed part; turns of one tile per compute unit and, per K-tile, what a turn, a busier chip, rows at odd elements (`odd`: the share
+        // of a tile's rows) and operands along their rows take longer; the traffic of C (MB), of which rows off 16 bytes; and `more`: short sums a sum
+        // that ends inside a K-tile and old columns of C that end inside a piece, per turn; long ones the second launch and the partial sums of slices.
+        // Fitted to all tiles on 1700 sizes of 32 to 7000 and sums of 32 to 8192, a third each with odd and with padded leading dimensions (5 to 11 %,
+        // register-staged 10 to 15 % rms).  Fitted to half and chosen for the other half: 1.018 times the fastest, 51 of 946 more than 5 % behind, up to 1.28.
+        struct AnyCost {
+            double fixed, turn, busy, turn_ktile, busy_ktile, odd, lines, c, turn_beta, c_stray, more[2];
+        };
+        static const TileChoice any_tiles[] = {{"hany16_256x128x64_w4x2", 256, 128, 64, 0.f, 0.f, 1},
+                                               {"hany16_192x128x64_w2x4", 192, 128, 64, 0.f, 0.f, 1},
+                                               {"hany16_128x128x64_w2x4", 128, 128, 64, 0.f, 0.f, 1},
+                                               {"hany16_128x64x64_w4x2", 128, 64, 64, 0.f, 0.f, 1},
+                                               {"hany16_64x64x64_w2x2", 64, 64, 64, 0.f, 0.f, 1},
+                                               {"hmfma_64x64x64_w2x2", 64, 64, 64, 0.f, 0.f, 1},
+                                               {"hmfma_128x64x64_w2x2", 128, 64, 64, 0.f, 0.f, 1},
+                                               {"hmfma_128x128x64_w2x2", 128, 128, 64, 0.f, 0.f, 1},
+                                               {"hmfma_256x256x64_w2x2", 256, 256, 64, 0.f, 0.f, 1}};
+        constexpr int kAnyStaged = 5, kAnyCount = 9;         // index of the first register-staged one
+        static const AnyCost any_costs[2][kAnyCount] = {{{3.96, 5.20, 0.0, 0.726, 0.0, 0.153, 0.192, 0.187, 0.685, 0.054, {0.0, 1.95}},
+                                                         {3.52, 4.27, 1.82, 0.587, 0.0, 0.118, 0.201, 0.028, 0.129, 0.055, {0.0, 2.13}},
+                                                         {2.87, 3.84, 0.0, 0.407, 0.0, 0.167, 0.153, 0.170, 0.359, 0.029, {0.0, 0.80}},
+                                                         {4.07, 1.22, 0.55, 0.249, 0.0, 0.114, 0.117, 0.035, 0.132, 0.017, {0.0, 0.53}},
+                                                         {4.38, 0.49, 0.45, 0.173, 0.0, 0.059, 0.043, 0.0, 0.121, 0.066, {0.0, 0.24}},
+                                                         {4.84, 0.48, 0.0, 0.075, 0.118, 0.018, 0.040, 0.0, 0.102, 0.039, {0.12, 0.57}},
+                                                         {6.01, 0.70, 0.0, 0.137, 0.167, 0.034, 0.102, 0.0, 0.067, 0.058, {0.19, 1.70}},
+                                                         {7.04, 1.36, 0.0, 0.400, 0.069, 0.0, 0.041, 0.0, 0.283, 0.105, {0.34, 4.13}},
+                                                         {5.77, 7.98, 0.0, 0.803, 0.786, 0.172, 0.419, 0.0, 1.017, 0.087, {0.0, 11.2}}},
+                                                        {{5.26, 4.19, 0.0, 0.678, 0.113, 0.150, 0.0, 0.264, 1.347, 0.024, {1.09, 0.337}},
+                                                         {4.65, 3.33, 0.0, 0.571, 0.070, 0.115, 0.003, 0.294, 1.058, 0.009, {1.35, 0.359}},
+                                                         {3.27, 3.55, 0.0, 0.435, 0.066, 0.100, 0.012, 0.215, 0.807, 0.040, {1.72, 0.365}},
+                                                         {4.57, 0.53, 0.0, 0.331, 0.015, 0.077, 0.008, 0.271, 0.423, 0.045, {1.89, 0.462}},
+                                                         {4.63, 0.0, 0.40, 0.256, 0.002, 0.033, 0.025, 0.048, 0.294, 0.141, {1.79, 0.419}},
+                                                         {}, {}, {},
+                                                         {5.65, 7.07, 4.47, 1.103, 0.127, 0.144, 0.028, 0.0, 5.391, 0.128, {0.0, 0.0}}}};
+        const bool any_short = p.k <= 320;
+        const bool any_family = !f32 && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 && p.k >= 8 && !dma_ragged_operands(p, alignment);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
         // LDS; the smaller the tile, the more that shows.  Measured rates relative to the (m, k) order (A along m,
         // B along k; tiles up to 128 x 64 / up to 256 x 128 / 256 x 256): both operands along k 1.10 / 1.06 / 1.02,
@@ -414,9 +454,9 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         };
         static const SplitCost split_costs[2] = {{8.2, 1.95, 0.75, 0.18}, {5.8, 1.06, 0.41, 0.16}};
         static const double f32_round_cost[5] = {0.0, 0.0, 1.0e6, 2.0e6, 1.8e6};
-        const TileChoice *tiles = f32 ? f32_tiles : f16_tiles;
-        const int count = f32 ? 7 : (ragged_family ? 14 : 9);
-        const int smallest = f32 ? 4 : (ragged_family ? kRaggedSmallest : 7);
+        const TileChoice *tiles = f32 ? f32_tiles : (any_family ? any_tiles : f16_tiles);
+        const int count = f32 ? 7 : (any_family ? kAnyCount : (ragged_family ? 14 : 9));
+        const int smallest = f32 ? 4 : (any_family ? -1 : (ragged_family ? kRaggedSmallest : 7));
         bool tried[14] = {false};
         // work-groups that do something: of a product whose C is a triangle, the tiles that touch it (as the kernels skip the others)
         const bool triangle = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
@@ -429,6 +469,23 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         // estimated time (in 1e-6 us) of tile i with the sum cut into `slices`
         auto estimate = [&](int i, int slices) {
             const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn) * slices;
+            if (any_family) {
+                const AnyCost &cost = any_costs[any_short ? 0 : 1][i];
+                const double x = static_cast<double>(blocks) / kComputeUnits, turns = ceil(x), ktiles = static_cast<double>(ceil_div(ceil_div(p.k, 64), slices));
+                const double bm = tiles[i].bm, bn = tiles[i].bn;
+                const double odd = ((p.lda % 2 != 0 ? bm : 0.0) + (p.ldb % 2 != 0 ? bn : 0.0)) / (bm + bn), lines = ((p.a_trans ? 0.0 : bm) + (p.b_trans ? bn : 0.0)) / (bm + bn);
+                const double c_mb = 2.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (triangle ? 0.5 : 1.0);
+                double us = cost.fixed + turns * cost.turn + x * cost.busy + ktiles * (turns * (cost.turn_ktile + cost.lines * lines) + x * cost.busy_ktile + (turns + x) * cost.odd * odd);
+                us += cost.c * c_mb + (p.beta != 0.f ? turns * cost.turn_beta : 0.0);
+                if (slices == 1 && p.ldc % 8 != 0) us += cost.c_stray * c_mb;
+                if (any_short) us += turns * ((p.k % 64 != 0 ? cost.more[0] : 0.0) + (p.beta != 0.f && p.m % 8 != 0 ? cost.more[1] : 0.0));
+                else if (slices > 1) us += cost.more[0] * (1.0 + 0.1 * slices) + cost.more[1] * 2.0 * slices * c_mb;
+                // (a nearly full turn of 64 x 64 tiles and long sums runs 5 to 8 % above that: (1672, 560, 3264) 22.9 us, 128 x 64 in two slices 22.3)
+                if (!any_short && i == kAnyStaged - 1 && slices == 1 && x > 0.5 && x <= 1.0 && ktiles >= 30.0) us *= 1.07;
+                // (masked stores of a triangle fetch the old C piece by piece there: SYRK 690 x 1408 with beta 13.9 us on 64 x 64 register-staged tiles, 10.7 on these)
+                if (i >= kAnyStaged && triangle) us += turns * (p.beta != 0.f ? 2.5 : 0.4);
+                return us * 1.0e6;
+            }
             const double tile_flops = 2.0 * tiles[i].bm * tiles[i].bn * static_cast<double>(p.k) / slices;
             const int64_t full = static_cast<int64_t>(kComputeUnits) * tiles[i].resident;   // work-groups the chip holds
             double order = 1.0;
@@ -638,7 +695,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // 175 us, 114)
             if (ragged_family && i == kStagedLargest && (narrowed || (triangle && (p.beta != 0.f || wanted_tiles(256, 256) > kComputeUnits * 3 / 4)) || (p.m % 256 == 0 && p.n % 256 == 0 && p.k % 64 == 0))) continue;
             // (tiles of a triangle are counted for heights that are multiples of the width)
-            if (!f32 && triangle && i >= kRagged && tiles[i].bm % tiles[i].bn != 0) continue;
+            if (!f32 && triangle && (any_family || i >= kRagged) && tiles[i].bm % tiles[i].bn != 0) continue;
+            // (and only square tiles have a grid of the wanted ones: SYRK (3603, 578) 256 x 128 37.9 us, 128 x 128 register-staged 25.2)
+            if (any_family && triangle && tiles[i].bm != tiles[i].bn) continue;
+            if (any_family && !any_short && (any_costs[1][i].fixed == 0.0 || (i == kAnyCount - 1 && p.k > 1024))) continue;
             const bool last = i == smallest;
             const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
             const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn);
@@ -654,8 +714,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             const bool short_triangle = !f32 && triangle && unsliced < (i >= kRagged ? 5.0e6 : 10.0e6);
             if (!in_place && !short_triangle && !(narrowed && blocks > kComputeUnits / 4)) {
                 if (last && !ragged_family) options[n_options++] = pick_split(blocks, ktiles);
-                if (blocks < 2 * kComputeUnits && (!ragged_family || i >= kRagged))
-                    for (int sl = 2; sl <= (ragged_family ? 8 : 16) && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
+                if (blocks < 2 * kComputeUnits && (any_family ? i < kAnyStaged : !ragged_family || i >= kRagged))
+                    for (int sl = 2; sl <= (ragged_family || any_family ? 8 : 16) && ktiles / sl >= 4; sl *= 2) options[n_options++] = sl;
             }
             for (int o = 0; o < n_options; ++o) {
                 const int sl = options[o];
@@ -699,7 +759,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // 26.9, 2304 40.9 / 36.1, 2560 45.1 / 39.5, 2816 52.6 / 44.3, 3072 x 1024 40.5 / 33.6, 3328 60.2 / 61.4, 4096 89.2 / 89.7), with one
             // measured exception: when the 256 x 256 direct-to-LDS grid leaves compute units idle anyway, the 128 x 128 tiles
             // balance the unequal work better (3072: 55.5 against 65.4 us)
-            if (!f32 && p.shape != MG_SHAPE_GENERAL && !triangle && best == 0 && !tried[2] &&
+            if (!f32 && !any_family && p.shape != MG_SHAPE_GENERAL && !triangle && best == 0 && !tried[2] &&
                 ceil_div(p.m, 256) * ceil_div(p.n, 256) <= (kComputeUnits * 3) / 4)
                 best = 2;
             tried[best] = true;
