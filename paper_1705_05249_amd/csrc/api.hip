@@ -34,6 +34,7 @@ const std::vector<KernelEntry> &table()
         register_gemv(g_table);
         register_batched(g_table);
         register_batched_tile(g_table);
+        register_batched_lines(g_table);
         for (size_t i = 0; i < g_table.size(); ++i) g_table[i].cfg.kernel_id = static_cast<int32_t>(i);
     });
     return g_table;

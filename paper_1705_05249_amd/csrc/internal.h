@@ -187,6 +187,7 @@ void register_mfma(std::vector<KernelEntry> &table);
 void register_gemv(std::vector<KernelEntry> &table);
 void register_batched(std::vector<KernelEntry> &table);
 void register_batched_tile(std::vector<KernelEntry> &table);
+void register_batched_lines(std::vector<KernelEntry> &table);
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

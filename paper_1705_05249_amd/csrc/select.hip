@@ -806,6 +806,43 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         const int32_t id = find(table, name);
         return id >= 0 && table[id].legal_batched(p) ? id : -1;
     };
+    // Whole instances through LDS (batched_lines.hip), one, four or eight wavefronts each.  From 420 random calls (8 to 160 in an extent, 1 to 20000
+    // instances, every kernel forced):
+    //   * up to 32 in every extent only FP16 that is not along k on both sides, whose register blocks take two bytes per load (us, those / these: 27 x 28 x 30,
+    //     7000 instances 17.0 / 9.6; 26^3 along k, 1752 instances 4.7 / 5.2; FP32 23^3, 1200 instances 5.2 / 6.5);
+    //   * FP32 of 41 to 64 rows and columns fills the 64 x 64 tile (48^3, 14200 instances 81 / 86; 35^3, 6415 instances 45 / 37), FP16 of 64 x 64 too
+    //     (1702 instances of 64^3 10.0 / 11.6);
+    //   * whole 32^3 with A along m and B along k has unchecked register blocks (FP16, 1800 instances 4.4 / 5.2);
+    //   * FP32 sums far longer than their few blocks are wide stay with the tiles in large batches (48 x 32 x 135, 3926 instances 39 / 51);
+    //   * a handful of large instances is cut into tiles below (20 of 76^3 FP32 5.6 / 8.0);
+    //   * one wavefront each where there are enough instances for the chip and few blocks of 16 x 16 in them (45 x 37 x 16, 9600 FP16 instances: old 41,
+    //     one wavefront 21.5, four 24.8; 126 x 28 x 12, 15300 instances 100 / 58 / 50);
+    //   * four where a compute unit has several instances, else eight (74^3, 485 instances: old 11.7, four 7.3, eight 6.8).
+    const auto lines = [&]() -> int32_t {
+        const int64_t most = p.m > p.n ? (p.m > p.k ? p.m : p.k) : (p.n > p.k ? p.n : p.k), blocks = ceil_div(p.m, 16) * ceil_div(p.n, 16);
+        const bool f32 = p.dtype == MG_F32;
+        if (most <= 16 || (most <= 32 && (f32 || (p.a_trans && !p.b_trans)))) return -1;
+        if (most <= 20 && p.a_trans) return -1;                       // (6900 x 18^3, A along k, B along n 7.3 / 8.8)
+        if (p.batch < 130 && blocks > 12) return -1;
+        if (f32 && p.m > 40 && p.m <= 64 && p.n > 40 && p.n <= 64 && p.k > 16) return -1;
+        if (!f32 && p.m == 64 && p.n == 64) return -1;
+        if (!f32 && take("batched_wave_32", "_full") >= 0) return -1;
+        if (f32 && p.batch >= 1000 && blocks >= 4 && p.m <= 48 && p.n <= 48 && p.k * p.k > 6 * p.m * p.n) return -1;
+        if (p.batch >= 1000 && blocks <= (f32 ? 6 : 12)) {
+            const int32_t id = take("batched_lines_w1", "");
+            // (FP32 lines along the rows of 24 x 40 x 24: two work-groups' LDS per compute unit, 5900 instances 20.9 / 28.4)
+            if (id >= 0 && !(f32 && blocks > 4 && p.k > 16)) return id;
+        }
+        if (blocks < 2 && p.k > 64 && p.batch >= 1000) return -1;
+        const int32_t four = take("batched_lines_w4", "");
+        if (four >= 0 && p.batch >= 256) return four;
+        const int32_t eight = blocks >= 6 ? take("batched_lines_w8", "") : -1;
+        return eight >= 0 ? eight : four;
+    };
+    {
+        const int32_t id = lines();
+        if (id >= 0) return id;
+    }
     // (FP32 instances that fill the 32 x 32 block and stream from memory lose more to the one-wavefront kernel's 4-byte and
     // unaligned requests than its shorter latency chain gains: 31^3, four operand orders, LDS-staged / one wavefront: 10000
     // instances 28 / 35 us, 1000 instances 6.6 / 5.8 us; 28^3 24.5 / 21-25 us, FP16 31^3 26-34 / 20-24 us; whole 32^3 with A along m
