@@ -1026,14 +1026,15 @@ static size_t level3_workspace_bytes(int routine, int dtype, int layout, int sid
     if (m < 0 || n < 0 || k < 0 || m >= lim || n >= lim || k >= lim) return 0;
     const size_t elem = dtype == MG_F32 ? 4 : 2;
     const int64_t lead = layout == MG_COL_MAJOR ? m : n;
-    // the product's own scratch: what the same product without a triangle wants and what this one does (kernels for small problems,
-    // which need none, skip no triangle: such products run on tiles, in slices where those are few)
+    // the product's own scratch: what the same product without a triangle wants and what this one wants on tiles, in slices where those are
+    // few (small ones run on a kernel that needs none; a configuration that is forced finds room)
     auto product = [&](int ta, int tb, int64_t kk, int64_t lda, int64_t ldb, int64_t ldc, int lower, int upper) {
         size_t most = mg_gemm_workspace_bytes(dtype, layout, ta, tb, m, n, kk, lda, ldb, ldc);
         if (check_shape(layout, ta, tb, m, n, kk, lda, ldb, ldc) != MG_OK) return most;
         for (const int shape : {lower, upper}) {
             Problem p = canonical(dtype, layout, ta, tb, m, n, kk, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr, shape);
             p.mask_c = routine == MG_ROUTINE_SYRK;
+            p.tiles_only = true;
             const size_t need = preferred_bytes_anywhere(p);
             if (need > most) most = need;
         }

@@ -51,6 +51,7 @@ struct Problem {
     bool mask_c;               // shape C_LOWER / C_UPPER only: nothing outside that triangle of C may be written (or read);
                                // set only for kernels whose KernelEntry says masks_triangle
     bool fp32_pipes = false;   // FP32: only kernels on the FP32 matrix pipes are ranked
+    bool tiles_only = false;   // the kernels for small problems are not ranked (workspace queries)
     bool unfolded = false;     // op(A) is a column matrix that the launch in front writes: its loads find it in other dies' caches
     int fringe_m = 0, fringe_n = 0;
     // Rows and columns of C that exist when the tiles cover more (operands padded to whole tiles in a workspace, C

@@ -137,8 +137,8 @@ int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t wor
 //   beside them 8192 x 8200 44.5 / 49.4 and 6144 x 10240 42.9 / 44.5), with neither few work-groups of it along the outputs
 //   (1024 x 65536 44.1 / 46.2, 192 x 260416 33.4 / 43.7) nor one of the panel kernel per compute unit (16384 x 4096 48.7 /
 //   52.3); the outputs leave most lanes of an axpy work-group idle (64 x 390625 36.2 / 20.6, FP16 256 x 390625 54.9 / 37.7;
-//   128 x 390625 38.9 / 37.9, FP16 512 x 195312 40.1 / 43.9); or they end inside a lane's run, which that kernel reads
-//   element by element (FP16 1500 x 66666 123 / 58);
+//   128 x 390625 38.9 / 37.9, FP16 512 x 195312 40.1 / 43.9); or they end inside a lane's run
+//   (FP16 1500 x 66666 123 / 58, when that kernel read such runs element by element);
 //   the axpy kernel also where its work-groups fill the chip by themselves (10^6 x 64: 40 / 66).
 void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
                              int32_t *kernel, int32_t *split)
@@ -249,16 +249,17 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
     // 1.2), where the time of ranking the tiles, 0.5 us, comes on top.  More blocks than compute units: 1.2 to 1.8.
     // (with fringe rows / columns taken off, the tiles cover tm x tn of C)
     const int64_t tm = p.m - p.fringe_m, tn = p.n - p.fringe_n;
-    const int64_t blocks32 = ceil_div(p.m, 32) * ceil_div(p.n, 32);
+    // (of a triangle of C the blocks that touch it)
+    const bool triangular_c = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
+    const int64_t blocks32 = triangular_c ? ceil_div(p.m, 32) * (ceil_div(p.m, 32) + 1) / 2 : ceil_div(p.m, 32) * ceil_div(p.n, 32);
     const char *order_tag = p.a_trans ? (p.b_trans ? "kn" : "kk") : (p.b_trans ? "mn" : "mk");
-    const bool few_blocks = p.shape == MG_SHAPE_GENERAL && blocks32 <= kComputeUnits && p.m > 1 && p.n > 1;
+    const bool few_blocks = !p.tiles_only && blocks32 <= kComputeUnits && p.m > 1 && p.n > 1;
     // FP16 products of whole 64 x 64 tiles (aligned operands) and few K-tiles of 64 are ranked with the tiles, below: the register-staged ones without
     // checks start their products after one load, five work-groups to a compute unit.
     const bool whole64 = !f32 && p.conv == nullptr && p.m % 64 == 0 && p.n % 64 == 0 && p.k % 64 == 0 && dma_ragged_operands(p, alignment);
     const bool whole_short = whole64 && p.shape == MG_SHAPE_GENERAL && (p.k <= 256 || (p.k <= 384 && p.m / 64 * (p.n / 64) <= kComputeUnits));
     // (of a triangle of C they always are: over 123 SYRK of up to four K-tiles 64 x 64 ones take 0.93 of the time of what was chosen before the direct-to-LDS tiles
     // for any size, at most 1.01, and within 1 % of the fastest of all; (640, 64) 4.1 us, 4.5 on those tiles)
-    const bool triangular_c = p.shape == MG_SHAPE_C_LOWER || p.shape == MG_SHAPE_C_UPPER;
     if (triangular_c && whole64 && p.k <= 256) {
         char name[48];
         snprintf(name, sizeof name, "hmfma_64x64x64_w2x2_%s", order_tag);
@@ -813,7 +814,7 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
     //   * FP32 of 41 to 64 rows and columns fills the 64 x 64 tile (48^3, 14200 instances 81 / 86; 35^3, 6415 instances 45 / 37), FP16 of 64 x 64 too
     //     (1702 instances of 64^3 10.0 / 11.6);
     //   * whole 32^3 with A along m and B along k has unchecked register blocks (FP16, 1800 instances 4.4 / 5.2);
-    //   * FP32 sums far longer than their few blocks are wide stay with the tiles in large batches (48 x 32 x 135, 3926 instances 39 / 51);
+    //   * FP32 sums of more than 80 terms stay with the tiles in large batches (48 x 32 x 135, 3926 instances 39 / 51);
     //   * a handful of large instances is cut into tiles below (20 of 76^3 FP32 5.6 / 8.0);
     //   * one wavefront each where there are enough instances for the chip and few blocks of 16 x 16 in them (45 x 37 x 16, 9600 FP16 instances: old 41,
     //     one wavefront 21.5, four 24.8; 126 x 28 x 12, 15300 instances 100 / 58 / 50);
@@ -827,7 +828,7 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         if (f32 && p.m > 40 && p.m <= 64 && p.n > 40 && p.n <= 64 && p.k > 16) return -1;
         if (!f32 && p.m == 64 && p.n == 64) return -1;
         if (!f32 && take("batched_wave_32", "_full") >= 0) return -1;
-        if (f32 && p.batch >= 1000 && blocks >= 4 && p.m <= 48 && p.n <= 48 && p.k * p.k > 6 * p.m * p.n) return -1;
+        if (f32 && p.batch >= 1000 && p.k > 80) return -1;
         if (p.batch >= 1000 && blocks <= (f32 ? 6 : 12)) {
             const int32_t id = take("batched_lines_w1", "");
             // (FP32 lines along the rows of 24 x 40 x 24: two work-groups' LDS per compute unit, 5900 instances 20.9 / 28.4)
