@@ -112,28 +112,6 @@ template <int N> __device__ __forceinline__ void lines_step(floatx4 (&c)[N], con
     for (int i = 0; i < N; ++i) lines_mma(c[i], x[i], y);
 }
 
-// v moved down by `by` elements
-template <typename T> __device__ __forceinline__ u32x4 shift_elements(u32x4 v, int by)
-{
-    return shift_down(v, sizeof(T) == 4 ? 2 * by : by);
-}
-
-// the first `valid` (1 to V - 1) elements of a piece: halves of the piece, of the rest, ...
-template <typename T> __device__ __forceinline__ void store_first(T *out, const Pack<T, 16 / sizeof(T)> &o, int valid)
-{
-    const u32x4 w = __builtin_bit_cast(u32x4, o);
-    if constexpr (sizeof(T) == 2) {
-        if (valid & 4) *reinterpret_cast<Pack<T, 4> *>(out) = __builtin_bit_cast(Pack<T, 4>, u32x2{w.x, w.y});
-        const uint32_t two = valid & 4 ? w.z : w.x, next = valid & 4 ? w.w : w.y;
-        if (valid & 2) *reinterpret_cast<Pack<T, 2> *>(out + (valid & 4)) = __builtin_bit_cast(Pack<T, 2>, two);
-        const uint16_t one = static_cast<uint16_t>(valid & 2 ? next : two);
-        if (valid & 1) out[valid & 6] = __builtin_bit_cast(T, one);
-    } else {
-        if (valid & 2) *reinterpret_cast<Pack<T, 2> *>(out) = __builtin_bit_cast(Pack<T, 2>, u32x2{w.x, w.y});
-        if (valid & 1) out[valid & 2] = __builtin_bit_cast(T, valid & 2 ? w.z : w.x);
-    }
-}
-
 // An operand's pieces tid + i * NT, i < U, to registers, and from there to LDS
 template <typename T, int NT, int U> struct LinesLoader {
     static constexpr int V = 16 / static_cast<int>(sizeof(T));

@@ -20,9 +20,11 @@
 // FP16 40.0 / 9.9 (33 MB, 3.4 TB/s, the launch included), FP32 30.6 / 19.8; FP16 64^3 (3111, both transposed) 46 / 17.5, 81^3 (800)
 // 105 / 15, (19, 80, 144) x 2100 171 / 23; FP32 64^3 (5000, B along n) 103 / 69 (328 MB, 4.8 TB/s), 93^3 (856) 63 / 31, 99^3 (4122)
 // 313 / 191: there the MFMAs of the padded blocks take half of the time and do not hide behind the loads.
+// The piece that a column of C ends in takes its old values from the 16 bytes that end with the column and goes out as 8, 4 and 2 bytes; element by
+// element, each behind its old value, it cost a memory latency per element (FP32 73^3, 569 instances, beta 22.2 / 19.4; FP16 121 x 150 x 27 62 / 42).
 // A team skips the columns of 16x16 blocks that the instance does not have, and its columns of blocks are dealt out evenly.
 #include "batched_walk.h"
-#include "mfma_kernel.h"
+#include "mfma_any_kernel.h"
 
 namespace mg {
 namespace {
@@ -252,8 +254,10 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
         if (beta == 0.f) return;
         static_for<PASSES>([&](auto P) __attribute__((always_inline)) {
             constexpr int p = decltype(P)::value;
-            if (has(piece_c[p], bj) && piece_row[p] + PER <= mt)
-                old[p] = *reinterpret_cast<const Pack<T, PER> *>(C + column(piece_c[p], bj) * a.ldc + piece_row[p]);
+            // (of a piece that ends beyond the column the 16 bytes that end with it)
+            const int beyond = piece_row[p] + PER > mt ? piece_row[p] + PER - mt : 0;
+            if (has(piece_c[p], bj) && a.m >= PER)
+                old[p] = *reinterpret_cast<const Pack<T, PER> *>(C + column(piece_c[p], bj) * a.ldc + piece_row[p] - beyond);
         });
     };
 
@@ -314,21 +318,16 @@ __global__ __launch_bounds__(256) void batched_tile_kernel(const TileBatchArgs a
                 const floatx4 x = *reinterpret_cast<const floatx4 *>(stage + (c * STAGE_LD + row + 4 * h) * 4);
                 v[4 * h] = x.x; v[4 * h + 1] = x.y; v[4 * h + 2] = x.z; v[4 * h + 3] = x.w;
             }
-            if (valid >= PER) {
-                Pack<T, PER> o;
-#pragma unroll
-                for (int e = 0; e < PER; ++e)
-                    o.v[e] = static_cast<T>(beta != 0.f ? fmaf(beta, static_cast<float>(now[p].v[e]), alpha * v[e]) : alpha * v[e]);
-                *reinterpret_cast<Pack<T, PER> *>(out) = o;
-            } else {
-#pragma unroll
-                for (int e = 0; e < PER; ++e)
-                    if (e < valid) {
-                        float o = alpha * v[e];
-                        if (beta != 0.f) o = fmaf(beta, load_as_float(out + e), o);
-                        store_from_float(out + e, o);
-                    }
+            if (beta != 0.f && valid < PER) {
+                if (a.m >= PER) now[p] = __builtin_bit_cast(Pack<T, PER>, shift_elements<T>(__builtin_bit_cast(u32x4, now[p]), PER - valid));
+                else now[p] = __builtin_bit_cast(Pack<T, PER>, gather_chunk<T>(out, valid));
             }
+            Pack<T, PER> o;
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+                o.v[e] = static_cast<T>(beta != 0.f ? fmaf(beta, static_cast<float>(now[p].v[e]), alpha * v[e]) : alpha * v[e]);
+            if (valid >= PER) *reinterpret_cast<Pack<T, PER> *>(out) = o;
+            else store_first<T>(out, o, valid);
         });
     });
 }

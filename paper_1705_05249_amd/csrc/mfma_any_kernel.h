@@ -29,6 +29,28 @@ __device__ __forceinline__ u32x4 shift_down(u32x4 v, int by)
     return by >= 8 ? u32x4{0u, 0u, 0u, 0u} : v;
 }
 
+// v moved down by `by` elements
+template <typename T> __device__ __forceinline__ u32x4 shift_elements(u32x4 v, int by)
+{
+    return shift_down(v, sizeof(T) == 4 ? 2 * by : by);
+}
+
+// the first `valid` (1 to V - 1) elements of a piece: halves of the piece, of the rest, ...
+template <typename T> __device__ __forceinline__ void store_first(T *out, const Pack<T, 16 / sizeof(T)> &o, int valid)
+{
+    const u32x4 w = __builtin_bit_cast(u32x4, o);
+    if constexpr (sizeof(T) == 2) {
+        if (valid & 4) *reinterpret_cast<Pack<T, 4> *>(out) = __builtin_bit_cast(Pack<T, 4>, u32x2{w.x, w.y});
+        const uint32_t two = valid & 4 ? w.z : w.x, next = valid & 4 ? w.w : w.y;
+        if (valid & 2) *reinterpret_cast<Pack<T, 2> *>(out + (valid & 4)) = __builtin_bit_cast(Pack<T, 2>, two);
+        const uint16_t one = static_cast<uint16_t>(valid & 2 ? next : two);
+        if (valid & 1) out[valid & 6] = __builtin_bit_cast(T, one);
+    } else {
+        if (valid & 2) *reinterpret_cast<Pack<T, 2> *>(out) = __builtin_bit_cast(Pack<T, 2>, u32x2{w.x, w.y});
+        if (valid & 1) out[valid & 2] = __builtin_bit_cast(T, valid & 2 ? w.z : w.x);
+    }
+}
+
 // One operand tile (ROWS rows x 64 k): global -> registers -> LDS
 template <int ROWS, int NT, bool KCONTIG, int RB, int DEPTH> struct AnyLoader {
     static constexpr int LDS_BYTES = ROWS * 128;

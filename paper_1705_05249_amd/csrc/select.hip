@@ -814,7 +814,8 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
     //   * FP32 of 41 to 64 rows and columns fills the 64 x 64 tile (48^3, 14200 instances 81 / 86; 35^3, 6415 instances 45 / 37), FP16 of 64 x 64 too
     //     (1702 instances of 64^3 10.0 / 11.6);
     //   * whole 32^3 with A along m and B along k has unchecked register blocks (FP16, 1800 instances 4.4 / 5.2);
-    //   * FP32 sums of more than 80 terms stay with the tiles in large batches (48 x 32 x 135, 3926 instances 39 / 51);
+    //   * FP32 sums of more than 80 terms, and of more than 48 on 17 to 33 rows or columns, stay with the tiles in large batches (48 x 32 x 135, 3926
+    //     instances 39 / 51; 19 x 23 x 56, 15100 instances 44 / 55; 72 x 12 x 52, 9800 instances 72 / 48);
     //   * a handful of large instances is cut into tiles below (20 of 76^3 FP32 5.6 / 8.0);
     //   * one wavefront each where there are enough instances for the chip and few blocks of 16 x 16 in them (45 x 37 x 16, 9600 FP16 instances: old 41,
     //     one wavefront 21.5, four 24.8; 126 x 28 x 12, 15300 instances 100 / 58 / 50);
@@ -828,7 +829,8 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         if (f32 && p.m > 40 && p.m <= 64 && p.n > 40 && p.n <= 64 && p.k > 16) return -1;
         if (!f32 && p.m == 64 && p.n == 64) return -1;
         if (!f32 && take("batched_wave_32", "_full") >= 0) return -1;
-        if (f32 && p.batch >= 1000 && p.k > 80) return -1;
+        const int64_t thin = p.m < p.n ? p.m : p.n;
+        if (f32 && p.batch >= 1000 && (p.k > 80 || (p.k > 48 && thin > 16 && thin <= 33))) return -1;
         if (p.batch >= 1000 && blocks <= (f32 ? 6 : 12)) {
             const int32_t id = take("batched_lines_w1", "");
             // (FP32 lines along the rows of 24 x 40 x 24: two work-groups' LDS per compute unit, 5900 instances 20.9 / 28.4)
