@@ -26,10 +26,13 @@ template <typename U, int V> struct alignas(sizeof(U) * V) Pack {
 // (i >= j) or the upper triangle; what src holds in its other triangle is never used.  One work-group
 // takes the tile (ti, tj), ti >= tj, of the lower half through LDS and writes it twice: in place and
 // mirrored, both as runs of E contiguous elements per lane, LPC lanes side by side.  E x element size is
-// 16 bytes when the columns of dst start on 16 bytes (LPC = 16), else E = 1 (LPC = 64); src is read at element alignment
+// 16 bytes when the columns of dst start on 16 bytes (64 x 64 tiles), else E = 1 (32 x 32); src is read at element alignment
 // and dst written up to the end of a run, in the columns' padding (n = 1151 in FP16: 8.3 us element by element).  The tile edge is
 // LPC * E.  LDS is written and read element by element (an odd pitch in words keeps the transposed
 // reads spread over the banks).
+// Bound by latency up to about 1500 rows: all of a thread's runs are asked for at once, and the tiles are small enough for a work-group on most compute
+// units (four runs at a time on 128 x 128 tiles, FP16, or sixteen single elements of 64 x 64 ones: n = 171 6.6 us, 1344 8.2).  Whole SYMM calls, us, before / now:
+// FP16 171 x 219 12.9 / 9.8, 1344 x 207 16.5 / 13.5, FP32 119 x 578 from the right 15.5 / 12.3; 0.78 (FP16) and 0.91 (FP32) of the time over 81 random ones.
 template <typename U, int E, int LPC>
 __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *__restrict__ src, int64_t ld, bool lower,
                                                                U *__restrict__ dst, int64_t ldd)
@@ -55,8 +58,9 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
     if (ti < tj) return;
     const int tx = threadIdx.x % LPC, ty0 = threadIdx.x / LPC;
     const int r0 = ti * TS, c0 = tj * TS;
-#pragma unroll 4
-    for (int ty = ty0; ty < TS; ty += STEP) {
+#pragma unroll
+    for (int it = 0; it < TS / STEP; ++it) {
+        const int ty = ty0 + it * STEP;
         if (lower) {
             // rows a .. a+E-1 of column b: contiguous in src
             const int a = E * tx, b = ty;
@@ -76,8 +80,9 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
         }
     }
     __syncthreads();
-#pragma unroll 4
-    for (int ty = ty0; ty < TS; ty += STEP) {
+#pragma unroll
+    for (int it = 0; it < TS / STEP; ++it) {
+        const int ty = ty0 + it * STEP;
         const int a = E * tx, b = ty;
         if (r0 + a < n && c0 + b < n) {
             Run w;
@@ -106,7 +111,8 @@ __global__ __launch_bounds__(256) void expand_symmetric_kernel(int n, const U *_
 // on a unit diagonal; neither the other triangle of tri nor (unit) its diagonal is read.  blockIdx.z == 1: dst
 // (leading dimension ldd) <- src (leading dimension lds), `minor` contiguous elements in each of `major` runs.  The
 // grid covers the larger of the two.  V > 1: the columns of full and dst start on 16 bytes and have room for whole runs (the
-// sources are read at element alignment; FP16 n = 3159 17.5 us element by element).
+// sources are read at element alignment; FP16 n = 3159 17.5 us element by element).  Runs of zeros are stored without the tests of
+// the diagonal's (the call of FP16 213 x 2813 from the right 36.5 / 29.7 us).
 template <typename T, int V>
 __global__ __launch_bounds__(256) void trmm_prepare_kernel(int n, const T *__restrict__ tri, int64_t ld, bool lower, bool unit,
                                                            T *__restrict__ full, int64_t ldf, int minor, int major,
@@ -143,13 +149,16 @@ __global__ __launch_bounds__(256) void trmm_prepare_kernel(int n, const T *__res
             const Loose in = *reinterpret_cast<const Loose *>(tri + i + j * ld);
 #pragma unroll
             for (int e = 0; e < V; ++e) out.v[e] = in.v[e];
+        } else if (all_out) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) out.v[e] = static_cast<T>(0.f);
         } else {
 #pragma unroll
             for (int e = 0; e < V; ++e) {
                 const int r = i + e;
                 const bool in = r < n && (lower ? r >= j : r <= j);
                 T v = static_cast<T>(0.f);
-                if (!all_out && in) v = (unit && r == j) ? static_cast<T>(1.f) : tri[r + j * ld];
+                if (in) v = (unit && r == j) ? static_cast<T>(1.f) : tri[r + j * ld];
                 out.v[e] = v;
             }
         }
@@ -306,7 +315,7 @@ hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_
 {
     const int elem = dtype == MG_F32 ? 4 : 2;
     const bool wide = runs_fit(n, src, ld, dst, ldd, elem);
-    const int edge = wide ? 16 * (16 / elem) : 64;
+    const int edge = wide ? 64 : 32;
     const unsigned tiles = static_cast<unsigned>(ceil_div(n, edge));
     if (tiles > kMaxGridY) return hipErrorInvalidValue;
     const dim3 grid(tiles, tiles);
@@ -315,12 +324,12 @@ hipError_t launch_expand_symmetric(int dtype, int64_t n, const void *src, int64_
         const uint32_t *s = static_cast<const uint32_t *>(src);
         uint32_t *d = static_cast<uint32_t *>(dst);
         if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 4, 16>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
-        else hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 1, 64>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
+        else hipLaunchKernelGGL((expand_symmetric_kernel<uint32_t, 1, 32>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
     } else {
         const uint16_t *s = static_cast<const uint16_t *>(src);
         uint16_t *d = static_cast<uint16_t *>(dst);
-        if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 8, 16>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
-        else hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 1, 64>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
+        if (wide) hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 8, 8>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
+        else hipLaunchKernelGGL((expand_symmetric_kernel<uint16_t, 1, 32>), grid, dim3(256), 0, stream, nn, s, ld, lower, d, ldd);
     }
     return hipGetLastError();
 }
