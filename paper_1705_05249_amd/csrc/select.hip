@@ -275,7 +275,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
         if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
     }
-    if (p.m >= 16 && p.n >= 16) {
+    // Thin products (fewer than 16 rows or columns) beyond the shared-sum kernel's range are ranked like the others: most of a tile is empty, but the kernel
+    // below, for any problem, loads element by element and does not slice its sums (us, that kernel / ranked: FP16 8 x 5416 x 4000 755 / 16, 13 x 1381 x 6016
+    // 909 / 12, FP32 8 x 576 x 4952 530 / 15, 8 x 24720 x 8040 1455 / 211, 28481 x 12 x 621 94 / 27; sums of up to 48 terms stay on it).
+    const bool thin = (p.m < 16 || p.n < 16) && p.m > 1 && p.n > 1 && p.k > 48;
+    if ((p.m >= 16 && p.n >= 16) || thin) {
         // The macro tile (and number of K slices) with the smallest estimated time, see `estimate` below: a chip
         // that is not full runs ceil(tiles / 256) work-groups per compute unit at a rate that grows with them up to
         // the kernel's ceiling; a full chip works through rounds of 256 x resident work-groups.  Rates (Mflop/us per
@@ -765,6 +769,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 best = 2;
             tried[best] = true;
             const TileChoice &tc = tiles[best];
+            if (thin && want == 1 && few_blocks) {       // (no room for slices, or nothing to gain from them)
+                char name[48];
+                snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
+                if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
+            }
             // a factor whose last slice would be empty is illegal: take the next smaller one
             for (int w = want; w >= 1; --w)
                 if (try_mfma(table, p, alignment, tc.tag, w, kernel, split)) {
@@ -772,6 +781,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                     return;
                 }
         }
+    }
+    if (thin) {                                          // (FP16 of fewer than eight rows that no ranked tile takes: 4 x 30797 x 5268 1267 / 104 us)
+        char name[48];
+        snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
+        if (try_pick(table, p, alignment, name, 1, kernel, split)) return;
     }
     try_pick(table, p, alignment, f32 ? "direct_f32_64x64x16" : "direct_f16_64x64x16", 1, kernel, split);
 }

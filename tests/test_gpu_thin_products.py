@@ -1,0 +1,22 @@
+"""Products of 2 to 15 rows or columns, whose sums are longer than one block's wavefronts share or which have more blocks than the chip has compute
+units: with the workspace the library asks for and without, against the CPU oracle."""
+import pytest
+
+import helpers as H
+from paper_1705_05249_amd import gemm as G
+from paper_1705_05249_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+C, R, N, T = W.COL_MAJOR, W.ROW_MAJOR, W.NO_TRANS, W.TRANS
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("layout,ta,tb", [(C, N, N), (C, T, N), (C, N, T), (R, T, T)])
+@pytest.mark.parametrize("m,n,k", [(2, 2, 4001), (3, 9001, 70), (8, 8, 2600), (8, 8300, 49), (15, 37, 3000), (500, 7, 1700), (5, 8209, 129)])
+@pytest.mark.parametrize("workspace", ["auto", None])
+def test_thin(oracle, dtype, layout, ta, tb, m, n, k, workspace):
+    case = (W.skinny_case if dtype == "f32" else W.hgemm_case)(m, n, k, case=m + n + k, layout=layout, ta=ta, tb=tb, beta=0.5)
+    H.check_case(case, oracle, workspace=workspace)
+    args = (G.MG_F32 if dtype == "f32" else G.MG_F16, layout, ta, tb, m, n, k, case.lda, case.ldb, case.ldc)
+    assert not G.mg_kernel_name(G.mg_query_selected(*args)["kernel_id"]).startswith("direct")
