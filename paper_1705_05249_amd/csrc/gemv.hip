@@ -17,7 +17,7 @@
 //   panel the same order, with a work-group on fewer outputs and more of the sum.
 // Outputs that end inside a lane's run (axpy, panel): the run is taken as the V outputs that end with the last one and its first elements dropped, so
 // that every lane loads 16 bytes, eight columns in flight (element by element that one lane's column loop set the time of the call; us, before / now:
-// FP16 1518 outputs of 8038 terms 17.7 / 9.2, 5003 of 10368 39 / 24, FP32 14419 of 5564 88 / 55; 0.85 over 128 ragged calls, others within 2 %).
+// FP16 1518 outputs of 8038 terms 17.7 / 9.2, 5003 of 10368 39 / 24, FP32 14419 of 5564 88 / 55; 0.85 over 128 ragged calls; others have flavours without, 1 % faster).
 // Few outputs and a long sum leave most compute units idle, so both kernels can cut the sum into
 // `split` slices (grid.y): each slice writes FP32 partial sums to the workspace and a small
 // second kernel adds them and applies alpha and beta.
@@ -127,7 +127,8 @@ __global__ __launch_bounds__(256) void gemv_dot_kernel(int64_t outputs, int64_t 
     }
 }
 
-template <typename T>
+// RAGGED: the outputs end inside a lane's run
+template <typename T, bool RAGGED>
 __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t k, int64_t k_per_split,
                                                          const T *__restrict__ mat, int64_t stride_l,
                                                          const T *__restrict__ vec, int64_t stride_v,
@@ -149,9 +150,9 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
     // a run that ends beyond the outputs is taken as the V outputs that end with them; the first `known` are the run's before it
-    const int64_t at = o + V <= outputs ? o : outputs - V;
-    const int known = static_cast<int>(o - at);
-    if (o < outputs && at >= 0) {
+    const int64_t at = !RAGGED || o + V <= outputs ? o : outputs - V;
+    const int known = RAGGED ? static_cast<int>(o - at) : 0;
+    if (o < outputs && (!RAGGED || at >= 0)) {
         const T *__restrict__ col = mat + at;
         int64_t l = k0 + w;
         for (; l + 4 * (U - 1) < k1; l += 4 * U) {
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[e] = fmaf(static_cast<float>(a.v[e]), x, acc[e]);
         }
-    } else if (o < outputs) {
+    } else if (RAGGED && o < outputs) {
         // fewer than V outputs: element by element
         for (int64_t l = k0 + w; l < k1; l += 4) {
             const float x = static_cast<float>(vec[l * stride_v]);
@@ -182,8 +183,8 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
                 if (o + e < outputs) acc[e] = fmaf(static_cast<float>(mat[o + e + l * stride_l]), x, acc[e]);
         }
     }
-    const int dropped = at >= 0 ? known : 0;
-    if (dropped == 0) {
+    const int dropped = RAGGED && at >= 0 ? known : 0;
+    if (!RAGGED || dropped == 0) {
 #pragma unroll
         for (int e = 0; e < V; ++e) part[w][lane * V + e] = acc[e];
     } else {
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
 // run of LR x 16 bytes of a column, the other 64 / LR lanes of the wavefront the next columns, and sixteen wavefronts share
 // the sum of one work-group; lanes, then wavefronts (through LDS), are added at the end.
 // STREAM: non-temporal loads, see gemv_launch.
-template <typename T, int LR, bool STREAM>
+template <typename T, int LR, bool STREAM, bool RAGGED>
 __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64_t k, int64_t k_per_split,
                                                            const T *__restrict__ mat, int64_t stride_l,
                                                            const T *__restrict__ vec, int64_t stride_v,
@@ -239,9 +240,9 @@ __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
     int64_t l = k0 + w * CL + lane / LR;
     // (the last run as in the kernel above)
-    const int64_t at = o + V <= outputs ? o : outputs - V;
-    const int known = static_cast<int>(o - at);
-    if (o < outputs && at >= 0) {
+    const int64_t at = !RAGGED || o + V <= outputs ? o : outputs - V;
+    const int known = RAGGED ? static_cast<int>(o - at) : 0;
+    if (o < outputs && (!RAGGED || at >= 0)) {
         const T *__restrict__ col = mat + at;
         for (; l + STEP * (U - 1) < k1; l += STEP * U) {
             Vec a[U];
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[e] = fmaf(static_cast<float>(a.v[e]), x, acc[e]);
         }
-    } else if (o < outputs) {
+    } else if (RAGGED && o < outputs) {
         // fewer than V outputs: element by element
         for (; l < k1; l += STEP) {
             const float x = static_cast<float>(vec[l * stride_v]);
@@ -277,8 +278,8 @@ __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64
 #pragma unroll
         for (int e = 0; e < V; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
     if (lane < LR) {
-        const int dropped = at >= 0 ? known : 0;
-        if (dropped == 0) {
+        const int dropped = RAGGED && at >= 0 ? known : 0;
+        if (!RAGGED || dropped == 0) {
 #pragma unroll
             for (int e = 0; e < V; ++e) part[w][lane * V + e] = acc[e];
         } else {
@@ -392,11 +393,13 @@ template <typename T, int R> hipError_t gemv_launch(const Problem &p, int split)
         // with plain loads, a larger one as a stream: three FP32 matrices in turn, us plain / streamed: 4096^2 (67 MB) 13.0 / 14.2,
         // 4160 x 4096 11.7 / 14.1, 5120^2 (105 MB) 20.0 / 19.8, 8192^2 45.5 / 42.8, 65536 x 2048 91 / 80
         const bool stream = static_cast<double>(v.outputs) * static_cast<double>(v.k) * sizeof(T) > 96.0e6;
-        hipLaunchKernelGGL((stream ? gemv_panel_kernel<T, -R, true> : gemv_panel_kernel<T, -R, false>), grid, dim3(1024), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
+        const bool ragged = v.outputs % S::V != 0;
+        hipLaunchKernelGGL((stream ? (ragged ? gemv_panel_kernel<T, -R, true, true> : gemv_panel_kernel<T, -R, true, false>)
+                                   : (ragged ? gemv_panel_kernel<T, -R, false, true> : gemv_panel_kernel<T, -R, false, false>)), grid, dim3(1024), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
                            static_cast<const T *>(v.mat), v.stride_l, static_cast<const T *>(v.vec), v.stride_v,
                            static_cast<T *>(p.C), v.stride_out, partial, p.alpha, p.beta);
     } else {
-        hipLaunchKernelGGL(gemv_axpy_kernel<T>, grid, dim3(256), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
+        hipLaunchKernelGGL((v.outputs % S::V != 0 ? gemv_axpy_kernel<T, true> : gemv_axpy_kernel<T, false>), grid, dim3(256), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
                            static_cast<const T *>(v.mat), v.stride_l, static_cast<const T *>(v.vec), v.stride_v,
                            static_cast<T *>(p.C), v.stride_out, partial, p.alpha, p.beta);
     }

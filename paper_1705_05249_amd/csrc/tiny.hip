@@ -177,7 +177,8 @@ template <typename T, bool KCONTIG> struct TinySide {
     }
 };
 
-template <typename T, bool A_KCONTIG, bool B_KCONTIG>
+// SHAPED: with a triangular operand or C (the tests of the shape cost the others 0.1 us: 256^3 4.36 / 4.47)
+template <typename T, bool A_KCONTIG, bool B_KCONTIG, bool SHAPED>
 __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a)
 {
 #if defined(__HIP_DEVICE_COMPILE__)      // the host pass needs the kernel's symbol only (LDS address-space code is device code)
@@ -193,7 +194,7 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
     // larger operand instead of all of it.  Before / after, us: (150, 1500, 600) FP32 11.8 / 9.7, FP16 (512, 196, 2304) 10.9 / 9.9,
     // (300, 800, 1500) 12.3 / 10.2, (190, 1200, 2000) 10.5 / 8.9.
     int m0, n0;
-    if (a.shape < MG_SHAPE_C_LOWER) {
+    if (!SHAPED || a.shape < MG_SHAPE_C_LOWER) {
         const int xcd = blockIdx.x % 8;
         const int id = xcd * a.share + (xcd < a.rest ? xcd : a.rest) + blockIdx.x / 8;
         const int outer = id / a.minor, inner = id - outer * a.minor;
@@ -205,7 +206,7 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
         n0 *= 32;
     }
     int kb = 0, ke = a.k;
-    narrow_to_shape<32, 32, 32>(a.shape, m0, n0, kb, ke);
+    if constexpr (SHAPED) narrow_to_shape<32, 32, 32>(a.shape, m0, n0, kb, ke);
 
     // whole pairs, an eighth to each wavefront; what is left is the last wavefront's
     const int pairs = whole_pairs(ke - kb, a.kept, PAIR), share = (pairs + kWaves - 1) / kWaves;
@@ -226,8 +227,8 @@ __global__ __launch_bounds__(kWaves * 64) void tiny_gemm_kernel(const TinyArgs a
     for (int i = 0; i < 2; ++i) {
         const int mi = tid % 32, ni = tid / 32 + 16 * i;
         mine[i] = m0 + mi < a.m && n0 + ni < a.n;
-        if (a.shape == MG_SHAPE_C_LOWER) mine[i] = mine[i] && m0 + mi >= n0 + ni;
-        if (a.shape == MG_SHAPE_C_UPPER) mine[i] = mine[i] && m0 + mi <= n0 + ni;
+        if (SHAPED && a.shape == MG_SHAPE_C_LOWER) mine[i] = mine[i] && m0 + mi >= n0 + ni;
+        if (SHAPED && a.shape == MG_SHAPE_C_UPPER) mine[i] = mine[i] && m0 + mi <= n0 + ni;
         if (mine[i] && a.beta != 0.f) old[i] = load_as_float(C + (m0 + mi) + (n0 + ni) * a.ldc);
     }
     // [n][m]; FP32: four sets, by value of k modulo 4 of a lane's piece, added pairwise at the end.  A wavefront's share is whole pairs, so with one
@@ -344,10 +345,12 @@ template <typename T, bool AK, bool BKC> struct TinyConfig {
 
     static size_t workspace(const Problem &, int) { return 0; }
 
-    static hipError_t launch(const Problem &p, int)
+    static hipError_t launch(const Problem &p, int) { return p.shape == MG_SHAPE_GENERAL ? launch_flavour<false>(p) : launch_flavour<true>(p); }
+
+    template <bool SHAPED> static hipError_t launch_flavour(const Problem &p)
     {
         static bool attr_set = false;
-        auto kernel = tiny_gemm_kernel<T, AK, BKC>;
+        auto kernel = tiny_gemm_kernel<T, AK, BKC, SHAPED>;
         if (!attr_set) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
             if (e != hipSuccess) return e;
