@@ -14,8 +14,8 @@
 //   * all address arithmetic but the instance's base is 32 bits wide;
 //   * results turn through LDS of the wavefront's own, two blocks at a time, and leave as 16-byte pieces, the ends of columns as 8, 4 and 2 bytes.
 // us, the kernels before / this (traffic at 6.5 TB/s): FP16 7141 x 68^3 with odd strides 124 / 55 (41), 19400 x 36^3 63 / 39 (23), 8456 x (13, 103, 8) 65 / 22 (9),
-// 3660 x 103^3 70 / 55 (36); FP32 7608 x 71^3 202 / 145 (94), 10300 x (22, 122, 9) 72 / 48 (42), 7118 x (152, 8, 8) 63 / 27 (16); 0.87 over 420 random calls (FP16 0.81, FP32
-// 0.945).  Eight pieces per lane and operand, for instances of up to 128^3 in FP32, lose to the tiles (86^3 226 / 188): one work-group per compute unit.
+// 3660 x 103^3 70 / 55 (36); FP32 7608 x 71^3 202 / 145 (94), 10300 x (22, 122, 9) 72 / 48 (42), 7118 x (152, 8, 8) 63 / 27 (16); over 4000 random calls of 8 to 160 in an
+// extent, those not taken included, FP16 0.83 (3.8 % of them more than 5 % slower, up to 1.26) and FP32 0.94 (1.1 %, up to 1.17) of the time.  Eight pieces per lane and operand, for instances of up to 128^3 in FP32, lose to the tiles (86^3 226 / 188): one work-group per compute unit.
 // LDS: lines of an operand along k are an odd number of 16 bytes apart (fragments of 16 rows x 8 or 16 bytes touch every bank equally often), lines along
 // the rows too (FP32: four reads of 16 consecutive floats at lines 4g, 16 banks apart), or an odd number of 32 bytes (FP16: transposing reads).
 #include "mfma_any_kernel.h"
@@ -352,6 +352,24 @@ template <typename T, int TEAM, int U> bool plan_lines(const BatchedProblem &p, 
     return true;
 }
 
+// work-groups that the chip holds: by their LDS, and four (of eight wavefronts two) of a compute unit by their registers
+template <int TEAM> int64_t resident_groups(int64_t group_lds)
+{
+    constexpr int64_t MOST = TEAM == 8 ? 2 : 4;
+    const int64_t fit = 160 * 1024 / group_lds;
+    return LINES_CUS * (fit < MOST ? fit : MOST);
+}
+
+template <int TEAM> bool shape_of(const BatchedProblem &p, LinesShape *shape)
+{
+    constexpr int TEAMS = TEAM == 1 ? 4 : 1;
+    LinesArgs a{};
+    if (!plan_lines<float, TEAM, 4>(p, a)) return false;
+    shape->pieces = a.a.pieces + a.b.pieces;
+    shape->resident = resident_groups<TEAM>(a.team_lds * TEAMS) * TEAMS;
+    return true;
+}
+
 template <typename T, int TEAM, int U, bool A_KC, bool B_KC> struct LinesConfig {
     static constexpr int DTYPE = sizeof(T) == 4 ? MG_F32 : MG_F16, TEAMS = TEAM == 1 ? 4 : 1;
     static bool legal(const BatchedProblem &p)
@@ -376,9 +394,7 @@ template <typename T, int TEAM, int U, bool A_KC, bool B_KC> struct LinesConfig 
         a.a.stride = p.stride_a;
         a.b.stride = p.stride_b;
         a.stride_c = p.stride_c;
-        constexpr int64_t MOST_GROUPS = TEAM == 8 ? 2 : 4;                   // of a compute unit, by their registers
-        const int64_t group_lds = a.team_lds * TEAMS, fit = 160 * 1024 / group_lds;
-        const int64_t resident = LINES_CUS * (fit < MOST_GROUPS ? fit : MOST_GROUPS);
+        const int64_t group_lds = a.team_lds * TEAMS, resident = resident_groups<TEAM>(group_lds);
         hipError_t e = hipSuccess;
         constexpr int64_t MOST = int64_t(1) << 30;
         for (int64_t inst0 = 0; inst0 < p.batch && e == hipSuccess; inst0 += MOST) {
@@ -424,6 +440,15 @@ template <typename T, int TEAM, int U, bool A_KC, bool B_KC> struct LinesConfig 
     table.push_back(LinesConfig<T, TEAM, U, true, false>::entry(tag "_kn"));
 
 }  // namespace
+
+bool batched_lines_shape(const BatchedProblem &p, int team, LinesShape *shape)
+{
+    switch (team) {
+    case 1: return shape_of<1>(p, shape);
+    case 4: return shape_of<4>(p, shape);
+    default: return shape_of<8>(p, shape);
+    }
+}
 
 void register_batched_lines(std::vector<KernelEntry> &table)
 {

@@ -169,6 +169,13 @@ bool batched_dma_fits(const BatchedProblem &p);
 bool batched_dma_pays(const BatchedProblem &p);
 hipError_t launch_batched_dma(const BatchedProblem &p, int tile = -1);
 
+// What an FP32 batched call is to the kernels of batched_lines.hip with `team` wavefronts (1, 4, 8) per instance: 16-byte pieces of both operands of an
+// instance, and instances that the chip holds at once.  false: they do not take it.
+struct LinesShape {
+    int64_t pieces, resident;
+};
+bool batched_lines_shape(const BatchedProblem &p, int team, LinesShape *shape);
+
 // One compiled kernel (or kernel family instance) in the configuration table.
 struct KernelEntry {
     const char *name;

@@ -790,6 +790,76 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
     try_pick(table, p, alignment, f32 ? "direct_f32_64x64x16" : "direct_f16_64x64x16", 1, kernel, split);
 }
 
+namespace {
+
+// Estimated us of an FP32 batched call on the kernels of batched_lines.hip (team: 1, 4, 8 wavefronts per instance) and on the tiles of batched_tile.hip that
+// select_batched takes otherwise (32 x 32, 32 x 64, 64 x 64), fitted to 22000 random calls (1 to 700 in an extent, 1 to 200000 instances, both routes in one
+// build), 7 to 8 % rms.  Whether the device's scalars add the old C of a generic call the host does not know: counted as half of them.
+struct BatchedTerms {
+    double per_cu, far_mb, c, old_c, bytes, steps, blocks;
+    bool generic, stray;
+
+    explicit BatchedTerms(const BatchedProblem &p)
+    {
+        per_cu = static_cast<double>(p.batch) / kComputeUnits;                                    // instances
+        bytes = 4.0 * static_cast<double>(p.m * p.k + p.k * p.n + p.m * p.n);                     // of an instance
+        far_mb = static_cast<double>(p.batch) * bytes * 1.0e-6 - 250.0;                           // beyond the last-level cache
+        if (far_mb < 0.0) far_mb = 0.0;
+        old_c = p.strided ? (p.beta != 0.f ? 1.0 : 0.0) : 0.5;
+        c = per_cu * static_cast<double>(p.m * p.n) * 1.0e-3;
+        steps = static_cast<double>(ceil_div(p.k, 16));
+        blocks = static_cast<double>(ceil_div(p.m, 16) * ceil_div(p.n, 16));
+        generic = !p.strided;
+        stray = p.m % 4 != 0;                                                                     // columns of C end inside a piece
+    }
+};
+
+double batched_lines_us(const BatchedProblem &p, int team, const LinesShape &shape)
+{
+    // per turn of the resident teams: a unit of blocks, its K-steps, its stray ends, an instance's offsets, columns of C shorter than a piece;
+    // per compute unit: an instance, K-steps of blocks, 100 pieces of a generic instance, 1000 old elements of C, 10000 bytes
+    struct Cost {
+        double fixed, unit, instance, block_step, far_mb, stray_unit, generic_turn, generic_pieces, old_c, short_unit, unit_step, bytes;
+    };
+    static const Cost costs[3] = {{3.65, 0.586, 0.0535, 0.00476, 0.0673, 0.0713, 0.236, 0.00324, 0.0919, 0.201, 0.0796, 0.208},
+                                  {3.79, 0.566, 0.172, 0.0113, 0.0446, 0.0843, 0.23, 0.0, 0.0961, 0.349, 0.0804, 0.16},
+                                  {4.02, 0.585, 0.391, 0.0129, 0.0336, 0.101, 0.246, 0.0, 0.0985, 0.436, 0.0875, 0.135}};
+    const Cost &k = costs[team == 1 ? 0 : (team == 4 ? 1 : 2)];
+    const BatchedTerms t(p);
+    const int64_t rows = ceil_div(p.m, 16), cols = ceil_div(p.n, 16), groups = ceil_div(rows, 2);
+    const int64_t rows_per_group = groups * cols < team ? 1 : ceil_div(rows, groups);            // as the kernel deals its units out
+    const double units = static_cast<double>(ceil_div(ceil_div(rows, rows_per_group) * cols, team)), turns = static_cast<double>(ceil_div(p.batch, shape.resident));
+    double us = k.fixed + turns * units * (k.unit + k.unit_step * static_cast<double>(rows_per_group) * t.steps);
+    if (t.stray) us += turns * units * k.stray_unit;
+    if (p.m < 4) us += turns * units * t.old_c * k.short_unit;
+    us += t.per_cu * (k.instance + k.block_step * t.blocks * t.steps + k.bytes * t.bytes * 1.0e-4) + k.old_c * t.old_c * t.c + k.far_mb * t.far_mb;
+    if (t.generic) us += turns * k.generic_turn + t.per_cu * k.generic_pieces * static_cast<double>(shape.pieces) * 1.0e-2;
+    return us;
+}
+
+double batched_tile_us(const BatchedProblem &p, int64_t tm, int64_t tn)
+{
+    // a chunk of the sum; turns of four work-groups per compute unit, and of the columns of blocks that a wavefront has in them; per compute unit: a tile,
+    // K-steps of blocks, chunks with lines that end inside a piece, 1000 old elements of C, 10000 bytes
+    struct Cost {
+        double fixed, chunk, turn, tile, block_step, far_mb, stray_old, stray_chunk, old_c, turn_col, turn_col_step, chunk_col, bytes;
+    };
+    static const Cost costs[3] = {{3.25, 0.44, 0.608, 0.0, 0.00639, 0.0396, 0.54, 0.00727, 0.238, 0.0, 0.118, 0.164, 0.106},
+                                  {3.63, 0.0548, 0.0, 0.298, 0.0112, 0.0101, 0.461, 0.00889, 0.0786, 0.146, 0.105, 0.114, 0.128},
+                                  {3.39, 0.26, 0.0, 0.324, 0.0117, 0.0261, 0.579, 0.0212, 0.102, 0.394, 0.0817, 0.174, 0.158}};
+    const Cost &k = costs[tn == 32 ? 0 : (tm == 32 ? 1 : 2)];
+    const BatchedTerms t(p);
+    const int64_t tiles = ceil_div(p.m, tm) * ceil_div(p.n, tn), blocks_n = ceil_div(p.n, 16);
+    const double chunks = static_cast<double>(ceil_div(p.k, 32)), turns = static_cast<double>(ceil_div(p.batch * tiles, 4 * kComputeUnits));
+    const double cols = (tn == 32 ? blocks_n : ceil_div(blocks_n, 2)) > 1 ? 2.0 : 1.0;
+    const double stray_lines = ((p.a_trans ? p.k : p.m) % 4 != 0 ? 1.0 : 0.0) + ((p.b_trans ? p.n : p.k) % 4 != 0 ? 1.0 : 0.0);
+    double us = k.fixed + chunks * (k.chunk + k.chunk_col * cols) + turns * (k.turn + cols * (k.turn_col + k.turn_col_step * t.steps));
+    us += t.per_cu * (static_cast<double>(tiles) * (k.tile + k.stray_chunk * stray_lines * chunks) + k.block_step * t.blocks * t.steps + k.bytes * t.bytes * 1.0e-4);
+    return us + (t.stray ? k.stray_old * t.old_c : 0.0) + k.old_c * t.old_c * t.c + k.far_mb * t.far_mb;
+}
+
+}  // namespace
+
 int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProblem &p)
 {
     // One wavefront per instance while the instance fits the register blocks (<= 32 in every extent); with more 16^3
@@ -839,9 +909,14 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         const bool f32 = p.dtype == MG_F32;
         if (most <= 16 || (most <= 32 && (f32 || (p.a_trans && !p.b_trans)))) return -1;
         if (most <= 20 && p.a_trans) return -1;                       // (6900 x 18^3, A along k, B along n 7.3 / 8.8)
+        // (8000 x 17^3 9.0 / 10.9; 23 calls 1.06)
+        if (most <= 17 && !p.a_trans && !p.b_trans && p.batch >= kComputeUnits) return -1;
         if (p.batch < 130 && blocks > 12) return -1;
         if (f32 && p.m > 40 && p.m <= 64 && p.n > 40 && p.n <= 64 && p.k > 16) return -1;
         if (!f32 && p.m == 64 && p.n == 64) return -1;
+        // (of a generic batch, whose instances may lie anywhere, whole pieces that fill most of a tile and its chunk: 48^3 and 56^3, 130 calls of all orders 1.14 times
+        // as long, 9500 x 48^3 1.23, 16610 x 56^3 63 / 86 us; strided 0.97)
+        if (!f32 && !p.strided && p.batch >= 1000 && p.m > 40 && p.m <= 64 && p.n > 40 && p.n <= 64 && p.k > 32 && p.k <= 64 && p.m % 8 == 0 && p.n % 8 == 0 && p.k % 8 == 0) return -1;
         if (!f32 && take("batched_wave_32", "_full") >= 0) return -1;
         const int64_t thin = p.m < p.n ? p.m : p.n;
         if (f32 && p.batch >= 1000 && (p.k > 80 || (p.k > 48 && thin > 16 && thin <= 33))) return -1;
@@ -856,9 +931,16 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         const int32_t eight = blocks >= 6 ? take("batched_lines_w8", "") : -1;
         return eight >= 0 ? eight : four;
     };
+    // (FP32 calls that they are estimated to lose stay below, with the estimates' error on the side of these kernels.  By the lines above alone 15 % of the FP32 calls
+    // were more than 5 % slower than below, up to 1.7 times: 2982 x (32, 16, 40) 8.9 / 12.6, 2855 x (24, 104, 48) 27 / 39, 76 x (7, 152, 6) 4.6 / 6.1; with the
+    // estimates 3 %, up to 1.27, and 0.7 % give up more than 5 %.  Fitted to half of the calls, counted on the others.  FP16: 3 %, without.)
     {
+        const bool small = p.m <= 32 && p.n <= 32, narrow = ceil_div(p.m, 32) % 2 != 0;
         const int32_t id = lines();
-        if (id >= 0) return id;
+        LinesShape shape;
+        const int team = id >= 0 ? table[id].cfg.waves_n : 0;
+        if (id >= 0 && (p.dtype != MG_F32 || !batched_lines_shape(p, team, &shape) ||
+                        batched_lines_us(p, team, shape) < 1.02 * batched_tile_us(p, small || narrow ? 32 : 64, small ? 32 : 64))) return id;
     }
     // (FP32 instances that fill the 32 x 32 block and stream from memory lose more to the one-wavefront kernel's 4-byte and
     // unaligned requests than its shorter latency chain gains: 31^3, four operand orders, LDS-staged / one wavefront: 10000
