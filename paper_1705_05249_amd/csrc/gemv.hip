@@ -18,9 +18,13 @@
 // Outputs that end inside a lane's run (axpy, panel): the run is taken as the V outputs that end with the last one and its first elements dropped, so
 // that every lane loads 16 bytes, eight columns in flight (element by element that one lane's column loop set the time of the call; us, before / now:
 // FP16 1518 outputs of 8038 terms 17.7 / 9.2, 5003 of 10368 39 / 24, FP32 14419 of 5564 88 / 55; 0.85 over 128 ragged calls; others have flavours without, 1 % faster).
+// What such a call of a few microseconds pays for it is kept below 0.2 us: every lane stores its run with the same masked stores (two ways of
+// storing, one per kind of lane, took FP16 9 x 15 from 2.8 to 3.1 us; now 2.9).
 // Few outputs and a long sum leave most compute units idle, so both kernels can cut the sum into
 // `split` slices (grid.y): each slice writes FP32 partial sums to the workspace and a small
 // second kernel adds them and applies alpha and beta.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace mg {
@@ -127,8 +131,18 @@ __global__ __launch_bounds__(256) void gemv_dot_kernel(int64_t outputs, int64_t 
     }
 }
 
-// RAGGED: the outputs end inside a lane's run
-template <typename T, bool RAGGED>
+// Where the outputs end: with a lane's run of V, inside one, or (FP16) inside the first.  A flavour for FP16 calls of fewer than eight outputs: the masked stores of
+// the second cost them 0.2 of 3.6 us; FP32 ones of fewer than four lose as much to the element loop by itself (2 outputs of 2487 terms 4.8 / 5.5 us).
+enum class Ends { whole, ragged, few };
+template <typename T> Ends ends_of(int64_t outputs)
+{
+    constexpr int64_t V = 16 / static_cast<int>(sizeof(T));
+    return sizeof(T) == 2 && outputs < V ? Ends::few : (outputs % V != 0 ? Ends::ragged : Ends::whole);
+}
+// fewer than V outputs may come
+template <typename T, Ends ENDS> constexpr bool SHORT_RUN = ENDS == Ends::few || (ENDS == Ends::ragged && sizeof(T) == 4);
+
+template <typename T, Ends ENDS>
 __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t k, int64_t k_per_split,
                                                          const T *__restrict__ mat, int64_t stride_l,
                                                          const T *__restrict__ vec, int64_t stride_v,
@@ -149,10 +163,10 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
     float acc[V];
 #pragma unroll
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
-    // a run that ends beyond the outputs is taken as the V outputs that end with them; the first `known` are the run's before it
-    const int64_t at = !RAGGED || o + V <= outputs ? o : outputs - V;
-    const int known = RAGGED ? static_cast<int>(o - at) : 0;
-    if (o < outputs && (!RAGGED || at >= 0)) {
+    // a run that ends beyond the outputs is taken as the V outputs that end with them; the first `dropped` are the run's before it
+    const int64_t at = ENDS != Ends::ragged || o + V <= outputs ? o : outputs - V;
+    const int dropped = ENDS == Ends::ragged && (!SHORT_RUN<T, ENDS> || at >= 0) ? static_cast<int>(o - at) : 0;
+    if (ENDS != Ends::few && o < outputs && (!SHORT_RUN<T, ENDS> || at >= 0)) {
         const T *__restrict__ col = mat + at;
         int64_t l = k0 + w;
         for (; l + 4 * (U - 1) < k1; l += 4 * U) {
@@ -174,8 +188,8 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[e] = fmaf(static_cast<float>(a.v[e]), x, acc[e]);
         }
-    } else if (RAGGED && o < outputs) {
-        // fewer than V outputs: element by element
+    } else if (SHORT_RUN<T, ENDS> && o < outputs) {
+        // element by element
         for (int64_t l = k0 + w; l < k1; l += 4) {
             const float x = static_cast<float>(vec[l * stride_v]);
 #pragma unroll
@@ -183,15 +197,9 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
                 if (o + e < outputs) acc[e] = fmaf(static_cast<float>(mat[o + e + l * stride_l]), x, acc[e]);
         }
     }
-    const int dropped = RAGGED && at >= 0 ? known : 0;
-    if (!RAGGED || dropped == 0) {
 #pragma unroll
-        for (int e = 0; e < V; ++e) part[w][lane * V + e] = acc[e];
-    } else {
-#pragma unroll
-        for (int e = 1; e < V; ++e)
-            if (e >= dropped) part[w][lane * V + e - dropped] = acc[e];
-    }
+    for (int e = 0; e < V; ++e)
+        if (ENDS != Ends::ragged || e >= dropped) part[w][lane * V + e - dropped] = acc[e];
     __syncthreads();
     for (int i = threadIdx.x; i < OB; i += 256) {
         const int64_t oo = first + i;
@@ -207,7 +215,7 @@ __global__ __launch_bounds__(256) void gemv_axpy_kernel(int64_t outputs, int64_t
 // run of LR x 16 bytes of a column, the other 64 / LR lanes of the wavefront the next columns, and sixteen wavefronts share
 // the sum of one work-group; lanes, then wavefronts (through LDS), are added at the end.
 // STREAM: non-temporal loads, see gemv_launch.
-template <typename T, int LR, bool STREAM, bool RAGGED>
+template <typename T, int LR, bool STREAM, Ends ENDS>
 __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64_t k, int64_t k_per_split,
                                                            const T *__restrict__ mat, int64_t stride_l,
                                                            const T *__restrict__ vec, int64_t stride_v,
@@ -240,9 +248,9 @@ __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64
     for (int e = 0; e < V; ++e) acc[e] = 0.f;
     int64_t l = k0 + w * CL + lane / LR;
     // (the last run as in the kernel above)
-    const int64_t at = !RAGGED || o + V <= outputs ? o : outputs - V;
-    const int known = RAGGED ? static_cast<int>(o - at) : 0;
-    if (o < outputs && (!RAGGED || at >= 0)) {
+    const int64_t at = ENDS != Ends::ragged || o + V <= outputs ? o : outputs - V;
+    const int dropped = ENDS == Ends::ragged && (!SHORT_RUN<T, ENDS> || at >= 0) ? static_cast<int>(o - at) : 0;
+    if (ENDS != Ends::few && o < outputs && (!SHORT_RUN<T, ENDS> || at >= 0)) {
         const T *__restrict__ col = mat + at;
         for (; l + STEP * (U - 1) < k1; l += STEP * U) {
             Vec a[U];
@@ -264,8 +272,8 @@ __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64
 #pragma unroll
             for (int e = 0; e < V; ++e) acc[e] = fmaf(static_cast<float>(a.v[e]), x, acc[e]);
         }
-    } else if (RAGGED && o < outputs) {
-        // fewer than V outputs: element by element
+    } else if (SHORT_RUN<T, ENDS> && o < outputs) {
+        // (likewise)
         for (; l < k1; l += STEP) {
             const float x = static_cast<float>(vec[l * stride_v]);
 #pragma unroll
@@ -278,15 +286,9 @@ __global__ __launch_bounds__(1024) void gemv_panel_kernel(int64_t outputs, int64
 #pragma unroll
         for (int e = 0; e < V; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
     if (lane < LR) {
-        const int dropped = RAGGED && at >= 0 ? known : 0;
-        if (!RAGGED || dropped == 0) {
 #pragma unroll
-            for (int e = 0; e < V; ++e) part[w][lane * V + e] = acc[e];
-        } else {
-#pragma unroll
-            for (int e = 1; e < V; ++e)
-                if (e >= dropped) part[w][lane * V + e - dropped] = acc[e];
-        }
+        for (int e = 0; e < V; ++e)
+            if (ENDS != Ends::ragged || e >= dropped) part[w][lane * V + e - dropped] = acc[e];
     }
     __syncthreads();
     const int i = threadIdx.x;
@@ -382,6 +384,7 @@ template <typename T, int R> hipError_t gemv_launch(const Problem &p, int split)
     using S = GemvShape<T, R>;
     const View v = view_of(p);
     float *partial = split > 1 ? static_cast<float *>(p.workspace) : nullptr;
+    [[maybe_unused]] const Ends ends = ends_of<T>(v.outputs);
     const dim3 grid(static_cast<unsigned>(ceil_div(v.outputs, S::OUTPUTS_PER_GROUP)), static_cast<unsigned>(split));
     if constexpr (R > 0) {
         hipLaunchKernelGGL((gemv_dot_kernel<T, R>), grid, dim3(256), 0, p.stream, v.outputs, v.k,
@@ -393,13 +396,16 @@ template <typename T, int R> hipError_t gemv_launch(const Problem &p, int split)
         // with plain loads, a larger one as a stream: three FP32 matrices in turn, us plain / streamed: 4096^2 (67 MB) 13.0 / 14.2,
         // 4160 x 4096 11.7 / 14.1, 5120^2 (105 MB) 20.0 / 19.8, 8192^2 45.5 / 42.8, 65536 x 2048 91 / 80
         const bool stream = static_cast<double>(v.outputs) * static_cast<double>(v.k) * sizeof(T) > 96.0e6;
-        const bool ragged = v.outputs % S::V != 0;
-        hipLaunchKernelGGL((stream ? (ragged ? gemv_panel_kernel<T, -R, true, true> : gemv_panel_kernel<T, -R, true, false>)
-                                   : (ragged ? gemv_panel_kernel<T, -R, false, true> : gemv_panel_kernel<T, -R, false, false>)), grid, dim3(1024), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
+        auto flavour = [ends](auto STREAM) {
+            constexpr bool streamed = decltype(STREAM)::value;
+            return ends == Ends::whole ? gemv_panel_kernel<T, -R, streamed, Ends::whole>
+                                       : (ends == Ends::ragged ? gemv_panel_kernel<T, -R, streamed, Ends::ragged> : gemv_panel_kernel<T, -R, streamed, Ends::few>);
+        };
+        hipLaunchKernelGGL((stream ? flavour(std::true_type{}) : flavour(std::false_type{})), grid, dim3(1024), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
                            static_cast<const T *>(v.mat), v.stride_l, static_cast<const T *>(v.vec), v.stride_v,
                            static_cast<T *>(p.C), v.stride_out, partial, p.alpha, p.beta);
     } else {
-        hipLaunchKernelGGL((v.outputs % S::V != 0 ? gemv_axpy_kernel<T, true> : gemv_axpy_kernel<T, false>), grid, dim3(256), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
+        hipLaunchKernelGGL((ends == Ends::whole ? gemv_axpy_kernel<T, Ends::whole> : (ends == Ends::ragged ? gemv_axpy_kernel<T, Ends::ragged> : gemv_axpy_kernel<T, Ends::few>)), grid, dim3(256), 0, p.stream, v.outputs, v.k, S::k_per_split(p, split),
                            static_cast<const T *>(v.mat), v.stride_l, static_cast<const T *>(v.vec), v.stride_v,
                            static_cast<T *>(p.C), v.stride_out, partial, p.alpha, p.beta);
     }

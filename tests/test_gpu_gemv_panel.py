@@ -71,3 +71,21 @@ def test_sums_sliced_over_a_streamed_matrix(dtype, outputs, length, ld):
     ws = torch.empty(G.mg_gemv_workspace_bytes(G.MG_F32 if f32 else G.MG_F16, C, N, outputs, length, ld), dtype=torch.uint8, device="cuda")
     (G.mg_sgemv if f32 else G.mg_hgemv)(C, N, outputs, length, 2.0, A, ld, x, 1, -1.0, y, 1, ws)
     assert torch.equal(y, want.to(kind))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("outputs", [1, 3, 4, 5, 7, 8, 9, 257, 511, 513, 519])
+@pytest.mark.parametrize("length", [1, 40, 700])
+def test_where_the_outputs_end(oracle, dtype, outputs, length):
+    """inside the first run, with a run, inside a later one and inside the first run of a work-group, on every kernel along the outputs"""
+    case = W.gemv_case(dtype, C, N, outputs, length, incy=2, alpha=2.0, beta=-1.0, integer=True, pad=1, case=outputs + length)
+    ran = 0
+    try:
+        for t in G.kernel_table():
+            if t["name"].startswith(("gemv_panel", "gemv_axpy")) and t["name"].endswith(dtype):
+                G.mg_override_config(t["kernel_id"], 1)
+                H.check_gemv(case, oracle)
+                ran += 1
+    finally:
+        G.mg_clear_override()
+    assert ran >= 4
