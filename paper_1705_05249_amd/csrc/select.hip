@@ -269,7 +269,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
     // (FP16 on 1500 aligned products: neither operand along k, which the tiles read by transposing loads as well, its time over that of the tiles 1.06 to 1.12 up to 640 terms, 250 of
     // 275 slower, 0.96 from there to 1024; other orders 1.0 down to 0.85 from 65 to 640)
     const bool aligned16 = !f32 && dma_ragged_operands(p, alignment) && dma_offsets_fit(p, 192, 64);
-    const int64_t least = aligned16 && !p.a_trans && p.b_trans ? 641 : 48, most = f32 ? most_f32 : 2560;
+    // (FP16 products with a triangular operand, whose sums are half as long: on tiles / here up to 64 terms 54 calls 1.07 times as long, to 128 1.04, to 256 1.02, to 512
+    // 0.92, to 1024 0.82; (64, 64) 8.1 / 8.5 us with the copies in front; thin ones have no better kernel below)
+    const bool short_triangle_operand = !f32 && p.shape != MG_SHAPE_GENERAL && !triangular_c && p.m >= 16 && p.n >= 16;
+    const int64_t least = aligned16 && !p.a_trans && p.b_trans ? 641 : (short_triangle_operand ? 129 : 48), most = f32 ? most_f32 : 2560;
     if (few_blocks && !whole_short && p.k >= least && p.k <= most) {
         char name[48];
         snprintf(name, sizeof name, "%ctiny_32x32_%s", f32 ? 's' : 'h', order_tag);
