@@ -389,20 +389,24 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         // that ends inside a K-tile and old columns of C that end inside a piece, per turn; long ones the second launch and the partial sums of slices.
         // Fitted to all tiles on 1700 sizes of 32 to 7000 and sums of 32 to 8192, a third each with odd and with padded leading dimensions (5 to 11 %,
         // register-staged 10 to 15 % rms).  Fitted to half and chosen for the other half: 1.018 times the fastest, 51 of 946 more than 5 % behind, up to 1.28.
+        // Short sums on more than three 64 x 64 tiles per compute unit have costs of their own, with what the register-staged tiles' one-by-one ends take (rows and values of k
+        // behind the last piece) and rounds of the work-groups that a compute unit holds: with those of all short sums, most of them on small grids, 27 % of 4700 such calls
+        // were more than 5 % slower than on the best register-staged tile, up to 1.38 ((2816, 7337, 10) 28.3 / 36.0 us, (1137, 2758, 128) 9.2 / 10.7), with their own 12 %.
         struct AnyCost {
             double fixed, turn, busy, turn_ktile, busy_ktile, odd, lines, c, turn_beta, c_stray, more[2];
+            double rows_behind, old_rows_behind, terms_behind, round, round_ktile;
         };
         static const TileChoice any_tiles[] = {{"hany16_256x128x64_w4x2", 256, 128, 64, 0.f, 0.f, 1},
                                                {"hany16_192x128x64_w2x4", 192, 128, 64, 0.f, 0.f, 1},
                                                {"hany16_128x128x64_w2x4", 128, 128, 64, 0.f, 0.f, 1},
                                                {"hany16_128x64x64_w4x2", 128, 64, 64, 0.f, 0.f, 1},
                                                {"hany16_64x64x64_w2x2", 64, 64, 64, 0.f, 0.f, 1},
-                                               {"hmfma_64x64x64_w2x2", 64, 64, 64, 0.f, 0.f, 1},
-                                               {"hmfma_128x64x64_w2x2", 128, 64, 64, 0.f, 0.f, 1},
-                                               {"hmfma_128x128x64_w2x2", 128, 128, 64, 0.f, 0.f, 1},
+                                               {"hmfma_64x64x64_w2x2", 64, 64, 64, 0.f, 0.f, 5},
+                                               {"hmfma_128x64x64_w2x2", 128, 64, 64, 0.f, 0.f, 3},
+                                               {"hmfma_128x128x64_w2x2", 128, 128, 64, 0.f, 0.f, 2},
                                                {"hmfma_256x256x64_w2x2", 256, 256, 64, 0.f, 0.f, 1}};
         constexpr int kAnyStaged = 5, kAnyCount = 9;         // index of the first register-staged one
-        static const AnyCost any_costs[2][kAnyCount] = {{{3.96, 5.20, 0.0, 0.726, 0.0, 0.153, 0.192, 0.187, 0.685, 0.054, {0.0, 1.95}},
+        static const AnyCost any_costs[3][kAnyCount] = {{{3.96, 5.20, 0.0, 0.726, 0.0, 0.153, 0.192, 0.187, 0.685, 0.054, {0.0, 1.95}},
                                                          {3.52, 4.27, 1.82, 0.587, 0.0, 0.118, 0.201, 0.028, 0.129, 0.055, {0.0, 2.13}},
                                                          {2.87, 3.84, 0.0, 0.407, 0.0, 0.167, 0.153, 0.170, 0.359, 0.029, {0.0, 0.80}},
                                                          {4.07, 1.22, 0.55, 0.249, 0.0, 0.114, 0.117, 0.035, 0.132, 0.017, {0.0, 0.53}},
@@ -417,7 +421,16 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                          {4.57, 0.53, 0.0, 0.331, 0.015, 0.077, 0.008, 0.271, 0.423, 0.045, {1.89, 0.462}},
                                                          {4.63, 0.0, 0.40, 0.256, 0.002, 0.033, 0.025, 0.048, 0.294, 0.141, {1.79, 0.419}},
                                                          {}, {}, {},
-                                                         {5.65, 7.07, 4.47, 1.103, 0.127, 0.144, 0.028, 0.0, 5.391, 0.128, {0.0, 0.0}}}};
+                                                         {5.65, 7.07, 4.47, 1.103, 0.127, 0.144, 0.028, 0.0, 5.391, 0.128, {0.0, 0.0}}},
+                                                        {{4.84, 5.96, 0.0, 0.584, 0.0928, 0.165, 0.176, 0.114, 1.45, 0.0513, {0.0, 0.473}},
+                                                         {4.54, 4.67, 0.0, 0.518, 0.0, 0.127, 0.168, 0.129, 1.32, 0.0479, {0.0667, 0.479}},
+                                                         {4.08, 4.01, 0.0, 0.411, 0.0, 0.141, 0.144, 0.125, 0.86, 0.0254, {0.0, 0.0855}},
+                                                         {4.53, 1.87, 0.0, 0.259, 0.0, 0.0965, 0.0514, 0.0479, 0.311, 0.0217, {0.0, 0.0689}},
+                                                         {5.82, 0.233, 0.0, 0.166, 0.0, 0.0618, 0.0264, 0.398, 0.194, 0.0261, {0.00326, 0.0385}},
+                                                         {5.84, 0.0, 0.0, 0.115, 0.0934, 0.0216, 0.0, 0.3, 0.187, 0.00816, {0.0424, 0.0}, 0.0649, 0.364, 0.221, 0.0945, 0.0278},
+                                                         {5.62, 0.0, 0.0, 0.0857, 0.145, 0.0428, 0.0, 0.125, 0.438, 0.0208, {0.0, 0.0768}, 0.27, 0.959, 0.401, 1.92, 0.29},
+                                                         {6.54, 0.0, 0.0, 0.0, 0.212, 0.0553, 0.0, 0.105, 1.12, 0.0388, {0.0, 0.365}, 0.645, 2.56, 0.609, 2.72, 0.527},
+                                                         {8.64, 2.09, 0.0, 0.647, 0.78, 0.12, 0.0694, 0.0997, 3.56, 0.053, {0.0, 2.68}, 3.57, 9.17, 1.15, 1.2, 0.599}}};
         const bool any_short = p.k <= 320;
         const bool any_family = !f32 && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 && p.k >= 8 && !dma_ragged_operands(p, alignment);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
@@ -475,10 +488,11 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             return triangle ? triangle_tiles(p.shape == MG_SHAPE_C_LOWER, across_m, across_n, bm, bn) : across_m * across_n;
         };
         // estimated time (in 1e-6 us) of tile i with the sum cut into `slices`
+        const bool any_large = any_family && any_short && wanted_tiles(64, 64) > 3 * kComputeUnits;
         auto estimate = [&](int i, int slices) {
             const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn) * slices;
             if (any_family) {
-                const AnyCost &cost = any_costs[any_short ? 0 : 1][i];
+                const AnyCost &cost = any_costs[any_short ? (any_large ? 2 : 0) : 1][i];
                 const double x = static_cast<double>(blocks) / kComputeUnits, turns = ceil(x), ktiles = static_cast<double>(ceil_div(ceil_div(p.k, 64), slices));
                 const double bm = tiles[i].bm, bn = tiles[i].bn;
                 const double odd = ((p.lda % 2 != 0 ? bm : 0.0) + (p.ldb % 2 != 0 ? bn : 0.0)) / (bm + bn), lines = ((p.a_trans ? 0.0 : bm) + (p.b_trans ? bn : 0.0)) / (bm + bn);
@@ -487,7 +501,12 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 us += cost.c * c_mb + (p.beta != 0.f ? turns * cost.turn_beta : 0.0);
                 if (slices == 1 && p.ldc % 8 != 0) us += cost.c_stray * c_mb;
                 if (any_short) us += turns * ((p.k % 64 != 0 ? cost.more[0] : 0.0) + (p.beta != 0.f && p.m % 8 != 0 ? cost.more[1] : 0.0));
-                else if (slices > 1) us += cost.more[0] * (1.0 + 0.1 * slices) + cost.more[1] * 2.0 * slices * c_mb;
+                if (any_short && any_large) {
+                    const double rounds = ceil(x / tiles[i].resident), rows = static_cast<double>(p.m % 8) / 8.0;
+                    us += turns * (rows * (cost.rows_behind + (p.beta != 0.f ? cost.old_rows_behind : 0.0)) + cost.terms_behind * static_cast<double>(p.k % 8) / 8.0);
+                    us += rounds * (cost.round + cost.round_ktile * ktiles);
+                }
+                if (!any_short && slices > 1) us += cost.more[0] * (1.0 + 0.1 * slices) + cost.more[1] * 2.0 * slices * c_mb;
                 // (a nearly full turn of 64 x 64 tiles and long sums runs 5 to 8 % above that: (1672, 560, 3264) 22.9 us, 128 x 64 in two slices 22.3)
                 if (!any_short && i == kAnyStaged - 1 && slices == 1 && x > 0.5 && x <= 1.0 && ktiles >= 30.0) us *= 1.07;
                 // (masked stores of a triangle fetch the old C piece by piece there: SYRK 690 x 1408 with beta 13.9 us on 64 x 64 register-staged tiles, 10.7 on these)

@@ -331,3 +331,10 @@ def test_short_fp16_sums_with_beta_whose_rows_of_c_end_inside_a_piece(m, n, k, t
     """us, 192 x 192 direct-to-LDS tiles / checked 64 x 64: 23.3 / 12.7, 66.6 / 36.8, 42.1 / 26.2, 20.3 / 13.0"""
     args = (G.MG_F16, C, T, tb, m, n, k, k, k if tb == N else n, ldc)
     assert G.mg_query_selected(*args, 1.0, 0.5)["name"].startswith("hmfma_64x64")
+
+
+@pytest.mark.parametrize("ta,tb,m,n,k,beta", [(N, T, 7337, 2816, 10, 0.5), (N, N, 1137, 2758, 128, 0.7)])
+def test_short_sums_off_16_bytes_on_large_grids(ta, tb, m, n, k, beta):
+    """the register-staged tiles, several work-groups to a compute unit: (7337, 2816, 10) 28.3 us, 36.0 on the any-element tiles; (1137, 2758, 128) 9.2, 10.7"""
+    sel = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, beta, 2)
+    assert G.mg_kernel_name(sel["kernel_id"]).startswith("hmfma_"), G.mg_kernel_name(sel["kernel_id"])
