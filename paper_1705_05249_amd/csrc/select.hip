@@ -726,6 +726,10 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             // (and only square tiles have a grid of the wanted ones: SYRK (3603, 578) 256 x 128 37.9 us, 128 x 128 register-staged 25.2)
             if (any_family && triangle && tiles[i].bm != tiles[i].bn) continue;
             if (any_family && !any_short && (any_costs[1][i].fixed == 0.0 || (i == kAnyCount - 1 && p.k > 1024))) continue;
+            // (of fewer than eight rows or columns, which no other tile takes, the largest one only in grids that nearly fill the chip, of both operands along k or of a long op(A)
+            // with op(B) along k: (60393, 7, 401), both along k, 19.4 us, 32.0 on the shared-sum kernel below, (49555, 3, 540) 22.9 / 35.5; else (7, 9000, 700) 54.7 / 12.2, both
+            // along k 25.0 / 9.8, (39488, 4, 464) 22.4 / 17.6, (7, 60462, 747) 89 / 52)
+            if (any_family && !any_short && (p.m < 8 || p.n < 8) && !(!p.b_trans && (p.a_trans || p.m > p.n) && wanted_tiles(256, 256) > 160)) continue;
             const bool last = i == smallest;
             const int64_t ktiles = ceil_div(p.k, tiles[i].bk);
             const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn);

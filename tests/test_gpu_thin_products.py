@@ -20,3 +20,12 @@ def test_thin(oracle, dtype, layout, ta, tb, m, n, k, workspace):
     H.check_case(case, oracle, workspace=workspace)
     args = (G.MG_F32 if dtype == "f32" else G.MG_F16, layout, ta, tb, m, n, k, case.lda, case.ldb, case.ldc)
     assert not G.mg_kernel_name(G.mg_query_selected(*args)["kernel_id"]).startswith("direct")
+
+
+@pytest.mark.parametrize("layout,ta,tb,m,n,k", [(C, N, N, 7, 9000, 700), (C, T, N, 7, 9000, 700), (R, T, T, 12001, 7, 1001), (C, N, T, 4, 30000, 400)])
+def test_fewer_than_eight_rows_share_their_sums(oracle, layout, ta, tb, m, n, k):
+    """no 256 x 256 tile for them: (7, 9000, 700) 54.7 / 12.2 us"""
+    case = W.hgemm_case(m, n, k, case=m + n + k, layout=layout, ta=ta, tb=tb, beta=0.5)
+    sel = G.mg_query_selected(G.MG_F16, layout, ta, tb, m, n, k, case.lda, case.ldb, case.ldc)
+    assert G.mg_kernel_name(sel["kernel_id"]).startswith("htiny_32x32")
+    H.check_case(case, oracle)

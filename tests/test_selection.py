@@ -338,3 +338,11 @@ def test_short_sums_off_16_bytes_on_large_grids(ta, tb, m, n, k, beta):
     """the register-staged tiles, several work-groups to a compute unit: (7337, 2816, 10) 28.3 us, 36.0 on the any-element tiles; (1137, 2758, 128) 9.2, 10.7"""
     sel = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m, 1.0, beta, 2)
     assert G.mg_kernel_name(sel["kernel_id"]).startswith("hmfma_"), G.mg_kernel_name(sel["kernel_id"])
+
+
+@pytest.mark.parametrize("ta,tb,m,n,k,kernel", [(N, N, 7, 9000, 700, "htiny_32x32"), (T, N, 7, 9000, 700, "htiny_32x32"), (N, N, 4, 30000, 400, "htiny_32x32"),
+                                                (T, N, 60393, 7, 401, "hmfma_256x256"), (N, N, 7, 60000, 747, "htiny_32x32")])
+def test_fewer_than_eight_rows_or_columns_of_fp16(ta, tb, m, n, k, kernel):
+    """the largest tile only for both operands along k in grids that nearly fill the chip"""
+    sel = G.mg_query_selected(G.MG_F16, C, ta, tb, m, n, k, m if ta == N else k, k if tb == N else n, m)
+    assert G.mg_kernel_name(sel["kernel_id"]).startswith(kernel), G.mg_kernel_name(sel["kernel_id"])
