@@ -262,8 +262,8 @@ mg_status mg_hgemm_strided_batched(int layout, int trans_a, int trans_b, int64_t
  * the library, one per GPU, held until the process ends; the call allocates and frees nothing.
  * Arguments, results and errors as mg_sgemm, with these differences: a problem that would be slow
  * without more scratch than the array holds (mg_gemm_workspace_bytes() > MG_STATIC_SCRATCH_BYTES, and
- * the best configuration on the FP32 matrix pipes asks for more too) is refused with MG_ERR_WORKSPACE
- * and nothing is launched; MG_ERR_LAUNCH if the array's address
+ * the best configuration on the FP32 matrix pipes asks for more too; at least 16 rows and columns of C)
+ * is refused with MG_ERR_WORKSPACE and nothing is launched; MG_ERR_LAUNCH if the array's address
  * on the current device cannot be had.  Every call on a GPU uses that GPU's one array: calls that
  * overlap in time on one GPU (different streams, different threads) race on it and must be
  * ordered by the caller.  Nothing in the array has to start at zero (every slice of the sum

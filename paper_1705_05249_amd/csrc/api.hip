@@ -882,8 +882,9 @@ mg_status mg_sgemm_static(int layout, int ta, int tb, int64_t m, int64_t n, int6
 {
     // Refused is what is slow without more scratch, a long sum over a C that leaves the chip idle: the problems whose configuration on the
     // FP32 pipes wants it too.  Slices of the kernels on the bf16 pipes may only round off a last turn ((3200, 2752, 3840) would ask for
-    // 141 MB): such problems take what fits.  (0 for invalid arguments: run_gemm names the error.)
-    if (mg_gemm_workspace_bytes(MG_F32, layout, ta, tb, m, n, k, lda, ldb, ldc) > MG_STATIC_SCRATCH_BYTES) {
+    // 141 MB): such problems take what fits.  So do those of fewer than 16 rows or columns, which were never refused (with as many slices as fit (35500, 15, 4000)
+    // takes 182 us, 750 before thin products had slices).  (0 for invalid arguments: run_gemm names the error.)
+    if (m >= 16 && n >= 16 && mg_gemm_workspace_bytes(MG_F32, layout, ta, tb, m, n, k, lda, ldb, ldc) > MG_STATIC_SCRATCH_BYTES) {
         Problem p = canonical(MG_F32, layout, ta, tb, m, n, k, 1.f, nullptr, lda, nullptr, ldb, 1.f, nullptr, ldc, nullptr, 0, nullptr);
         p.fp32_pipes = true;
         int32_t kernel = -1, split = 1;

@@ -29,3 +29,16 @@ def test_fewer_than_eight_rows_share_their_sums(oracle, layout, ta, tb, m, n, k)
     sel = G.mg_query_selected(G.MG_F16, layout, ta, tb, m, n, k, case.lda, case.ldb, case.ldc)
     assert G.mg_kernel_name(sel["kernel_id"]).startswith("htiny_32x32")
     H.check_case(case, oracle)
+
+
+def test_static_scratch_takes_the_slices_that_fit():
+    """17 MB of partial sums would be preferred, the array holds 16; integers, exact"""
+    import torch
+    m, n, k = 35500, 15, 4000
+    assert G.mg_gemm_workspace_bytes(G.MG_F32, C, N, N, m, n, k, m, k, m) > G.MG_STATIC_SCRATCH_BYTES
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    A = torch.randint(-2, 3, (k, m), device="cuda", generator=gen).float()
+    B = torch.randint(-2, 3, (n, k), device="cuda", generator=gen).float()
+    out = torch.full((n, m), float("nan"), device="cuda")
+    G.mg_sgemm_static(C, N, N, m, n, k, 1.0, A, m, B, k, 0.0, out, m)
+    assert torch.equal(out.double(), B.double() @ A.double())

@@ -229,6 +229,25 @@ for m, n, k, ta, tb in ((1024, 896, 8448, T, N), (3200, 2752, 3840, T, N), (1443
     assert run.stdout.split() == ["-12"] * 5 + ["-10"]                 # the last one in eight slices on any pipes: 48 MB
 
 
+def test_static_scratch_refuses_no_thin_product():
+    """fewer than 16 rows or columns: with the slices that fit, however many the query names (no device: the launch fails)"""
+    program = """
+import sys
+sys.path.insert(0, sys.argv[1])
+import torch
+assert torch.cuda.device_count() == 0
+from paper_1705_05249_amd import gemm as G
+for m, n, k in ((35500, 15, 4000), (15, 35500, 4000), (61424, 14, 426080), (2, 3000000, 9000)):
+    assert m < 100 or G.mg_gemm_workspace_bytes(G.MG_F32, G.MG_COL_MAJOR, G.MG_NO_TRANS, G.MG_NO_TRANS, m, n, k, m, k, m) > G.MG_STATIC_SCRATCH_BYTES
+    for layout, ld in ((G.MG_COL_MAJOR, (m, k, m)), (G.MG_ROW_MAJOR, (k, n, n))):
+        print(G.lib().mg_sgemm_static(layout, G.MG_NO_TRANS, G.MG_NO_TRANS, m, n, k, 1.0, 4096, ld[0], 4096, ld[1], 0.0, 4096, ld[2], None))
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    run = subprocess.run([sys.executable, "-c", program, ROOT], capture_output=True, text=True, timeout=300, env=env)
+    assert run.returncode == 0, run.stderr
+    assert run.stdout.split() == ["-12"] * 8
+
+
 def test_the_workspace_query_covers_every_beta():
     """what the query returns holds the slices of the configuration that would be chosen with all the workspace there is"""
     import random
