@@ -48,7 +48,8 @@ struct Problem {
     size_t workspace_bytes;
     hipStream_t stream;
     int shape;                 // ProblemShape: where an operand is known to hold zeros / which part of C is wanted
-    bool mask_c;               // shape C_LOWER / C_UPPER only: nothing outside that triangle of C may be written (or read);
+    bool mask_c;               // shape C_LOWER / C_UPPER only: nothing outside that triangle of C may be written or count in a result (a kernel
+                               // may fetch the 16 bytes around its diagonal, which lie between wanted elements of C);
                                // set only for kernels whose KernelEntry says masks_triangle
     bool fp32_pipes = false;   // FP32: only kernels on the FP32 matrix pipes are ranked
     bool tiles_only = false;   // the kernels for small problems are not ranked (workspace queries)

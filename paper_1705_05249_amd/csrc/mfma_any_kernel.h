@@ -190,7 +190,9 @@ __device__ __forceinline__ void any_epilogue(const floatx4 (&acc)[FN][FM], const
         }
         if (last <= first) continue;
         u32x4 old = {0u, 0u, 0u, 0u};
-        // (of a piece that ends beyond the column the 16 bytes that end with it; C has eight rows or more)
+        // (of a piece that ends beyond the column the 16 bytes that end with it; C has eight rows or more.  Under the mask they may hold elements of the other
+        // triangle, which are dropped: they lie between wanted ones in memory, and fetching the wanted ones alone, one by one, took SYRK (1161, 167) from 7.0 to 8.5 us,
+        // without branches to 7.8.)
         if (beta != 0.f) old = load_unaligned_chunk<_Float16>(p - beyond);
         const floatx4 lo = *reinterpret_cast<const floatx4 *>(lds + col * COL + row * 4), hi = *reinterpret_cast<const floatx4 *>(lds + col * COL + row * 4 + 16);
         if (beyond > 0) old = shift_down(old, beyond);

@@ -79,7 +79,7 @@ struct MfmaArgs {
     int shape;             // ProblemShape: K range per tile narrowed to the non-zero part / tiles outside C's triangle skipped
     int reversed;          // walk the tiles in reverse order (longest K ranges first)
     int early_c;           // ask for the old C before the K loop (SHORT kernels)
-    int mask;              // with shape C_LOWER / C_UPPER: write (and read) nothing outside that triangle of C
+    int mask;              // with shape C_LOWER / C_UPPER: write nothing outside that triangle of C (see Problem::mask_c)
     ConvGeom conv;         // kernels built with CONV: A is the image, op(A) its column matrix (m = oh * ow positions)
 };
 

@@ -84,6 +84,34 @@ def test_triangles_of_c(level3_oracle, tile, uplo, tiles, trans, slices, beta):
         G.mg_clear_override()
 
 
+@pytest.mark.parametrize("tile", [(128, 128), (64, 64)])
+@pytest.mark.parametrize("uplo", [W.UPPER, W.LOWER])
+@pytest.mark.parametrize("n", [61, 125, 131, 259])
+def test_the_other_triangle_of_c_may_hold_anything(tile, uplo, n):
+    """beta with NaN and infinities outside the wanted triangle, which stay as they are; integers, exact"""
+    import torch
+    k, ldc = 137, n + 3
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randint(-2, 3, (n, k), device="cuda", generator=gen).half()                     # row by row: n x k, contiguous along k
+    want = torch.ones(n, n, dtype=torch.bool, device="cuda")
+    want = want.tril() if uplo == W.LOWER else want.triu()
+    before = torch.randint(-3, 4, (n, n), device="cuda", generator=gen).half()
+    before[~want] = torch.tensor([float("nan"), float("inf")], device="cuda").half().repeat(n * n)[:int((~want).sum())]
+    buffer = torch.full((n * ldc,), float("nan"), device="cuda", dtype=torch.float16)
+    inside = buffer.view(n, ldc)[:, :n].T                                                      # column-major: inside[i, j]
+    inside.copy_(before)
+    workspace = torch.empty(G.mg_syrk_workspace_bytes(G.MG_F16, C, T, n, k) + 4 * n * n + 256, dtype=torch.uint8, device="cuda")
+    try:
+        G.mg_override_config(kernel(tile, "kk"), 1)
+        G.mg_hsyrk(C, uplo, T, n, k, 1.0, A, k, -1.0, buffer, ldc, workspace)
+    finally:
+        G.mg_clear_override()
+    after = torch.where(want, (A.double() @ A.double().T - before.double()).half(), before)
+    bits = lambda x: x.contiguous().view(torch.int16)  # noqa: E731
+    assert torch.equal(bits(inside), bits(after))
+    assert bool(buffer.view(n, ldc)[:, n:].isnan().all())
+
+
 def test_too_few_elements_for_a_piece_are_refused():
     for m, n, k in ((7, 64, 64), (64, 7, 64), (64, 64, 7)):
         try:
