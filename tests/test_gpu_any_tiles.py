@@ -1,7 +1,9 @@
 """The FP16 kernels whose pieces come from any element (csrc/mfma_any_kernel.h): sizes one short of a tile, one over it and below a piece's length
 beyond one, leading dimensions and pointers at odd elements, sums shorter than the pipeline and sums that end inside a piece, all
-operand orders, slices, triangles of C, against the CPU oracle, bit for bit on integers; what lies between the columns is NaN in A and B and
+operand orders, slices, triangles of C and of an operand, against the CPU oracle, bit for bit on integers; what lies between the columns is NaN in A and B and
 stays as it was in C."""
+import itertools
+
 import pytest
 
 import helpers as H
@@ -82,6 +84,38 @@ def test_triangles_of_c(level3_oracle, tile, uplo, tiles, trans, slices, beta):
         H.check_level3(case, level3_oracle, workspace=workspace)
     finally:
         G.mg_clear_override()
+
+
+@pytest.mark.parametrize("layout,side,uplo,trans", list(itertools.product([C, W.ROW_MAJOR], [W.LEFT, W.RIGHT], [W.UPPER, W.LOWER], [N, T])))
+@pytest.mark.parametrize("m,n", [(641, 9), (70, 401), (129, 193), (401, 209)])
+def test_triangular_operands(level3_oracle, layout, side, uplo, trans, m, n):
+    """TRMM on every tile, one to four slices, of which those wholly among the operand's zeros add nothing"""
+    import torch
+    case = W.level3_case("trmm", "f16", layout, m, n, side=side, uplo=uplo, trans=trans, alpha=1.0, integer=True, case=m + n)
+    workspace = torch.empty((m + n) * (m + n + 64) * 4 + 4 * 4 * m * n + 4096, dtype=torch.uint8, device="cuda")
+    ran = set()
+    try:
+        for t in G.kernel_table():
+            if not t["name"].startswith("hany16"):
+                continue
+            for slices in (1, 2, 4):
+                G.mg_override_config(t["kernel_id"], slices)
+                try:
+                    H.check_level3(case, level3_oracle, workspace=workspace)
+                    ran.add((t["name"].rsplit("_", 1)[0], slices))
+                except G.MgError as e:
+                    assert e.status == -11               # another operand order, an empty slice
+    finally:
+        G.mg_clear_override()
+    longest = m if side == W.LEFT else n
+    assert len({name for name, slices in ran if slices == 1}) == 5 and (longest < 193 or len({name for name, slices in ran if slices == 4}) == 5), ran
+
+
+@pytest.mark.parametrize("layout,side,uplo,trans", [(C, W.LEFT, W.LOWER, N), (C, W.RIGHT, W.UPPER, T), (W.ROW_MAJOR, W.LEFT, W.UPPER, T), (W.ROW_MAJOR, W.RIGHT, W.LOWER, N)])
+def test_triangular_operands_of_odd_sizes(level3_oracle, layout, side, uplo, trans):
+    """more blocks than the shared-sum kernel takes, sums beyond the register-staged tiles: what selection chooses"""
+    m, n = (1001, 303) if side == W.LEFT else (303, 1001)
+    H.check_level3(W.level3_case("trmm", "f16", layout, m, n, side=side, uplo=uplo, trans=trans, alpha=1.0, integer=True, case=m + n), level3_oracle)
 
 
 @pytest.mark.parametrize("tile", [(128, 128), (64, 64)])
