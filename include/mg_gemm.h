@@ -339,7 +339,9 @@ const char *mg_kernel_name(int32_t kernel_id);
 
 /* Which configuration a non-batched call with these arguments would run right now
  * (honours an active override).  pointer_alignment: the smallest alignment in bytes of
- * A, B, C (pass 256 when unknown-but-aligned). */
+ * A, B, C (pass 256 when unknown-but-aligned).  A large FP16 call whose rows start off 16 bytes
+ * and whose workspace has room may run on padded copies of A and B instead; what is named here
+ * is the kernel that takes the operands where they lie. */
 mg_status mg_query_selected(int dtype, int layout, int trans_a, int trans_b,
                             int64_t m, int64_t n, int64_t k,
                             int64_t lda, int64_t ldb, int64_t ldc, float alpha, float beta,

@@ -191,11 +191,10 @@ size_t preferred_bytes_anywhere(Problem p)
 
 // Indirect GEMM, the paper's Section 3.2 route for problems that break the fast kernel's assumptions: copy the
 // operands into zero-padded, aligned buffers whose sizes are whole tiles and run the fast kernel there.  FP16 needs it:
-// ragged or unaligned FP16 problems otherwise run the bounds-checked register-staged kernels at 0.2-0.6 of the
-// direct-to-LDS rate (4097^3: 525 us; an odd leading dimension puts every other row at 2-byte alignment), while the
-// copies are O(n^2) (~30 us at 4097^3).  The padded buffers live in the caller's workspace; without enough of it
-// the direct route runs.  C stays where it is (run_indirect), but for a sliced sum, whose result is copied back bit for
-// bit.  One rounding as always.
+// with rows off 16 bytes the direct-to-LDS kernels fetch less than 16 bytes a lane, or the checked ones stage through registers, below
+// the rate of whole 16-byte rows for all k terms, while the copies are O(n^2) (~30 us at 4097^3).  The padded buffers live
+// in the caller's workspace; without enough of it the direct route runs.  C stays where it is (run_indirect), but for a
+// sliced sum, whose result is copied back bit for bit.  One rounding as always.
 struct IndirectPlan {
     int64_t mp, np, kp;
     size_t a_bytes, b_bytes, c_bytes;
@@ -232,11 +231,10 @@ bool indirect_plan(const Problem &p, bool pointers_known, IndirectPlan *plan)
                              (!pointers_known || (pointer_alignment(p.A) >= 16 && pointer_alignment(p.B) >= 16));
         if (whole && aligned) return false;                            // the fast kernels take it directly
         if (pointers_known && dma_ragged_operands(p, 16) && dma_offsets_fit(p, 192, 64)) return false;       // so do those for sizes that end inside a tile
-        // The bounds-checked kernels run their whole K-tiles on the fast flavour's schedule: up to about 900 multiply-adds per
-        // element moved the two routes' estimates are compared; beyond, the copies always pay.  Even leading dimensions, us
-        // direct / through the copies of A and B (A along m | along k): 1300^3 21.6 / 25.1 | 19.2 / 25.1, 1500^3 37 / 27 | 33 /
-        // 28, 1800^3 30 / 27 | 29 / 28, 2050^3 45 / 41 | 47 / 40, 2500^3 60 / 49 | 59 / 50, 2700^3 59 / 58 | 60 / 60, (8200,
-        // 1030, 2050) - | 62 / 76, (4100, 4100, 512) 53 / 54 | -.
+        // The kernels that take any element (FP16 rows off 16 bytes) are at the padded product's rate less what their loads cost:
+        // copies / in place, geometric means over 38 600 calls by multiply-adds per element moved: 1.19 at 350-450, 1.15 to
+        // 550, 1.07 to 700, 1.03 to 900, 0.96 to 1100, 0.88 to 1400.  In place below 350, up to 900 by comparing the two routes'
+        // estimates, beyond always through the copies, by which 24 % of the calls of 900-1100 and 8 % of 1100-1400 lose over 5 %.
         const double moved = static_cast<double>(p.m) * p.k + static_cast<double>(p.k) * p.n + static_cast<double>(p.m) * p.n;
         if (work < 350.0 * moved) return false;
         compare = work < 900.0 * moved;
@@ -320,8 +318,10 @@ mg_status run_indirect(const Problem &p, const IndirectPlan &plan, bool *taken, 
             best_plan = candidate;
         }
         if (plan.compare) {
-            // the copies of A and B: a launch, the gap behind it and their traffic at ~3.5 TB/s (the bounds-checked kernels run
-            // 10-25 % above their estimate at these sizes)
+            // The copies of A and B: a launch, the gap behind it and their traffic at ~3.5 TB/s.  Over 13 800 calls the route takes
+            // 1.34 times this estimate at 350-550 multiply-adds per element moved (27 us for 20), 1.04 at 550-700 and 0.93 at
+            // 700-900, the direct one 1.01-1.03 of its own.  The route taken is over 5 % slower than the other in 51 % of the calls
+            // of 350-450 and 29 % of 450-600 (all but a few through the copies), 16 % of 600-750 and 19 % of 750-900 (up to 1.9).
             const double copies_us = 5.0 + 4.0 * static_cast<double>(p.k) * (static_cast<double>(p.m) + static_cast<double>(p.n)) / 3.5e6;
             direct->p = p;
             double us = 0.0;

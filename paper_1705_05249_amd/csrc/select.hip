@@ -137,8 +137,8 @@ int pick_gemv_split(const mg_config &cfg, int64_t outputs, int64_t k, size_t wor
 //   beside them 8192 x 8200 44.5 / 49.4 and 6144 x 10240 42.9 / 44.5), with neither few work-groups of it along the outputs
 //   (1024 x 65536 44.1 / 46.2, 192 x 260416 33.4 / 43.7) nor one of the panel kernel per compute unit (16384 x 4096 48.7 /
 //   52.3); the outputs leave most lanes of an axpy work-group idle (64 x 390625 36.2 / 20.6, FP16 256 x 390625 54.9 / 37.7;
-//   128 x 390625 38.9 / 37.9, FP16 512 x 195312 40.1 / 43.9); or they end inside a lane's run
-//   (FP16 1500 x 66666 123 / 58, when that kernel read such runs element by element);
+//   128 x 390625 38.9 / 37.9, FP16 512 x 195312 40.1 / 43.9); or they end inside a lane's run (about even: FP16 1500 x 66666
+//   33.8 / 37.3, 9001 x 8000 28.7 / 25.4, 6001 x 9000 25.8 / 20.1, FP32 3001 x 12000 24.9 / 25.2, 14001 x 4001 35.7 / 39.6);
 //   the axpy kernel also where its work-groups fill the chip by themselves (10^6 x 64: 40 / 66).
 void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Problem &p, int64_t alignment, size_t workspace_bytes,
                              int32_t *kernel, int32_t *split)
@@ -158,10 +158,12 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
                              outputs >= 8 * cfg.tile_m && outputs < 16 * lane_elems * kComputeUnits;
         by_axpy = !(collide || outputs <= (f32 ? 64 : 256) || outputs % lane_elems != 0);
     }
-    // A sum of a few terms is over before sixteen wavefronts have met, unless ragged outputs make the axpy kernel read elements
-    // (us, axpy / panel with 16 lanes: 1000 x 4 2.1 / 2.3, 16384 x 16 2.4 / 2.6, 40000 x 32 3.1 / 3.8, 65472 x 32 3.1 / 4.4, 65535 x 32 4.8 / 4.4,
-    // FP16 65472 x 32 3.3 / 3.9; 16384 x 64 3.6 / 2.7), and where FP32 panels would be three or more work-groups a compute unit
-    // (40000 x 64 4.0 / 4.4, 65472 x 128 7.1 / 7.7, x 192 9.4 / 9.6; FP16 x 64 4.3 / 4.0)
+    // A sum of a few terms is over before sixteen wavefronts have met (us, axpy / panel with 16 lanes: 1000 x 4 2.1 / 2.3, 16384 x 16
+    // 2.4 / 2.6, 40000 x 32 3.1 / 3.8, 65472 x 32 3.1 / 4.4, FP16 65472 x 32 3.3 / 3.9; 16384 x 64 3.6 / 2.7), and where FP32 panels
+    // would be three or more work-groups a compute unit (40000 x 64 4.0 / 4.4, 65472 x 128 7.1 / 7.7, x 192 9.4 / 9.6; FP16 x 64 4.3 /
+    // 4.0).  Not where the outputs end inside a lane's run: there (tight columns, which start off 16 bytes) FP32 sums of 33 to 128 terms
+    // take 1.3 times the panels' time (20 of 20 slower, 53963 x 126 9.3 / 6.5), and shorter ones go either way (65535 x 32 4.7 / 5.4, 9494 x 31
+    // 4.2 / 3.5, FP16 68847 x 12 3.6 / 5.7, 42201 x 23 5.6 / 4.7).
     const bool even = outputs % lane_elems == 0;
     if (p.k <= 8 || (even && (p.k <= 32 || (f32 && p.k <= 128 && outputs > 32768)))) by_axpy = true;
     if (by_axpy) {
@@ -202,7 +204,7 @@ void pick_gemv_along_outputs(const std::vector<KernelEntry> &table, const Proble
 
 // Longest sum that FP32 products of `blocks32` 32 x 32 blocks share among a block's wavefronts.  (Both operands along k, up to 64 blocks: 0.94 up to 1280 terms, 1.05 to 1.15
 // up to 1792, 15 of 16 slower.  Behind the unfold pass, 51 layers of 1281 to 2048 terms: up to 64 blocks 1.08 up to 1536 terms, more 0.98 up to 1536, 0.98
-// with two of nine up to 1.11 beyond; where there is room for slices, which products thinner than 16 do not take)
+// with two of nine up to 1.11 beyond; where there is room for slices)
 int64_t most_shared_f32(const Problem &p, int64_t blocks32, bool unfolded)
 {
     if (blocks32 > 64) return unfolded ? 1536 : 2048;
