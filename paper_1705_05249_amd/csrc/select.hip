@@ -433,6 +433,8 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                                                          {5.62, 0.0, 0.0, 0.0857, 0.145, 0.0428, 0.0, 0.125, 0.438, 0.0208, {0.0, 0.0768}, 0.27, 0.959, 0.401, 1.92, 0.29},
                                                          {6.54, 0.0, 0.0, 0.0, 0.212, 0.0553, 0.0, 0.105, 1.12, 0.0388, {0.0, 0.365}, 0.645, 2.56, 0.609, 2.72, 0.527},
                                                          {8.64, 2.09, 0.0, 0.647, 0.78, 0.12, 0.0694, 0.0997, 3.56, 0.053, {0.0, 2.68}, 3.57, 9.17, 1.15, 1.2, 0.599}}};
+        // (long sums of a triangle of C, on the largest of them: fitted to half of 300 SYRK of 2000 to 7000 rows and 321 to 6000 terms; see `uneven` below)
+        static const AnyCost triangle_largest = {8.3, 8.2, 0.0, 1.03, 0.45, 0.076, 0.009, 0.22, 0.0, 0.0, {0.0, 0.0}};
         const bool any_short = p.k <= 320;
         const bool any_family = !f32 && p.conv == nullptr && p.clip_m == 0 && p.clip_n == 0 && p.k >= 8 && !dma_ragged_operands(p, alignment);
         // The register-staged FP16 kernels transpose operands that are not contiguous along k on their way to
@@ -494,8 +496,13 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
         auto estimate = [&](int i, int slices) {
             const int64_t blocks = wanted_tiles(tiles[i].bm, tiles[i].bn) * slices;
             if (any_family) {
-                const AnyCost &cost = any_costs[any_short ? (any_large ? 2 : 0) : 1][i];
-                const double x = static_cast<double>(blocks) / kComputeUnits, turns = ceil(x), ktiles = static_cast<double>(ceil_div(ceil_div(p.k, 64), slices));
+                const AnyCost &cost = triangle && !any_short && i == kAnyCount - 1 ? triangle_largest : any_costs[any_short ? (any_large ? 2 : 0) : 1][i];
+                // (the checked tiles of a triangle have a work-group for each tile of the square, which go to the 32 groups of eight compute units in turn, and the busiest group has
+                // a tenth more wanted ones than its share: 8 of 210 on 20 x 20 tiles and of the lower 231 on 21 x 21, 9 of the upper ones and of 253 on 22 x 22, which take a
+                // second turn.  SYRK on 256 x 256, (5283, 274) lower 28.2 us, (5287, 480) upper 45.2, (5120, 140) 24.4, (5435, 100) 34.7, 23.8 on 128 x 128; two of these at once
+                // on a compute unit, (3640, 207) 17.2 on 29 x 29, (3865, 220) 24.1 on 31 x 31, 17.7 on the direct-to-LDS ones)
+                const bool uneven = triangle && i >= kAnyStaged && (any_large || !any_short);
+                const double x = static_cast<double>(blocks) / kComputeUnits, filled = uneven ? (p.shape == MG_SHAPE_C_UPPER ? 1.11 : 1.105) * x : x, turns = ceil(filled), ktiles = static_cast<double>(ceil_div(ceil_div(p.k, 64), slices));
                 const double bm = tiles[i].bm, bn = tiles[i].bn;
                 const double odd = ((p.lda % 2 != 0 ? bm : 0.0) + (p.ldb % 2 != 0 ? bn : 0.0)) / (bm + bn), lines = ((p.a_trans ? 0.0 : bm) + (p.b_trans ? bn : 0.0)) / (bm + bn);
                 const double c_mb = 2.0e-6 * static_cast<double>(p.m) * static_cast<double>(p.n) * (triangle ? 0.5 : 1.0);
@@ -504,7 +511,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 if (slices == 1 && p.ldc % 8 != 0) us += cost.c_stray * c_mb;
                 if (any_short) us += turns * ((p.k % 64 != 0 ? cost.more[0] : 0.0) + (p.beta != 0.f && p.m % 8 != 0 ? cost.more[1] : 0.0));
                 if (any_short && any_large) {
-                    const double rounds = ceil(x / tiles[i].resident), rows = static_cast<double>(p.m % 8) / 8.0;
+                    const double rounds = ceil(filled / tiles[i].resident), rows = uneven ? 0.0 : static_cast<double>(p.m % 8) / 8.0;
                     us += turns * (rows * (cost.rows_behind + (p.beta != 0.f ? cost.old_rows_behind : 0.0)) + cost.terms_behind * static_cast<double>(p.k % 8) / 8.0);
                     us += rounds * (cost.round + cost.round_ktile * ktiles);
                 }
@@ -512,7 +519,18 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
                 // (a nearly full turn of 64 x 64 tiles and long sums runs 5 to 8 % above that: (1672, 560, 3264) 22.9 us, 128 x 64 in two slices 22.3)
                 if (!any_short && i == kAnyStaged - 1 && slices == 1 && x > 0.5 && x <= 1.0 && ktiles >= 30.0) us *= 1.07;
                 // (masked stores of a triangle fetch the old C piece by piece there: SYRK 690 x 1408 with beta 13.9 us on 64 x 64 register-staged tiles, 10.7 on these)
-                if (i >= kAnyStaged && triangle) us += turns * (p.beta != 0.f ? 2.5 : 0.4);
+                // (many tiles: masked ends go one by one at any height of C, and those of the diagonal are waited for once.  With this and the turns above 276 SYRK of up to 320
+                // terms, not those it was fitted to, take 1.012 times the fastest of the square tiles, at most 1.18; with a charge per turn 1.033, at most 1.84: (5409, 103) with
+                // beta 63.1 us, 34.2 on 128 x 128.  161 of more terms 1.010, with that charge and no 256 x 256 tiles beyond 1024 terms 1.056: (5551, 587) with beta 88.5 on these,
+                // 57.1 on 128 x 128, (5077, 3771) 116 on these, 181)
+                if (uneven) {
+                    const bool old = p.beta != 0.f;
+                    if (!any_short) us += old ? 18.9 : 0.0;
+                    else if (bm > 128.0) us += old ? 14.0 : 2.5;
+                    else if (bm > 64.0) us += old ? 8.8 : 0.9;
+                    else us += old ? 4.3 : 0.6;
+                    if (any_short && p.a_trans) us += x * (bm > 128.0 ? (old ? 2.8 : 0.74) : bm > 64.0 ? (old ? 1.4 : 0.7) : (old ? 0.32 : 0.08));
+                } else if (i >= kAnyStaged && triangle) us += turns * (p.beta != 0.f ? 2.5 : 0.4);
                 return us * 1.0e6;
             }
             const double tile_flops = 2.0 * tiles[i].bm * tiles[i].bn * static_cast<double>(p.k) / slices;
@@ -727,7 +745,7 @@ void select_config(const std::vector<KernelEntry> &table, const Problem &p, int6
             if (!f32 && triangle && (any_family || i >= kRagged) && tiles[i].bm % tiles[i].bn != 0) continue;
             // (and only square tiles have a grid of the wanted ones: SYRK (3603, 578) 256 x 128 37.9 us, 128 x 128 register-staged 25.2)
             if (any_family && triangle && tiles[i].bm != tiles[i].bn) continue;
-            if (any_family && !any_short && (any_costs[1][i].fixed == 0.0 || (i == kAnyCount - 1 && p.k > 1024))) continue;
+            if (any_family && !any_short && (any_costs[1][i].fixed == 0.0 || (i == kAnyCount - 1 && !triangle && p.k > 1024))) continue;
             // (of fewer than eight rows or columns, which no other tile takes, the largest one only in grids that nearly fill the chip, of both operands along k or of a long op(A)
             // with op(B) along k: (60393, 7, 401), both along k, 19.4 us, 32.0 on the shared-sum kernel below, (49555, 3, 540) 22.9 / 35.5; else (7, 9000, 700) 54.7 / 12.2, both
             // along k 25.0 / 9.8, (39488, 4, 464) 22.4 / 17.6, (7, 60462, 747) 89 / 52)
