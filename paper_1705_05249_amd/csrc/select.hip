@@ -985,7 +985,11 @@ int32_t select_batched(const std::vector<KernelEntry> &table, const BatchedProbl
         const int32_t id = lines();
         LinesShape shape;
         const int team = id >= 0 ? table[id].cfg.waves_n : 0;
-        if (id >= 0 && (p.dtype != MG_F32 || !batched_lines_shape(p, team, &shape) ||
+        // (from 33 rows and columns the tiles' estimates are 5 to 10 % too low, mostly with beta: of 770 calls of up to 96 rows and columns and more than 32 terms they sent 78 to
+        // slower tiles and 22 to faster ones, 5415 x 38^3 with beta 31.5 us / 34.6, 7331 x (63, 68, 68) 119 / 155, and of 305 strided ones with beta of any larger size 12 and 2)
+        const int64_t thin = p.m < p.n ? p.m : p.n, wide = p.m < p.n ? p.n : p.m;
+        const bool stands = thin > 32 && ((wide <= 96 && p.k > 32) || (p.strided && p.beta != 0.f));
+        if (id >= 0 && (p.dtype != MG_F32 || stands || !batched_lines_shape(p, team, &shape) ||
                         batched_lines_us(p, team, shape) < 1.02 * batched_tile_us(p, small || narrow ? 32 : 64, small ? 32 : 64))) return id;
     }
     // (FP32 instances that fill the 32 x 32 block and stream from memory lose more to the one-wavefront kernel's 4-byte and

@@ -26,7 +26,13 @@ FASTER = [("f16", 68, 68, 68, 0, 0, 7141, 0, 1),         # 124 / 55
           ("f16", 45, 37, 16, 0, 0, 9600, 0, 1),         # 41 / 21.5
           ("f32", 71, 71, 71, 0, 0, 7608, 1, 1),         # 202 / 145
           ("f32", 22, 122, 9, 0, 0, 10300, 0, 1),        # 72 / 48
-          ("f32", 152, 8, 8, 0, 0, 7118, 0, 0)]          # 63 / 27
+          ("f32", 152, 8, 8, 0, 0, 7118, 0, 0),          # 63 / 27
+          ("f32", 38, 38, 38, 1, 0, 5415, 0, 1),         # 34.6 / 31.5
+          ("f32", 35, 35, 35, 1, 1, 18139, 0, 1),        # 106 / 95
+          ("f32", 39, 51, 52, 1, 0, 3199, 1, 1),         # 32.7 / 29.0
+          ("f32", 34, 43, 40, 1, 1, 20000, 1, 1),        # 121 / 108
+          ("f32", 63, 68, 68, 1, 0, 7331, 0, 1),         # 155 / 119
+          ("f32", 54, 66, 67, 1, 0, 8072, 1, 0)]         # 140 / 116
 
 
 @pytest.fixture(scope="module")
